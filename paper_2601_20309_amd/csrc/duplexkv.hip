@@ -70,6 +70,7 @@ bool config_ok(const kv_config *c)
 using dkv::Marks;
 using dkv::kClaimStride;
 using dkv::kRing;
+using dkv::kReadPasses;
 using dkv::list_bad;
 
 bool out_of_range(const int32_t *p, int32_t n, int32_t lim)
@@ -951,8 +952,8 @@ void free_engine(kv_engine *e)
     if (e->s_read) (void)hipStreamDestroy(e->s_read);
     if (e->read_ids) (void)hipFree(e->read_ids);
     if (e->read_ids_host) (void)hipHostFree(e->read_ids_host);
-    if (e->read_acc) (void)hipFree(e->read_acc);
-    if (e->read_acc_host) (void)hipHostFree(e->read_acc_host);
+    if (e->read_part) (void)hipFree(e->read_part);
+    if (e->read_sums) (void)hipHostFree(e->read_sums);
     for (hipEvent_t &x : e->read_ev) ev(x);
     if (e->desc_host) (void)hipHostFree(e->desc_host);
     if (e->desc_dev) (void)hipFree(e->desc_dev);
@@ -1536,19 +1537,25 @@ int kv_probe_link(uint64_t bytes, int32_t reps, double *d2h, double *h2d, double
 
 int kv_reader_start(kv_engine *e, const int32_t *ids, int32_t n, int32_t passes, int32_t max_wgs)
 {
-    if (!e || list_bad(ids, n) || passes < 1 || passes > 256 || max_wgs < 0) return KV_EINVAL;
+    if (!e || list_bad(ids, n) || passes < 1 || passes > kReadPasses || max_wgs < 0) return KV_EINVAL;
     if (e->sticky != KV_OK) return e->sticky;
     if (e->read_passes != 0) return KV_EINVAL;  // previous reader not waited for
     if (out_of_range(ids, n, e->cfg.n_hbm_blocks)) return KV_ERANGE;
     if ((int64_t)n > 2 * (int64_t)e->cfg.n_hbm_blocks) return KV_EINVAL;
     if (e->seg % 16 != 0 || ((uintptr_t)e->hbm & 15u) != 0) return KV_EUNSUP;
+    // Workgroups: 5.5 per CU.  With one row in flight per wave (kReadDepth) that is 5.6 MiB
+    // in flight, just enough for the HBM rate alone, and what a rotation beside it can bear
+    // (8 + 8 GiB alone / beside a swap-out of 4 GiB, reader TB/s, and the swap-out's GB/s):
+    // 5 per CU 6.57 / 5.3, 56.9;  5.5 6.69 / 6.09, 56.7;  6 6.82 / 6.35, 52.4;  7 6.91 / 5.9, 44.3.
+    const int most_wgs = 11 * (e->n_cus > 0 ? e->n_cus : 256) / 2;
     if (!e->s_read) {
         const size_t idb = 2 * (size_t)e->cfg.n_hbm_blocks * sizeof(int32_t);
         if (hipMalloc((void **)&e->read_ids, idb) != hipSuccess ||
             hipHostMalloc((void **)&e->read_ids_host, idb, hipHostMallocDefault) != hipSuccess ||
-            hipMalloc((void **)&e->read_acc, sizeof(unsigned long long) + 256 * sizeof(unsigned int)) != hipSuccess ||
-            hipHostMalloc((void **)&e->read_acc_host, sizeof(unsigned long long), hipHostMallocDefault) !=
-                hipSuccess) {
+            hipMalloc((void **)&e->read_part, (size_t)most_wgs * sizeof(unsigned long long) +
+                                                  dkv::kReadGroups * dkv::kReadStride * sizeof(unsigned int)) != hipSuccess ||
+            hipHostMalloc((void **)&e->read_sums, (size_t)most_wgs * sizeof(unsigned long long),
+                          hipHostMallocDefault) != hipSuccess) {
             (void)hipGetLastError();
             return KV_ENOMEM;
         }
@@ -1559,44 +1566,57 @@ int kv_reader_start(kv_engine *e, const int32_t *ids, int32_t n, int32_t passes,
         HIPTRY(e, hipEventCreate(&x));
         e->read_ev.push_back(x);
     }
-    constexpr int U = 8;
     dkv::ReadParams p{};
     p.hbm = e->hbm;
-    p.ids = e->read_ids;
-    p.acc = e->read_acc;
+    p.part = e->read_part;
+    p.result = e->read_sums;
+    p.passes = (uint32_t)passes;
     hbm_strides(e, p.hbm_plane_stride, p.hbm_block_stride);
     p.n = (uint32_t)n;
-    p.n_planes = e->n_planes;
     p.vec_per_seg = (uint32_t)(e->seg / 16);
-    p.tiles_per_seg = (p.vec_per_seg + dkv::kThreads * U - 1) / (dkv::kThreads * U);
-    if (!dir_tiles(p.n, p.n_planes, p.tiles_per_seg, p.tiles)) return KV_EUNSUP;
-    *e->read_acc_host = 0;
-    HIPTRY(e, hipMemsetAsync(e->read_acc, 0, sizeof(unsigned long long) + 256 * sizeof(unsigned int), e->s_read));
+    // the limit on what one pass may name: 2^31 tiles, each within a segment (rows of the
+    // flat sequence fit 32 bits then: n is at most twice the blocks there is memory for)
+    uint32_t by_segment;
+    if (!dir_tiles(p.n, e->n_planes, (p.vec_per_seg + dkv::kReadVecs - 1) / dkv::kReadVecs, by_segment))
+        return KV_EUNSUP;
+    p.n_vecs = (uint64_t)p.n * e->n_planes * p.vec_per_seg;
+    p.tiles = (uint32_t)((p.n_vecs + dkv::kReadVecs - 1) / dkv::kReadVecs);
+    // a rounded-up reciprocal is exact while index * divisor stays below 2^64 (and 2^64 / 1 has no room)
+    if (p.vec_per_seg > 1 && p.n_vecs <= ~0ull / p.vec_per_seg) p.seg_magic = ~0ull / p.vec_per_seg + 1;
+    p.next = reinterpret_cast<unsigned int *>(e->read_part + most_wgs);
     if (n > 0) {
         memcpy(e->read_ids_host, ids, (size_t)n * sizeof(int32_t));
-        HIPTRY(e, hipMemcpyAsync(e->read_ids, e->read_ids_host, (size_t)n * sizeof(int32_t),
-                                 hipMemcpyHostToDevice, e->s_read));
+        const unsigned g = std::min(64u, ((unsigned)n + dkv::kThreads - 1) / dkv::kThreads);
+        hipLaunchKernelGGL(dkv::kv_reader_begin_kernel, dim3(g), dim3(dkv::kThreads), 0, e->s_read, e->read_ids_host,
+                           e->read_ids, p.n, p.next);
+        HIPTRY(e, hipGetLastError());
     }
-    // Measured per pass over 37.5 GiB, TB/s by workgroups per CU (claims of 32
-    // tiles): 4 -> 5.70, 5 -> 6.56, 5.5 -> 6.68, 6 -> 6.75, 8 -> 6.85.  From 6 per
-    // CU on the persistent workgroups hold so much of every CU for a whole pass
-    // (~6 ms) that another kernel's waves wait for the pass to end before they
-    // start, which no model execution made of many short kernels would do to a
-    // rotation; 5.5 per CU gives up 2 % and leaves that room.
-    int wgs = 11 * (e->n_cus > 0 ? e->n_cus : 256) / 2;
+    int wgs = most_wgs;
     if (max_wgs > 0) wgs = std::min(wgs, (int)max_wgs);
     wgs = (int)std::min<uint32_t>((uint32_t)wgs, std::max<uint32_t>(p.tiles, 1u));
+    // Who reads which tile.  Short passes (under four rounds of the grid): every workgroup
+    // takes its fixed share, no counter.  Longer ones: half in fixed shares, the rest
+    // claimed.  (37.5 GiB passes, TB/s alone / beside a rotation / beside a swap-out: all
+    // claimed 6.38 / 5.09 / 5.87; half 6.69 / 5.36 / 6.09; all fixed 6.77 / 4.66 / 2.94,
+    // where the workgroups that the copy slows set the pace.)
+    const uint32_t rounds = p.tiles / (uint32_t)wgs;
+    p.fixed = rounds < 4 ? rounds + 1 : rounds / 2;
+    const bool rows = p.vec_per_seg % dkv::kWave == 0;
     HIPTRY(e, hipEventRecord(e->read_ev[0], e->s_read));
     for (int32_t k = 0; k < passes; k++) {
         if (p.tiles > 0) {
-            p.next = reinterpret_cast<unsigned int *>(e->read_acc + 1) + k;
-            hipLaunchKernelGGL((dkv::kv_reader_kernel<U>), dim3((unsigned)wgs), dim3(dkv::kThreads), 0, e->s_read, p);
+            p.pass = (uint32_t)k;
+            if (rows)
+                hipLaunchKernelGGL((dkv::kv_reader_kernel<true>), dim3((unsigned)wgs), dim3(dkv::kThreads), 0, e->s_read, p,
+                                   e->read_ids);
+            else
+                hipLaunchKernelGGL((dkv::kv_reader_kernel<false>), dim3((unsigned)wgs), dim3(dkv::kThreads), 0, e->s_read, p,
+                                   e->read_ids);
             HIPTRY(e, hipGetLastError());
         }
         HIPTRY(e, hipEventRecord(e->read_ev[(size_t)k + 1], e->s_read));
     }
-    HIPTRY(e, hipMemcpyAsync(e->read_acc_host, e->read_acc, sizeof(unsigned long long), hipMemcpyDeviceToHost,
-                             e->s_read));
+    e->read_wgs = p.tiles > 0 ? wgs : 0;
     e->read_passes = passes;
     return KV_OK;
 }
@@ -1607,7 +1627,9 @@ int kv_reader_wait(kv_engine *e, uint64_t *checksum, double *ms_per_pass)
     if (e->sticky != KV_OK) return e->sticky;
     if (e->read_passes == 0) return KV_EINVAL;
     HIPTRY(e, hipStreamSynchronize(e->s_read));
-    *checksum = (uint64_t)*e->read_acc_host;
+    uint64_t sum = 0;
+    for (int w = 0; w < e->read_wgs; w++) sum += e->read_sums[w];
+    *checksum = sum;
     if (ms_per_pass) {
         for (int32_t k = 0; k < e->read_passes; k++) {
             float ms = 0;

@@ -64,6 +64,7 @@ struct Hazards {
 };
 
 constexpr int kRing = 8;  // descriptor sets that may be in flight
+constexpr int kReadPasses = 256;  // most passes of one kv_reader_start
 // Tile counters of the link-bound kernels: one pair per stream (launches on a
 // stream run one after the other), each pair in a 256-byte stretch of its own.
 constexpr int kClaimStride = 64;
@@ -146,8 +147,9 @@ struct kv_engine {
     hipStream_t s_read = nullptr;
     int32_t *read_ids = nullptr;               // device, 2 * n_hbm_blocks ints
     int32_t *read_ids_host = nullptr;          // pinned
-    unsigned long long *read_acc = nullptr;    // device: [0] sum, then one 32-bit tile counter per pass
-    unsigned long long *read_acc_host = nullptr;  // pinned
+    unsigned long long *read_part = nullptr;   // device: one sum per workgroup, then the tile counters
+    unsigned long long *read_sums = nullptr;   // pinned: one sum per workgroup over all passes
+    int read_wgs = 0;                          // workgroups of the reader under way
     std::vector<hipEvent_t> read_ev;           // passes + 1 timestamps
     int32_t read_passes = 0;
 };

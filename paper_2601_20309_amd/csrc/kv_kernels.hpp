@@ -408,80 +408,201 @@ __global__ __launch_bounds__(kThreads) void kv_stage_kernel(const StageParams p,
 
 // Synthetic decode reader: streams every segment of the named blocks, plane by
 // plane (layer-major, as attention over the running requests would), and adds
-// up all 32-bit words modulo 2^64.  HBM-bound; read-only.  One tile is
-// kThreads * U 16-byte vectors of one segment.  Persistent workgroups claim
-// runs of kReadClaim tiles from a counter, in tile order, so at any moment the
-// chip streams one contiguous front of the cache, and a CU that is slowed by a
-// co-running kernel simply claims less (with a fixed share per workgroup the
-// slowest CU sets the pace of the whole pass).  One short-lived workgroup per
-// few tiles, left to the hardware dispatcher, measured 27 % slower.  The loads
-// are non-temporal (nothing is read twice): worth 3 % when the blocks come in
-// random order and 16 % on the block-first cache, whose segments lie a whole
-// block apart (5.54 -> 6.43 TB/s), nothing on consecutive blocks.
+// up all 32-bit words modulo 2^64.  HBM-bound; read-only.
+//
+// The bytes to read are one flat sequence of 16-byte vectors, [plane][block][vector],
+// cut into tiles of kReadRows rows of 64 vectors (32 KiB, 8 KiB per wave), so a
+// tile is full whatever the segment size.  (Tiles that ended with their segment
+// read 1500 blocks of 64 x 4 KiB in 243 us, 1/8 of each tile used; 68 us = 5.8
+// TB/s now.)
+//
+// A wave has kReadDepth rows in flight.  One is right: 22 waves per CU with a row
+// each are 5.6 MiB over the chip, which is the HBM rate times its latency.  More
+// only queue in front of HBM, and a copy over the link that runs beside the
+// reader stands in the same queues: eight rows per wave read 6.6 TB/s alone like
+// one does, but take a rotation beside them from 100 to 58 GB/s (one: 100.0).
+//
+// No two workgroups meet on an address while they read.  An atomic on one address
+// is served every ~14 ns: one counter for the tiles limits claims to 2.3 TB/s per
+// 32 KiB, and one sum for all waves (5632 atomics) ended every pass with ~80 us
+// of waiting.  So the tiles of a pass are claimed from kReadGroups counters, and
+// each workgroup leaves its sum in a place of its own.
 struct ReadParams {
     const uint8_t *hbm;
-    const int32_t *ids;
-    unsigned long long *acc;  // one 64-bit accumulator in device memory
+    unsigned long long *part;    // one sum per workgroup, in device memory, from pass to pass
+    unsigned long long *result;  // the same in pinned host memory: where the last pass leaves them
     uint64_t hbm_block_stride;
     uint64_t hbm_plane_stride;
+    uint64_t n_vecs;         // n * n_planes * vec_per_seg
+    uint64_t seg_magic;      // ceil(2^64 / vec_per_seg) where that divides every n_vecs' index exactly, else 0
     uint32_t n;              // blocks
-    uint32_t n_planes;
     uint32_t vec_per_seg;    // seg_bytes / 16
-    uint32_t tiles_per_seg;
-    uint32_t tiles;          // n * n_planes * tiles_per_seg
-    unsigned int *next;      // tile counter of this pass, zero at launch
+    uint32_t tiles;
+    uint32_t fixed;          // tiles each workgroup takes without asking (see kv_reader_kernel)
+    uint32_t pass, passes;   // pass 0: part[] holds nothing yet, the counters are zero
+    unsigned int *next;      // kReadGroups counters, kReadStride apart, of claimed tiles
 };
 
-// Tiles a workgroup claims per turn.  One counter serves the whole chip, and at
-// 6.5 TB/s a 32 KiB tile lasts 5 ns: measured over 37.5 GiB, 5.5 workgroups per
-// CU, TB/s by claim size: 2 -> 4.65, 4 -> 6.51, 8 -> 6.65, 16 -> 6.74, 32 -> 6.68,
-// 64 -> 6.62, 128 -> 6.53 (beyond 16 the pass ends more raggedly than the counter
-// saves).
-constexpr uint32_t kReadClaim = 16;
-constexpr uint32_t kReadClaimTail = 4;  // within the last 2 * kReadClaim tiles per workgroup of a pass
+constexpr int kReadU = 8;      // rows per wave and tile
+constexpr int kReadDepth = 1;  // rows in flight per wave
+constexpr uint32_t kReadRows = (uint32_t)kReadU * (kThreads / kWave);  // rows per tile
+constexpr uint32_t kReadVecs = kReadRows * kWave;                      // vectors per tile
+// Counters.  Workgroups that follow one another share one: they lie on different
+// XCDs, so a group loses as much to a copy beside it as any other (every 64th
+// workgroup instead, all on one XCD: 3.5 instead of 6.1 TB/s beside a swap-out).
+// Fewer groups meet more often on their counter (8: 6.44 TB/s alone, 64: 6.69).
+constexpr uint32_t kReadGroups = 64;
+constexpr uint32_t kReadStride = 32;  // 32-bit words from one counter to the next
 
-template <int U>
-__global__ __launch_bounds__(kThreads) void kv_reader_kernel(const ReadParams p)
-{
-    const uint32_t tid = threadIdx.x;
-    unsigned long long sum = 0;
-    __shared__ uint32_t claimed;
-    // near the end of the pass the claims get short, so that the workgroups end
-    // within a few tiles of each other (a long last claim on a slowed CU would
-    // hold up the whole pass)
-    const uint32_t tail = 2u * kReadClaim * gridDim.x, short_from = p.tiles > tail ? p.tiles - tail : 0u;
-    uint32_t want = short_from ? kReadClaim : kReadClaimTail;
-    for (;;) {
-        if (tid == 0) claimed = atomicAdd(p.next, want);
-        __syncthreads();
-        const uint32_t t0 = claimed;
-        __syncthreads();
-        if (t0 >= p.tiles) break;
-        const uint32_t t1 = min(p.tiles, t0 + want);
-        want = t1 < short_from ? kReadClaim : kReadClaimTail;
-        for (uint32_t t = t0; t < t1; t++) {
-        const uint32_t segidx = t / p.tiles_per_seg;
-        const uint32_t tin = t - segidx * p.tiles_per_seg;
-        const uint32_t pl = segidx / p.n;
-        const uint32_t i = segidx - pl * p.n;
-        const u32x4 *src = reinterpret_cast<const u32x4 *>(
-            p.hbm + (uint64_t)pl * p.hbm_plane_stride + (uint64_t)(uint32_t)p.ids[i] * p.hbm_block_stride);
-        const uint32_t v0 = tin * (kThreads * U) + tid;
-        u32x4 v[U];
-#pragma unroll
-        for (int u = 0; u < U; u++) {
-            const uint32_t vi = v0 + u * kThreads;
-            v[u] = vi < p.vec_per_seg ? __builtin_nontemporal_load(src + vi) : u32x4{0u, 0u, 0u, 0u};
-        }
-#pragma unroll
-        for (int u = 0; u < U; u++)
-            sum += (unsigned long long)v[u].x + v[u].y + (unsigned long long)v[u].z + v[u].w;
-        }
+// Quotient of a lane's small step past a segment's (or the list's) first entry,
+// x < d + 64 * kReadU, without a branch: at d >= 64 * kReadU it is 0 or 1; below,
+// the rounded-up reciprocal is exact because x * d < 2^32 (and 1 has none that
+// fits, there the quotient is x).
+struct SmallDiv {
+    uint32_t d, big, magic, one;
+    __device__ __forceinline__ explicit SmallDiv(uint32_t div)
+        : d(div), big(div >= (uint32_t)(kWave * kReadU) ? div : ~0u),
+          magic(div >= (uint32_t)(kWave * kReadU) || div == 1u ? 0u : ~0u / div + 1u), one(div == 1u ? ~0u : 0u)
+    {
     }
-    // wave reduction, then one atomic per wave
+    __device__ __forceinline__ uint32_t quotient(uint32_t x) const
+    {
+        return (x >= big ? 1u : 0u) + __umulhi(x, magic) + (x & one);
+    }
+};
+
+// One wave's share of tile t: kReadU rows.  ROWS: segments are whole rows, so a
+// row has one block id, fetched with a scalar load.  Otherwise rows straddle
+// segments and every lane finds its own block and fetches its id itself.  All
+// ids are fetched before the first row is.  Past the end of the sequence a row
+// (or a lane) repeats the last one that exists, so that no load is conditional,
+// and is left out of the sum.  The loads are non-temporal (nothing is read
+// twice): worth 16 % on the block-first cache, whose segments lie a whole block apart.
+template <bool ROWS>
+__device__ __forceinline__ unsigned long long read_tile(const ReadParams &p, const int32_t *__restrict__ ids, uint32_t t,
+                                                         uint32_t wave, uint32_t lane)
+{
+    const uint32_t row0 = t * kReadRows + wave * (uint32_t)kReadU;
+    const uint64_t g0 = (uint64_t)row0 * kWave;
+    if (g0 >= p.n_vecs) return 0;
+    // vectors from this wave's first to the end, as far as they matter here
+    const uint32_t left = (uint32_t)min(p.n_vecs - g0, (uint64_t)(kReadU * kWave));
+    const u32x4 *src[kReadU];
+    if constexpr (ROWS) {
+        const uint32_t rps = p.vec_per_seg / kWave, n_rows = left / kWave;
+        const uint32_t segidx = __builtin_amdgcn_readfirstlane(row0 / rps);
+        uint32_t pl = __builtin_amdgcn_readfirstlane(segidx / p.n);
+        uint32_t r = row0 - segidx * rps, i = segidx - pl * p.n;
+        uint32_t id[kReadU], plane[kReadU], at[kReadU];
+#pragma unroll
+        for (uint32_t u = 0; u < (uint32_t)kReadU; u++) {
+            id[u] = (uint32_t)ids[i];
+            plane[u] = pl;
+            at[u] = r;
+            const uint32_t step = u + 1u < n_rows ? 1u : 0u;  // the last row that exists stays
+            r += step;
+            const uint32_t wrap = r == rps ? 1u : 0u;
+            r = wrap ? 0u : r;
+            i += wrap;
+            const uint32_t next_plane = i == p.n ? 1u : 0u;
+            i = next_plane ? 0u : i;
+            pl += next_plane;
+        }
+#pragma unroll
+        for (int u = 0; u < kReadU; u++)
+            src[u] = reinterpret_cast<const u32x4 *>(p.hbm + (uint64_t)plane[u] * p.hbm_plane_stride +
+                                                     (uint64_t)id[u] * p.hbm_block_stride) + at[u] * kWave + lane;
+    } else {
+        const uint32_t segidx = (uint32_t)(p.seg_magic ? __umul64hi(g0, p.seg_magic) : g0 / p.vec_per_seg);
+        const uint32_t off0 = (uint32_t)(g0 - (uint64_t)segidx * p.vec_per_seg);
+        const uint32_t pl0 = __builtin_amdgcn_readfirstlane(segidx / p.n), i0 = segidx - pl0 * p.n;
+        const SmallDiv by_seg(p.vec_per_seg), by_list(p.n);
+        const uint32_t last = left - 1u;
+        uint32_t id[kReadU], plane[kReadU], at[kReadU];
+#pragma unroll
+        for (int u = 0; u < kReadU; u++) {
+            const uint32_t x = off0 + min(u * kWave + lane, last), s = by_seg.quotient(x);
+            const uint32_t y = i0 + s, w = by_list.quotient(y);
+            id[u] = (uint32_t)ids[y - w * p.n];
+            plane[u] = pl0 + w;
+            at[u] = x - s * p.vec_per_seg;
+        }
+#pragma unroll
+        for (int u = 0; u < kReadU; u++)
+            src[u] = reinterpret_cast<const u32x4 *>(p.hbm + (uint64_t)plane[u] * p.hbm_plane_stride +
+                                                     (uint64_t)id[u] * p.hbm_block_stride) + at[u];
+    }
+    unsigned long long sum = 0;
+#pragma unroll
+    for (int u0 = 0; u0 < kReadU; u0 += kReadDepth) {
+        u32x4 v[kReadDepth];
+#pragma unroll
+        for (int k = 0; k < kReadDepth; k++) v[k] = __builtin_nontemporal_load(src[u0 + k]);
+#pragma unroll
+        for (int k = 0; k < kReadDepth; k++) {
+            const unsigned long long s = (unsigned long long)v[k].x + v[k].y + (unsigned long long)v[k].z + v[k].w;
+            sum += (u0 + k) * kWave + lane < left ? s : 0ull;
+        }
+        asm volatile("" : "+v"(sum));  // the next loads are not issued before these have arrived
+    }
+    return sum;
+}
+
+template <bool ROWS>
+__global__ __launch_bounds__(kThreads) void kv_reader_kernel(const ReadParams p, const int32_t *__restrict__ ids)
+{
+    const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1u);
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    __shared__ uint32_t claimed[2];
+    __shared__ unsigned long long sums[kThreads / kWave];
+    // first the fixed share, a tile every gridDim.x ...
+    const uint32_t n_fixed = (uint32_t)min((uint64_t)p.fixed * gridDim.x, (uint64_t)p.tiles);
+    // ... then tiles n_fixed + group + n_groups * c, c drawn from the group's counter.
+    // A pass takes one draw per tile and one more per workgroup from it, so where the
+    // counter stands when a later pass begins is known and it is never reset.
+    const uint32_t per_group = (gridDim.x + kReadGroups - 1u) / kReadGroups, group = blockIdx.x / per_group;
+    const uint32_t n_groups = (gridDim.x + per_group - 1u) / per_group, shared = p.tiles - n_fixed;
+    const uint32_t n_claims = (shared + n_groups - 1u - group) / n_groups;
+    const uint32_t members = min(per_group, gridDim.x - group * per_group);
+    const uint32_t base = p.pass * (n_claims + members);
+    unsigned int *const next = p.next + group * kReadStride;
+    // the next claim is always in flight while the tile before it is read
+    uint32_t pending = 0;
+    if (shared && tid == 0) pending = atomicAdd(next, 1u);
+    unsigned long long sum = 0;
+    uint32_t t = blockIdx.x, end = n_fixed;
+    for (uint32_t turn = 0;; turn ^= 1u) {
+        for (; t < end; t += gridDim.x) sum += read_tile<ROWS>(p, ids, t, wave, lane);
+        if (!shared) break;
+        if (tid == 0) claimed[turn] = pending - base;
+        __syncthreads();  // one per claim: the two slots alternate
+        const uint32_t c = __builtin_amdgcn_readfirstlane(claimed[turn]);
+        if (c >= n_claims) break;
+        if (tid == 0) pending = atomicAdd(next, 1u);
+        t = n_fixed + group + n_groups * c;
+        end = t + 1u;
+    }
+    // one sum per workgroup, in a place of its own (the host adds them up)
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) sum += __shfl_down(sum, off, 64);
-    if ((tid & 63u) == 0) atomicAdd(p.acc, sum);
+    if (lane == 0) sums[wave] = sum;
+    __syncthreads();
+    if (tid == 0) {
+        for (int w = 1; w < kThreads / kWave; w++) sum += sums[w];
+        if (p.pass > 0) sum += p.part[blockIdx.x];
+        if (p.pass + 1u < p.passes) p.part[blockIdx.x] = sum;
+        else __builtin_nontemporal_store(sum, p.result + blockIdx.x);
+    }
+}
+
+// Before the passes: the id list from pinned host memory to the device, the
+// counters to zero.
+__global__ __launch_bounds__(kThreads) void kv_reader_begin_kernel(const int32_t *__restrict__ from, int32_t *__restrict__ ids,
+                                                                   uint32_t n, unsigned int *next)
+{
+    const uint32_t t = blockIdx.x * kThreads + threadIdx.x;
+    for (uint32_t i = t; i < n; i += gridDim.x * kThreads) ids[i] = from[i];
+    if (t < kReadGroups) next[t * kReadStride] = 0u;
 }
 
 }  // namespace dkv

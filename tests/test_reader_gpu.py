@@ -6,7 +6,7 @@ import pytest
 from oracle import kv_oracle as O
 from paper_2601_20309_amd import binding as B
 from paper_2601_20309_amd import workloads as W
-from tests.gpu_harness import make_case
+from tests.gpu_harness import GpuCase, make_case
 
 pytestmark = pytest.mark.gpu
 
@@ -64,3 +64,24 @@ def test_reader_on_block_first_cache():
     rc, got, _ = case.eng.kv_reader_wait()
     assert rc == 0 and got == (2 * want) % (1 << 64)
     case.close()
+
+
+@pytest.mark.parametrize("vecs", [1, 3, 63, 64, 65, 192, 511, 512, 513, 2049])
+def test_reader_tiles_that_span_segments(vecs):
+    """Segments of `vecs` 16-byte vectors: a tile (2048 vectors, rows of 64) begins and
+    ends inside segments, spans many, or is one of several in a segment; lists of
+    one block, with repeats, and long enough that workgroups claim tiles beyond
+    their fixed share (few workgroups).  A sum of whole numbers: equal or wrong."""
+    sh = W.KVShape(2, 1, 8 * vecs, 1, n_hbm_blocks=max(24, 12288 // vecs), n_host_slots=4)
+    rng = np.random.default_rng(vecs)
+    cache = rng.integers(0, 65536, 4 * sh.n_hbm_blocks * 8 * vecs, dtype=np.uint16)
+    for hbm_layout in (B.KV_HBM_LAYER_FIRST, B.KV_HBM_BLOCK_FIRST):
+        case = GpuCase(sh, B.KV_HOST_BLOCK_FIRST, B.KV_PATH_AUTO, cache, cache[:4 * 4 * 8 * vecs], hbm_layout=hbm_layout)
+        every = rng.permutation(sh.n_hbm_blocks)
+        for ids, passes, wgs in [(every, 2, 0), (every, 3, 1), (every, 1, 3), (every[:1], 2, 0),
+                                 (np.array([5, 5, 7, 5]), 1, 0), (every[:-3], 2, 2)]:
+            rc, want = O.read_checksum(case.oshape, case.ref_cache.view(np.uint8), ids)
+            assert rc == 0 and case.eng.kv_reader_start(ids, passes, wgs) == 0
+            rc, got, _ = case.eng.kv_reader_wait()
+            assert rc == 0 and got == (want * passes) % (1 << 64), (hbm_layout, len(ids), passes, wgs)
+        case.close()
