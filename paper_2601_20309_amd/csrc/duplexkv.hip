@@ -147,15 +147,20 @@ struct MoveIds {
     const int32_t *out_ids, *out_slots, *in_ids, *in_slots;
 };
 
-// `wgs` workgroups of `lanes` lanes; the waves among them are the workers, and
-// no more of them are launched than the launch has steps.
+// A launch's shape: workgroups, lanes per workgroup, vectors per lane per tile;
+// short_steps: with no more steps than this, a wave per step; limit_u: the
+// vectors per lane by which dir_tiles() counts.
+struct LinkShape { int wgs, lanes, u, short_steps, limit_u; };
+
+// The waves of the launch are the workers, and no more of them are launched than
+// it has steps.
 template <int U, bool LINK>
-void launch_move_v(int vec, int wgs, int lanes, hipStream_t s, const MoveParams &p, const MoveIds &d)
+void launch_move_v(int vec, const LinkShape &sh, hipStream_t s, const MoveParams &p, const MoveIds &d)
 {
     const uint32_t steps = p.mix_q ? p.in.tiles : std::max(p.out.tiles, p.in.tiles);
-    const uint32_t waves_per_wg = (uint32_t)lanes / dkv::kWave;
-    wgs = (int)std::max<uint32_t>(1u, std::min<uint32_t>((uint32_t)wgs, (steps + waves_per_wg - 1) / waves_per_wg));
-    dim3 g((unsigned)wgs), b((unsigned)lanes);
+    const uint32_t waves_per_wg = (uint32_t)sh.lanes / dkv::kWave, most = (steps + waves_per_wg - 1) / waves_per_wg;
+    const uint32_t wgs = steps <= (uint32_t)sh.short_steps ? most : std::min<uint32_t>((uint32_t)sh.wgs, most);
+    dim3 g(std::max(1u, wgs)), b((unsigned)sh.lanes);
 #define DKV_LAUNCH(V) \
     hipLaunchKernelGGL((dkv::kv_move_kernel<V, U, LINK>), g, b, 0, s, p, d.out_ids, d.out_slots, d.in_ids, d.in_slots)
     switch (vec) {
@@ -169,21 +174,21 @@ void launch_move_v(int vec, int wgs, int lanes, hipStream_t s, const MoveParams 
 }
 
 // link: the far side is host memory (zero-copy paths); else HBM staging.
-void launch_move(int u, int vec, int wgs, int lanes, hipStream_t s, const MoveParams &p, const MoveIds &d, bool link)
+void launch_move(const LinkShape &sh, int vec, hipStream_t s, const MoveParams &p, const MoveIds &d, bool link)
 {
     if (link) {
-        switch (u) {
-        case 1: launch_move_v<1, true>(vec, wgs, lanes, s, p, d); break;
-        case 2: launch_move_v<2, true>(vec, wgs, lanes, s, p, d); break;
-        case 4: launch_move_v<4, true>(vec, wgs, lanes, s, p, d); break;
-        default: launch_move_v<8, true>(vec, wgs, lanes, s, p, d); break;
+        switch (sh.u) {
+        case 1: launch_move_v<1, true>(vec, sh, s, p, d); break;
+        case 2: launch_move_v<2, true>(vec, sh, s, p, d); break;
+        case 4: launch_move_v<4, true>(vec, sh, s, p, d); break;
+        default: launch_move_v<8, true>(vec, sh, s, p, d); break;
         }
     } else {
-        switch (u) {
-        case 1: launch_move_v<1, false>(vec, wgs, lanes, s, p, d); break;
-        case 2: launch_move_v<2, false>(vec, wgs, lanes, s, p, d); break;
-        case 4: launch_move_v<4, false>(vec, wgs, lanes, s, p, d); break;
-        default: launch_move_v<8, false>(vec, wgs, lanes, s, p, d); break;
+        switch (sh.u) {
+        case 1: launch_move_v<1, false>(vec, sh, s, p, d); break;
+        case 2: launch_move_v<2, false>(vec, sh, s, p, d); break;
+        case 4: launch_move_v<4, false>(vec, sh, s, p, d); break;
+        default: launch_move_v<8, false>(vec, sh, s, p, d); break;
         }
     }
 }
@@ -199,20 +204,38 @@ void hbm_strides(const kv_engine *e, uint64_t &plane_stride, uint64_t &block_str
     }
 }
 
-// Fills the fields common to every launch; `u` = vectors per lane per tile.
-MoveParams base_params(const kv_engine *e, int u)
+// Fills the fields common to every launch.
+MoveParams base_params(const kv_engine *e)
 {
     MoveParams p{};
     p.hbm = e->hbm;
-    p.seg_bytes = e->seg;
     hbm_strides(e, p.hbm_plane_stride, p.hbm_block_stride);
+    p.plane_skip = p.hbm_plane_stride - e->seg;
     p.plane0 = 0;
     p.n_planes = e->n_planes;
     p.vec_per_seg = (uint32_t)(e->seg / (uint64_t)e->vec);
-    const uint32_t tile = (uint32_t)dkv::kWave * (uint32_t)u;
-    p.tiles_per_seg = (p.vec_per_seg + tile - 1) / tile;
-    p.full_tiles = p.vec_per_seg % tile == 0 ? 1u : 0u;
     return p;
+}
+
+// Vectors of one group (see MoveParams) over `planes` planes.  Segments that are
+// whole tiles are groups by themselves; others are joined to the whole entry where
+// the far side holds it in one piece.
+uint64_t group_vecs(uint64_t vec_per_seg, uint32_t planes, bool plane_major, bool whole)
+{
+    const uint64_t entry = vec_per_seg * planes;
+    return whole || plane_major || entry >= 0x7FFFFFFFull ? vec_per_seg : entry;
+}
+
+// Cuts the planes [plane0, plane0 + n_planes) of every entry into tiles of `u` vectors per lane.
+void cut_tiles(MoveParams &p, int u)
+{
+    const bool whole = p.vec_per_seg % ((uint32_t)dkv::kWave * (uint32_t)u) == 0;
+    const uint32_t tile = (uint32_t)dkv::kWave * (uint32_t)(whole ? u : std::min(u, dkv::kMaxRaggedU));
+    p.group_vecs = (uint32_t)group_vecs(p.vec_per_seg, p.n_planes, p.plane_major != 0, whole);
+    p.groups_per_entry = p.group_vecs == p.vec_per_seg ? p.n_planes : 1u;
+    p.by_tiles = dkv::make_div((p.group_vecs + tile - 1) / tile);
+    p.by_seg = p.groups_per_entry == 1 ? dkv::make_div(p.vec_per_seg) : dkv::Div{1, 0, 0};
+    p.full_tiles = whole ? 1u : 0u;
 }
 
 void pool_strides(const kv_engine *e, uint64_t &slot_stride, uint64_t &plane_stride)
@@ -234,6 +257,22 @@ bool dir_tiles(uint32_t n, uint32_t planes, uint32_t tiles_per_seg, uint32_t &ti
     if (t >= 0x7FFFFFFFull) return false;
     tiles = (uint32_t)t;
     return true;
+}
+
+// The same for a launch whose tiles are cut; the limit is that of tiles of
+// `limit_u` vectors per lane, each within a segment.
+bool dir_tiles(const MoveParams &p, uint32_t n, int limit_u, uint32_t &tiles)
+{
+    const uint32_t tile = (uint32_t)dkv::kWave * (uint32_t)limit_u;
+    return dir_tiles(n, p.n_planes, (p.vec_per_seg + tile - 1) / tile, tiles) &&
+           dir_tiles(n, p.groups_per_entry, p.by_tiles.d, tiles);
+}
+
+// One direction's list of n entries, its tiles counted; false if they are too many.
+bool fill_dir(const MoveParams &p, uint32_t n, uint32_t iota, int limit_u, DirDesc &d)
+{
+    d = DirDesc{n, 0, iota, dkv::make_div(std::max(1u, p.plane_major ? n : p.groups_per_entry))};
+    return dir_tiles(p, n, limit_u, d.tiles);
 }
 
 int acquire_ring(kv_engine *e, int &k)
@@ -324,27 +363,61 @@ int mark_end(kv_engine *e, bool out_side, int k, hipStream_t s)
 // A configured vecs_per_lane is kept (the wave count follows it); max_copy_wgs
 // counts workgroups of wg_lanes lanes and set alone keeps 256-lane workgroups;
 // wg_lanes set alone keeps the number of waves.
+//
+// Segments that no tile divides are moved in tiles that span segments where the
+// pool holds a block in one piece, and keep the vectors per lane above unless
+// those would leave more than an eighth of the tiles empty; otherwise tiles end
+// with their segment.  Either way the waves are as many more as the tiles are
+// emptier, so that as many bytes are in flight.  (Segments of 1200 bytes, 701 of
+// 57600-byte blocks out and 633 in: tiles of one segment, 11 of the second one's
+// 64 lanes used, 1001 us; 846 us now.)  Vectors narrower than 16 bytes (odd
+// segments or pointers) get more of them per lane for the same reason.
 enum LinkKind { kBoth, kInHeavy, kOutOnly, kInOnly };
-struct LinkShape { int wgs, lanes, u; };
+// A launch of no more than kShortKib per direction gets a wave per tile: no step
+// counter (its atomics, ~14 ns each on one address, are as long as the transfer),
+// no second round trip over the link, and what a co-runner loses lasts no longer
+// than the link needs for it, 10 us.  (12 launches of 32 KiB: 134 us with 112 waves
+// that draw, 111 us; 8 + 8 blocks of 16 KiB: 33.6 and 31.5 us.)
+constexpr int kShortKib = 512;
 
 LinkShape link_shape(const kv_engine *e, LinkKind kind)
 {
     const int cw = e->cfg.max_copy_wgs, cl = e->cfg.wg_lanes, cu = e->cfg.vecs_per_lane;
+    const uint64_t vec_per_seg = e->seg / (uint64_t)e->vec;
+    const bool plane_major = e->cfg.host_layout == KV_HOST_LAYER_FIRST;
+    const uint32_t planes = e->cfg.chunk_layers > 0 ? std::min(2u * (uint32_t)e->cfg.chunk_layers, e->n_planes) : e->n_planes;
     int u = cu ? cu : (kind == kOutOnly ? 8 : kind == kInOnly || kind == kInHeavy ? 4 : 1);
-    if (!cu) {  // whole tiles only: the segment must be a multiple of the tile
-        const uint64_t vec_per_seg = e->seg / (uint64_t)e->vec;
-        while (u > 1 && vec_per_seg % ((uint64_t)dkv::kWave * (uint64_t)u) != 0) u >>= 1;
+    int limit_u = u, kib = u;  // kib: KiB per tile and direction that the table below is looked up by
+    double fill = 1.0;         // share of a tile that is not padding, on average
+    if (!cu) {
+        if (vec_per_seg % dkv::kWave == 0) {  // whole tiles only: the segment must be a multiple of the tile
+            while (u > 1 && vec_per_seg % ((uint64_t)dkv::kWave * (uint64_t)u) != 0) u >>= 1;
+            limit_u = u;
+        } else {
+            limit_u = 1;
+            u = std::min(dkv::kMaxRaggedU, u * 16 / e->vec);
+            auto filled = [&](int w) {
+                const uint64_t tile = (uint64_t)dkv::kWave * (uint64_t)w, g = group_vecs(vec_per_seg, planes, plane_major, false);
+                return (double)g / (double)((g + tile - 1) / tile * tile);
+            };
+            while (u > 1 && filled(u) < 0.875) u >>= 1;
+            fill = filled(u);
+        }
+        kib = u * e->vec / 16;
     }
     int waves;
     switch (kind) {
-    case kOutOnly: waves = u >= 8 ? 12 : u == 4 ? 16 : u == 2 ? 32 : 64; break;
-    case kInOnly: waves = u >= 8 ? 16 : u == 4 ? 24 : u == 2 ? 44 : 80; break;
-    default: waves = u >= 8 ? 20 : u == 4 ? 32 : u == 2 ? 64 : 112; break;  // kBoth and kInHeavy differ in u
+    case kOutOnly: waves = kib >= 8 ? 12 : kib >= 4 ? 16 : kib >= 2 ? 32 : 64; break;
+    case kInOnly: waves = kib >= 8 ? 16 : kib >= 4 ? 24 : kib >= 2 ? 44 : 80; break;
+    default: waves = kib >= 8 ? 20 : kib >= 4 ? 32 : kib >= 2 ? 64 : 112; break;  // kBoth and kInHeavy differ in u
     }
+    waves = (int)(waves * std::min(4.0, 1.0 / fill));
     LinkShape s;
     s.u = u;
+    s.limit_u = limit_u;
     s.lanes = cl ? cl : (cw ? dkv::kThreads : dkv::kWave);
     s.wgs = cw ? cw : std::max(1, waves * dkv::kWave / s.lanes);
+    s.short_steps = cw || cl || cu ? 0 : kShortKib / std::max(1, kib);
     return s;
 }
 
@@ -390,10 +463,11 @@ int launch_link(kv_engine *e, const LinkShape &sh, hipStream_t s, const MovePara
         MoveParams q = whole;
         q.plane0 = p0;
         q.n_planes = std::min(per_chunk, whole.n_planes - p0);
-        q.out.tiles = q.out.n * q.n_planes * q.tiles_per_seg;  // fits: the whole call's count was checked
-        q.in.tiles = q.in.n * q.n_planes * q.tiles_per_seg;
+        cut_tiles(q, sh.u);
+        // fits: the whole call's counts were checked
+        if (!fill_dir(q, q.out.n, 0, sh.limit_u, q.out) || !fill_dir(q, q.in.n, 0, sh.limit_u, q.in)) return KV_EUNSUP;
         q.mix_q = whole.mix_q && q.out.tiles ? (((uint64_t)q.out.tiles << 32) + q.in.tiles - 1) / q.in.tiles : 0;
-        launch_move(sh.u, e->vec, sh.wgs, sh.lanes, s, q, ids, true);
+        launch_move(sh, e->vec, s, q, ids, true);
         HIPTRY(e, hipGetLastError());
         e->acc.n_launches += 1;
         if (ev) HIPTRY(e, hipEventRecord((*ev)[c], s));
@@ -406,7 +480,7 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
     int32_t *dh = e->desc_host + (size_t)k * e->desc_cap;
     const bool fused = path == KV_PATH_FUSED && no > 0 && ni > 0;
     auto params = [&](int u, unsigned int *claim) {
-        MoveParams q = base_params(e, u);
+        MoveParams q = base_params(e);
         q.claim = claim;
         q.far_out = e->pool;
         q.far_in = e->pool;
@@ -414,6 +488,7 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
         q.far_slot_stride_in = q.far_slot_stride_out;
         q.far_plane_stride_in = q.far_plane_stride_out;
         q.plane_major = e->cfg.host_layout == KV_HOST_LAYER_FIRST ? 1u : 0u;
+        cut_tiles(q, u);
         return q;
     };
     // The link-bound kernels fetch ids and slots with scalar loads.  Where one list
@@ -435,11 +510,7 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
         HIPTRY(e, hipMemcpyAsync(dd + a, dh + a, (b - a) * sizeof(int32_t), hipMemcpyHostToDevice, s));
         return KV_OK;
     };
-    const DirDesc none{0, 0, 0, 0};
-    auto desc = [](const MoveParams &q, int32_t n, DirDesc &d) {
-        d = DirDesc{(uint32_t)n, 0, 0, 0};
-        return dir_tiles((uint32_t)n, q.n_planes, q.tiles_per_seg, d.tiles);
-    };
+    const DirDesc none{};
 
     if (fused) {
         // one launch on stream_out carries both directions; stream_in is joined
@@ -457,7 +528,9 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
         const LinkShape sh_rest = link_shape(e, kOutOnly);
         MoveParams p = params(sh.u, e->claim), p_rest = params(sh_rest.u, e->claim);
         p_rest.in = none;
-        if (!desc(p, no_paired, p.out) || !desc(p, ni, p.in) || !desc(p_rest, n_rest, p_rest.out)) return KV_EUNSUP;
+        if (!fill_dir(p, (uint32_t)no_paired, 0, sh.limit_u, p.out) || !fill_dir(p, (uint32_t)ni, 0, sh.limit_u, p.in) ||
+            !fill_dir(p_rest, (uint32_t)n_rest, 0, sh_rest.limit_u, p_rest.out))
+            return KV_EUNSUP;
         // in list longer: spread the out tiles over it instead of pairing 1:1
         if (p.in.tiles > p.out.tiles)
             p.mix_q = (((uint64_t)p.out.tiles << 32) + p.in.tiles - 1) / p.in.tiles;
@@ -484,7 +557,7 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
         e->layer_on_out = layered;
         e->layer_on_in = false;
         if (n_rest > 0) {
-            launch_move(sh_rest.u, e->vec, sh_rest.wgs, sh_rest.lanes, e->s_out, p_rest,
+            launch_move(sh_rest, e->vec, e->s_out, p_rest,
                         MoveIds{d_o + no_paired, d_o + no + no_paired, nullptr, nullptr}, true);
             HIPTRY(e, hipGetLastError());
             e->acc.n_launches += 1;
@@ -504,13 +577,15 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
     if (no > 0 && ni > 0 && !e->cfg.max_copy_wgs && !e->cfg.wg_lanes && !e->cfg.vecs_per_lane) {
         sh_out.wgs = sh_in.wgs = 9 * (e->n_cus > 0 ? e->n_cus : 256) / 8;
         sh_out.lanes = sh_in.lanes = dkv::kWave;
-        sh_out.u = sh_in.u = 1;
+        sh_out.u = sh_in.u = sh_out.limit_u = sh_in.limit_u = 1;
     }
     const MoveIds ids_out{d_o, d_o + no, nullptr, nullptr}, ids_in{nullptr, nullptr, d_i, d_i + ni};
     // launches on stream_out draw from the first pair of counters, those on stream_in from the second
     MoveParams p_out = params(sh_out.u, e->claim), p_in = params(sh_in.u, e->claim + kClaimStride);
     p_out.in = p_in.out = none;
-    if (!desc(p_out, no, p_out.out) || !desc(p_in, ni, p_in.in)) return KV_EUNSUP;  // before anything is enqueued
+    if (!fill_dir(p_out, (uint32_t)no, 0, sh_out.limit_u, p_out.out) ||
+        !fill_dir(p_in, (uint32_t)ni, 0, sh_in.limit_u, p_in.in))
+        return KV_EUNSUP;  // before anything is enqueued
     // The block table promises that no block or slot is overwritten while an
     // earlier transfer still reads it, and none read while an earlier one still
     // writes it.  Its lists are conflict-free within a call but reuse, across
@@ -712,7 +787,7 @@ int chunk_copies(kv_engine *e, bool to_host, uint8_t *stage, const int32_t *sort
 
 MoveParams stage_params(const kv_engine *e, uint8_t *stage, uint32_t nb, uint32_t p0, uint32_t np, int u)
 {
-    MoveParams p = base_params(e, u);
+    MoveParams p = base_params(e);
     p.plane0 = p0;
     p.n_planes = np;
     p.far_out = p.far_in = stage;
@@ -730,6 +805,7 @@ MoveParams stage_params(const kv_engine *e, uint8_t *stage, uint32_t nb, uint32_
     p.far_out = p.far_in = stage - (uint64_t)p0 * ps;
     p.far_slot_stride_out = p.far_slot_stride_in = ss;
     p.far_plane_stride_out = p.far_plane_stride_in = ps;
+    cut_tiles(p, u);
     return p;
 }
 
@@ -767,6 +843,7 @@ int run_staged(kv_engine *e, int k, const int32_t *oi, const int32_t *os, int32_
     int32_t *d_out = dd, *d_in = dd + 2 * (size_t)no;
     constexpr int U = 4;                         // capped launches: persistent waves, 4 KiB tiles
     const int cap_wgs = e->cfg.max_copy_wgs;     // 0: one wave per 1 KiB tile, kv_stage_kernel
+    const LinkShape capped{cap_wgs, dkv::kThreads, U, 0, U};
     ChunkPlan po{}, pi{};
     if (no > 0) {
         int rc = plan_chunks(e, (uint32_t)no, po);
@@ -821,10 +898,8 @@ int run_staged(kv_engine *e, int k, const int32_t *oi, const int32_t *os, int32_
             const uint32_t p1 = std::min<uint32_t>(co.p0 + po.planes_per_chunk, e->n_planes);
             if (cap_wgs > 0) {
                 MoveParams p = stage_params(e, e->stage_out, j1 - co.j0, co.p0, p1 - co.p0, U);
-                p.out = DirDesc{j1 - co.j0, 0, 1, 0};
-                if (!dir_tiles(p.out.n, p.n_planes, p.tiles_per_seg, p.out.tiles)) return KV_EUNSUP;
-                launch_move(U, e->vec, (int)std::min<uint32_t>((uint32_t)cap_wgs, p.out.tiles), dkv::kThreads, e->s_out,
-                            p, MoveIds{d_out + co.j0, nullptr, nullptr, nullptr}, false);
+                if (!fill_dir(p, j1 - co.j0, 1, U, p.out)) return KV_EUNSUP;
+                launch_move(capped, e->vec, e->s_out, p, MoveIds{d_out + co.j0, nullptr, nullptr, nullptr}, false);
             } else {
                 dkv::StageParams q;
                 if (!stage_kernel_params(e, e->stage_out, j1 - co.j0, co.p0, p1 - co.p0, q)) return KV_EUNSUP;
@@ -846,9 +921,8 @@ int run_staged(kv_engine *e, int k, const int32_t *oi, const int32_t *os, int32_
                 return KV_EHIP;
             if (cap_wgs > 0) {
                 MoveParams p = stage_params(e, e->stage_in, j1 - ci.j0, ci.p0, p1 - ci.p0, U);
-                p.in = DirDesc{j1 - ci.j0, 0, 1, 0};
-                if (!dir_tiles(p.in.n, p.n_planes, p.tiles_per_seg, p.in.tiles)) return KV_EUNSUP;
-                launch_move(U, e->vec, (int)std::min<uint32_t>((uint32_t)cap_wgs, p.in.tiles), dkv::kThreads, e->s_in, p,
+                if (!fill_dir(p, j1 - ci.j0, 1, U, p.in)) return KV_EUNSUP;
+                launch_move(capped, e->vec, e->s_in, p,
                             MoveIds{nullptr, nullptr, d_in + ci.j0, nullptr}, false);
             } else {
                 dkv::StageParams q;
@@ -1411,16 +1485,14 @@ int kv_rotate_static(const kv_config *cfg, void *hbm_cache, void *host_pool, voi
     if (no == 0 && ni == 0) return KV_OK;
     const LinkKind kind = no == 0 ? kInOnly : ni == 0 ? kOutOnly : ni >= 2 * (int64_t)no ? kInHeavy : kBoth;
     const LinkShape sh = link_shape(e, kind);
-    MoveParams p = base_params(e, sh.u);
+    MoveParams p = base_params(e);
     p.far_out = p.far_in = e->pool;
     pool_strides(e, p.far_slot_stride_out, p.far_plane_stride_out);
     p.far_slot_stride_in = p.far_slot_stride_out;
     p.far_plane_stride_in = p.far_plane_stride_out;
     p.plane_major = cfg->host_layout == KV_HOST_LAYER_FIRST ? 1u : 0u;
-    p.out = DirDesc{(uint32_t)no, 0, 0, 0};
-    p.in = DirDesc{(uint32_t)ni, 0, 0, 0};
-    if (!dir_tiles(p.out.n, p.n_planes, p.tiles_per_seg, p.out.tiles) ||
-        !dir_tiles(p.in.n, p.n_planes, p.tiles_per_seg, p.in.tiles))
+    cut_tiles(p, sh.u);
+    if (!fill_dir(p, (uint32_t)no, 0, sh.limit_u, p.out) || !fill_dir(p, (uint32_t)ni, 0, sh.limit_u, p.in))
         return KV_EUNSUP;
     if (p.out.tiles > 0 && p.in.tiles > p.out.tiles)
         p.mix_q = (((uint64_t)p.out.tiles << 32) + p.in.tiles - 1) / p.in.tiles;
@@ -1450,7 +1522,7 @@ int kv_rotate_static(const kv_config *cfg, void *hbm_cache, void *host_pool, voi
         HIPTRY((kv_engine *)nullptr, hipGetLastError());
         done += n;
     }
-    launch_move(sh.u, e->vec, sh.wgs, sh.lanes, s, p,
+    launch_move(sh, e->vec, s, p,
                 MoveIds{ids, ids + no, ids + 2 * (size_t)no, ids + 2 * (size_t)no + ni}, true);
     HIPTRY((kv_engine *)nullptr, hipGetLastError());
     return KV_OK;

@@ -22,16 +22,34 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kWave = 64;          // a wave is the unit of work: one tile at a time
 constexpr int kThreads = 256;      // lanes per workgroup of the HBM-bound launches and of the reader (4 waves)
+// Vectors per lane where a tile may span segments: every vector has pointers of its
+// own there, and with eight they would not fit the registers of a 1024-lane workgroup.
+constexpr int kMaxRaggedU = 4;
 constexpr int kMaxThreads = 1024;  // workgroups only pack waves; any multiple of 64 up to this
+
+// Division by a number that is the same for a whole launch, x < 2^31: a multiply
+// and a shift by host-made constants, on the scalar unit where x is uniform.  (The
+// compiler's own division is ~25 vector instructions; a step has up to six.)
+struct Div {
+    uint32_t d, m, s;
+    __device__ __forceinline__ uint32_t quotient(uint32_t x) const { return __umulhi(x << 1, m) >> s; }
+};
+
+inline Div make_div(uint32_t d)  // 1 <= d < 2^31
+{
+    uint32_t s = 0;
+    while ((1u << s) < d) s++;
+    return Div{d, (uint32_t)(((1ull << (31 + s)) + d - 1) / d), s};  // x * (m * d - 2^(31+s)) < 2^31 * d <= 2^(31+s)
+}
 
 // One direction's block list as the kernel sees it.  The id arrays themselves
 // are separate __restrict__ kernel arguments so that the compiler fetches them
 // with scalar loads (their own counter, off the vector-memory critical path).
 struct DirDesc {
     uint32_t n;      // blocks
-    uint32_t tiles;  // n * n_planes * tiles_per_seg
+    uint32_t tiles;  // n * groups_per_entry * tiles_per_group
     uint32_t iota;   // 1: far-side slot of list entry i is i itself (staging); 0: slots[i]
-    uint32_t pad;
+    Div inner;       // by the faster of the two group indices' range: plane-major n, else groups_per_entry
 };
 
 // Addressing (Section 4.3.1 of the paper: layer x block x segment):
@@ -42,63 +60,66 @@ struct MoveParams {
     uint8_t *hbm;
     uint8_t *far_out;  // destination of the out direction (host pool or staging)
     uint8_t *far_in;   // source of the in direction
-    uint64_t seg_bytes;
     uint64_t hbm_plane_stride;  // layer-first cache: blocks * seg; block-first cache: seg
     uint64_t hbm_block_stride;  // layer-first cache: seg;          block-first cache: planes * seg
     uint64_t far_slot_stride_out, far_plane_stride_out;
     uint64_t far_slot_stride_in, far_plane_stride_in;
     uint32_t plane0;         // first plane this launch covers
     uint32_t n_planes;       // planes this launch covers
-    uint32_t vec_per_seg;    // seg_bytes / sizeof(V)
-    uint32_t tiles_per_seg;  // ceil(vec_per_seg / (64 * U))
-    uint32_t plane_major;    // tile order: 1 = [plane][i][tile], 0 = [i][plane][tile]
-    uint32_t full_tiles;     // 1: vec_per_seg is a multiple of the tile, no lane is ever out of range
+    uint32_t vec_per_seg;    // segment bytes / sizeof(V)
+    // A group is what tiles are cut from: one segment, or (segments that are no whole
+    // number of tiles, far side [i][plane]...) all segments of a list entry, which
+    // are one range on the far side and planes apart in the cache.
+    uint32_t group_vecs;        // vec_per_seg, or n_planes * vec_per_seg
+    uint32_t groups_per_entry;  // n_planes, or 1
+    Div by_tiles;               // by tiles_per_group = ceil(group_vecs / (64 * U))
+    Div by_seg;                 // by vec_per_seg (quotient 0 where a group is one segment)
+    uint32_t plane_major;       // group order: 1 = [plane][i], 0 = [i][plane]
+    uint32_t full_tiles;        // 1: group_vecs is a multiple of the tile and a group one segment
+    uint64_t plane_skip;        // cache bytes between the end of a segment and the same block's next one
     // 0, or ceil(out.tiles * 2^32 / in.tiles) when the in list is the longer one and
     // the out tiles are to be spread evenly over it (see make_job)
     uint64_t mix_q;
-    // nullptr: wave w of W takes tiles w, w + W, ...; else two counters in device
-    // memory, zero at launch, [0] the next unclaimed tile, [1] the waves that are done
+    // link-bound launches: two counters in device memory, zero at launch, [0] the
+    // next unclaimed tile, [1] the waves that are done
     unsigned int *claim;
     DirDesc out, in;
 };
 
 
-// Tile t of direction d -> byte offsets (segment base + tile start) on both sides.
+// Tile t of direction d -> byte offsets of its group on both sides, and its place
+// within the group.
 __device__ __forceinline__ void locate(const MoveParams &p, const DirDesc &d,
                                        const int32_t *__restrict__ ids,
                                        const int32_t *__restrict__ slots, uint32_t t,
                                        uint64_t slot_stride, uint64_t plane_stride,
-                                       uint32_t tile_bytes, uint64_t &hbm_off, uint64_t &far_off)
+                                       uint64_t &hbm_off, uint64_t &far_off, uint32_t &tin)
 {
-    const uint32_t segidx = t / p.tiles_per_seg;
-    const uint32_t tin = t - segidx * p.tiles_per_seg;
-    uint32_t i, pl;
-    if (p.plane_major) {
-        pl = segidx / d.n;
-        i = segidx - pl * d.n;
-    } else {
-        i = segidx / p.n_planes;
-        pl = segidx - i * p.n_planes;
-    }
-    pl += p.plane0;
+    const uint32_t group = p.by_tiles.quotient(t);
+    tin = t - group * p.by_tiles.d;
+    const uint32_t q = d.inner.quotient(group), r = group - q * d.inner.d;
+    const uint32_t i = p.plane_major ? r : q, pl = p.plane0 + (p.plane_major ? q : r);
     const uint32_t id = (uint32_t)ids[i];
     const uint32_t slot = d.iota ? i : (uint32_t)slots[i];
-    hbm_off = (uint64_t)pl * p.hbm_plane_stride + (uint64_t)id * p.hbm_block_stride + (uint64_t)tin * tile_bytes;
-    far_off = (uint64_t)slot * slot_stride + (uint64_t)pl * plane_stride + (uint64_t)tin * tile_bytes;
+    hbm_off = (uint64_t)pl * p.hbm_plane_stride + (uint64_t)id * p.hbm_block_stride;
+    far_off = (uint64_t)slot * slot_stride + (uint64_t)pl * plane_stride;
 }
 
 // What one wave does in one step: an in tile, an out tile, or one of each.
-// Everything in it is uniform over the wave except the lane's own pointers.
-template <typename V>
+// The lane's pointers are worked out a step ahead, all of them: an address
+// computed where its load is issued lands in a register of the step before, and
+// the wave waits for that step's accesses first.  In a FULL tile one pointer per
+// side serves all vectors of the lane; elsewhere the group may continue in
+// another plane of the cache, or end.
+template <typename V, int U, bool FULL>
 struct Job {
-    const V *src_i;
-    V *dst_i;
-    const V *src_o;
-    V *dst_o;
+    static constexpr int N = FULL ? 1 : U;
+    const V *src_i[N];
+    V *dst_i[N];
+    const V *src_o[N];
+    V *dst_o[N];
     uint32_t do_in, do_out;
-    // this lane's first vector within the segment, per direction (range checks of
-    // ragged tiles; the two differ when the out tiles are spread over the in tiles)
-    uint32_t v0_i, v0_o;
+    uint32_t n_i, n_o;  // vectors of the group from this lane's first one on (not FULL: what the stores go by)
 };
 
 // Step t of a launch.  Normally step t is tile t of the out list and tile t of
@@ -117,14 +138,35 @@ struct Job {
 // mirror case gains nothing: with the out list longer, what limits is the
 // upstream direction, which carries the out data and the read requests of the
 // in data, and that sum does not depend on the order.)
-template <typename V, int U>
-__device__ __forceinline__ Job<V> make_job(const MoveParams &p, const int32_t *__restrict__ out_ids,
-                                           const int32_t *__restrict__ out_slots,
-                                           const int32_t *__restrict__ in_ids,
-                                           const int32_t *__restrict__ in_slots, uint32_t t, uint32_t lane)
+// The lane's pointers into one tile; past the end of the group, to its last vector.
+template <typename V, int U, bool FULL, int N>
+__device__ __forceinline__ void lane_pointers(const MoveParams &p, uint64_t hbm_off, uint8_t *far, uint32_t tin,
+                                              uint32_t lane, V *(&in_cache)[N], V *(&in_far)[N], uint32_t &n)
 {
-    constexpr uint32_t tile_vecs = kWave * U, tile_bytes = tile_vecs * (uint32_t)sizeof(V);
-    Job<V> j{nullptr, nullptr, nullptr, nullptr, 0u, 0u, 0u, 0u};
+    const uint32_t v0 = tin * (kWave * U) + lane;
+    n = p.group_vecs - v0;
+#pragma unroll
+    for (int u = 0; u < N; u++) {
+        uint32_t v = v0 + u * kWave;
+        uint64_t off = hbm_off;
+        if constexpr (!FULL) {
+            v = min(v, p.group_vecs - 1u);
+            off += (uint64_t)p.by_seg.quotient(v) * p.plane_skip;
+        }
+        in_cache[u] = reinterpret_cast<V *>(p.hbm + off) + v;
+        in_far[u] = reinterpret_cast<V *>(far) + v;
+    }
+    if (v0 >= p.group_vecs) n = 0u;
+}
+
+template <typename V, int U, bool FULL>
+__device__ __forceinline__ Job<V, U, FULL> make_job(const MoveParams &p, const int32_t *__restrict__ out_ids,
+                                                    const int32_t *__restrict__ out_slots,
+                                                    const int32_t *__restrict__ in_ids,
+                                                    const int32_t *__restrict__ in_slots, uint32_t t, uint32_t lane)
+{
+    Job<V, U, FULL> j{};
+    constexpr int N = Job<V, U, FULL>::N;
     uint32_t t_out = t;
     if (p.mix_q) {
         const uint64_t a = (uint64_t)t * p.mix_q, b = a + p.mix_q;
@@ -138,48 +180,48 @@ __device__ __forceinline__ Job<V> make_job(const MoveParams &p, const int32_t *_
         j.do_in = t < p.in.tiles ? 1u : 0u;
         j.do_out = t < p.out.tiles ? 1u : 0u;
     }
-    j.v0_i = (t % p.tiles_per_seg) * tile_vecs + lane;
-    j.v0_o = p.mix_q ? (t_out % p.tiles_per_seg) * tile_vecs + lane : j.v0_i;
+    uint64_t ho, fo;
+    uint32_t tin;
     if (j.do_in) {
-        uint64_t ho, fo;
-        locate(p, p.in, in_ids, in_slots, t, p.far_slot_stride_in, p.far_plane_stride_in, tile_bytes, ho, fo);
-        j.src_i = reinterpret_cast<const V *>(p.far_in + fo) + lane;
-        j.dst_i = reinterpret_cast<V *>(p.hbm + ho) + lane;
+        locate(p, p.in, in_ids, in_slots, t, p.far_slot_stride_in, p.far_plane_stride_in, ho, fo, tin);
+        V *far[N];
+        lane_pointers<V, U, FULL, N>(p, ho, p.far_in + fo, tin, lane, j.dst_i, far, j.n_i);
+#pragma unroll
+        for (int u = 0; u < N; u++) j.src_i[u] = far[u];
     }
     if (j.do_out) {
-        uint64_t ho, fo;
-        locate(p, p.out, out_ids, out_slots, t_out, p.far_slot_stride_out, p.far_plane_stride_out, tile_bytes, ho,
-               fo);
-        j.src_o = reinterpret_cast<const V *>(p.hbm + ho) + lane;
-        j.dst_o = reinterpret_cast<V *>(p.far_out + fo) + lane;
+        locate(p, p.out, out_ids, out_slots, t_out, p.far_slot_stride_out, p.far_plane_stride_out, ho, fo, tin);
+        V *cache[N];
+        lane_pointers<V, U, FULL, N>(p, ho, p.far_out + fo, tin, lane, cache, j.dst_o, j.n_o);
+#pragma unroll
+        for (int u = 0; u < N; u++) j.src_o[u] = cache[u];
     }
     return j;
 }
 
 // Loads of one job: the far-side (host) loads first, they have the long
-// latency; then the HBM loads.  FULL: the segment is a whole number of tiles, no
-// lane is ever out of range, and all loads issue back to back.  In an HBM-bound
-// launch (pack / unpack, !LINK) loads and stores alike are marked non-temporal:
-// nothing a mover touches is touched twice.
+// latency; then the HBM loads.  Lanes past the group's end load nothing from the
+// host (a vector that many lanes repeat crosses the link once for every 16 of
+// them), and repeat the group's last vector from HBM.  In an HBM-bound launch (pack / unpack, !LINK)
+// loads and stores alike are marked non-temporal: nothing a mover touches is
+// touched twice.
 template <typename V, int U, bool LINK, bool FULL>
-__device__ __forceinline__ void job_loads(const MoveParams &p, const Job<V> &j, V (&vi)[U], V (&vo)[U])
+__device__ __forceinline__ void job_loads(const Job<V, U, FULL> &j, V (&vi)[U], V (&vo)[U])
 {
     if (j.do_in) {
 #pragma unroll
         for (int u = 0; u < U; u++) {
-            if (FULL || j.v0_i + u * kWave < p.vec_per_seg) {
-                if constexpr (LINK) vi[u] = j.src_i[u * kWave];
-                else vi[u] = __builtin_nontemporal_load(j.src_i + u * kWave);
-            }
+            const V *src = FULL ? j.src_i[0] + u * kWave : j.src_i[FULL ? 0 : u];
+            if constexpr (!LINK) vi[u] = __builtin_nontemporal_load(src);
+            else if (FULL || (uint32_t)(u * kWave) < j.n_i) vi[u] = *src;
         }
     }
     if (j.do_out) {
 #pragma unroll
         for (int u = 0; u < U; u++) {
-            if (FULL || j.v0_o + u * kWave < p.vec_per_seg) {
-                if constexpr (LINK) vo[u] = j.src_o[u * kWave];
-                else vo[u] = __builtin_nontemporal_load(j.src_o + u * kWave);
-            }
+            const V *src = FULL ? j.src_o[0] + u * kWave : j.src_o[FULL ? 0 : u];
+            if constexpr (LINK) vo[u] = *src;
+            else vo[u] = __builtin_nontemporal_load(src);
         }
     }
 }
@@ -194,20 +236,22 @@ __device__ __forceinline__ void job_loads(const MoveParams &p, const Job<V> &j, 
 // plain loads and stores 109 us, non-temporal stores 100 us, non-temporal loads
 // and stores 95 us (HIP events around the launch).
 template <typename V, int U, bool LINK, bool FULL>
-__device__ __forceinline__ void job_stores(const MoveParams &p, const Job<V> &j, const V (&vi)[U],
-                                           const V (&vo)[U])
+__device__ __forceinline__ void job_stores(const Job<V, U, FULL> &j, const V (&vi)[U], const V (&vo)[U])
 {
     if (j.do_out) {
 #pragma unroll
-        for (int u = 0; u < U; u++)
-            if (FULL || j.v0_o + u * kWave < p.vec_per_seg) __builtin_nontemporal_store(vo[u], j.dst_o + u * kWave);
+        for (int u = 0; u < U; u++) {
+            V *dst = FULL ? j.dst_o[0] + u * kWave : j.dst_o[FULL ? 0 : u];
+            if (FULL || (uint32_t)(u * kWave) < j.n_o) __builtin_nontemporal_store(vo[u], dst);
+        }
     }
     if (j.do_in) {
 #pragma unroll
         for (int u = 0; u < U; u++) {
-            if (FULL || j.v0_i + u * kWave < p.vec_per_seg) {
-                if constexpr (LINK) j.dst_i[u * kWave] = vi[u];
-                else __builtin_nontemporal_store(vi[u], j.dst_i + u * kWave);
+            V *dst = FULL ? j.dst_i[0] + u * kWave : j.dst_i[FULL ? 0 : u];
+            if (FULL || (uint32_t)(u * kWave) < j.n_i) {
+                if constexpr (LINK) *dst = vi[u];
+                else __builtin_nontemporal_store(vi[u], dst);
             }
         }
     }
@@ -244,70 +288,81 @@ __device__ __forceinline__ void run_fixed(const MoveParams &p, const int32_t *__
     uint32_t t = wave;
     if (t >= n_steps) return;
     V vi[U], vo[U];
-    Job<V> cur = make_job<V, U>(p, out_ids, out_slots, in_ids, in_slots, t, lane);
+    Job<V, U, FULL> cur = make_job<V, U, FULL>(p, out_ids, out_slots, in_ids, in_slots, t, lane);
     for (;;) {
-        job_loads<V, U, LINK, FULL>(p, cur, vi, vo);
+        job_loads<V, U, LINK, FULL>(cur, vi, vo);
         t += n_waves;
         const bool more = t < n_steps;
-        Job<V> nxt = cur;
-        if (more) nxt = make_job<V, U>(p, out_ids, out_slots, in_ids, in_slots, t, lane);
-        job_stores<V, U, LINK, FULL>(p, cur, vi, vo);
+        Job<V, U, FULL> nxt = cur;
+        if (more) nxt = make_job<V, U, FULL>(p, out_ids, out_slots, in_ids, in_slots, t, lane);
+        job_stores<V, U, LINK, FULL>(cur, vi, vo);
         if (!more) break;
         cur = nxt;
     }
 }
 
-// Drawn steps.  A draw takes kDrawChunk consecutive steps (one atomic per step
-// would be ~50 M a second on one address, which beside an HBM-bound kernel is
-// what limits the launch: 93 GB/s whatever the number of waves), except near the
-// end, where steps are drawn singly so that the waves still finish within one
-// step of each other.  The draw for the next chunk is issued when the current
-// chunk starts and read when it ends.  Every draw the wave issues is read back
-// before the function returns.
+// Drawn steps.  Wave w begins with step w; the steps from n_waves on are drawn from
+// p.claim[0], which counts them from there.  A draw takes kDrawChunk consecutive
+// steps (one atomic per step would be ~50 M a second on one address, which beside
+// an HBM-bound kernel is what limits the launch: 93 GB/s whatever the number of
+// waves), except near the end, where steps are drawn singly so that the waves
+// still finish within one step of each other.  The draw for the next chunk is issued when the current
+// chunk starts and read when it ends.
+//
+// Every draw the wave issued has been read back when it finds no step left, so
+// the counter holds all of its increments before the wave reports itself done in
+// p.claim[1]; the wave that sees every other one done puts both back to zero for
+// the next launch on the stream.
 constexpr uint32_t kDrawChunk = 4;
 
 template <typename V, int U, bool LINK, bool FULL>
 __device__ __forceinline__ void run_drawn(const MoveParams &p, const int32_t *__restrict__ out_ids,
                                           const int32_t *__restrict__ out_slots,
                                           const int32_t *__restrict__ in_ids,
-                                          const int32_t *__restrict__ in_slots, uint32_t n_steps, uint32_t n_waves,
-                                          uint32_t lane)
+                                          const int32_t *__restrict__ in_slots, uint32_t n_steps, uint32_t wave,
+                                          uint32_t n_waves, uint32_t lane)
 {
+    if (wave >= n_steps) return;  // only where workgroups of several waves round the launch up: see below
+    V vi[U], vo[U];
+    Job<V, U, FULL> cur = make_job<V, U, FULL>(p, out_ids, out_slots, in_ids, in_slots, wave, lane);
+    if (n_steps <= n_waves) {  // a step each: no counter at all
+        job_loads<V, U, LINK, FULL>(cur, vi, vo);
+        job_stores<V, U, LINK, FULL>(cur, vi, vo);
+        return;
+    }
     // steps at or beyond `single` are drawn one at a time
     const uint32_t tail = 2u * kDrawChunk * n_waves, single = n_steps > tail ? n_steps - tail : 0u;
-    uint32_t c = single ? kDrawChunk : 1u;
-    uint32_t t = drawn(draw(p, lane, c));  // current step
-    uint32_t e = t + c;                    // end of the chunk it belongs to
-    uint32_t cn = t < single ? kDrawChunk : 1u;
-    uint32_t d = draw(p, lane, cn);        // the next chunk, in flight
-    if (t < n_steps) {
-        V vi[U], vo[U];
-        Job<V> cur = make_job<V, U>(p, out_ids, out_slots, in_ids, in_slots, t, lane);
-        for (;;) {
-            job_loads<V, U, LINK, FULL>(p, cur, vi, vo);
-            // The next step.  At the end of a chunk the pending draw is read: here,
-            // where the loads have to be waited for anyway (the draw is older than
-            // they are), and before the stores: the vector memory counter retires in
-            // order, so reading it behind the stores would wait for them, and a wave
-            // would then pay store latency and load latency in turn.  As it is, a
-            // step's stores have the whole next step to retire.
-            uint32_t tn = t + 1u;
-            if (tn >= e) {
-                tn = drawn(d);
-                e = tn + cn;
-                cn = tn < single ? kDrawChunk : 1u;
-                d = draw(p, lane, cn);
-            }
-            const bool more = tn < n_steps;
-            Job<V> nxt = cur;
-            if (more) nxt = make_job<V, U>(p, out_ids, out_slots, in_ids, in_slots, tn, lane);
-            job_stores<V, U, LINK, FULL>(p, cur, vi, vo);
-            if (!more) break;
-            cur = nxt;
-            t = tn;
+    uint32_t t = wave, e = wave + 1u;  // current step, end of the chunk it belongs to
+    uint32_t cn = n_waves < single ? kDrawChunk : 1u;
+    uint32_t d = draw(p, lane, cn);    // the next chunk, in flight
+    for (;;) {
+        job_loads<V, U, LINK, FULL>(cur, vi, vo);
+        // The next step.  At the end of a chunk the pending draw is read: here,
+        // where the loads have to be waited for anyway (the draw is older than
+        // they are), and before the stores: the vector memory counter retires in
+        // order, so reading it behind the stores would wait for them, and a wave
+        // would then pay store latency and load latency in turn.  As it is, a
+        // step's stores have the whole next step to retire.
+        uint32_t tn = t + 1u;
+        if (tn >= e) {
+            tn = n_waves + drawn(d);
+            e = tn + cn;
+            cn = tn < single ? kDrawChunk : 1u;
+            if (tn < n_steps) d = draw(p, lane, cn);
         }
+        const bool more = tn < n_steps;
+        Job<V, U, FULL> nxt = cur;
+        if (more) nxt = make_job<V, U, FULL>(p, out_ids, out_slots, in_ids, in_slots, tn, lane);
+        job_stores<V, U, LINK, FULL>(cur, vi, vo);
+        if (!more) break;
+        cur = nxt;
+        t = tn;
     }
-    (void)drawn(d);
+    (void)drawn(d);  // still in flight if the last chunk ran past the last step
+    if (lane == 0 && atomicAdd(&p.claim[1], 1u) == n_waves - 1u) {
+        p.claim[0] = 0u;
+        p.claim[1] = 0u;
+    }
 }
 
 // V: vector moved per lane (16 bytes when the segment allows it).
@@ -320,7 +375,7 @@ __device__ __forceinline__ void run_drawn(const MoveParams &p, const int32_t *__
 // while they are in flight, and stores.  What keeps the link busy is the number
 // of waves: a second step in flight per wave buys what a second wave buys.
 //
-// Which step a wave takes next: with p.claim the waves draw step indices from a
+// Which step a wave takes next: link-bound waves draw step indices from a
 // counter (the draw for the step after next is issued a whole step ahead, so
 // its latency is never waited for).  With a fixed share per wave the waves of a
 // link-bound launch drift apart by several per cent and the launch ends with a
@@ -339,26 +394,21 @@ __global__ __launch_bounds__(kMaxThreads) void kv_move_kernel(const MoveParams p
                                                               const int32_t *__restrict__ in_slots)
 {
     const uint32_t lane = threadIdx.x & (kWave - 1u), waves_per_wg = blockDim.x / kWave;
-    const uint32_t wave = blockIdx.x * waves_per_wg + threadIdx.x / kWave, n_waves = gridDim.x * waves_per_wg;
+    const uint32_t wave = blockIdx.x * waves_per_wg + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const uint32_t n_waves = gridDim.x * waves_per_wg;
     const uint32_t n_steps = p.mix_q ? p.in.tiles : (p.out.tiles > p.in.tiles ? p.out.tiles : p.in.tiles);
-    if (!p.claim) {
+    constexpr int UR = U < kMaxRaggedU ? U : kMaxRaggedU;  // what cut_tiles() cut by when tiles are not whole
+    if constexpr (!LINK) {
         if (p.full_tiles)
             run_fixed<V, U, LINK, true>(p, out_ids, out_slots, in_ids, in_slots, n_steps, wave, n_waves, lane);
         else
-            run_fixed<V, U, LINK, false>(p, out_ids, out_slots, in_ids, in_slots, n_steps, wave, n_waves, lane);
+            run_fixed<V, UR, LINK, false>(p, out_ids, out_slots, in_ids, in_slots, n_steps, wave, n_waves, lane);
         return;
     }
     if (p.full_tiles)
-        run_drawn<V, U, LINK, true>(p, out_ids, out_slots, in_ids, in_slots, n_steps, n_waves, lane);
+        run_drawn<V, U, LINK, true>(p, out_ids, out_slots, in_ids, in_slots, n_steps, wave, n_waves, lane);
     else
-        run_drawn<V, U, LINK, false>(p, out_ids, out_slots, in_ids, in_slots, n_steps, n_waves, lane);
-    // Every draw this wave issued has been read back, so the counter holds all of
-    // its increments before the wave reports itself done; the wave that sees
-    // every other one done can therefore put the counters back.
-    if (lane == 0 && atomicAdd(&p.claim[1], 1u) == n_waves - 1u) {
-        p.claim[0] = 0u;
-        p.claim[1] = 0u;
-    }
+        run_drawn<V, UR, LINK, false>(p, out_ids, out_slots, in_ids, in_slots, n_steps, wave, n_waves, lane);
 }
 
 // Pack / unpack of the DMA-staged path when nothing caps the launch: both sides

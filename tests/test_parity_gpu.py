@@ -380,3 +380,33 @@ def test_query_polls_without_blocking(path):
     assert case.eng.kv_query() == 0
     case.check()
     case.close()
+
+
+@pytest.mark.parametrize("host_layout", LAYOUTS)
+@pytest.mark.parametrize("vecs,planes", [(1, 4), (63, 6), (75, 48), (257, 4), (768, 2), (1000, 6)])
+def test_tiles_that_span_segments(vecs, planes, host_layout):
+    """Segments of `vecs` 16-byte vectors that no tile divides (768: by 8 vectors per
+    lane only): a tile covers several segments, ends inside one, or is the last,
+    partly empty one of its block.  Balanced, in-heavy, out-heavy and one-way lists,
+    forced vector counts, chunks of a layer, both cache layouts, capped pack kernels
+    and the call without an engine, every byte against the oracle."""
+    sh = W.KVShape(planes // 2, 1, 8 * vecs, 1, n_hbm_blocks=41, n_host_slots=31)
+    for hbm_layout, path, kw in [(0, B.KV_PATH_AUTO, {}), (1, B.KV_PATH_AUTO, {}), (0, B.KV_PATH_AUTO, dict(vecs_per_lane=8)),
+                                 (0, B.KV_PATH_AUTO, dict(chunk_layers=1)), (0, B.KV_PATH_ZEROCOPY, {}),
+                                 (0, B.KV_PATH_SDMA_STAGED, dict(max_copy_wgs=3))]:
+        for n_out, n_in in [(11, 9), (2, 20), (20, 2), (13, 0), (0, 13)]:
+            rot = W.simple_rotation(sh, n_out, n_in, seed=vecs + n_out)
+            case, _ = make_case(sh, host_layout, path, rot=rot, hbm_layout=hbm_layout, **kw)
+            case.rotate(rot)
+            case.check()
+            if not kw and path == B.KV_PATH_AUTO:
+                dev, pool = case.dev_cache, torch.from_numpy(case.pool_u8.view(np.int16).copy()).pin_memory()
+                inv = rot.inverse()
+                assert B.kv_rotate_static(case.cfg, dev.data_ptr(), pool.data_ptr(), 0, inv.out_ids, inv.out_slots,
+                                          inv.in_ids, inv.in_slots) == 0
+                torch.cuda.synchronize()
+                case.pool_u8[:] = pool.numpy().view(np.uint8)
+                assert O.rotate(case.oshape, case.ref_cache.view(np.uint8), case.ref_pool.view(np.uint8), inv.out_ids,
+                                inv.out_slots, inv.in_ids, inv.in_slots) == 0
+                case.check()
+            case.close()
