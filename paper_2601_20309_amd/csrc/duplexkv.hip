@@ -16,6 +16,7 @@
 //                contiguous region on both sides, one hipMemcpyAsync per block
 //                (the paper's "merged segments"), runs of consecutive pairs merged.
 #include <hip/hip_runtime.h>
+#include <hip/hip_ext.h>
 
 #include <algorithm>
 #include <chrono>
@@ -153,16 +154,23 @@ struct MoveIds {
 struct LinkShape { int wgs, lanes, u, short_steps, limit_u; };
 
 // The waves of the launch are the workers, and no more of them are launched than
-// it has steps.
+// it has steps.  `stop` (may be nullptr) is recorded by the launch itself.
 template <int U, bool LINK>
-void launch_move_v(int vec, const LinkShape &sh, hipStream_t s, const MoveParams &p, const MoveIds &d)
+void launch_move_v(int vec, const LinkShape &sh, hipStream_t s, const MoveParams &p, const MoveIds &d, hipEvent_t stop)
 {
     const uint32_t steps = p.mix_q ? p.in.tiles : std::max(p.out.tiles, p.in.tiles);
     const uint32_t waves_per_wg = (uint32_t)sh.lanes / dkv::kWave, most = (steps + waves_per_wg - 1) / waves_per_wg;
     const uint32_t wgs = steps <= (uint32_t)sh.short_steps ? most : std::min<uint32_t>((uint32_t)sh.wgs, most);
     dim3 g(std::max(1u, wgs)), b((unsigned)sh.lanes);
-#define DKV_LAUNCH(V) \
-    hipLaunchKernelGGL((dkv::kv_move_kernel<V, U, LINK>), g, b, 0, s, p, d.out_ids, d.out_slots, d.in_ids, d.in_slots)
+#define DKV_LAUNCH(V)                                                                                              \
+    do {                                                                                                           \
+        if (stop)                                                                                                  \
+            hipExtLaunchKernelGGL((dkv::kv_move_kernel<V, U, LINK>), g, b, 0, s, nullptr, stop, 0, p, d.out_ids,   \
+                                  d.out_slots, d.in_ids, d.in_slots);                                              \
+        else                                                                                                       \
+            hipLaunchKernelGGL((dkv::kv_move_kernel<V, U, LINK>), g, b, 0, s, p, d.out_ids, d.out_slots, d.in_ids, \
+                               d.in_slots);                                                                        \
+    } while (0)
     switch (vec) {
     case 16: DKV_LAUNCH(dkv::u32x4); break;
     case 8: DKV_LAUNCH(dkv::u32x2); break;
@@ -174,21 +182,22 @@ void launch_move_v(int vec, const LinkShape &sh, hipStream_t s, const MoveParams
 }
 
 // link: the far side is host memory (zero-copy paths); else HBM staging.
-void launch_move(const LinkShape &sh, int vec, hipStream_t s, const MoveParams &p, const MoveIds &d, bool link)
+void launch_move(const LinkShape &sh, int vec, hipStream_t s, const MoveParams &p, const MoveIds &d, bool link,
+                 hipEvent_t stop = nullptr)
 {
     if (link) {
         switch (sh.u) {
-        case 1: launch_move_v<1, true>(vec, sh, s, p, d); break;
-        case 2: launch_move_v<2, true>(vec, sh, s, p, d); break;
-        case 4: launch_move_v<4, true>(vec, sh, s, p, d); break;
-        default: launch_move_v<8, true>(vec, sh, s, p, d); break;
+        case 1: launch_move_v<1, true>(vec, sh, s, p, d, stop); break;
+        case 2: launch_move_v<2, true>(vec, sh, s, p, d, stop); break;
+        case 4: launch_move_v<4, true>(vec, sh, s, p, d, stop); break;
+        default: launch_move_v<8, true>(vec, sh, s, p, d, stop); break;
         }
     } else {
         switch (sh.u) {
-        case 1: launch_move_v<1, false>(vec, sh, s, p, d); break;
-        case 2: launch_move_v<2, false>(vec, sh, s, p, d); break;
-        case 4: launch_move_v<4, false>(vec, sh, s, p, d); break;
-        default: launch_move_v<8, false>(vec, sh, s, p, d); break;
+        case 1: launch_move_v<1, false>(vec, sh, s, p, d, stop); break;
+        case 2: launch_move_v<2, false>(vec, sh, s, p, d, stop); break;
+        case 4: launch_move_v<4, false>(vec, sh, s, p, d, stop); break;
+        default: launch_move_v<8, false>(vec, sh, s, p, d, stop); break;
         }
     }
 }
@@ -283,6 +292,7 @@ int acquire_ring(kv_engine *e, int &k)
     if (e->ring_out_rec[k]) HIPTRY(e, hipEventSynchronize(e->ring_out[k]));
     if (e->ring_in_rec[k]) HIPTRY(e, hipEventSynchronize(e->ring_in[k]));
     e->ring_out_rec[k] = e->ring_in_rec[k] = false;
+    if (e->in_behind == e->ring_out[k]) e->in_behind = nullptr;  // waited for just now
     return KV_OK;
 }
 
@@ -311,17 +321,17 @@ int mark_start(kv_engine *e, bool out_side, hipStream_t s)
 }
 
 // Last work of a direction in this call: releases descriptor set k and is the
-// end timestamp so far.
-int mark_end(kv_engine *e, bool out_side, int k, hipStream_t s)
+// end timestamp so far.  `recorded`: the last launch recorded the event itself.
+int mark_end(kv_engine *e, bool out_side, int k, hipStream_t s, bool recorded = false)
 {
     if (out_side) {
-        HIPTRY(e, hipEventRecord(e->ring_out[k], s));
+        if (!recorded) HIPTRY(e, hipEventRecord(e->ring_out[k], s));
         e->ring_out_rec[k] = true;
         e->b_o1 = e->ring_out[k];
         e->out_pending = true;
         e->out_dirty = true;
     } else {
-        HIPTRY(e, hipEventRecord(e->ring_in[k], s));
+        if (!recorded) HIPTRY(e, hipEventRecord(e->ring_in[k], s));
         e->ring_in_rec[k] = true;
         e->b_i1 = e->ring_in[k];
         e->in_pending = true;
@@ -454,8 +464,13 @@ void launch_stage(int vec, hipStream_t s, const dkv::StageParams &p, const int32
 // that whoever consumes the blocks (the model's layer l, a writer of the pool)
 // can start on a layer while the later ones still move.  A chunk is the same
 // kernel over planes [p0, p1) of every block of the call.
+// An event that follows a launch is recorded by the launch (its completion signal)
+// on the engine's own streams: as a packet of its own it costs the stream 2.8 us
+// (20 launches of 20 us: 497 us with records behind them, 442 us without or with
+// signals).  The caller's streams may be under capture, which records events only.
+// `end` (may be nullptr): the event behind a call that does not run layer by layer.
 int launch_link(kv_engine *e, const LinkShape &sh, hipStream_t s, const MoveParams &whole, const MoveIds &ids,
-                std::vector<hipEvent_t> *ev)
+                std::vector<hipEvent_t> *ev, hipEvent_t end = nullptr)
 {
     const uint32_t per_chunk = ev ? 2u * (uint32_t)e->cfg.chunk_layers : whole.n_planes;
     uint32_t c = 0;
@@ -467,10 +482,10 @@ int launch_link(kv_engine *e, const LinkShape &sh, hipStream_t s, const MovePara
         // fits: the whole call's counts were checked
         if (!fill_dir(q, q.out.n, 0, sh.limit_u, q.out) || !fill_dir(q, q.in.n, 0, sh.limit_u, q.in)) return KV_EUNSUP;
         q.mix_q = whole.mix_q && q.out.tiles ? (((uint64_t)q.out.tiles << 32) + q.in.tiles - 1) / q.in.tiles : 0;
-        launch_move(sh, e->vec, s, q, ids, true);
+        launch_move(sh, e->vec, s, q, ids, true, !ev ? end : e->own_streams ? (*ev)[c] : nullptr);
         HIPTRY(e, hipGetLastError());
         e->acc.n_launches += 1;
-        if (ev) HIPTRY(e, hipEventRecord((*ev)[c], s));
+        if (ev && !e->own_streams) HIPTRY(e, hipEventRecord((*ev)[c], s));
     }
     return KV_OK;
 }
@@ -550,21 +565,27 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
                 e->b_i0 = e->ev_i0;
             }
         }
+        // the event behind the whole call: recorded by its last launch, or a packet of its own
+        const hipEvent_t end = e->own_streams && !layered ? e->ring_out[k] : nullptr;
         if (launch_link(e, sh, e->s_out, p, MoveIds{d_o, d_o + no, d_i, d_i + ni},
-                        layered ? &e->layer_ev_out : nullptr) != KV_OK)
+                        layered ? &e->layer_ev_out : nullptr, n_rest > 0 ? nullptr : end) != KV_OK)
             return KV_EHIP;
         e->layer_chunk = layered ? e->cfg.chunk_layers : 0;
         e->layer_on_out = layered;
         e->layer_on_in = false;
         if (n_rest > 0) {
             launch_move(sh_rest, e->vec, e->s_out, p_rest,
-                        MoveIds{d_o + no_paired, d_o + no + no_paired, nullptr, nullptr}, true);
+                        MoveIds{d_o + no_paired, d_o + no + no_paired, nullptr, nullptr}, true, end);
             HIPTRY(e, hipGetLastError());
             e->acc.n_launches += 1;
         }
-        if (mark_end(e, true, k, e->s_out) != KV_OK) return KV_EHIP;
+        if (mark_end(e, true, k, e->s_out, end != nullptr) != KV_OK) return KV_EHIP;
         e->b_i1 = e->ring_out[k];
-        HIPTRY(e, hipStreamWaitEvent(e->s_in, e->ring_out[k], 0));
+        // What is enqueued on stream_in from now on comes after this call.  Nobody but the
+        // engine enqueues on a stream of its own, so there the wait can be left until
+        // something is (7 us of host time, and of a queue, per call that has no use for it).
+        if (e->own_streams) e->in_behind = e->ring_out[k];
+        else HIPTRY(e, hipStreamWaitEvent(e->s_in, e->ring_out[k], 0));
         e->out_dirty = false;
         return KV_OK;
     }
@@ -612,16 +633,18 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
     if (no > 0) {
         if (upload_ids(true, false, e->s_out) != KV_OK) return KV_EHIP;
         if (mark_start(e, true, e->s_out) != KV_OK) return KV_EHIP;
-        if (launch_link(e, sh_out, e->s_out, p_out, ids_out, layered ? &e->layer_ev_out : nullptr) != KV_OK)
+        const hipEvent_t end = e->own_streams && !layered ? e->ring_out[k] : nullptr;
+        if (launch_link(e, sh_out, e->s_out, p_out, ids_out, layered ? &e->layer_ev_out : nullptr, end) != KV_OK)
             return KV_EHIP;
-        if (mark_end(e, true, k, e->s_out) != KV_OK) return KV_EHIP;
+        if (mark_end(e, true, k, e->s_out, end != nullptr) != KV_OK) return KV_EHIP;
     }
     if (ni > 0) {
         if (upload_ids(false, true, e->s_in) != KV_OK) return KV_EHIP;
         if (mark_start(e, false, e->s_in) != KV_OK) return KV_EHIP;
-        if (launch_link(e, sh_in, e->s_in, p_in, ids_in, layered ? &e->layer_ev_in : nullptr) != KV_OK)
+        const hipEvent_t end = e->own_streams && !layered ? e->ring_in[k] : nullptr;
+        if (launch_link(e, sh_in, e->s_in, p_in, ids_in, layered ? &e->layer_ev_in : nullptr, end) != KV_OK)
             return KV_EHIP;
-        if (mark_end(e, false, k, e->s_in) != KV_OK) return KV_EHIP;
+        if (mark_end(e, false, k, e->s_in, end != nullptr) != KV_OK) return KV_EHIP;
     }
     return KV_OK;
 }
@@ -978,6 +1001,10 @@ int transfer(kv_engine *e, const int32_t *oi, const int32_t *os, int32_t no, con
         rc = ensure_staging(e);
         if (rc != KV_OK) return rc;
     }
+    if (ni > 0 && !joins && e->in_behind) {
+        HIPTRY(e, hipStreamWaitEvent(e->s_in, e->in_behind, 0));
+        e->in_behind = nullptr;
+    }
     open_batch(e);
     e->layer_chunk = 0;  // the kernel paths set it again when they run layer by layer
     if (path == KV_PATH_NAIVE) {
@@ -1330,14 +1357,19 @@ int kv_wait(kv_engine *e)
 {
     if (!e) return KV_EINVAL;
     if (e->sticky != KV_OK) return e->sticky;
-    // Only streams this engine put work on are waited for.
+    // Only streams this engine put work on are waited for.  On its own streams the event
+    // behind the last call is the end of all there is, and is waited for in 3 us less than
+    // the stream (which a launch that records its own event leaves without a last packet).
     for (int side = 0; side < 2; side++) {
         const bool pending = side == 0 ? e->out_pending : e->in_pending;
         if (!pending) continue;
-        HIPTRY(e, hipStreamSynchronize(side == 0 ? e->s_out : e->s_in));
+        const hipEvent_t last = side == 0 ? e->b_o1 : e->b_i1;
+        if (e->own_streams && last) HIPTRY(e, hipEventSynchronize(last));
+        else HIPTRY(e, hipStreamSynchronize(side == 0 ? e->s_out : e->s_in));
     }
     e->out_pending = e->in_pending = false;
     e->out_dirty = e->in_dirty = false;
+    e->in_behind = nullptr;
     e->hazards.join();
     e->idle_epoch++;
     for (int k = 0; k < kRing; k++) e->ring_out_rec[k] = e->ring_in_rec[k] = false;
@@ -1374,6 +1406,7 @@ int kv_query(kv_engine *e)
     }
     // nothing runs any more, so nothing can race with what comes next
     e->out_dirty = e->in_dirty = false;
+    e->in_behind = nullptr;
     e->hazards.join();
     e->idle_epoch++;
     return KV_OK;

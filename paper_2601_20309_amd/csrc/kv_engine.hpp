@@ -118,6 +118,7 @@ struct kv_engine {
     bool out_pending = false, in_pending = false;  // work enqueued since the last kv_wait
     bool in_dirty = false;                         // stream_in holds work stream_out has not joined
     bool out_dirty = false;                        // stream_out holds work stream_in has not joined
+    hipEvent_t in_behind = nullptr;                // own streams: what the next work on stream_in has to wait for
     bool in_after_out = false;                     // block table in use: in-only work waits for earlier out work
     int n_tables = 0;                              // block tables attached (kv_destroy refuses while any is)
     // Goes up every time the engine has seen all of its enqueued work finished

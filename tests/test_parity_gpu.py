@@ -410,3 +410,58 @@ def test_tiles_that_span_segments(vecs, planes, host_layout):
                                 inv.out_slots, inv.in_ids, inv.in_slots) == 0
                 case.check()
             case.close()
+
+
+@pytest.mark.parametrize("blocks", [1, 24])
+def test_bytes_are_there_the_moment_the_wait_returns(blocks):
+    """kv_wait is the only thing between a transfer and its reader: the CPU reads the
+    pool, and a kernel on another stream the cache, with nothing else enqueued in
+    between, and other bytes every time (a copy that lingered in a cache would show the
+    previous ones)."""
+    sh = W.KVShape(4, 2, 64, 16, n_hbm_blocks=256, n_host_slots=256)
+    rng = np.random.default_rng(5)
+    words = V.n_cache_elems(sh) // sh.n_hbm_blocks
+    cache = torch.from_numpy(rng.integers(-32768, 32767, (sh.n_hbm_blocks, words), dtype=np.int16)).cuda()
+    torch.cuda.synchronize()
+    eng = B.Engine(B.make_config(sh, hbm_layout=B.KV_HBM_BLOCK_FIRST), cache.data_ptr())
+    pool = eng.host_pool_array().view(np.int16).reshape(sh.n_host_slots, words)
+    pool[:] = rng.integers(-32768, 32767, pool.shape, dtype=np.int16)
+    img = cache.cpu().numpy()
+    side = torch.cuda.Stream()
+    lo = np.arange(blocks, dtype=np.int32)                       # the place that is read, out of the way of the sources
+    for k in range(300):
+        src = (lo + blocks + rng.integers(0, 256 - 2 * blocks)).astype(np.int32)
+        # out and in alone, and both in one call, over the same places
+        if k % 3 == 0:
+            assert eng.kv_swap_out(src, lo) == 0 and eng.kv_wait() == 0
+            assert np.array_equal(pool[lo], img[src]), k
+        elif k % 3 == 1:
+            assert eng.kv_swap_in(src, lo) == 0 and eng.kv_wait() == 0
+            with torch.cuda.stream(side):
+                got = cache[:blocks].clone()
+            side.synchronize()
+            assert np.array_equal(got.cpu().numpy(), pool[src]), k
+        else:
+            assert eng.kv_rotate(src, lo, lo, src) == 0 and eng.kv_wait() == 0
+            assert np.array_equal(pool[lo], img[src]), k
+            with torch.cuda.stream(side):
+                got = cache[:blocks].clone()
+            side.synchronize()
+            assert np.array_equal(got.cpu().numpy(), pool[src]), k
+    eng.kv_destroy()
+
+
+def test_calls_of_one_direction_keep_their_order_behind_joint_launches():
+    """Un-waited calls on the engine's own streams: a swap-in enqueued behind a rotation
+    (one launch, on the other stream) overwrites blocks and slots' copies the rotation
+    still moves, and must come second; then rounds of both past the descriptor ring."""
+    sh = W.KVShape(8, 8, 128, 16, n_hbm_blocks=200, n_host_slots=200)     # 512 KiB blocks: a rotation of 60 + 60 takes 0.6 ms
+    perm = np.random.default_rng(9).permutation(200).astype(np.int32)
+    rot = W.Rotation(perm[:60], perm[:60].copy(), perm[60:120], perm[60:120].copy())
+    case, _ = make_case(sh, B.KV_HOST_BLOCK_FIRST, B.KV_PATH_AUTO, rot=rot)
+    for k in range(10):
+        case.rotate(rot)
+        case.swap_in(rot.out_slots[: 20 + k], rot.in_ids[: 20 + k])      # reads slots the rotation writes, into blocks it fills
+        case.rotate(rot.inverse())
+    case.check()
+    case.close()
