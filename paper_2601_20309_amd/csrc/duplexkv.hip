@@ -321,17 +321,17 @@ int mark_start(kv_engine *e, bool out_side, hipStream_t s)
 }
 
 // Last work of a direction in this call: releases descriptor set k and is the
-// end timestamp so far.  `recorded`: the last launch recorded the event itself.
-int mark_end(kv_engine *e, bool out_side, int k, hipStream_t s, bool recorded = false)
+// end timestamp so far.
+int mark_end(kv_engine *e, bool out_side, int k, hipStream_t s)
 {
     if (out_side) {
-        if (!recorded) HIPTRY(e, hipEventRecord(e->ring_out[k], s));
+        HIPTRY(e, hipEventRecord(e->ring_out[k], s));
         e->ring_out_rec[k] = true;
         e->b_o1 = e->ring_out[k];
         e->out_pending = true;
         e->out_dirty = true;
     } else {
-        if (!recorded) HIPTRY(e, hipEventRecord(e->ring_in[k], s));
+        HIPTRY(e, hipEventRecord(e->ring_in[k], s));
         e->ring_in_rec[k] = true;
         e->b_i1 = e->ring_in[k];
         e->in_pending = true;
@@ -464,13 +464,12 @@ void launch_stage(int vec, hipStream_t s, const dkv::StageParams &p, const int32
 // that whoever consumes the blocks (the model's layer l, a writer of the pool)
 // can start on a layer while the later ones still move.  A chunk is the same
 // kernel over planes [p0, p1) of every block of the call.
-// An event that follows a launch is recorded by the launch (its completion signal)
-// on the engine's own streams: as a packet of its own it costs the stream 2.8 us
-// (20 launches of 20 us: 497 us with records behind them, 442 us without or with
-// signals).  The caller's streams may be under capture, which records events only.
-// `end` (may be nullptr): the event behind a call that does not run layer by layer.
+// On the engine's own streams the launch records the event itself (its completion
+// signal): as a packet of its own it costs the stream 2.8 us (20 launches of 20 us:
+// 497 us with records behind them, 442 us without or with signals).  The caller's
+// streams may be under capture, which knows recorded events only.
 int launch_link(kv_engine *e, const LinkShape &sh, hipStream_t s, const MoveParams &whole, const MoveIds &ids,
-                std::vector<hipEvent_t> *ev, hipEvent_t end = nullptr)
+                std::vector<hipEvent_t> *ev)
 {
     const uint32_t per_chunk = ev ? 2u * (uint32_t)e->cfg.chunk_layers : whole.n_planes;
     uint32_t c = 0;
@@ -482,7 +481,7 @@ int launch_link(kv_engine *e, const LinkShape &sh, hipStream_t s, const MovePara
         // fits: the whole call's counts were checked
         if (!fill_dir(q, q.out.n, 0, sh.limit_u, q.out) || !fill_dir(q, q.in.n, 0, sh.limit_u, q.in)) return KV_EUNSUP;
         q.mix_q = whole.mix_q && q.out.tiles ? (((uint64_t)q.out.tiles << 32) + q.in.tiles - 1) / q.in.tiles : 0;
-        launch_move(sh, e->vec, s, q, ids, true, !ev ? end : e->own_streams ? (*ev)[c] : nullptr);
+        launch_move(sh, e->vec, s, q, ids, true, ev && e->own_streams ? (*ev)[c] : nullptr);
         HIPTRY(e, hipGetLastError());
         e->acc.n_launches += 1;
         if (ev && !e->own_streams) HIPTRY(e, hipEventRecord((*ev)[c], s));
@@ -565,21 +564,19 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
                 e->b_i0 = e->ev_i0;
             }
         }
-        // the event behind the whole call: recorded by its last launch, or a packet of its own
-        const hipEvent_t end = e->own_streams && !layered ? e->ring_out[k] : nullptr;
         if (launch_link(e, sh, e->s_out, p, MoveIds{d_o, d_o + no, d_i, d_i + ni},
-                        layered ? &e->layer_ev_out : nullptr, n_rest > 0 ? nullptr : end) != KV_OK)
+                        layered ? &e->layer_ev_out : nullptr) != KV_OK)
             return KV_EHIP;
         e->layer_chunk = layered ? e->cfg.chunk_layers : 0;
         e->layer_on_out = layered;
         e->layer_on_in = false;
         if (n_rest > 0) {
             launch_move(sh_rest, e->vec, e->s_out, p_rest,
-                        MoveIds{d_o + no_paired, d_o + no + no_paired, nullptr, nullptr}, true, end);
+                        MoveIds{d_o + no_paired, d_o + no + no_paired, nullptr, nullptr}, true);
             HIPTRY(e, hipGetLastError());
             e->acc.n_launches += 1;
         }
-        if (mark_end(e, true, k, e->s_out, end != nullptr) != KV_OK) return KV_EHIP;
+        if (mark_end(e, true, k, e->s_out) != KV_OK) return KV_EHIP;
         e->b_i1 = e->ring_out[k];
         // What is enqueued on stream_in from now on comes after this call.  Nobody but the
         // engine enqueues on a stream of its own, so there the wait can be left until
@@ -633,18 +630,16 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
     if (no > 0) {
         if (upload_ids(true, false, e->s_out) != KV_OK) return KV_EHIP;
         if (mark_start(e, true, e->s_out) != KV_OK) return KV_EHIP;
-        const hipEvent_t end = e->own_streams && !layered ? e->ring_out[k] : nullptr;
-        if (launch_link(e, sh_out, e->s_out, p_out, ids_out, layered ? &e->layer_ev_out : nullptr, end) != KV_OK)
+        if (launch_link(e, sh_out, e->s_out, p_out, ids_out, layered ? &e->layer_ev_out : nullptr) != KV_OK)
             return KV_EHIP;
-        if (mark_end(e, true, k, e->s_out, end != nullptr) != KV_OK) return KV_EHIP;
+        if (mark_end(e, true, k, e->s_out) != KV_OK) return KV_EHIP;
     }
     if (ni > 0) {
         if (upload_ids(false, true, e->s_in) != KV_OK) return KV_EHIP;
         if (mark_start(e, false, e->s_in) != KV_OK) return KV_EHIP;
-        const hipEvent_t end = e->own_streams && !layered ? e->ring_in[k] : nullptr;
-        if (launch_link(e, sh_in, e->s_in, p_in, ids_in, layered ? &e->layer_ev_in : nullptr, end) != KV_OK)
+        if (launch_link(e, sh_in, e->s_in, p_in, ids_in, layered ? &e->layer_ev_in : nullptr) != KV_OK)
             return KV_EHIP;
-        if (mark_end(e, false, k, e->s_in, end != nullptr) != KV_OK) return KV_EHIP;
+        if (mark_end(e, false, k, e->s_in) != KV_OK) return KV_EHIP;
     }
     return KV_OK;
 }
@@ -1357,15 +1352,13 @@ int kv_wait(kv_engine *e)
 {
     if (!e) return KV_EINVAL;
     if (e->sticky != KV_OK) return e->sticky;
-    // Only streams this engine put work on are waited for.  On its own streams the event
-    // behind the last call is the end of all there is, and is waited for in 3 us less than
-    // the stream (which a launch that records its own event leaves without a last packet).
+    // Only streams this engine put work on are waited for.  (Waiting for the event behind
+    // the last call instead is 3 us shorter, and leaves the runtime with a stream it has
+    // not seen idle: every allocation and device-wide wait of the process pays for that.)
     for (int side = 0; side < 2; side++) {
         const bool pending = side == 0 ? e->out_pending : e->in_pending;
         if (!pending) continue;
-        const hipEvent_t last = side == 0 ? e->b_o1 : e->b_i1;
-        if (e->own_streams && last) HIPTRY(e, hipEventSynchronize(last));
-        else HIPTRY(e, hipStreamSynchronize(side == 0 ? e->s_out : e->s_in));
+        HIPTRY(e, hipStreamSynchronize(side == 0 ? e->s_out : e->s_in));
     }
     e->out_pending = e->in_pending = false;
     e->out_dirty = e->in_dirty = false;
