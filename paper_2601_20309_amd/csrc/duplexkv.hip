@@ -146,12 +146,20 @@ int pick_vec(const kv_engine *e)
 // used, or whose slots are the list indices, passes nullptr).
 struct MoveIds {
     const int32_t *out_ids, *out_slots, *in_ids, *in_slots;
+    bool on_host = false;  // the pointers are the host's, and the lists few enough to be kernel arguments
 };
 
 // A launch's shape: workgroups, lanes per workgroup, vectors per lane per tile;
 // short_steps: with no more steps than this, a wave per step; limit_u: the
 // vectors per lane by which dir_tiles() counts.
 struct LinkShape { int wgs, lanes, u, short_steps, limit_u; };
+
+template <typename... P, typename... A>
+void launch(void (*kernel)(P...), dim3 g, dim3 b, hipStream_t s, hipEvent_t stop, const A &...args)
+{
+    if (stop) hipExtLaunchKernelGGL(kernel, g, b, 0, s, nullptr, stop, 0, args...);
+    else hipLaunchKernelGGL(kernel, g, b, 0, s, args...);
+}
 
 // The waves of the launch are the workers, and no more of them are launched than
 // it has steps.  `stop` (may be nullptr) is recorded by the launch itself.
@@ -162,15 +170,17 @@ void launch_move_v(int vec, const LinkShape &sh, hipStream_t s, const MoveParams
     const uint32_t waves_per_wg = (uint32_t)sh.lanes / dkv::kWave, most = (steps + waves_per_wg - 1) / waves_per_wg;
     const uint32_t wgs = steps <= (uint32_t)sh.short_steps ? most : std::min<uint32_t>((uint32_t)sh.wgs, most);
     dim3 g(std::max(1u, wgs)), b((unsigned)sh.lanes);
-#define DKV_LAUNCH(V)                                                                                              \
-    do {                                                                                                           \
-        if (stop)                                                                                                  \
-            hipExtLaunchKernelGGL((dkv::kv_move_kernel<V, U, LINK>), g, b, 0, s, nullptr, stop, 0, p, d.out_ids,   \
-                                  d.out_slots, d.in_ids, d.in_slots);                                              \
-        else                                                                                                       \
-            hipLaunchKernelGGL((dkv::kv_move_kernel<V, U, LINK>), g, b, 0, s, p, d.out_ids, d.out_slots, d.in_ids, \
-                               d.in_slots);                                                                        \
-    } while (0)
+    if constexpr (LINK) {
+        if (d.on_host) {
+            dkv::IdArgs a;
+            int32_t *to = a.v;
+            for (auto list : {std::make_pair(d.out_ids, p.out.n), {d.out_slots, p.out.n}, {d.in_ids, p.in.n}, {d.in_slots, p.in.n}})
+                to = std::copy(list.first, list.first + list.second, to);
+            launch(dkv::kv_move_inline_kernel<dkv::u32x4, U>, g, b, s, stop, p, a);
+            return;
+        }
+    }
+#define DKV_LAUNCH(V) launch(dkv::kv_move_kernel<V, U, LINK>, g, b, s, stop, p, d.out_ids, d.out_slots, d.in_ids, d.in_slots)
     switch (vec) {
     case 16: DKV_LAUNCH(dkv::u32x4); break;
     case 8: DKV_LAUNCH(dkv::u32x2); break;
@@ -179,6 +189,12 @@ void launch_move_v(int vec, const LinkShape &sh, hipStream_t s, const MoveParams
     default: DKV_LAUNCH(unsigned char); break;
     }
 #undef DKV_LAUNCH
+}
+
+// Whether a call's lists go into its launches' arguments.
+bool ids_inline(const kv_engine *e, int32_t no, int32_t ni)
+{
+    return e->vec == 16 && 2 * ((int64_t)no + ni) <= (int64_t)dkv::kInlineIds;
 }
 
 // link: the far side is host memory (zero-copy paths); else HBM staging.
@@ -515,7 +531,9 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
     // link traffic (4 KiB segments, one layer: 83 instead of 93 GB/s), so the set
     // is uploaded first, ~5 us on the launch's stream.
     const uint64_t visit_bytes = e->cfg.host_layout == KV_HOST_LAYER_FIRST ? e->seg : e->block_bytes;
-    const bool upload = visit_bytes < (256u << 10);
+    // A call of few blocks has no such choice to make: its lists are kernel arguments.
+    const bool on_host = ids_inline(e, no, ni);
+    const bool upload = !on_host && visit_bytes < (256u << 10);
     int32_t *dd = upload ? e->desc_dev + (size_t)k * e->desc_cap : dh;
     int32_t *d_o = dd, *d_i = dd + 2 * (size_t)no;  // each: [ids | slots]
     auto upload_ids = [&](bool out_part, bool in_part, hipStream_t s) -> int {
@@ -564,7 +582,7 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
                 e->b_i0 = e->ev_i0;
             }
         }
-        if (launch_link(e, sh, e->s_out, p, MoveIds{d_o, d_o + no, d_i, d_i + ni},
+        if (launch_link(e, sh, e->s_out, p, MoveIds{d_o, d_o + no, d_i, d_i + ni, on_host},
                         layered ? &e->layer_ev_out : nullptr) != KV_OK)
             return KV_EHIP;
         e->layer_chunk = layered ? e->cfg.chunk_layers : 0;
@@ -572,7 +590,7 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
         e->layer_on_in = false;
         if (n_rest > 0) {
             launch_move(sh_rest, e->vec, e->s_out, p_rest,
-                        MoveIds{d_o + no_paired, d_o + no + no_paired, nullptr, nullptr}, true);
+                        MoveIds{d_o + no_paired, d_o + no + no_paired, nullptr, nullptr, on_host}, true);
             HIPTRY(e, hipGetLastError());
             e->acc.n_launches += 1;
         }
@@ -597,7 +615,7 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
         sh_out.lanes = sh_in.lanes = dkv::kWave;
         sh_out.u = sh_in.u = sh_out.limit_u = sh_in.limit_u = 1;
     }
-    const MoveIds ids_out{d_o, d_o + no, nullptr, nullptr}, ids_in{nullptr, nullptr, d_i, d_i + ni};
+    const MoveIds ids_out{d_o, d_o + no, nullptr, nullptr, on_host}, ids_in{nullptr, nullptr, d_i, d_i + ni, on_host};
     // launches on stream_out draw from the first pair of counters, those on stream_in from the second
     MoveParams p_out = params(sh_out.u, e->claim), p_in = params(sh_in.u, e->claim + kClaimStride);
     p_out.in = p_in.out = none;
@@ -1528,6 +1546,13 @@ int kv_rotate_static(const kv_config *cfg, void *hbm_cache, void *host_pool, voi
     p.claim = reinterpret_cast<unsigned int *>(sc);
     int32_t *ids = reinterpret_cast<int32_t *>(sc + kStaticIdsOff);
     hipStream_t s = (hipStream_t)stream;
+    // Few blocks: the lists are arguments of the one launch.  (1 + 1 blocks of 120 KiB: 31.9 us
+    // with the launch that puts them into the array, 28.6 without; 4 + 3 of 2 MiB: 203.6 and 199.6.)
+    if (ids_inline(e, no, ni)) {
+        launch_move(sh, e->vec, s, p, MoveIds{oi, os, ii, is, true}, true);
+        HIPTRY((kv_engine *)nullptr, hipGetLastError());
+        return KV_OK;
+    }
     // the four lists, back to back, through kernel arguments
     const int32_t *src[4] = {oi, os, ii, is};
     const uint32_t len[4] = {(uint32_t)no, (uint32_t)no, (uint32_t)ni, (uint32_t)ni};
@@ -1682,13 +1707,6 @@ int kv_reader_start(kv_engine *e, const int32_t *ids, int32_t n, int32_t passes,
     // a rounded-up reciprocal is exact while index * divisor stays below 2^64 (and 2^64 / 1 has no room)
     if (p.vec_per_seg > 1 && p.n_vecs <= ~0ull / p.vec_per_seg) p.seg_magic = ~0ull / p.vec_per_seg + 1;
     p.next = reinterpret_cast<unsigned int *>(e->read_part + most_wgs);
-    if (n > 0) {
-        memcpy(e->read_ids_host, ids, (size_t)n * sizeof(int32_t));
-        const unsigned g = std::min(64u, ((unsigned)n + dkv::kThreads - 1) / dkv::kThreads);
-        hipLaunchKernelGGL(dkv::kv_reader_begin_kernel, dim3(g), dim3(dkv::kThreads), 0, e->s_read, e->read_ids_host,
-                           e->read_ids, p.n, p.next);
-        HIPTRY(e, hipGetLastError());
-    }
     int wgs = most_wgs;
     if (max_wgs > 0) wgs = std::min(wgs, (int)max_wgs);
     wgs = (int)std::min<uint32_t>((uint32_t)wgs, std::max<uint32_t>(p.tiles, 1u));
@@ -1699,17 +1717,27 @@ int kv_reader_start(kv_engine *e, const int32_t *ids, int32_t n, int32_t passes,
     // where the workgroups that the copy slows set the pace.)
     const uint32_t rounds = p.tiles / (uint32_t)wgs;
     p.fixed = rounds < 4 ? rounds + 1 : rounds / 2;
-    const bool rows = p.vec_per_seg % dkv::kWave == 0;
+    const bool rows = p.vec_per_seg % dkv::kWave == 0, on_host = n <= (int32_t)dkv::kInlineIds;
+    dkv::IdArgs a;
+    if (on_host) std::copy(ids, ids + n, a.v);
+    if (n > 0 && (!on_host || rounds >= 4)) {
+        memcpy(e->read_ids_host, ids, (size_t)n * sizeof(int32_t));
+        const unsigned g = std::min(64u, ((unsigned)n + dkv::kThreads - 1) / dkv::kThreads);
+        hipLaunchKernelGGL(dkv::kv_reader_begin_kernel, dim3(g), dim3(dkv::kThreads), 0, e->s_read, e->read_ids_host,
+                           e->read_ids, p.n, p.next);
+        HIPTRY(e, hipGetLastError());
+    }
     HIPTRY(e, hipEventRecord(e->read_ev[0], e->s_read));
     for (int32_t k = 0; k < passes; k++) {
         if (p.tiles > 0) {
             p.pass = (uint32_t)k;
-            if (rows)
-                hipLaunchKernelGGL((dkv::kv_reader_kernel<true>), dim3((unsigned)wgs), dim3(dkv::kThreads), 0, e->s_read, p,
-                                   e->read_ids);
+            const dim3 g((unsigned)wgs), b(dkv::kThreads);
+            if (on_host)
+                launch(rows ? dkv::kv_reader_inline_kernel<true> : dkv::kv_reader_inline_kernel<false>, g, b, e->s_read,
+                       nullptr, p, a);
             else
-                hipLaunchKernelGGL((dkv::kv_reader_kernel<false>), dim3((unsigned)wgs), dim3(dkv::kThreads), 0, e->s_read, p,
-                                   e->read_ids);
+                launch(rows ? dkv::kv_reader_kernel<true> : dkv::kv_reader_kernel<false>, g, b, e->s_read, nullptr, p,
+                       (const int32_t *)e->read_ids);
             HIPTRY(e, hipGetLastError());
         }
         HIPTRY(e, hipEventRecord(e->read_ev[(size_t)k + 1], e->s_read));

@@ -20,6 +20,16 @@ namespace dkv {
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
+// Id lists of a call that names few blocks, handed over as a kernel argument: the
+// runtime keeps arguments where the device reads them like its own memory.  From
+// pinned host memory the first ids of a launch cost it a round trip over the
+// link before its first byte moves (2-6 us), and a launch or copy that brings
+// them to device memory costs 5.
+constexpr uint32_t kInlineIds = 896;  // 3.5 of the 4 KiB that a kernel's arguments may take
+struct IdArgs {
+    int32_t v[kInlineIds];
+};
+
 constexpr int kWave = 64;          // a wave is the unit of work: one tile at a time
 constexpr int kThreads = 256;      // lanes per workgroup of the HBM-bound launches and of the reader (4 waves)
 // Vectors per lane where a tile may span segments: every vector has pointers of its
@@ -387,11 +397,9 @@ __device__ __forceinline__ void run_drawn(const MoveParams &p, const int32_t *__
 // kv_stage_kernel) move a tile in ~2 ns chip-wide, too fast for one counter, and
 // use the fixed share.
 template <typename V, int U, bool LINK>
-__global__ __launch_bounds__(kMaxThreads) void kv_move_kernel(const MoveParams p,
-                                                              const int32_t *__restrict__ out_ids,
-                                                              const int32_t *__restrict__ out_slots,
-                                                              const int32_t *__restrict__ in_ids,
-                                                              const int32_t *__restrict__ in_slots)
+__device__ __forceinline__ void move(const MoveParams &p, const int32_t *__restrict__ out_ids,
+                                     const int32_t *__restrict__ out_slots, const int32_t *__restrict__ in_ids,
+                                     const int32_t *__restrict__ in_slots)
 {
     const uint32_t lane = threadIdx.x & (kWave - 1u), waves_per_wg = blockDim.x / kWave;
     const uint32_t wave = blockIdx.x * waves_per_wg + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -409,6 +417,23 @@ __global__ __launch_bounds__(kMaxThreads) void kv_move_kernel(const MoveParams p
         run_drawn<V, U, LINK, true>(p, out_ids, out_slots, in_ids, in_slots, n_steps, wave, n_waves, lane);
     else
         run_drawn<V, UR, LINK, false>(p, out_ids, out_slots, in_ids, in_slots, n_steps, wave, n_waves, lane);
+}
+
+template <typename V, int U, bool LINK>
+__global__ __launch_bounds__(kMaxThreads) void kv_move_kernel(const MoveParams p,
+                                                              const int32_t *__restrict__ out_ids,
+                                                              const int32_t *__restrict__ out_slots,
+                                                              const int32_t *__restrict__ in_ids,
+                                                              const int32_t *__restrict__ in_slots)
+{
+    move<V, U, LINK>(p, out_ids, out_slots, in_ids, in_slots);
+}
+
+// The lists, back to back, in the arguments: out ids, out slots, in ids, in slots.
+template <typename V, int U>
+__global__ __launch_bounds__(kMaxThreads) void kv_move_inline_kernel(const MoveParams p, const IdArgs a)
+{
+    move<V, U, true>(p, a.v, a.v + p.out.n, a.v + 2 * p.out.n, a.v + 2 * p.out.n + p.in.n);
 }
 
 // Pack / unpack of the DMA-staged path when nothing caps the launch: both sides
@@ -599,7 +624,7 @@ __device__ __forceinline__ unsigned long long read_tile(const ReadParams &p, con
 }
 
 template <bool ROWS>
-__global__ __launch_bounds__(kThreads) void kv_reader_kernel(const ReadParams p, const int32_t *__restrict__ ids)
+__device__ __forceinline__ void read_pass(const ReadParams &p, const int32_t *__restrict__ ids)
 {
     const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1u);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -645,8 +670,20 @@ __global__ __launch_bounds__(kThreads) void kv_reader_kernel(const ReadParams p,
     }
 }
 
-// Before the passes: the id list from pinned host memory to the device, the
-// counters to zero.
+template <bool ROWS>
+__global__ __launch_bounds__(kThreads) void kv_reader_kernel(const ReadParams p, const int32_t *__restrict__ ids)
+{
+    read_pass<ROWS>(p, ids);
+}
+
+template <bool ROWS>
+__global__ __launch_bounds__(kThreads) void kv_reader_inline_kernel(const ReadParams p, const IdArgs a)
+{
+    read_pass<ROWS>(p, a.v);
+}
+
+// Before the passes, where they need it: the id list from pinned host memory to the
+// device, the counters to zero.
 __global__ __launch_bounds__(kThreads) void kv_reader_begin_kernel(const int32_t *__restrict__ from, int32_t *__restrict__ ids,
                                                                    uint32_t n, unsigned int *next)
 {
