@@ -786,6 +786,18 @@ void sorted_desc(kv_engine *e, const int32_t *ids, const int32_t *slots, int32_t
 }
 
 // Copies of one chunk between staging and pool.  `to_host` picks the direction.
+//
+// A copy costs its DMA engine 5-10 us beyond its bytes, so short rows of equal
+// length at equal distances on both sides go as one two-dimensional copy, which the
+// engines take like any other (64 rows of 32 KiB: 603 us as 64 copies, 46 us as
+// one): the planes of a run of slots in a layer-first pool, and the blocks of a run
+// when a chunk holds some of their planes.  Rows of kOwnCopy and more keep a copy
+// each: those run both ways at 45 GB/s and up, while two-dimensional copies of the
+// two directions may come to share one engine (54 GB/s).  For the same reason
+// scattered whole blocks are not joined in pairs, though any two are equally spaced:
+// 120 + 96 blocks of 2 MiB took 8965 us in pairs, 5885 one by one.
+constexpr uint64_t kOwnCopy = 512ull << 10;
+
 int chunk_copies(kv_engine *e, bool to_host, uint8_t *stage, const int32_t *sorted_slots, uint32_t j0,
                  uint32_t j1, uint32_t p0, uint32_t p1, hipStream_t s, int32_t &n_copies)
 {
@@ -797,24 +809,35 @@ int chunk_copies(kv_engine *e, bool to_host, uint8_t *stage, const int32_t *sort
         return to_host ? hipMemcpyAsync(e->pool + pool_off, stage + stage_off, bytes, hipMemcpyDeviceToHost, s)
                        : hipMemcpyAsync(stage + stage_off, e->pool + pool_off, bytes, hipMemcpyHostToDevice, s);
     };
-    const bool block_first = e->cfg.host_layout == KV_HOST_BLOCK_FIRST;
+    auto copy_rows = [&](uint64_t pool_off, uint64_t pool_pitch, uint64_t stage_off, uint64_t stage_pitch, uint64_t width,
+                         uint32_t rows) -> hipError_t {
+        const uint64_t odd = ((uint64_t)(uintptr_t)e->pool | pool_off | stage_off | pool_pitch | stage_pitch | width) & 3u;
+        if (rows == 1 || width >= kOwnCopy || odd || pool_pitch > 0x7FFFFFFFull || stage_pitch > 0x7FFFFFFFull) {
+            hipError_t rc = hipSuccess;
+            for (uint32_t r = 0; r < rows && rc == hipSuccess; r++)
+                rc = copy(pool_off + r * pool_pitch, stage_off + r * stage_pitch, width);
+            return rc;
+        }
+        n_copies++;
+        return to_host ? hipMemcpy2DAsync(e->pool + pool_off, pool_pitch, stage + stage_off, stage_pitch, width, rows,
+                                          hipMemcpyDeviceToHost, s)
+                       : hipMemcpy2DAsync(stage + stage_off, stage_pitch, e->pool + pool_off, pool_pitch, width, rows,
+                                          hipMemcpyHostToDevice, s);
+    };
+    const bool block_first = e->cfg.host_layout == KV_HOST_BLOCK_FIRST, whole = np == e->n_planes;
+    const uint64_t row = (uint64_t)np * e->seg;  // block-first: one block's part of the chunk
     uint32_t j = j0;
     while (j < j1) {  // run of consecutive slots [j, r)
         uint32_t r = j + 1;
         while (r < j1 && sorted_slots[r] == sorted_slots[r - 1] + 1) r++;
         const uint64_t slot = (uint64_t)sorted_slots[j];
-        if (block_first) {
-            if (np == e->n_planes) {  // whole blocks: the run is one range
-                HIPTRY(e, copy(slot * ss, (uint64_t)(j - j0) * np * e->seg, (uint64_t)(r - j) * np * e->seg));
-            } else {
-                for (uint32_t b = j; b < r; b++)
-                    HIPTRY(e, copy((uint64_t)sorted_slots[b] * ss + (uint64_t)p0 * ps,
-                                   (uint64_t)(b - j0) * np * e->seg, (uint64_t)np * e->seg));
-            }
+        if (block_first && whole) {  // the run is one range
+            HIPTRY(e, copy(slot * ss, (j - j0) * row, (r - j) * row));
+        } else if (block_first) {
+            HIPTRY(e, copy_rows(slot * ss + (uint64_t)p0 * ps, ss, (j - j0) * row, row, row, r - j));
         } else {
-            for (uint32_t pl = p0; pl < p1; pl++)
-                HIPTRY(e, copy(slot * ss + (uint64_t)pl * ps,
-                               ((uint64_t)(pl - p0) * nb + (j - j0)) * e->seg, (uint64_t)(r - j) * e->seg));
+            HIPTRY(e, copy_rows(slot * ss + (uint64_t)p0 * ps, ps, (uint64_t)(j - j0) * e->seg, (uint64_t)nb * e->seg,
+                                (uint64_t)(r - j) * e->seg, np));
         }
         j = r;
     }

@@ -465,3 +465,29 @@ def test_calls_of_one_direction_keep_their_order_behind_joint_launches():
         case.rotate(rot.inverse())
     case.check()
     case.close()
+
+
+@pytest.mark.parametrize("host_layout", LAYOUTS)
+@pytest.mark.parametrize("tokens,heads,chunk_layers,staging", [(16, 8, 0, 0), (5, 3, 0, 0), (16, 1, 2, 0), (7, 1, 0, 1 << 16),
+                                                              (1, 1, 1, 0)])
+def test_staged_copies_of_several_rows(host_layout, tokens, heads, chunk_layers, staging):
+    """The DMA-staged path where its copies are joined: runs of slots of many lengths,
+    single slots, planes of a layer-first pool, partial planes of a block-first one,
+    rows of odd and of 4-byte lengths, chunks that cut the list; whole cache and pool
+    against the oracle, both directions and each alone."""
+    sh = W.KVShape(6, heads, 40, tokens, n_hbm_blocks=120, n_host_slots=110)
+    rng = np.random.default_rng(tokens * 10 + heads)
+    ids = rng.permutation(120).astype(np.int32)
+    slots = np.delete(np.arange(110), rng.permutation(110)[:34]).astype(np.int32)     # 76 slots in runs of 1, 2, 3, ...
+    out_slots, in_slots = np.concatenate([slots[:40:1][::2], slots[40:60]]), np.concatenate([slots[1:40:2], slots[60:]])
+    rot = W.Rotation(ids[:len(out_slots)], out_slots, ids[len(out_slots):len(out_slots) + len(in_slots)], in_slots)
+    case, _ = make_case(sh, host_layout, B.KV_PATH_SDMA_STAGED, rot=rot, chunk_layers=chunk_layers, staging_bytes=staging)
+    case.rotate(rot)
+    case.check()
+    case.swap_out(rot.in_ids, rot.out_slots[:len(rot.in_ids)])
+    case.check()
+    case.swap_in(rot.in_slots, rot.out_ids[:len(rot.in_slots)])
+    case.check()
+    case.rotate(W.Rotation(rot.in_ids, rot.in_slots, rot.out_ids, rot.out_slots))
+    case.check()
+    case.close()
