@@ -1694,12 +1694,13 @@ int kv_reader_start(kv_engine *e, const int32_t *ids, int32_t n, int32_t passes,
     // (8 + 8 GiB alone / beside a swap-out of 4 GiB, reader TB/s, and the swap-out's GB/s):
     // 5 per CU 6.57 / 5.3, 56.9;  5.5 6.69 / 6.09, 56.7;  6 6.82 / 6.35, 52.4;  7 6.91 / 5.9, 44.3.
     const int most_wgs = 11 * (e->n_cus > 0 ? e->n_cus : 256) / 2;
+    constexpr size_t kReadCounters = (size_t)dkv::kReadGroups * dkv::kReadStride;  // words of a pass's counters
     if (!e->s_read) {
         const size_t idb = 2 * (size_t)e->cfg.n_hbm_blocks * sizeof(int32_t);
         if (hipMalloc((void **)&e->read_ids, idb) != hipSuccess ||
             hipHostMalloc((void **)&e->read_ids_host, idb, hipHostMallocDefault) != hipSuccess ||
             hipMalloc((void **)&e->read_part, (size_t)most_wgs * sizeof(unsigned long long) +
-                                                  dkv::kReadGroups * dkv::kReadStride * sizeof(unsigned int)) != hipSuccess ||
+                                                  kReadPasses * kReadCounters * sizeof(unsigned int)) != hipSuccess ||
             hipHostMalloc((void **)&e->read_sums, (size_t)most_wgs * sizeof(unsigned long long),
                           hipHostMallocDefault) != hipSuccess) {
             (void)hipGetLastError();
@@ -1729,17 +1730,23 @@ int kv_reader_start(kv_engine *e, const int32_t *ids, int32_t n, int32_t passes,
     p.tiles = (uint32_t)((p.n_vecs + dkv::kReadVecs - 1) / dkv::kReadVecs);
     // a rounded-up reciprocal is exact while index * divisor stays below 2^64 (and 2^64 / 1 has no room)
     if (p.vec_per_seg > 1 && p.n_vecs <= ~0ull / p.vec_per_seg) p.seg_magic = ~0ull / p.vec_per_seg + 1;
-    p.next = reinterpret_cast<unsigned int *>(e->read_part + most_wgs);
+    unsigned int *const next = reinterpret_cast<unsigned int *>(e->read_part + most_wgs);
     int wgs = most_wgs;
     if (max_wgs > 0) wgs = std::min(wgs, (int)max_wgs);
     wgs = (int)std::min<uint32_t>((uint32_t)wgs, std::max<uint32_t>(p.tiles, 1u));
     // Who reads which tile.  Short passes (under four rounds of the grid): every workgroup
-    // takes its fixed share, no counter.  Longer ones: half in fixed shares, the rest
-    // claimed.  (37.5 GiB passes, TB/s alone / beside a rotation / beside a swap-out: all
-    // claimed 6.38 / 5.09 / 5.87; half 6.69 / 5.36 / 6.09; all fixed 6.77 / 4.66 / 2.94,
-    // where the workgroups that the copy slows set the pace.)
+    // takes its fixed share, no counter.  Longer ones: a quarter in fixed shares, the rest
+    // claimed from the workgroup's group, and in passes of 32 rounds and more, which a
+    // last look at other groups' counters does not lengthen, from 16 groups behind it.
+    // 37.5 GiB passes, TB/s alone / beside a rotation of 112, 144, 192 copy waves / beside a
+    // swap-out: all claimed 6.49 / 5.54, 4.99, 3.71 / 5.93; a quarter fixed 6.63 / 5.62, 5.04,
+    // 3.74 / 6.04; half fixed 6.74 / 5.61, 5.04, 2.99 / 6.12, and without other groups
+    // 6.62 / 5.19, 3.95, 2.88 / 6.02; all fixed 6.77 / 4.66 / 2.94 beside 112 and a swap-out,
+    // where the workgroups that the copy slows set the pace.  (One counter for all, claims
+    // of 16 tiles: 6.61 / 5.27, 4.91, 4.36 / 5.94.)
     const uint32_t rounds = p.tiles / (uint32_t)wgs;
-    p.fixed = rounds < 4 ? rounds + 1 : rounds / 2;
+    p.fixed = rounds < 4 ? rounds + 1 : rounds / 4;
+    p.steal = rounds < 32 ? 0 : 16;
     const bool rows = p.vec_per_seg % dkv::kWave == 0, on_host = n <= (int32_t)dkv::kInlineIds;
     dkv::IdArgs a;
     if (on_host) std::copy(ids, ids + n, a.v);
@@ -1747,13 +1754,14 @@ int kv_reader_start(kv_engine *e, const int32_t *ids, int32_t n, int32_t passes,
         memcpy(e->read_ids_host, ids, (size_t)n * sizeof(int32_t));
         const unsigned g = std::min(64u, ((unsigned)n + dkv::kThreads - 1) / dkv::kThreads);
         hipLaunchKernelGGL(dkv::kv_reader_begin_kernel, dim3(g), dim3(dkv::kThreads), 0, e->s_read, e->read_ids_host,
-                           e->read_ids, p.n, p.next);
+                           e->read_ids, p.n, next, dkv::kReadGroups * (uint32_t)passes);
         HIPTRY(e, hipGetLastError());
     }
     HIPTRY(e, hipEventRecord(e->read_ev[0], e->s_read));
     for (int32_t k = 0; k < passes; k++) {
         if (p.tiles > 0) {
             p.pass = (uint32_t)k;
+            p.next = next + (size_t)k * kReadCounters;
             const dim3 g((unsigned)wgs), b(dkv::kThreads);
             if (on_host)
                 launch(rows ? dkv::kv_reader_inline_kernel<true> : dkv::kv_reader_inline_kernel<false>, g, b, e->s_read,

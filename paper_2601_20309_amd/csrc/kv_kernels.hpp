@@ -495,7 +495,7 @@ __global__ __launch_bounds__(kThreads) void kv_stage_kernel(const StageParams p,
 // each are 5.6 MiB over the chip, which is the HBM rate times its latency.  More
 // only queue in front of HBM, and a copy over the link that runs beside the
 // reader stands in the same queues: eight rows per wave read 6.6 TB/s alone like
-// one does, but take a rotation beside them from 100 to 58 GB/s (one: 100.0).
+// one does, but take a rotation beside them from 100 to 58 GB/s (one: 100.3).
 //
 // No two workgroups meet on an address while they read.  An atomic on one address
 // is served every ~14 ns: one counter for the tiles limits claims to 2.3 TB/s per
@@ -514,8 +514,9 @@ struct ReadParams {
     uint32_t vec_per_seg;    // seg_bytes / 16
     uint32_t tiles;
     uint32_t fixed;          // tiles each workgroup takes without asking (see kv_reader_kernel)
-    uint32_t pass, passes;   // pass 0: part[] holds nothing yet, the counters are zero
-    unsigned int *next;      // kReadGroups counters, kReadStride apart, of claimed tiles
+    uint32_t pass, passes;   // pass 0: part[] holds nothing yet
+    uint32_t steal;          // groups besides its own that a workgroup takes tiles from
+    unsigned int *next;      // this pass's kReadGroups counters of claimed tiles, kReadStride apart, zero at launch
 };
 
 constexpr int kReadU = 8;      // rows per wave and tile
@@ -523,8 +524,8 @@ constexpr int kReadDepth = 1;  // rows in flight per wave
 constexpr uint32_t kReadRows = (uint32_t)kReadU * (kThreads / kWave);  // rows per tile
 constexpr uint32_t kReadVecs = kReadRows * kWave;                      // vectors per tile
 // Counters.  Workgroups that follow one another share one: they lie on different
-// XCDs, so a group loses as much to a copy beside it as any other (every 64th
-// workgroup instead, all on one XCD: 3.5 instead of 6.1 TB/s beside a swap-out).
+// XCDs, so a group loses nearly as much to a copy beside it as any other (every
+// 64th workgroup instead, all on one XCD: 3.5 instead of 6.1 TB/s beside a swap-out).
 // Fewer groups meet more often on their counter (8: 6.44 TB/s alone, 64: 6.69).
 constexpr uint32_t kReadGroups = 64;
 constexpr uint32_t kReadStride = 32;  // 32-bit words from one counter to the next
@@ -632,30 +633,32 @@ __device__ __forceinline__ void read_pass(const ReadParams &p, const int32_t *__
     __shared__ unsigned long long sums[kThreads / kWave];
     // first the fixed share, a tile every gridDim.x ...
     const uint32_t n_fixed = (uint32_t)min((uint64_t)p.fixed * gridDim.x, (uint64_t)p.tiles);
-    // ... then tiles n_fixed + group + n_groups * c, c drawn from the group's counter.
-    // A pass takes one draw per tile and one more per workgroup from it, so where the
-    // counter stands when a later pass begins is known and it is never reset.
-    const uint32_t per_group = (gridDim.x + kReadGroups - 1u) / kReadGroups, group = blockIdx.x / per_group;
+    // ... then tiles n_fixed + group + n_groups * c, c drawn from the group's counter, and
+    // once the group has none left, from those of the next p.steal groups
+    const uint32_t per_group = (gridDim.x + kReadGroups - 1u) / kReadGroups;
     const uint32_t n_groups = (gridDim.x + per_group - 1u) / per_group, shared = p.tiles - n_fixed;
-    const uint32_t n_claims = (shared + n_groups - 1u - group) / n_groups;
-    const uint32_t members = min(per_group, gridDim.x - group * per_group);
-    const uint32_t base = p.pass * (n_claims + members);
-    unsigned int *const next = p.next + group * kReadStride;
+    uint32_t group = blockIdx.x / per_group, steals = min(p.steal, n_groups - 1u);
     // the next claim is always in flight while the tile before it is read
     uint32_t pending = 0;
-    if (shared && tid == 0) pending = atomicAdd(next, 1u);
+    if (shared && tid == 0) pending = atomicAdd(p.next + group * kReadStride, 1u);
     unsigned long long sum = 0;
     uint32_t t = blockIdx.x, end = n_fixed;
     for (uint32_t turn = 0;; turn ^= 1u) {
         for (; t < end; t += gridDim.x) sum += read_tile<ROWS>(p, ids, t, wave, lane);
         if (!shared) break;
-        if (tid == 0) claimed[turn] = pending - base;
+        if (tid == 0) claimed[turn] = pending;
         __syncthreads();  // one per claim: the two slots alternate
         const uint32_t c = __builtin_amdgcn_readfirstlane(claimed[turn]);
-        if (c >= n_claims) break;
-        if (tid == 0) pending = atomicAdd(next, 1u);
-        t = n_fixed + group + n_groups * c;
-        end = t + 1u;
+        const uint64_t claim = (uint64_t)c * n_groups + group;
+        if (claim >= shared) {
+            if (steals == 0) break;
+            steals--;
+            group = group + 1u == n_groups ? 0u : group + 1u;
+        } else {
+            t = n_fixed + (uint32_t)claim;
+            end = t + 1u;
+        }
+        if (tid == 0) pending = atomicAdd(p.next + group * kReadStride, 1u);
     }
     // one sum per workgroup, in a place of its own (the host adds them up)
 #pragma unroll
@@ -685,11 +688,11 @@ __global__ __launch_bounds__(kThreads) void kv_reader_inline_kernel(const ReadPa
 // Before the passes, where they need it: the id list from pinned host memory to the
 // device, the counters to zero.
 __global__ __launch_bounds__(kThreads) void kv_reader_begin_kernel(const int32_t *__restrict__ from, int32_t *__restrict__ ids,
-                                                                   uint32_t n, unsigned int *next)
+                                                                   uint32_t n, unsigned int *next, uint32_t counters)
 {
     const uint32_t t = blockIdx.x * kThreads + threadIdx.x;
     for (uint32_t i = t; i < n; i += gridDim.x * kThreads) ids[i] = from[i];
-    if (t < kReadGroups) next[t * kReadStride] = 0u;
+    for (uint32_t i = t; i < counters; i += gridDim.x * kThreads) next[i * kReadStride] = 0u;
 }
 
 }  // namespace dkv
