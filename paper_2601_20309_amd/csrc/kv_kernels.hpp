@@ -7,6 +7,7 @@
 //     directions locked 1:1 (measured faster in duplex than two independent
 //     kernels, and above the DMA engines' duplex rate);
 //   - a single direction (the other list empty): zero-copy swap-out or swap-in;
+//     (both also as kv_move_inline_kernel, few blocks, lists in the arguments)
 //   - pack / unpack between the scattered cache and a contiguous staging
 //     buffer in HBM (the "far" side is then device memory, slot = list index)
 //     when the launch is capped to a few workgroups; uncapped, pack / unpack
