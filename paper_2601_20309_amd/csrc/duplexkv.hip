@@ -1690,9 +1690,10 @@ int kv_reader_start(kv_engine *e, const int32_t *ids, int32_t n, int32_t passes,
     if ((int64_t)n > 2 * (int64_t)e->cfg.n_hbm_blocks) return KV_EINVAL;
     if (e->seg % 16 != 0 || ((uintptr_t)e->hbm & 15u) != 0) return KV_EUNSUP;
     // Workgroups: 5.5 per CU.  With one row in flight per wave (kReadDepth) that is 5.6 MiB
-    // in flight, just enough for the HBM rate alone, and what a rotation beside it can bear
-    // (8 + 8 GiB alone / beside a swap-out of 4 GiB, reader TB/s, and the swap-out's GB/s):
-    // 5 per CU 6.57 / 5.3, 56.9;  5.5 6.69 / 6.09, 56.7;  6 6.82 / 6.35, 52.4;  7 6.91 / 5.9, 44.3.
+    // in flight, enough for the HBM rate alone, and the most that a copy beside it bears
+    // without loss (8 GiB passes, TB/s alone / beside a swap-out, and its GB/s / a rotation):
+    // 5 per CU 6.61 / 5.11, 56.7 / 5.10;  5.5 6.83 / 5.94, 56.7 / 5.39;  6 6.91 / 6.69, 55.7 /
+    // 5.64 (the rotation 100.2 GB/s for 100.8);  7 6.90 / 3.25, 53.1 / 4.79.
     const int most_wgs = 11 * (e->n_cus > 0 ? e->n_cus : 256) / 2;
     constexpr size_t kReadCounters = (size_t)dkv::kReadGroups * dkv::kReadStride;  // words of a pass's counters
     if (!e->s_read) {
@@ -1734,19 +1735,23 @@ int kv_reader_start(kv_engine *e, const int32_t *ids, int32_t n, int32_t passes,
     int wgs = most_wgs;
     if (max_wgs > 0) wgs = std::min(wgs, (int)max_wgs);
     wgs = (int)std::min<uint32_t>((uint32_t)wgs, std::max<uint32_t>(p.tiles, 1u));
-    // Who reads which tile.  Short passes (under four rounds of the grid): every workgroup
-    // takes its fixed share, no counter.  Longer ones: a quarter in fixed shares, the rest
-    // claimed from the workgroup's group, and in passes of 32 rounds and more, which a
-    // last look at other groups' counters does not lengthen, from 16 groups behind it.
-    // 37.5 GiB passes, TB/s alone / beside a rotation of 112, 144, 192 copy waves / beside a
-    // swap-out: all claimed 6.49 / 5.54, 4.99, 3.71 / 5.93; a quarter fixed 6.63 / 5.62, 5.04,
-    // 3.74 / 6.04; half fixed 6.74 / 5.61, 5.04, 2.99 / 6.12, and without other groups
-    // 6.62 / 5.19, 3.95, 2.88 / 6.02; all fixed 6.77 / 4.66 / 2.94 beside 112 and a swap-out,
-    // where the workgroups that the copy slows set the pace.  (One counter for all, claims
-    // of 16 tiles: 6.61 / 5.27, 4.91, 4.36 / 5.94.)
+    // Who reads which tile.  Short passes (under four rounds of the grid, 176 MiB): every
+    // workgroup takes its fixed share, no counter.  Longer ones: a quarter in fixed shares,
+    // the rest claimed from the workgroup's group, and in passes of 64 rounds and more,
+    // which a last look at other groups' counters does not lengthen, from two groups behind it.
+    // TB/s alone / beside a swap-out / a swap-in / rotations of 112 and of 192 copy waves:
+    //   37.5 GiB from no other group 7.02 / 6.26 / 5.36 / 5.42, 3.33, from two 7.04 / 6.45 / 5.41 / 5.49, 3.73
+    //    8   GiB                     6.81 / 6.05 / 5.27 / 5.33, 3.06           6.81 / 5.94 / 5.33 / 5.38, 3.62
+    //    2   GiB                     6.47 / 5.66 / 5.18 / 5.11, 2.97           6.46 / 4.88 / 5.20 / 5.12, 3.18
+    //    256 MiB                     5.35 / 3.73 / 4.14 / 3.86, 1.59           5.24 / 2.69 / 3.95 / 3.60, 1.44
+    // (from four and sixteen beside a swap-out: 8 GiB 5.89 and 5.60, 2 GiB 4.89 and 3.94).  An
+    // eighth or a sixteenth in fixed shares changes nothing beyond 2 %; with half or all
+    // fixed, workgroups that a copy slows set the pace (all: 2.9 beside a swap-out of 4 GiB);
+    // under four rounds that is over before it matters: 64 and 128 MiB 37 and 43 us beside a
+    // swap-out, 17 and 27 alone.
     const uint32_t rounds = p.tiles / (uint32_t)wgs;
     p.fixed = rounds < 4 ? rounds + 1 : rounds / 4;
-    p.steal = rounds < 32 ? 0 : 16;
+    p.steal = rounds < 64 ? 0 : 2;
     const bool rows = p.vec_per_seg % dkv::kWave == 0, on_host = n <= (int32_t)dkv::kInlineIds;
     dkv::IdArgs a;
     if (on_host) std::copy(ids, ids + n, a.v);

@@ -524,12 +524,22 @@ constexpr int kReadU = 8;      // rows per wave and tile
 constexpr int kReadDepth = 1;  // rows in flight per wave
 constexpr uint32_t kReadRows = (uint32_t)kReadU * (kThreads / kWave);  // rows per tile
 constexpr uint32_t kReadVecs = kReadRows * kWave;                      // vectors per tile
-// Counters.  Workgroups that follow one another share one: they lie on different
-// XCDs, so a group loses nearly as much to a copy beside it as any other (every
-// 64th workgroup instead, all on one XCD: 3.5 instead of 6.1 TB/s beside a swap-out).
-// Fewer groups meet more often on their counter (8: 6.44 TB/s alone, 64: 6.69).
+// Counters, and the workgroups that share one: one of every 64 that follow one another,
+// each time one place further, so that a group lies on all XCDs and all over each, and
+// a copy beside the pass slows every group alike.  (37.5 GiB, TB/s alone / beside a
+// swap-out, claims of one tile: 64 groups of 22 workgroups that follow one another, that
+// is of the same three CUs of every XCD, 6.57 / 5.91; so placed 6.79 / 6.21.  Every 64th
+// workgroup, all on one XCD, had lost half beside a swap-out.  Fewer groups meet more
+// often on their counter: 8 read 4 % less alone.)
 constexpr uint32_t kReadGroups = 64;
 constexpr uint32_t kReadStride = 32;  // 32-bit words from one counter to the next
+// A claim is 4 tiles, 2 and at last 1: as long as the group has kReadMargin times as
+// many left for each of its workgroups.  A workgroup on a CU with a copy's waves reads
+// several times slower than the others and holds two claims, the one it reads and the
+// one behind it: they must not outlast the pass.  (8 GiB, TB/s alone / beside a swap-out /
+// a rotation: claims of 1 6.61 / 5.80 / 5.37, of 4 6.81 / 5.94 / 5.38, of 8 6.81 / 5.96 / 5.39;
+// claims of 16 with a margin of 2 came to 4.25 beside a swap-out.)
+constexpr uint32_t kReadMargin = 16;
 
 // Quotient of a lane's small step past a segment's (or the list's) first entry,
 // x < d + 64 * kReadU, without a branch: at d >= 64 * kReadU it is 0 or 1; below,
@@ -636,30 +646,38 @@ __device__ __forceinline__ void read_pass(const ReadParams &p, const int32_t *__
     const uint32_t n_fixed = (uint32_t)min((uint64_t)p.fixed * gridDim.x, (uint64_t)p.tiles);
     // ... then tiles n_fixed + group + n_groups * c, c drawn from the group's counter, and
     // once the group has none left, from those of the next p.steal groups
-    const uint32_t per_group = (gridDim.x + kReadGroups - 1u) / kReadGroups;
-    const uint32_t n_groups = (gridDim.x + per_group - 1u) / per_group, shared = p.tiles - n_fixed;
-    uint32_t group = blockIdx.x / per_group, steals = min(p.steal, n_groups - 1u);
-    // the next claim is always in flight while the tile before it is read
-    uint32_t pending = 0;
-    if (shared && tid == 0) pending = atomicAdd(p.next + group * kReadStride, 1u);
+    const uint32_t n_groups = min(gridDim.x, kReadGroups), per_group = (gridDim.x + n_groups - 1u) / n_groups;
+    const uint32_t shared = p.tiles - n_fixed, each = shared / n_groups, extra = shared - each * n_groups;
+    uint32_t group = (blockIdx.x + blockIdx.x / kReadGroups) % n_groups, steals = min(p.steal, n_groups - 1u);
+    uint32_t size = each + (group < extra ? 1u : 0u);  // tiles of the group
+    auto claim_size = [&](uint32_t c) {  // tiles of the claim that follows tile c of the group
+        const uint32_t left = size - min(c, size), round = kReadMargin * per_group;
+        return left > 4u * round ? 4u : left > 2u * round ? 2u : 1u;
+    };
+    // the next claim is always in flight while the tiles before it are read
+    uint32_t pending = 0, want = claim_size(0);
+    if (shared && tid == 0) pending = atomicAdd(p.next + group * kReadStride, want);
     unsigned long long sum = 0;
-    uint32_t t = blockIdx.x, end = n_fixed;
+    uint32_t t = blockIdx.x, end = n_fixed, step = gridDim.x;
     for (uint32_t turn = 0;; turn ^= 1u) {
-        for (; t < end; t += gridDim.x) sum += read_tile<ROWS>(p, ids, t, wave, lane);
+        for (; t < end; t += step) sum += read_tile<ROWS>(p, ids, t, wave, lane);
         if (!shared) break;
         if (tid == 0) claimed[turn] = pending;
         __syncthreads();  // one per claim: the two slots alternate
         const uint32_t c = __builtin_amdgcn_readfirstlane(claimed[turn]);
-        const uint64_t claim = (uint64_t)c * n_groups + group;
-        if (claim >= shared) {
+        if (c >= size) {
             if (steals == 0) break;
             steals--;
             group = group + 1u == n_groups ? 0u : group + 1u;
+            size = each + (group < extra ? 1u : 0u);
+            want = 1u;
         } else {
-            t = n_fixed + (uint32_t)claim;
-            end = t + 1u;
+            step = n_groups;
+            t = n_fixed + group + n_groups * c;
+            end = n_fixed + group + n_groups * min(c + want, size);
+            want = claim_size(c + want);
         }
-        if (tid == 0) pending = atomicAdd(p.next + group * kReadStride, 1u);
+        if (tid == 0) pending = atomicAdd(p.next + group * kReadStride, want);
     }
     // one sum per workgroup, in a place of its own (the host adds them up)
 #pragma unroll

@@ -2,6 +2,7 @@
 rotation runs."""
 import numpy as np
 import pytest
+import torch
 
 from oracle import kv_oracle as O
 from paper_2601_20309_amd import binding as B
@@ -85,3 +86,25 @@ def test_reader_tiles_that_span_segments(vecs):
             rc, got, _ = case.eng.kv_reader_wait()
             assert rc == 0 and got == (want * passes) % (1 << 64), (hbm_layout, len(ids), passes, wgs)
         case.close()
+
+
+@pytest.mark.parametrize("vecs", [64, 75])
+def test_reader_claims_every_tile_once(vecs):
+    """Passes long enough that tiles are claimed: groups of several workgroups, grids
+    that the 64 counters do not divide and smaller ones, claims of one, two and four
+    tiles, tiles taken from other groups (64 rounds of the grid and more), and the
+    default grid.  A tile left out or read twice changes the sum."""
+    nb = (3 << 29) // (64 * vecs)                                        # 1.5 GiB of blocks of 4 segments
+    sh = W.KVShape(2, 1, 8 * vecs, 1, n_hbm_blocks=nb, n_host_slots=4)
+    cache = torch.randint(-2**62, 2**62, (4, nb, 2 * vecs), device="cuda")      # 64-bit words of the [plane][block] segments
+    block = sum((w & 0xFFFFFFFF).sum(1) + ((w >> 32) & 0xFFFFFFFF).sum(1) for w in cache).cpu().numpy()
+    torch.cuda.synchronize()
+    eng = B.Engine(B.make_config(sh), cache.data_ptr())
+    ids = np.random.default_rng(vecs).integers(0, nb, 2 * nb).astype(np.int32)
+    for wgs, rounds, passes in [(0, 69, 2), (0, 30, 1), (1, 300, 2), (40, 5, 2), (63, 130, 1), (64, 66, 1), (65, 30, 2), (65, 200, 2),
+                                (100, 100, 1), (127, 65, 1), (128, 4, 1), (129, 90, 2), (1000, 40, 1)]:
+        n = min(2 * nb, (2 * rounds + 1) * (wgs or 1408) * 1024 // (4 * vecs) + 1)      # (rounds + 1/2) * workgroups tiles of 2048 vectors
+        assert eng.kv_reader_start(ids[:n], passes, wgs) == 0
+        rc, got, _ = eng.kv_reader_wait()
+        assert rc == 0 and got == int(block[ids[:n]].sum()) * passes % (1 << 64), (wgs, rounds, passes)
+    eng.kv_destroy()
