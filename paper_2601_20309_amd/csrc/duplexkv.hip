@@ -399,12 +399,12 @@ int mark_end(kv_engine *e, bool out_side, int k, hipStream_t s)
 // 64 lanes used, 1001 us; 846 us now.)  Vectors narrower than 16 bytes (odd
 // segments or pointers) get more of them per lane for the same reason.
 enum LinkKind { kBoth, kInHeavy, kOutOnly, kInOnly };
-// A launch of no more than kShortKib per direction gets a wave per tile: no step
-// counter (its atomics, ~14 ns each on one address, are as long as the transfer),
-// no second round trip over the link, and what a co-runner loses lasts no longer
-// than the link needs for it, 10 us.  (12 launches of 32 KiB: 134 us with 112 waves
-// that draw, 111 us; 8 + 8 blocks of 16 KiB: 33.6 and 31.5 us.)
-constexpr int kShortKib = 512;
+// A launch of no more than kShortKib per direction gets a wave per tile: no second round
+// trip over the link, and hardly more waves than the table above has.  (8 + 8 blocks of
+// 16 KiB 25.4 us, with the table's 112 waves 26.8; a reader beside loses the same.  With a
+// wave per tile up to 512 KiB the reader lost 10-14 ms per GiB moved instead of 2-4, from
+// 256 KiB on 8-14 instead of 5-7.)
+constexpr int kShortKib = 128;
 
 LinkShape link_shape(const kv_engine *e, LinkKind kind)
 {
@@ -614,6 +614,7 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
         sh_out.wgs = sh_in.wgs = 9 * (e->n_cus > 0 ? e->n_cus : 256) / 8;
         sh_out.lanes = sh_in.lanes = dkv::kWave;
         sh_out.u = sh_in.u = sh_out.limit_u = sh_in.limit_u = 1;
+        sh_out.short_steps = sh_in.short_steps = 0;
     }
     const MoveIds ids_out{d_o, d_o + no, nullptr, nullptr, on_host}, ids_in{nullptr, nullptr, d_i, d_i + ni, on_host};
     // launches on stream_out draw from the first pair of counters, those on stream_in from the second

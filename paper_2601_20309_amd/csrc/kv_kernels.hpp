@@ -288,7 +288,15 @@ __device__ __forceinline__ uint32_t drawn(uint32_t d)
     return __builtin_amdgcn_readfirstlane(d);
 }
 
-// Fixed share: wave w of W takes steps w, w + W, ...
+// Fixed share: wave w of W takes steps w, w + W, ...  HBM-bound launches, and link-bound
+// ones of at most kFixedRounds steps per wave (512 KiB per direction in the default
+// shapes): there the counter's atomics, ~14 ns each on one address, are as long as the
+// transfer and the waves have no time to drift apart.  32 launches of 512 KiB, us alone /
+// GB/s and a reader's TB/s beside it (7.05 alone): both ways, 112 waves that draw 688 / 44,
+// 6.53, fixed shares 689 / 59, 6.27; swap-outs by 12 waves 439 / 28, 6.79 and 405 / 38,
+// 6.43.  (A wave per step, 512 of them: 721 / 47, 3.7 and 379 / 40, 3.8.)
+constexpr uint32_t kFixedRounds = 6;
+
 template <typename V, int U, bool LINK, bool FULL>
 __device__ __forceinline__ void run_fixed(const MoveParams &p, const int32_t *__restrict__ out_ids,
                                           const int32_t *__restrict__ out_slots,
@@ -333,14 +341,8 @@ __device__ __forceinline__ void run_drawn(const MoveParams &p, const int32_t *__
                                           const int32_t *__restrict__ in_slots, uint32_t n_steps, uint32_t wave,
                                           uint32_t n_waves, uint32_t lane)
 {
-    if (wave >= n_steps) return;  // only where workgroups of several waves round the launch up: see below
     V vi[U], vo[U];
     Job<V, U, FULL> cur = make_job<V, U, FULL>(p, out_ids, out_slots, in_ids, in_slots, wave, lane);
-    if (n_steps <= n_waves) {  // a step each: no counter at all
-        job_loads<V, U, LINK, FULL>(cur, vi, vo);
-        job_stores<V, U, LINK, FULL>(cur, vi, vo);
-        return;
-    }
     // steps at or beyond `single` are drawn one at a time
     const uint32_t tail = 2u * kDrawChunk * n_waves, single = n_steps > tail ? n_steps - tail : 0u;
     uint32_t t = wave, e = wave + 1u;  // current step, end of the chunk it belongs to
@@ -407,7 +409,7 @@ __device__ __forceinline__ void move(const MoveParams &p, const int32_t *__restr
     const uint32_t n_waves = gridDim.x * waves_per_wg;
     const uint32_t n_steps = p.mix_q ? p.in.tiles : (p.out.tiles > p.in.tiles ? p.out.tiles : p.in.tiles);
     constexpr int UR = U < kMaxRaggedU ? U : kMaxRaggedU;  // what cut_tiles() cut by when tiles are not whole
-    if constexpr (!LINK) {
+    if (!LINK || n_steps <= (uint64_t)kFixedRounds * n_waves) {
         if (p.full_tiles)
             run_fixed<V, U, LINK, true>(p, out_ids, out_slots, in_ids, in_slots, n_steps, wave, n_waves, lane);
         else

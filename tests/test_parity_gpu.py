@@ -491,3 +491,30 @@ def test_staged_copies_of_several_rows(host_layout, tokens, heads, chunk_layers,
     case.rotate(W.Rotation(rot.in_ids, rot.in_slots, rot.out_ids, rot.out_slots))
     case.check()
     case.close()
+
+
+@pytest.mark.parametrize("vecs", [64, 75])
+@pytest.mark.parametrize("wgs,lanes", [(1, 64), (3, 64), (1, 256), (2, 320)])
+def test_launches_at_the_edge_of_the_fixed_share(wgs, lanes, vecs):
+    """Launches of up to six steps per wave take fixed shares, longer ones draw from the
+    counter, which the next call finds at zero: one to a few steps around one, six and
+    fourteen rounds of the launch's waves (where all draws are single, and where the
+    first are of four), each direction and both, whole tiles and partly empty ones,
+    every byte against the oracle."""
+    waves = wgs * lanes // 64
+    per_block = 4 * vecs // 64 if vecs % 64 == 0 else -(-4 * vecs // 64)          # steps of a block, tiles of 64 vectors
+    lengths = sorted({max(1, (r * waves + d) // per_block) for r in (1, 6, 14) for d in (-1, 0, per_block, 3 * per_block)})
+    n = 2 * max(lengths) + 2
+    sh = W.KVShape(2, 1, 8 * vecs, 1, n_hbm_blocks=n + 5, n_host_slots=n + 3)
+    rot = W.simple_rotation(sh, max(lengths), max(lengths), seed=vecs + waves)
+    case, _ = make_case(sh, B.KV_HOST_BLOCK_FIRST, B.KV_PATH_AUTO, rot=rot, max_copy_wgs=wgs, wg_lanes=lanes, vecs_per_lane=1)
+    for k in lengths:
+        part = W.Rotation(rot.out_ids[:k], rot.out_slots[:k], rot.in_ids[:k], rot.in_slots[:k])
+        case.rotate(part)
+        case.rotate(part.inverse())
+        case.swap_in(rot.in_slots[:k], rot.out_ids[:k])
+        case.wait()
+        case.swap_out(rot.in_ids[:k], rot.out_slots[:k])
+        case.rotate(W.Rotation(rot.out_ids[:1], rot.out_slots[:1], rot.in_ids[:k], rot.in_slots[:k]))
+        case.check()
+    case.close()
