@@ -386,7 +386,8 @@ int mark_end(kv_engine *e, bool out_side, int k, hipStream_t s)
 //  1024 : 2048   112 x 1  85.8 / 85.2 (5.09)    32 x 4  85.9 / 85.2 (5.38)
 //  1536 : 2048   112 x 1 100.1 / 98.8 (5.20)    32 x 4  99.6 / 97.9 (5.40)   (not taken: 112 x 1 stays)
 // The same waves packed four or sixteen to a workgroup do no better.
-// A configured vecs_per_lane is kept (the wave count follows it); max_copy_wgs
+// A configured vecs_per_lane is kept (the wave count follows it; 8 are cut to
+// kMaxRaggedU for segments that 8 do not divide); max_copy_wgs
 // counts workgroups of wg_lanes lanes and set alone keeps 256-lane workgroups;
 // wg_lanes set alone keeps the number of waves.
 //
@@ -397,7 +398,10 @@ int mark_end(kv_engine *e, bool out_side, int k, hipStream_t s)
 // emptier, so that as many bytes are in flight.  (Segments of 1200 bytes, 701 of
 // 57600-byte blocks out and 633 in: tiles of one segment, 11 of the second one's
 // 64 lanes used, 1001 us; 846 us now.)  Vectors narrower than 16 bytes (odd
-// segments or pointers) get more of them per lane for the same reason.
+// segments or pointers) get more of them per lane for the same reason.  All of this
+// goes by the tiles as they are cut, configured vectors or not: segments of 1000 vectors
+// with vecs_per_lane = 8 are cut by 4, and with the waves of 8 moved at 86 / 56 / 44 GB/s
+// both ways / out / in; 99 / 56 / 57 now.
 enum LinkKind { kBoth, kInHeavy, kOutOnly, kInOnly };
 // A launch of no more than kShortKib per direction gets a wave per tile: no second round
 // trip over the link, and hardly more waves than the table above has.  (8 + 8 blocks of
@@ -413,24 +417,24 @@ LinkShape link_shape(const kv_engine *e, LinkKind kind)
     const bool plane_major = e->cfg.host_layout == KV_HOST_LAYER_FIRST;
     const uint32_t planes = e->cfg.chunk_layers > 0 ? std::min(2u * (uint32_t)e->cfg.chunk_layers, e->n_planes) : e->n_planes;
     int u = cu ? cu : (kind == kOutOnly ? 8 : kind == kInOnly || kind == kInHeavy ? 4 : 1);
-    int limit_u = u, kib = u;  // kib: KiB per tile and direction that the table below is looked up by
-    double fill = 1.0;         // share of a tile that is not padding, on average
-    if (!cu) {
-        if (vec_per_seg % dkv::kWave == 0) {  // whole tiles only: the segment must be a multiple of the tile
-            while (u > 1 && vec_per_seg % ((uint64_t)dkv::kWave * (uint64_t)u) != 0) u >>= 1;
-            limit_u = u;
-        } else {
-            limit_u = 1;
-            u = std::min(dkv::kMaxRaggedU, u * 16 / e->vec);
-            auto filled = [&](int w) {
-                const uint64_t tile = (uint64_t)dkv::kWave * (uint64_t)w, g = group_vecs(vec_per_seg, planes, plane_major, false);
-                return (double)g / (double)((g + tile - 1) / tile * tile);
-            };
-            while (u > 1 && filled(u) < 0.875) u >>= 1;
-            fill = filled(u);
-        }
-        kib = u * e->vec / 16;
+    auto whole = [&](int w) { return vec_per_seg % ((uint64_t)dkv::kWave * (uint64_t)w) == 0; };
+    auto filled = [&](int w) {
+        const uint64_t tile = (uint64_t)dkv::kWave * (uint64_t)w, g = group_vecs(vec_per_seg, planes, plane_major, false);
+        return (double)g / (double)((g + tile - 1) / tile * tile);
+    };
+    int limit_u = u;
+    if (!cu && whole(1)) {  // whole tiles only: the segment must be a multiple of the tile
+        while (!whole(u)) u >>= 1;
+        limit_u = u;
+    } else if (!cu) {
+        limit_u = 1;
+        u = std::min(dkv::kMaxRaggedU, u * 16 / e->vec);
+        while (u > 1 && filled(u) < 0.875) u >>= 1;
     }
+    // what the waves follow: the vectors tiles are cut by (cut_tiles), in KiB per tile and
+    // direction, and the share of a tile that is not padding, on average
+    const int cut = whole(u) ? u : std::min(u, dkv::kMaxRaggedU), kib = cut * e->vec / 16;
+    const double fill = whole(u) ? 1.0 : filled(cut);
     int waves;
     switch (kind) {
     case kOutOnly: waves = kib >= 8 ? 12 : kib >= 4 ? 16 : kib >= 2 ? 32 : 64; break;

@@ -518,3 +518,30 @@ def test_launches_at_the_edge_of_the_fixed_share(wgs, lanes, vecs):
         case.rotate(W.Rotation(rot.out_ids[:1], rot.out_slots[:1], rot.in_ids[:k], rot.in_slots[:k]))
         case.check()
     case.close()
+
+
+@pytest.mark.parametrize("vecs", [1000, 768, 75])
+def test_configured_vectors_keep_the_link_busy(vecs):
+    """vecs_per_lane = 8 on segments that 64 * 8 vectors do not divide moves 128 MiB at
+    the rate of the engine's own choice (within 15 %; with half the bytes in flight it
+    takes 1.25 to 1.4 times as long), and to the same places."""
+    layers = 16
+    n = (128 << 20) // (2 * layers * 16 * vecs)
+    sh = W.KVShape(layers, 1, 8 * vecs, 1, n_hbm_blocks=2 * n, n_host_slots=2 * n)
+    rot = W.simple_rotation(sh, n, n, seed=vecs)
+    ms = {}
+    for v in (0, 8):
+        case, _ = make_case(sh, B.KV_HOST_BLOCK_FIRST, B.KV_PATH_AUTO, rot=rot, vecs_per_lane=v)
+        case.rotate(rot)
+        case.check()
+        for name, call in (("in", lambda: case.eng.kv_swap_in(rot.in_slots, rot.out_ids)),
+                           ("both", lambda: case.eng.kv_rotate(rot.out_ids, rot.out_slots, rot.in_ids, rot.in_slots))):
+            took = []
+            for _ in range(7):
+                assert call() == 0 and case.eng.kv_wait() == 0
+                st = case.eng.kv_last_stats()
+                took.append(max(st["ms_out"], st["ms_in"]))
+            ms[name, v] = sorted(took)[3]
+        case.close()
+    for name in ("in", "both"):
+        assert ms[name, 8] < 1.15 * ms[name, 0], (name, ms)
