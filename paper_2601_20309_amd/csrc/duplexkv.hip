@@ -792,16 +792,24 @@ void sorted_desc(kv_engine *e, const int32_t *ids, const int32_t *slots, int32_t
 
 // Copies of one chunk between staging and pool.  `to_host` picks the direction.
 //
-// A copy costs its DMA engine 5-10 us beyond its bytes, so short rows of equal
-// length at equal distances on both sides go as one two-dimensional copy, which the
-// engines take like any other (64 rows of 32 KiB: 603 us as 64 copies, 46 us as
-// one): the planes of a run of slots in a layer-first pool, and the blocks of a run
-// when a chunk holds some of their planes.  Rows of kOwnCopy and more keep a copy
-// each: those run both ways at 45 GB/s and up, while two-dimensional copies of the
-// two directions may come to share one engine (54 GB/s).  For the same reason
-// scattered whole blocks are not joined in pairs, though any two are equally spaced:
-// 120 + 96 blocks of 2 MiB took 8965 us in pairs, 5885 one by one.
-constexpr uint64_t kOwnCopy = 512ull << 10;
+// A copy costs its DMA engine 3-10 us beyond its bytes, so many short rows of equal
+// length at equal distances on both sides go as one two-dimensional copy: the planes of
+// a run of slots in a layer-first pool, and the blocks of a run when a chunk holds some
+// of their planes.  The DMA engines take such a copy whole at every distance (tried up
+// to 1.9 GiB; no kernel runs in its place).  But which engine it lands on depends on the
+// process's streams, and it can cost 50 us before its first byte, both directions sharing
+// an engine; so rows are joined only where that is still less than a copy each.  20 slots
+// out, us as 2, 8, 16, 32 and 80 copies each / joined, at best and at worst:
+//     8 KiB rows   155, 480, 930, 1800, 4700 / 230-1035, 260-960, 280-1150, 330-1180, 470
+//    64 KiB rows   455, 1660, 3310, 6630, 16500 / 275-1325, 414, 604, 980, 2110
+//   and 20 + 15 slots both ways: 64 KiB 515, 1760, 3450, 7000, 17200 / 311-1345, 1860,
+//   2780-3180, 3070-3560, 3900-4780;  256 KiB 2400, 2480, 4900, 9700, 24500 /
+//   1720-1850, 3060-3560, 3630-4370, 5090-6010, 8930-9460.
+// Rows of kOwnCopy and more keep a copy each: those run both ways at 45 GB/s and up.  For
+// the same reason scattered whole blocks are not joined in pairs, though any two are
+// equally spaced: 120 + 96 blocks of 2 MiB took 8965 us in pairs, 5885 one by one.
+constexpr uint64_t kOwnCopy = 512ull << 10, kWideRow = 64ull << 10;
+constexpr uint32_t kJoinRows = 32, kJoinWideRows = 16;
 
 int chunk_copies(kv_engine *e, bool to_host, uint8_t *stage, const int32_t *sorted_slots, uint32_t j0,
                  uint32_t j1, uint32_t p0, uint32_t p1, hipStream_t s, int32_t &n_copies)
@@ -817,7 +825,7 @@ int chunk_copies(kv_engine *e, bool to_host, uint8_t *stage, const int32_t *sort
     auto copy_rows = [&](uint64_t pool_off, uint64_t pool_pitch, uint64_t stage_off, uint64_t stage_pitch, uint64_t width,
                          uint32_t rows) -> hipError_t {
         const uint64_t odd = ((uint64_t)(uintptr_t)e->pool | pool_off | stage_off | pool_pitch | stage_pitch | width) & 3u;
-        if (rows == 1 || width >= kOwnCopy || odd || pool_pitch > 0x7FFFFFFFull || stage_pitch > 0x7FFFFFFFull) {
+        if (rows < (width < kWideRow ? kJoinRows : kJoinWideRows) || width >= kOwnCopy || odd || pool_pitch > 0x7FFFFFFFull || stage_pitch > 0x7FFFFFFFull) {
             hipError_t rc = hipSuccess;
             for (uint32_t r = 0; r < rows && rc == hipSuccess; r++)
                 rc = copy(pool_off + r * pool_pitch, stage_off + r * stage_pitch, width);

@@ -545,3 +545,61 @@ def test_configured_vectors_keep_the_link_busy(vecs):
         case.close()
     for name in ("in", "both"):
         assert ms[name, 8] < 1.15 * ms[name, 0], (name, ms)
+
+
+@pytest.mark.parametrize("host_layout,layers,heads,chunk_layers,run,joined", [
+    (B.KV_HOST_LAYER_FIRST, 15, 1, 0, 1, False), (B.KV_HOST_LAYER_FIRST, 16, 1, 0, 1, True),     # 30 and 32 rows of 4 KiB
+    (B.KV_HOST_LAYER_FIRST, 16, 1, 0, 3, True), (B.KV_HOST_LAYER_FIRST, 24, 1, 4, 1, False),     # of 12 KiB; 8 a chunk
+    (B.KV_HOST_LAYER_FIRST, 7, 16, 0, 1, False), (B.KV_HOST_LAYER_FIRST, 8, 16, 0, 1, True),     # 14 and 16 of 64 KiB
+    (B.KV_HOST_LAYER_FIRST, 12, 16, 0, 8, False),                                                # of 512 KiB
+    (B.KV_HOST_BLOCK_FIRST, 4, 2, 1, 31, False), (B.KV_HOST_BLOCK_FIRST, 4, 2, 1, 32, True)])    # blocks' parts of 16 KiB
+def test_staged_rows_are_joined_where_that_pays(host_layout, layers, heads, chunk_layers, run, joined):
+    """One copy for the rows of a run from 32 rows on (16 of 64 KiB and more), a copy each
+    below: a joined copy can cost 50 us before its first byte.  Counted by the
+    engine's own launches; every byte against the oracle."""
+    runs = 5
+    n = runs * run
+    sh = W.KVShape(layers, heads, 128, 16, n_hbm_blocks=2 * n + 3, n_host_slots=2 * runs * (run + 1))
+    at = (np.arange(2 * runs)[:, None] * (run + 1) + np.arange(run)).reshape(2, n).astype(np.int32)
+    ids = np.random.default_rng(run).permutation(2 * n + 3).astype(np.int32)
+    rot = W.Rotation(ids[:n], at[0], ids[n:2 * n], at[1])
+    case, _ = make_case(sh, host_layout, B.KV_PATH_SDMA_STAGED, rot=rot, chunk_layers=chunk_layers)
+    case.rotate(rot)
+    case.check()
+    chunks = -(-layers // chunk_layers) if chunk_layers else 1
+    rows = run if host_layout == B.KV_HOST_BLOCK_FIRST else 2 * (chunk_layers or layers)
+    assert case.eng.kv_last_stats()["n_launches"] == 2 * chunks * (1 + runs * (1 if joined else rows))
+    case.rotate(rot.inverse())
+    case.check()
+    case.close()
+
+
+def test_staged_rows_far_apart():
+    """Joined rows of a layer-first pool of real size, 128 MiB between the planes of a slot:
+    the named slots and blocks exchange their bytes, every other byte of the pool stays."""
+    planes, seg, slots = 32, 8192, 16384
+    sh = W.KVShape(planes // 2, 1, seg // 32, 16, n_hbm_blocks=64, n_host_slots=slots)
+    dev = torch.randint(-2**62, 2**62, (planes, 64, seg // 8), device="cuda")
+    torch.cuda.synchronize()
+    eng = B.Engine(B.make_config(sh, B.KV_HOST_LAYER_FIRST, B.KV_PATH_SDMA_STAGED), dev.data_ptr())
+    pool = torch.from_numpy(eng.host_pool_array().view(np.int64)).view(planes, slots, seg // 8)
+    for p in range(planes):
+        pool[p].fill_(p + 1)
+    rng = np.random.default_rng(128)
+    ids, at = rng.permutation(64), np.sort(rng.permutation(slots // 2)[:40]) * 2          # no two slots next to one another
+    out_ids, in_ids, out_at, in_at = ids[:20], ids[20:40], at[1::2], at[::2]
+    staged = torch.randint(-2**62, 2**62, (planes, 20, seg // 8))
+    pool[:, in_at] = staged
+    before = dev.cpu()
+    assert eng.kv_rotate(out_ids, out_at, in_ids, in_at) == 0 and eng.kv_wait() == 0
+    assert eng.kv_last_stats()["n_launches"] == 2 * (1 + 20)
+    want = before.clone()
+    want[:, in_ids] = staged
+    assert torch.equal(dev.cpu(), want)
+    assert torch.equal(pool[:, out_at], before[:, out_ids]) and torch.equal(pool[:, in_at], staged)
+    named = torch.zeros(slots, dtype=torch.bool, device="cuda")
+    named[torch.from_numpy(at).cuda()] = True
+    for p in range(planes):
+        plane = pool[p].cuda()
+        assert bool(((plane == p + 1).all(1) | named).all()), f"another slot's plane {p} changed"
+    eng.kv_destroy()
