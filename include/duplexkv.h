@@ -185,8 +185,8 @@ int kv_rotate(kv_engine *engine,
  * host pointer, kv_pool_bytes) and the hipStream_t to enqueue on (NULL = the
  * default stream), all on the current device.  The call allocates nothing, on
  * the device or through any library: the move kernel's step counters and the
- * device copy of the four id lists live in a fixed array of device memory that
- * belongs to the library (64 KiB + 256 bytes per GPU, held until the process
+ * device copy of longer id lists live in a fixed array of device memory that
+ * belongs to the library (64 + 2 KiB per GPU, held until the process
  * ends), which bounds a call to n_out + n_in <= KV_STATIC_MAX_BLOCKS (KV_E2BIG
  * beyond that; nothing enqueued).  Admission and result are kv_rotate's: one
  * launch carries both directions (or the one that is not empty).  Asynchronous:
@@ -194,13 +194,15 @@ int kv_rotate(kv_engine *engine,
  * (hipStreamSynchronize, or an event of the caller's).  Every call on a GPU
  * shares that GPU's array, so calls on one GPU must be ordered one after the
  * other (the same stream, or streams the caller orders): two calls that overlap
- * in time race on the id lists.  Host threads that call at the same time take
- * turns on a lock (the enqueue order is then theirs to define).  No
- * KV_EBUSY tracking: ordering against other work on the same blocks is the
- * stream's order.  The call may be recorded into a HIP graph (stream capture)
- * once one call on that device has been made outside any capture (the first
- * call looks up the array's device address); the id lists are then part of the
- * recording, and a replay moves what the blocks and slots hold at that moment.
+ * in time race on the id lists and the counters and may move the wrong blocks or
+ * leave some unmoved (calls that follow them in order are not affected).  Host
+ * threads that call at the same time take turns on a lock (the enqueue order is
+ * then theirs to define).  No KV_EBUSY tracking: ordering against other work on
+ * the same blocks is the stream's order.  The call may be recorded into a HIP
+ * graph (stream capture) once one call on that device has been made outside any
+ * capture (the first call looks up the array's device address); the id lists are
+ * then part of the recording, and a replay moves what the blocks and slots hold
+ * at that moment.
  */
 #define KV_STATIC_MAX_BLOCKS 8192
 int kv_rotate_static(const kv_config *cfg, void *hbm_cache, void *host_pool, void *stream,

@@ -161,15 +161,29 @@ void launch(void (*kernel)(P...), dim3 g, dim3 b, hipStream_t s, hipEvent_t stop
     else hipLaunchKernelGGL(kernel, g, b, 0, s, args...);
 }
 
-// The waves of the launch are the workers, and no more of them are launched than
-// it has steps.  `stop` (may be nullptr) is recorded by the launch itself.
+// Workgroups of a launch.  Its waves are the workers, and no more of them are launched
+// than it has steps.
+uint32_t grid_of(const LinkShape &sh, const MoveParams &p, uint32_t &steps)
+{
+    steps = p.mix_q ? p.in.tiles : std::max(p.out.tiles, p.in.tiles);
+    const uint32_t waves_per_wg = (uint32_t)sh.lanes / dkv::kWave, most = (steps + waves_per_wg - 1) / waves_per_wg;
+    return std::max(1u, steps <= (uint32_t)sh.short_steps ? most : std::min<uint32_t>((uint32_t)sh.wgs, most));
+}
+
+// Whether the waves of a link-bound launch draw steps from its counters.
+bool draws(const LinkShape &sh, const MoveParams &p)
+{
+    uint32_t steps;
+    const uint64_t waves = (uint64_t)grid_of(sh, p, steps) * ((uint32_t)sh.lanes / dkv::kWave);
+    return steps > dkv::kFixedRounds * waves;
+}
+
+// `stop` (may be nullptr) is recorded by the launch itself.
 template <int U, bool LINK>
 void launch_move_v(int vec, const LinkShape &sh, hipStream_t s, const MoveParams &p, const MoveIds &d, hipEvent_t stop)
 {
-    const uint32_t steps = p.mix_q ? p.in.tiles : std::max(p.out.tiles, p.in.tiles);
-    const uint32_t waves_per_wg = (uint32_t)sh.lanes / dkv::kWave, most = (steps + waves_per_wg - 1) / waves_per_wg;
-    const uint32_t wgs = steps <= (uint32_t)sh.short_steps ? most : std::min<uint32_t>((uint32_t)sh.wgs, most);
-    dim3 g(std::max(1u, wgs)), b((unsigned)sh.lanes);
+    uint32_t steps;
+    dim3 g(grid_of(sh, p, steps)), b((unsigned)sh.lanes);
     if constexpr (LINK) {
         if (d.on_host) {
             dkv::IdArgs a;
@@ -1121,9 +1135,16 @@ void free_engine(kv_engine *e)
 // of the move kernel and the device copy of the call's four id lists) lives,
 // for kv_rotate_static, in one file-scope array of device memory.  Every GPU the
 // library runs on holds its own copy of the array, at its own address, until
-// the process ends.  Layout: [0, 256) the counter pair, then the id lists as
+// the process ends.  Layout: counter pairs, 256 bytes apart, then the id lists as
 // [out_ids | out_slots | in_ids | in_slots].
-constexpr size_t kStaticIdsOff = 256;
+//
+// A call finds its counters at zero whatever calls before it did, also if some of
+// those overlapped in time, against the rule, and left the pair they shared at other
+// values.  Where the lists are uploaded, or the call is being captured (its pair then
+// belongs to the recording), a launch before it zeroes pair 0.  Other calls take the
+// other pairs in turn, and each zeroes the next one's: a launch saved.
+constexpr int kStaticPairs = 8;
+constexpr size_t kStaticPairBytes = 256, kStaticIdsOff = kStaticPairs * kStaticPairBytes;
 constexpr size_t kStaticBytes = kStaticIdsOff + 2 * (size_t)KV_STATIC_MAX_BLOCKS * sizeof(int32_t);
 static __device__ __align__(256) unsigned char scratch[kStaticBytes];
 
@@ -1132,10 +1153,11 @@ static __device__ __align__(256) unsigned char scratch[kStaticBytes];
 // device, and only that pointer is ever handed to a kernel.
 constexpr int kStaticMaxDevices = 64;
 unsigned char *g_scratch_ptr[kStaticMaxDevices] = {};
+int g_static_turn[kStaticMaxDevices] = {};  // of the next call that takes a pair in turn
 
-int static_scratch(unsigned char *&ptr)
+int static_scratch(unsigned char *&ptr, int &dev)
 {
-    int dev = -1;
+    dev = -1;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kStaticMaxDevices) {
         (void)hipGetLastError();
         return KV_EHIP;
@@ -1577,14 +1599,32 @@ int kv_rotate_static(const kv_config *cfg, void *hbm_cache, void *host_pool, voi
     if (p.out.tiles > 0 && p.in.tiles > p.out.tiles)
         p.mix_q = (((uint64_t)p.out.tiles << 32) + p.in.tiles - 1) / p.in.tiles;
     unsigned char *sc = nullptr;
-    rc = static_scratch(sc);
+    int dev;
+    rc = static_scratch(sc, dev);
     if (rc != KV_OK) return rc;
     p.claim = reinterpret_cast<unsigned int *>(sc);
     int32_t *ids = reinterpret_cast<int32_t *>(sc + kStaticIdsOff);
     hipStream_t s = (hipStream_t)stream;
+    static IdChunk chunk;  // one caller at a time
     // Few blocks: the lists are arguments of the one launch.  (1 + 1 blocks of 120 KiB: 31.9 us
     // with the launch that puts them into the array, 28.6 without; 4 + 3 of 2 MiB: 203.6 and 199.6.)
     if (ids_inline(e, no, ni)) {
+        if (draws(sh, p)) {
+            hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+            if (hipStreamIsCapturing(s, &capture) != hipSuccess) (void)hipGetLastError();
+            if (capture != hipStreamCaptureStatusNone) {
+                hipLaunchKernelGGL(kv_ids_kernel, dim3(1), dim3(256), 0, s, chunk, ids, 0u, p.claim);
+                HIPTRY((kv_engine *)nullptr, hipGetLastError());
+            } else {
+                auto pair = [&](int turn) {
+                    return reinterpret_cast<unsigned int *>(sc + (size_t)(1 + turn % (kStaticPairs - 1)) * kStaticPairBytes);
+                };
+                int &turn = g_static_turn[dev];
+                p.claim = pair(turn);
+                turn = (turn + 1) % (kStaticPairs - 1);
+                p.clear = pair(turn);
+            }
+        }
         launch_move(sh, e->vec, s, p, MoveIds{oi, os, ii, is, true}, true);
         HIPTRY((kv_engine *)nullptr, hipGetLastError());
         return KV_OK;
@@ -1593,7 +1633,6 @@ int kv_rotate_static(const kv_config *cfg, void *hbm_cache, void *host_pool, voi
     const int32_t *src[4] = {oi, os, ii, is};
     const uint32_t len[4] = {(uint32_t)no, (uint32_t)no, (uint32_t)ni, (uint32_t)ni};
     const uint32_t total = 2u * ((uint32_t)no + (uint32_t)ni);
-    static IdChunk chunk;  // one caller at a time
     uint32_t done = 0, list = 0, at = 0;
     while (done < total) {
         uint32_t n = 0;

@@ -94,6 +94,7 @@ struct MoveParams {
     // link-bound launches: two counters in device memory, zero at launch, [0] the
     // next unclaimed tile, [1] the waves that are done
     unsigned int *claim;
+    unsigned int *clear;  // nullptr, or a pair that a later launch draws from: put to zero
     DirDesc out, in;
 };
 
@@ -407,6 +408,7 @@ __device__ __forceinline__ void move(const MoveParams &p, const int32_t *__restr
     const uint32_t lane = threadIdx.x & (kWave - 1u), waves_per_wg = blockDim.x / kWave;
     const uint32_t wave = blockIdx.x * waves_per_wg + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const uint32_t n_waves = gridDim.x * waves_per_wg;
+    if (LINK && p.clear && blockIdx.x == 0 && threadIdx.x < 2) p.clear[threadIdx.x] = 0u;
     const uint32_t n_steps = p.mix_q ? p.in.tiles : (p.out.tiles > p.in.tiles ? p.out.tiles : p.in.tiles);
     constexpr int UR = U < kMaxRaggedU ? U : kMaxRaggedU;  // what cut_tiles() cut by when tiles are not whole
     if (!LINK || n_steps <= (uint64_t)kFixedRounds * n_waves) {

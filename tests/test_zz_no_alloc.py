@@ -246,3 +246,49 @@ def test_random_cases_match_the_oracle(seed):
         what = f"seed {seed} case {k}: {sh}, layout {layout}, {kw}"
         assert np.array_equal(got_cache, cache), what + ": cache"
         assert np.array_equal(got_pool, pool), what + ": pool"
+
+
+def test_calls_that_overlapped_do_not_spoil_later_ones():
+    """Calls on one GPU have to be ordered; two that overlap in time share what the library
+    keeps and may leave blocks unmoved.  Calls that follow them in order are not
+    affected: eager ones, ones with lists too long to be arguments, and replays of a
+    call recorded before."""
+    sh = W.KVShape(4, 8, 64, 16, n_hbm_blocks=2400, n_host_slots=2400)             # 128 KiB blocks
+    cfg = B.make_config(sh, hbm_layout=B.KV_HBM_BLOCK_FIRST)
+    words = B.kv_block_bytes(cfg) // 8
+    dev = torch.randint(-2**62, 2**62, (2400, words), device="cuda")
+    pool = torch.randint(-2**62, 2**62, (2400, words)).pin_memory()
+    streams = [torch.cuda.Stream() for _ in range(4)]
+    torch.cuda.synchronize()
+
+    def call(stream, first, n):         # blocks and slots [first, first + 2n): n out, n in
+        i = np.arange(first, first + 2 * n, dtype=np.int32)
+        assert B.kv_rotate_static(cfg, dev.data_ptr(), pool.data_ptr(), stream, i[:n], i[:n], i[n:], i[n:]) == 0
+
+    def check(what, first, n):
+        torch.cuda.synchronize()
+        assert torch.equal(pool[first:first + 2 * n], dev[first:first + 2 * n].cpu()), what
+        dev[first:first + 2 * n].random_(-2**62, 2**62)        # other bytes for the next time
+        pool[first:first + 2 * n] = torch.randint(-2**62, 2**62, (2 * n, words))
+        torch.cuda.synchronize()
+
+    call(streams[0].cuda_stream, 0, 30)
+    check("the first call", 0, 30)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=streams[0]):
+        call(torch.cuda.current_stream().cuda_stream, 100, 40)
+    for k in range(12):
+        for s in range(4):
+            call(streams[s].cuda_stream, 400 + 400 * s, 60 + 10 * k)
+        if k % 3 == 0:
+            with torch.cuda.stream(streams[k % 4]):
+                graph.replay()
+        torch.cuda.synchronize()
+        for a in range(2):
+            call(streams[a].cuda_stream, 0, 50)
+            check(f"call {a} after round {k}", 0, 50)
+        graph.replay()
+        check(f"replay after round {k}", 100, 40)
+        if k % 4 == 3:
+            call(streams[1].cuda_stream, 0, 240)
+            check(f"long lists after round {k}", 0, 240)
