@@ -146,3 +146,51 @@ def test_dma_staged_path_marks_its_layer_chunks(layout, staging):
         assert np.array_equal(snaps[l].cpu().numpy().view(np.uint16)[0], want[l]), f"layer {l}"
     case.check()
     case.close()
+
+
+@pytest.mark.parametrize("blocks", [1, 24])
+@pytest.mark.parametrize("own_streams", [True, False])
+def test_layers_are_there_the_moment_their_wait_returns(blocks, own_streams):
+    """kv_wait_layer and kv_stream_wait_layer are the only things between a layer's transfer
+    and its reader: the CPU reads the layer's part of the pool while later layers still
+    move, and a kernel on another stream the layer's part of the cache, at the same
+    places every time and with other bytes every time (what lingered in a cache, on
+    either side, would show the previous ones).  On the engine's own streams a mark is
+    the launch's completion signal, on the caller's a recorded event."""
+    sh = W.KVShape(8, 8, 64, 16, n_hbm_blocks=160, n_host_slots=160)            # 2 x 16 KiB a layer and block
+    cache = torch.randint(-2**62, 2**62, (160, 8, 4096), device="cuda")          # block-first: [block][layer][words of K and V]
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    cfg = B.make_config(sh, chunk_layers=1, hbm_layout=B.KV_HBM_BLOCK_FIRST)
+    eng = B.Engine(cfg, cache.data_ptr()) if own_streams else \
+        B.Engine(cfg, cache.data_ptr(), 0, *[s.cuda_stream for s in streams])
+    pool = eng.host_pool_array().view(np.int64).reshape(160, 8, 4096)
+    rng = np.random.default_rng(blocks)
+    pool[:] = rng.integers(-2**62, 2**62, pool.shape)
+    img = cache.cpu().numpy()
+    here = np.arange(blocks, dtype=np.int32)                                     # the place that is read
+    got = torch.empty((8, blocks, 4096), dtype=torch.int64, device="cuda")
+    for k in range(200):
+        src = (here + blocks + rng.integers(0, 160 - 2 * blocks)).astype(np.int32)
+        order = rng.permutation(8) if k % 2 else np.arange(8)
+        if k % 3 == 0:
+            assert eng.kv_swap_out(src, here) == 0
+            for l in order:
+                assert eng.kv_wait_layer(int(l)) == 0
+                assert np.array_equal(pool[here, l], img[src, l]), (k, l)
+        else:
+            if k % 3 == 1:
+                assert eng.kv_swap_in(src, here) == 0
+            else:
+                assert eng.kv_rotate(src, here, here, src) == 0
+            for l in order:
+                assert eng.kv_stream_wait_layer(side.cuda_stream, int(l)) == 0
+                with torch.cuda.stream(side):
+                    got[l].copy_(cache[:blocks, l])
+            side.synchronize()
+            assert np.array_equal(got.cpu().numpy(), pool[src].transpose(1, 0, 2)), k
+            if k % 3 == 2:
+                assert np.array_equal(pool[here], img[src]), k          # waited for by `side`: every layer's launch carries both directions
+        assert eng.kv_wait() == 0
+    eng.kv_destroy()

@@ -475,7 +475,7 @@ def test_staged_copies_of_several_rows(host_layout, tokens, heads, chunk_layers,
     single slots, planes of a layer-first pool, partial planes of a block-first one,
     rows of odd and of 4-byte lengths, chunks that cut the list; whole cache and pool
     against the oracle, both directions and each alone."""
-    sh = W.KVShape(6, heads, 40, tokens, n_hbm_blocks=120, n_host_slots=110)
+    sh = W.KVShape(16, heads, 40, tokens, n_hbm_blocks=120, n_host_slots=110)
     rng = np.random.default_rng(tokens * 10 + heads)
     ids = rng.permutation(120).astype(np.int32)
     slots = np.delete(np.arange(110), rng.permutation(110)[:34]).astype(np.int32)     # 76 slots in runs of 1, 2, 3, ...
@@ -603,3 +603,59 @@ def test_staged_rows_far_apart():
         plane = pool[p].cuda()
         assert bool(((plane == p + 1).all(1) | named).all()), f"another slot's plane {p} changed"
     eng.kv_destroy()
+
+
+@pytest.mark.parametrize("host_layout", LAYOUTS)
+@pytest.mark.parametrize("vecs,planes", [(64, 4), (75, 4), (520, 2)])
+@pytest.mark.parametrize("total", [447, 448, 449, 1300])
+def test_lists_at_and_beyond_what_arguments_hold(total, vecs, planes, host_layout):
+    """Lists of up to 448 blocks are kernel arguments, longer ones are read from memory: the
+    uploaded copy where a block or a plane's segment is small, else the pinned ring.
+    Fused, two kernels, each direction alone, layer by layer, and the call without an
+    engine, balanced and in-heavy, whole tiles and segments that no tile divides,
+    every byte against the oracle."""
+    sh = W.KVShape(planes // 2, 1, 8 * vecs, 1, n_hbm_blocks=total + 9, n_host_slots=total + 5)
+    n_out = total // 2
+    rot = W.simple_rotation(sh, n_out, total - n_out, seed=total + vecs)
+    cut = total // 5
+    heavy = W.Rotation(rot.out_ids[:cut], rot.out_slots[:cut], np.concatenate([rot.in_ids, rot.out_ids[cut:]]),
+                       np.concatenate([rot.in_slots, rot.out_slots[cut:]]))             # the same `total` blocks
+    for path, kw in [(B.KV_PATH_AUTO, {}), (B.KV_PATH_ZEROCOPY, {}), (B.KV_PATH_AUTO, dict(chunk_layers=1)),
+                     (B.KV_PATH_AUTO, dict(hbm_layout=B.KV_HBM_BLOCK_FIRST))]:
+        case, _ = make_case(sh, host_layout, path, rot=rot, **kw)
+        case.rotate(rot)
+        case.check()
+        case.rotate(heavy)
+        case.check()
+        case.swap_out(np.concatenate([rot.out_ids, rot.in_ids]), np.concatenate([rot.in_slots, rot.out_slots])[:total])
+        case.check()
+        case.swap_in(np.concatenate([rot.out_slots, rot.in_slots]), np.concatenate([rot.in_ids, rot.out_ids])[:total])
+        case.check()
+        if path == B.KV_PATH_AUTO and not kw:
+            dev, pool = case.dev_cache, torch.from_numpy(case.pool_u8.view(np.int16).copy()).pin_memory()
+            for r in (rot.inverse(), heavy):
+                assert B.kv_rotate_static(case.cfg, dev.data_ptr(), pool.data_ptr(), 0, r.out_ids, r.out_slots, r.in_ids,
+                                          r.in_slots) == 0
+                assert O.rotate(case.oshape, case.ref_cache.view(np.uint8), case.ref_pool.view(np.uint8), r.out_ids,
+                                r.out_slots, r.in_ids, r.in_slots) == 0
+            torch.cuda.synchronize()
+            case.pool_u8[:] = pool.numpy().view(np.uint8)
+            case.check()
+        case.close()
+
+
+@pytest.mark.parametrize("host_layout", LAYOUTS)
+@pytest.mark.parametrize("layers,n_out,n_in", [(5, 440, 7), (5, 440, 9), (1, 2250, 30)])
+def test_rest_of_an_out_heavy_rotation_moves_its_own_blocks(layers, n_out, n_in, host_layout):
+    """An out list 64 MiB and more beyond the in list runs as two launches, the second over
+    the rest of the list at its offsets: in arguments (447 blocks), in the pinned ring or
+    uploaded (449 blocks of 160 KiB, 2280 of 32 KiB)."""
+    sh = W.KVShape(layers, 4, 128, 16, n_hbm_blocks=n_out + n_in + 5, n_host_slots=n_out + n_in + 3)
+    rot = W.simple_rotation(sh, n_out, n_in, seed=layers)
+    case, _ = make_case(sh, host_layout, B.KV_PATH_AUTO, rot=rot)
+    case.rotate(rot)
+    case.check()
+    assert case.eng.kv_last_stats()["n_launches"] == 2
+    case.rotate(rot.inverse())
+    case.check()
+    case.close()
