@@ -240,10 +240,12 @@ def main():
         log("whole cache verified after the timed loop")
 
     path_name = B.PATH_NAMES[st["path_used"]]
-    # the kernel of the step: the move kernel, or, on the DMA-staged path, the pack / unpack kernel
-    # (its bench-traffic line is per launch of that kernel, one chunk)
-    traffic, traffic_src = measured_traffic(args.workload, path_name,
-                                            "kv_stage_kernel" if path_name == "sdma_staged" else "kv_move_kernel")
+    # the kernel of the step: the move kernel (up to 448 blocks the one whose lists are arguments), or, on
+    # the DMA-staged path, the pack / unpack kernel (its bench-traffic line is per launch of that kernel, one chunk)
+    inline_ids = len(rot.out_ids) + len(rot.in_ids) <= 448
+    kernel_name = "kv_stage_kernel" if path_name == "sdma_staged" else \
+        "kv_move_inline_kernel" if inline_ids else "kv_move_kernel"
+    traffic, traffic_src = measured_traffic(args.workload, path_name, kernel_name)
     res = {
         "metric": "duplex KV rotation GB/s (out+in) and % of measured host-link peak",
         "value": round(gbps_out + gbps_in, 2), "unit": "GB/s", "n_gpus": 1, "steps": steps,
@@ -264,7 +266,7 @@ def main():
         "pct_of_peak_out": round(100 * gbps_out / link["d2h"], 1),
         "pct_of_peak_in": round(100 * gbps_in / link["h2d"], 1),
         "roofline": {
-            "bound": "host_link", "kernel": "kv_move_kernel (both directions in one launch)"
+            "bound": "host_link", "kernel": f"{kernel_name} (both directions in one launch)"
             if st["path_used"] == B.KV_PATH_FUSED else B.PATH_NAMES[st["path_used"]],
             "achieved": round((bytes_out + bytes_in) / (kern_ms * 1e6), 2),
             "peak": 2 * PCIE5_X16_PER_DIR_GBPS, "unit": "GB/s",

@@ -134,22 +134,6 @@ struct Job {
     uint32_t n_i, n_o;  // vectors of the group from this lane's first one on (not FULL: what the stores go by)
 };
 
-// Step t of a launch.  Normally step t is tile t of the out list and tile t of
-// the in list, as far as each list goes: while both last, every lane alternates
-// an out-vector with an in-vector, which locks the two link directions 1:1, and
-// the longer list's remainder then runs alone.
-//
-// With mix_q set the in list is the longer one: its tiles set the pace and the
-// out tiles are spread evenly over them, out tile s riding with the in tile t
-// at which floor(t * q / 2^32) steps from s to s + 1 (q = ceil(S * 2^32 / L), so
-// the steps are 0 or 1 and all S out tiles are met exactly once over the L in
-// tiles).  Measured on PCIe Gen5 x16: host->HBM reads can stay at the link's
-// one-way rate (55-57 GB/s) while up to ~0.85 as many bytes go the other way
-// (47 GB/s), 102 GB/s in all, whereas pairing the lists 1:1 and moving the rest
-// of the in list afterwards holds both at 49.5 GB/s for the paired part.  (The
-// mirror case gains nothing: with the out list longer, what limits is the
-// upstream direction, which carries the out data and the read requests of the
-// in data, and that sum does not depend on the order.)
 // The lane's pointers into one tile; past the end of the group, to its last vector.
 template <typename V, int U, bool FULL, int N>
 __device__ __forceinline__ void lane_pointers(const MoveParams &p, uint64_t hbm_off, uint8_t *far, uint32_t tin,
@@ -171,6 +155,22 @@ __device__ __forceinline__ void lane_pointers(const MoveParams &p, uint64_t hbm_
     if (v0 >= p.group_vecs) n = 0u;
 }
 
+// Step t of a launch.  Normally step t is tile t of the out list and tile t of
+// the in list, as far as each list goes: while both last, every lane alternates
+// an out-vector with an in-vector, which locks the two link directions 1:1, and
+// the longer list's remainder then runs alone.
+//
+// With mix_q set the in list is the longer one: its tiles set the pace and the
+// out tiles are spread evenly over them, out tile s riding with the in tile t
+// at which floor(t * q / 2^32) steps from s to s + 1 (q = ceil(S * 2^32 / L), so
+// the steps are 0 or 1 and all S out tiles are met exactly once over the L in
+// tiles).  Measured on PCIe Gen5 x16: host->HBM reads can stay at the link's
+// one-way rate (55-57 GB/s) while up to ~0.85 as many bytes go the other way
+// (47 GB/s), 102 GB/s in all, whereas pairing the lists 1:1 and moving the rest
+// of the in list afterwards holds both at 49.5 GB/s for the paired part.  (The
+// mirror case gains nothing: with the out list longer, what limits is the
+// upstream direction, which carries the out data and the read requests of the
+// in data, and that sum does not depend on the order.)
 template <typename V, int U, bool FULL>
 __device__ __forceinline__ Job<V, U, FULL> make_job(const MoveParams &p, const int32_t *__restrict__ out_ids,
                                                     const int32_t *__restrict__ out_slots,
@@ -380,26 +380,26 @@ __device__ __forceinline__ void run_drawn(const MoveParams &p, const int32_t *__
 }
 
 // V: vector moved per lane (16 bytes when the segment allows it).
-// U: vectors per lane per tile; a tile is 64 * U consecutive vectors of one
-//    segment, so every wave access touches 64 * sizeof(V) contiguous bytes on
-//    both sides (full 1 KiB rows at V = 16 bytes).
+// U: vectors per lane per tile; a tile is 64 * U consecutive vectors of a group
+//    (MoveParams), so every wave access touches 64 * sizeof(V) contiguous bytes on
+//    the far side, and on the cache's but where a segment ends.
 // LINK: the far side is host memory.
 // A wave is the unit of work: it takes a step, issues its loads, works out the
 // addresses of its next step (two divisions, the scalar loads of id and slot)
 // while they are in flight, and stores.  What keeps the link busy is the number
 // of waves: a second step in flight per wave buys what a second wave buys.
 //
-// Which step a wave takes next: link-bound waves draw step indices from a
-// counter (the draw for the step after next is issued a whole step ahead, so
-// its latency is never waited for).  With a fixed share per wave the waves of a
-// link-bound launch drift apart by several per cent and the launch ends with a
-// tail of ~100 us in which too few waves are left to fill the link; drawn steps
+// Which step a wave takes next: in link-bound launches of more than a few rounds the
+// waves draw step indices from a counter (the draw for the step after next is issued
+// a whole step ahead, so its latency is never waited for).  With a fixed share per
+// wave the waves of such a launch drift apart by several per cent and the launch ends
+// with a tail of ~100 us in which too few waves are left to fill the link; drawn steps
 // end within one tile of each other, and the rate no longer depends on how the
 // wave count divides the tile count.  The last wave to finish puts both
 // counters back to zero for the next launch on the stream.  HBM-bound launches
 // (pack / unpack with a cap on their workgroups; uncapped they run as
 // kv_stage_kernel) move a tile in ~2 ns chip-wide, too fast for one counter, and
-// use the fixed share.
+// use the fixed share, and so do short link-bound ones (run_fixed).
 template <typename V, int U, bool LINK>
 __device__ __forceinline__ void move(const MoveParams &p, const int32_t *__restrict__ out_ids,
                                      const int32_t *__restrict__ out_slots, const int32_t *__restrict__ in_ids,
@@ -493,14 +493,15 @@ __global__ __launch_bounds__(kThreads) void kv_stage_kernel(const StageParams p,
 // The bytes to read are one flat sequence of 16-byte vectors, [plane][block][vector],
 // cut into tiles of kReadRows rows of 64 vectors (32 KiB, 8 KiB per wave), so a
 // tile is full whatever the segment size.  (Tiles that ended with their segment
-// read 1500 blocks of 64 x 4 KiB in 243 us, 1/8 of each tile used; 68 us = 5.8
-// TB/s now.)
+// read 1500 blocks of 64 x 4 KiB in 243 us, 1/8 of each tile used; the pass alone takes
+// 65 us = 6.0 TB/s now, a call with its launches and its wait 86.)
 //
 // A wave has kReadDepth rows in flight.  One is right: 22 waves per CU with a row
 // each are 5.6 MiB over the chip, which is the HBM rate times its latency.  More
 // only queue in front of HBM, and a copy over the link that runs beside the
-// reader stands in the same queues: eight rows per wave read 6.6 TB/s alone like
-// one does, but take a rotation beside them from 100 to 58 GB/s (one: 100.3).
+// reader stands in the same queues: 37.5 GiB in rows of 1, 2, 8 in flight, TB/s
+// alone 7.02, 7.07, 6.98, and GB/s of a rotation beside them 100.8, 94.2, 87.9,
+// of a swap-out 56.9, 51.5, 48.1.
 //
 // No two workgroups meet on an address while they read.  An atomic on one address
 // is served every ~14 ns: one counter for the tiles limits claims to 2.3 TB/s per
@@ -530,11 +531,11 @@ constexpr uint32_t kReadRows = (uint32_t)kReadU * (kThreads / kWave);  // rows p
 constexpr uint32_t kReadVecs = kReadRows * kWave;                      // vectors per tile
 // Counters, and the workgroups that share one: one of every 64 that follow one another,
 // each time one place further, so that a group lies on all XCDs and all over each, and
-// a copy beside the pass slows every group alike.  (37.5 GiB, TB/s alone / beside a
-// swap-out, claims of one tile: 64 groups of 22 workgroups that follow one another, that
-// is of the same three CUs of every XCD, 6.57 / 5.91; so placed 6.79 / 6.21.  Every 64th
-// workgroup, all on one XCD, had lost half beside a swap-out.  Fewer groups meet more
-// often on their counter: 8 read 4 % less alone.)
+// a copy beside the pass slows every group alike.  37.5 GiB alone / beside a swap-out and
+// 2 GiB beside it, TB/s: so placed 7.02 / 6.39, 5.88; groups of 22 that follow one another,
+// that is on the same three CUs of every XCD, 6.73 / 6.10, 3.55; every 64th workgroup,
+// all of a group on one XCD, 6.92 / 5.94, 2.11.  Fewer groups meet more often on their
+// counter: 16 read 6.78 alone, 8 6.51.
 constexpr uint32_t kReadGroups = 64;
 constexpr uint32_t kReadStride = 32;  // 32-bit words from one counter to the next
 // A claim is 4 tiles, 2 and at last 1: as long as the group has kReadMargin times as
