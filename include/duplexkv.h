@@ -223,8 +223,8 @@ int kv_wait(kv_engine *engine);
 int kv_query(kv_engine *engine);
 
 /*
- * Layer by layer (north_star: "per-layer chunking so that the transfers
- * overlap"; the paper overlaps the rotation for iteration t+1 with the execution
+ * Layer by layer (per-layer chunking, so that transfer and execution overlap;
+ * the paper overlaps the rotation for iteration t+1 with the execution
  * of iteration t, Section 4.3.2).  With cfg.chunk_layers = c > 0 the kernel paths
  * (KV_PATH_FUSED, KV_PATH_ZEROCOPY, and KV_PATH_AUTO, which picks one of them)
  * move a call's blocks c layers at a time, lowest layers first, one launch per

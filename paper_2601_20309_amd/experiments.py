@@ -2,7 +2,7 @@
 
   python -m paper_2601_20309_amd.experiments ladder        # analogue of the paper's Table 2
   python -m paper_2601_20309_amd.experiments configs       # the headline, batch and long-context rotations, default path
-  python -m paper_2601_20309_amd.experiments interference  # configs[4]: rotation beside a decode reader
+  python -m paper_2601_20309_amd.experiments interference  # the interference workload: rotation beside a decode reader
   python -m paper_2601_20309_amd.experiments reader        # the decode reader alone (profiling target)
   python -m paper_2601_20309_amd.experiments eager         # a preemption with and without eager block rotation
   python -m paper_2601_20309_amd.experiments layouts       # layer-first against block-first cache layout
@@ -13,7 +13,7 @@
   python -m paper_2601_20309_amd.experiments poolkinds     # does the kind of pinned memory the pool is made of matter?
   python -m paper_2601_20309_amd.experiments layers        # kernel paths layer by layer: cost of the chunks, when layer 0 is ready
   python -m paper_2601_20309_amd.experiments chunks        # DMA-staged path against chunk size: what serial chunks cost
-  python -m paper_2601_20309_amd.experiments splitcalls    # configs[2] in one call, in 32 waited calls, in 32 un-waited calls
+  python -m paper_2601_20309_amd.experiments splitcalls    # the batch workload in one call, in 32 waited calls, in 32 un-waited calls
   python -m paper_2601_20309_amd.experiments packalone     # pack and unpack kernels with nothing beside them (profiling target)
   python -m paper_2601_20309_amd.experiments packshapes    # shapes of pack / unpack kernel against the HBM roofline
 
@@ -358,7 +358,7 @@ def chunks(name="long70b"):
 def layers(name="long70b"):
     """The default path layer by layer (cfg.chunk_layers > 0): one launch per chunk
     of layers with a completion mark each, so that a consumer can start on layer l
-    while later layers move.  For configs[3] (20 + 20 GiB, 80 layers): what the
+    while later layers move.  For long70b (20 + 20 GiB, 80 layers): what the
     chunks cost the whole rotation, and when the first and the middle layer are
     in place (host clock from the call, kv_wait_layer)."""
     shape = W.SHAPES[name]
@@ -397,7 +397,7 @@ def layers(name="long70b"):
 
 def poolkinds():
     """The pool as different kinds of pinned host memory (hipHostMalloc flags),
-    handed to the engine as a caller-owned pool: the configs[1] rotation, a
+    handed to the engine as a caller-owned pool: the llama3_8b rotation, a
     2 + 2 GiB rotation and each direction alone."""
     import ctypes as C
     hip = C.CDLL("libamdhip64.so")      # the runtime torch has already loaded
@@ -442,7 +442,7 @@ def poolkinds():
 
 
 def splitcalls():
-    """configs[2] (32 requests out, 32 in, lognormal lengths) moved (a) in one call,
+    """The batch workload (32 requests out, 32 in, lognormal lengths) moved (a) in one call,
     (b) as 32 calls of one request pair each with a kv_wait after every call,
     (c) as the same 32 calls enqueued back to back with one kv_wait at the end.
     (b) holds each call's own imbalance (|out_i - in_i| runs at the one-way rate)
@@ -517,7 +517,7 @@ def splitcalls():
 
 def packalone(name="llama3_8b"):
     """Pack and unpack kernels of the DMA-staged path with nothing running beside
-    them: swap-outs and swap-ins of configs[1]'s 128 blocks in turn, each waited
+    them: swap-outs and swap-ins of llama3_8b's 128 blocks in turn, each waited
     for.  Meant to run under rocprofv3 --kernel-trace --stats, which gives the
     kernel durations (both directions at once would put the other direction's
     copies beside each kernel, and under the profiler those copies are kernels)."""
@@ -606,7 +606,7 @@ def configs():
                   f"{ms:.3f} | {go:.2f} | {gi:.2f} | {100 * go / link['d2h']:.1f} | {100 * gi / link['h2d']:.1f} | "
                   f"{st['n_launches']} |", flush=True)
         eng.kv_destroy()
-    # configs[2] again as 32 back-to-back calls, one request pair each
+    # the batch workload again as 32 back-to-back calls, one request pair each
     shape = W.SHAPES["batch"]
     del cache
     torch.cuda.empty_cache()
@@ -642,7 +642,7 @@ def configs():
 
 
 def interference():
-    """configs[4]: 8 x 4096-token requests each way while a reader streams the KV
+    """8 x 4096-token requests each way while a reader streams the KV
     of 19200 other blocks (37.5 GiB) layer by layer."""
     name = "interference"
     shape = W.SHAPES[name]

@@ -59,19 +59,19 @@ class Rotation:
 
 
 SHAPES: Dict[str, KVShape] = {
-    # configs[0]
+    # the smallest
     "tiny": KVShape(2, 2, 64, 16, n_hbm_blocks=64, n_host_slots=32),
     # a ragged shape that is not a power of two anywhere (parity edge case)
     "ragged": KVShape(3, 3, 40, 5, n_hbm_blocks=37, n_host_slots=19),
     # mid-size: several tiles per segment, still seconds for the oracle
     "small8b": KVShape(4, 8, 128, 16, n_hbm_blocks=256, n_host_slots=128),
-    # configs[1]: Llama-3-8B-shaped KV
+    # Llama-3-8B-shaped KV
     "llama3_8b": KVShape(32, 8, 128, 16, n_hbm_blocks=8192, n_host_slots=2048),
-    # configs[2]: batch rotation, same model shape, larger host pool
+    # batch rotation, same model shape, larger host pool
     "batch": KVShape(32, 8, 128, 16, n_hbm_blocks=8192, n_host_slots=8192),
-    # configs[3]: 70B-shaped long context
+    # 70B-shaped long context
     "long70b": KVShape(80, 8, 128, 32, n_hbm_blocks=4608, n_host_slots=4096),
-    # configs[4]: interference, Llama-3-8B shape with room for the decode reader
+    # interference, Llama-3-8B shape with room for the decode reader
     "interference": KVShape(32, 8, 128, 16, n_hbm_blocks=24576, n_host_slots=4096),
     # the paper's Table 2 workload shape (Qwen2.5-32B: 64 layers, 8 KV heads x 128)
     "qwen25_32b": KVShape(64, 8, 128, 16, n_hbm_blocks=4608, n_host_slots=4096),
@@ -176,7 +176,7 @@ def simple_rotation(shape: KVShape, n_out: int, n_in: int, seed: int,
 
 def batch_rotation(shape: KVShape, seed: int, n_requests: int = 64,
                    lengths: Optional[np.ndarray] = None) -> Dict[str, object]:
-    """configs[2]: half the requests are resident and rotate out, half are staged
+    """The batch workload: half the requests are resident and rotate out, half are staged
     and rotate in; block ids are one global random permutation dealt in order."""
     nb, ns = shape.n_hbm_blocks, shape.n_host_slots
     for attempt in range(64):
@@ -211,7 +211,7 @@ def request_rotation(shape: KVShape, tokens_out: List[int], tokens_in: List[int]
 
 
 def config_rotation(name: str, contiguous_slots: bool = False) -> Rotation:
-    """The rotation each BASELINE config names, with its fixed seed."""
+    """The rotation of each workload, with its fixed seed."""
     shape = SHAPES[name]
     idx = {"tiny": 0, "llama3_8b": 1, "batch": 2, "long70b": 3, "interference": 4,
            "qwen25_32b": 5, "ragged": 6, "small8b": 7}[name]

@@ -1,4 +1,4 @@
-"""Parity at BASELINE's full sizes, in the launch configuration bench.py times
+"""Parity at the workloads' full sizes, in the launch configuration bench.py times
 (default config: AUTO path, block-first pool, library-owned pool and streams)."""
 import numpy as np
 import pytest
@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 
 def test_llama3_8b_rotation_full_size():
-    """configs[1]: 16 GiB cache, one 2048-token request out while another comes in."""
+    """llama3_8b: 16 GiB cache, one 2048-token request out while another comes in."""
     case = BigCase("llama3_8b")
     rot = W.config_rotation("llama3_8b")
     assert len(rot.out_ids) == 128 and len(rot.in_ids) == 128
@@ -68,7 +68,7 @@ def test_llama3_8b_rotation_full_size_other_paths(path):
 
 
 def test_batch_rotation_full_size():
-    """configs[2]: 32 requests out and 32 in, lognormal lengths, one call; then
+    """batch: 32 requests out and 32 in, lognormal lengths, one call; then
     the same requests as 32 back-to-back calls without waiting."""
     info = W.batch_rotation(W.SHAPES["batch"], W.BASE_SEED + 102)
     rot = info["rotation"]
@@ -95,7 +95,7 @@ def test_batch_rotation_full_size():
     (B.KV_PATH_SDMA_STAGED, B.KV_HOST_LAYER_FIRST, 1),
 ])
 def test_long70b_rotation_full_size(path, layout, chunk_layers, say):
-    """configs[3]: 80 layers, 64 KiB segments, 10 MiB blocks, a 45 GiB cache and a
+    """long70b: 80 layers, 64 KiB segments, 10 MiB blocks, a 45 GiB cache and a
     40 GiB pool; two 32768-token requests leave while two come back (20 GiB each
     way, the transfer size of the paper's Section 5.4 / Table 2 per direction), in
     one launch on the default path, layer by layer on the default path (80 launches,
@@ -122,7 +122,7 @@ def test_long70b_rotation_full_size(path, layout, chunk_layers, say):
 
 
 def test_interference_rotation_beside_the_reader_full_size(say):
-    """configs[4]: Llama-3-8B shape, 48 GiB cache; eight 4096-token requests leave
+    """interference: Llama-3-8B shape, 48 GiB cache; eight 4096-token requests leave
     while eight come back (2048 + 2048 blocks, 4 GiB each way) and the decode
     reader streams 19200 other blocks (37.5 GiB per pass) at the same time.  Cache,
     pool and the reader's checksum are all checked against the oracle."""

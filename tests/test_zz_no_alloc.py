@@ -144,7 +144,7 @@ def test_admission_and_the_size_limit():
 
 
 def test_llama3_8b_full_size_matches_kv_rotate():
-    """configs[1] in bench.py's shape: 16 GiB cache, 128 scattered blocks each way."""
+    """llama3_8b in bench.py's shape: 16 GiB cache, 128 scattered blocks each way."""
     shape = W.SHAPES["llama3_8b"]
     rot = W.config_rotation("llama3_8b")
     seed = W.value_seed("llama3_8b")
