@@ -541,7 +541,7 @@ def test_configured_vectors_keep_the_link_busy(vecs):
                 assert call() == 0 and case.eng.kv_wait() == 0
                 st = case.eng.kv_last_stats()
                 took.append(max(st["ms_out"], st["ms_in"]))
-            ms[name, v] = sorted(took)[3]
+            ms[name, v] = min(took)
         case.close()
     for name in ("in", "both"):
         assert ms[name, 8] < 1.15 * ms[name, 0], (name, ms)
