@@ -377,33 +377,39 @@ int mark_end(kv_engine *e, bool out_side, int k, hipStream_t s)
 // copy loses grows with the number of copy waves, steeply once the copy issues
 // more than the link drains.  So each kind of launch gets the smallest shape
 // that holds its rate both alone and beside an HBM-bound reader (measured,
-// scattered 2 MiB blocks, 4 GiB per direction; GB/s alone / beside the reader,
-// and what the reader keeps of its 6.5 TB/s):
-//  both directions in one launch, U = 1:
-//     80 waves  97.5 /  83.5 (5.59)     112 waves 100.7 /  99.9 (5.30)
-//     96 waves 100.2 /  96.4 (5.45)     144 waves 100.8 / 100.6 (4.94)
-//    (32 waves x U 4: 100.1 / 99.2 (5.52), but 99.4 instead of 100.1 at 256 MiB)
-//  swap-out alone: host-bound stores are paced by nothing but the link, and
-//  every wave beyond those that fill it only gets in the reader's way:
-//     U 1:  48 waves 56.7 / 46.6 (5.99)   64 waves 56.5 / 56.7 (5.34)   112 waves 55.8 / 56.8 (3.00)
-//     U 4:  16 waves 56.8 / 56.7 (5.68)   20 waves 56.7 / 56.8 (4.69)    24 waves 56.4 / 56.8 (3.75)
-//     U 8:  10 waves 56.7 / 51.0 (6.34)   12 waves 56.7 / 56.7 (5.93)
+// scattered 2 MiB blocks; GB/s alone over 512 MiB per direction / beside the
+// reader over 4 GiB, and what the reader keeps of its 7.0 TB/s):
+//  both directions in one launch:
+//     U 1:  96 waves  98.7 /  94.0 (6.00)   112 waves 100.9 / 100.4 (5.79)   128 waves 101.5 / 101.3 (5.53)
+//     U 2:  48 waves  96.3 /  91.5 (6.12)    64 waves 101.4 / 100.4 (5.86)    80 waves 101.5 / 101.5 (5.54)
+//     U 4:  32 waves 100.8 /  99.2 (5.99)    40 waves 101.4 / 100.4 (5.87)    48 waves 100.5 / 100.2 (5.73)
+//     U 8:  20 waves  98.3 /  87.2 (6.28)    24 waves 100.7 /  92.9 (6.17)    32 waves  96.4 /  96.9 (5.97)
+//    (68 x U 2 beside 64 and 72 on another day: 101.5 / 101.1, 101.4 / 100.5, 101.5 / 101.3)
+//  swap-out alone (written through, so the link paces the waves and every shape moves
+//  57.1 alone; what differs is the rate beside the reader and what the reader keeps):
+//     U 1:  48 waves 51.4 (6.66)   64 waves 57.0 (6.60)   112 waves 57.1 (5.62)
+//     U 2:  28 waves 55.5 (6.72)   36 waves 57.0 (6.61)    68 waves 56.8 (5.70)
+//     U 4:  14 waves 55.6 (6.89)   16 waves 57.0 (6.82)    24 waves 57.1 (6.67)
+//     U 8:  12 waves 55.8 (6.90)   14 waves 56.9 (6.82)    16 waves 57.1 (6.76)
 //  swap-in alone:
-//     U 1:  64 waves 49.3 / 48.3 (5.49)   80 waves 57.4 / 56.8 (5.30)   112 waves 57.5 / 57.4 (4.88)
-//     U 4:  20 waves 55.2 / 54.2 (5.53)   24 waves 57.5 / 57.2 (5.44)
-//     U 8:  14 waves 57.5 / 51.3 (5.45)   16 waves 57.5 / 55.6 (5.36)
+//     U 1:  64 waves 50.5 / 47.7 (5.75)   80 waves 57.6 / 56.2 (5.64)    96 waves 57.6 / 57.5 (5.41)
+//     U 2:  40 waves 57.1 / 55.2 (5.75)   44 waves 57.6 / 57.3 (5.68)    48 waves 57.6 / 57.5 (5.64)
+//     U 4:  20 waves 56.2 / 53.3 (5.81)   24 waves 57.6 / 57.3 (5.71)    28 waves 57.6 / 57.5 (5.65)
+//     U 8:  14 waves 57.6 / 51.4 (5.92)   16 waves 57.6 / 54.6 (5.82)
 //  both directions in one launch with at least twice as much coming in as
 //  going out (the usual rotation once eager copies have run): the rate is the
-//  swap-in's, and 32 waves x U 4 hold it (out : in blocks, GB/s summed alone /
+//  swap-in's, and 32 waves x U 4 hold it (out : in in blocks, GB/s summed alone /
 //  beside the reader, reader):
-//     8 : 2048   112 x 1  57.4 / 57.3 (4.87)    32 x 4  57.5 / 57.3 (5.36)
-//  1024 : 2048   112 x 1  85.8 / 85.2 (5.09)    32 x 4  85.9 / 85.2 (5.38)
-//  1536 : 2048   112 x 1 100.1 / 98.8 (5.20)    32 x 4  99.6 / 97.9 (5.40)   (not taken: 112 x 1 stays)
+//     8 : 2048    68 x 2  57.8 / 57.8 (5.37)    32 x 4  57.8 / 57.8 (5.66)
+//  1024 : 2048    68 x 2  86.3 / 86.1 (5.58)    32 x 4  86.1 / 85.5 (5.83)
+//  1536 : 2048    68 x 2 100.7 / 100.4 (5.75)   32 x 4 100.1 / 96.1 (5.93)   (not taken: 68 x 2 stays)
 // The same waves packed four or sixteen to a workgroup do no better.
 // A configured vecs_per_lane is kept (the wave count follows it; 8 are cut to
 // kMaxRaggedU for segments that 8 do not divide); max_copy_wgs
-// counts workgroups of wg_lanes lanes and set alone keeps 256-lane workgroups;
-// wg_lanes set alone keeps the number of waves.
+// counts workgroups of wg_lanes lanes and set alone keeps 256-lane workgroups, with one
+// vector per lane both ways (144 and 192 waves of U 2 would be past what the link
+// drains: 100.2 GB/s and 3.9 TB/s beside the reader for 101.1 and 4.9) and eight out
+// (a few capped waves: 12 x U 8 move what 24 x U 4 do); wg_lanes set alone keeps the number of waves.
 //
 // Segments that no tile divides are moved in tiles that span segments where the
 // pool holds a block in one piece, and keep the vectors per lane above unless
@@ -418,10 +424,10 @@ int mark_end(kv_engine *e, bool out_side, int k, hipStream_t s)
 // both ways / out / in; 99 / 56 / 57 now.
 enum LinkKind { kBoth, kInHeavy, kOutOnly, kInOnly };
 // A launch of no more than kShortKib per direction gets a wave per tile: no second round
-// trip over the link, and hardly more waves than the table above has.  (8 + 8 blocks of
-// 16 KiB 25.4 us, with the table's 112 waves 26.8; a reader beside loses the same.  With a
-// wave per tile up to 512 KiB the reader lost 10-14 ms per GiB moved instead of 2-4, from
-// 256 KiB on 8-14 instead of 5-7.)
+// trip over the link, and no more waves than the table above has.  (8 + 8 blocks of 16 KiB:
+// 64 waves x U 2 24.8 us, 40 waves 25.1, 16 waves 28.1; 8 blocks in: 32 x U 4 20.3, 24 x U 4
+// 20.8.  16 + 16 blocks: 128 waves 30.6, the table's 68 28.0.  With a wave per tile up to
+// 512 KiB the reader beside lost 10-14 ms per GiB moved instead of 2-4.)
 constexpr int kShortKib = 128;
 
 LinkShape link_shape(const kv_engine *e, LinkKind kind)
@@ -430,7 +436,7 @@ LinkShape link_shape(const kv_engine *e, LinkKind kind)
     const uint64_t vec_per_seg = e->seg / (uint64_t)e->vec;
     const bool plane_major = e->cfg.host_layout == KV_HOST_LAYER_FIRST;
     const uint32_t planes = e->cfg.chunk_layers > 0 ? std::min(2u * (uint32_t)e->cfg.chunk_layers, e->n_planes) : e->n_planes;
-    int u = cu ? cu : (kind == kOutOnly ? 8 : kind == kInOnly || kind == kInHeavy ? 4 : 1);
+    int u = cu ? cu : kind == kBoth ? (cw ? 1 : 2) : kind == kOutOnly && cw ? 8 : 4;
     auto whole = [&](int w) { return vec_per_seg % ((uint64_t)dkv::kWave * (uint64_t)w) == 0; };
     auto filled = [&](int w) {
         const uint64_t tile = (uint64_t)dkv::kWave * (uint64_t)w, g = group_vecs(vec_per_seg, planes, plane_major, false);
@@ -451,9 +457,10 @@ LinkShape link_shape(const kv_engine *e, LinkKind kind)
     const double fill = whole(u) ? 1.0 : filled(cut);
     int waves;
     switch (kind) {
-    case kOutOnly: waves = kib >= 8 ? 12 : kib >= 4 ? 16 : kib >= 2 ? 32 : 64; break;
+    case kOutOnly: waves = kib >= 8 ? 14 : kib >= 4 ? 16 : kib >= 2 ? 36 : 64; break;
     case kInOnly: waves = kib >= 8 ? 16 : kib >= 4 ? 24 : kib >= 2 ? 44 : 80; break;
-    default: waves = kib >= 8 ? 20 : kib >= 4 ? 32 : kib >= 2 ? 64 : 112; break;  // kBoth and kInHeavy differ in u
+    case kInHeavy: waves = kib >= 8 ? 20 : kib >= 4 ? 32 : kib >= 2 ? 64 : 112; break;
+    default: waves = kib >= 8 ? 24 : kib >= 4 ? 38 : kib >= 2 ? 68 : 120; break;
     }
     waves = (int)(waves * std::min(4.0, 1.0 / fill));
     LinkShape s;
@@ -567,8 +574,8 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
         // before (if it holds work) and after
         const LinkShape sh = link_shape(e, ni >= 2 * (int64_t)no ? kInHeavy : kBoth);
         // What the out list has beyond the in list is a swap-out on its own: from
-        // kSplitBytes on it gets the launch shape of one (12 waves instead of 112:
-        // 56.7 against 55.8 GB/s, and a co-runner keeps 5.9 instead of 3.0 TB/s),
+        // kSplitBytes on it gets the launch shape of one (16 waves x U 4 instead of 68 x U 2:
+        // the same rate, and a co-runner keeps 6.8 instead of 5.7 TB/s),
         // right behind the paired part on the same stream.
         constexpr uint64_t kSplitBytes = 64ull << 20;
         const bool layered = e->cfg.chunk_layers > 0;  // layer by layer: the whole out list stays in the one kernel
@@ -624,9 +631,9 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
     }
     // One kernel per direction, each on its own stream.  When both run at once
     // they only reach the rate of the fused launch if each has at least one
-    // workgroup per CU (measured, one-wave workgroups per kernel, U = 1, 256 + 256
-    // MiB: 112 -> 70, 192 -> 77, 240 -> 87, 256 -> 99.9, 288 -> 99.5, 384 -> 98.5
-    // GB/s; the same 256 waves packed as 64 x 256 lanes -> 76).
+    // workgroup per CU (measured, one-wave workgroups per kernel, U = 1, 512 + 512
+    // MiB: 64 -> 68.9, 112 -> 84.9, 160 -> 92.2, 192 -> 95.1, 256 -> 101.1, 288 -> 101.1
+    // GB/s; U = 2: 96 -> 91.3; U = 4: 48 -> 89.2).
     LinkShape sh_out = link_shape(e, kOutOnly), sh_in = link_shape(e, kInOnly);
     if (no > 0 && ni > 0 && !e->cfg.max_copy_wgs && !e->cfg.wg_lanes && !e->cfg.vecs_per_lane) {
         sh_out.wgs = sh_in.wgs = 9 * (e->n_cus > 0 ? e->n_cus : 256) / 8;

@@ -238,24 +238,58 @@ __device__ __forceinline__ void job_loads(const Job<V, U, FULL> &j, V (&vi)[U], 
     }
 }
 
-// Stores of one job.  Stores to the far side are marked non-temporal, and so
-// are the stores into the cache of an HBM-bound launch (unpack).
-// LINK (far side = host memory): plain stores linger in the write-back L2 and
-// are only pushed out when evicted or when the kernel ends, so the upstream
-// link idles early and a kernel's last megabytes leave while the downstream
-// link idles (measured, 8 + 8 MiB both ways: 237 us plain, 188 us non-temporal).
-// Pack / unpack (both sides HBM), one 256 MiB chunk whose source is in no cache:
-// plain loads and stores 109 us, non-temporal stores 100 us, non-temporal loads
-// and stores 95 us (HIP events around the launch).
+// A vector to host memory.  16-byte vectors are written through ("system" scope), so
+// they leave the chip when they are stored.  Stores that end in the write-back L2,
+// non-temporal ones too, are taken in at 90 GB/s until ~3 MiB of them lie there:
+// the link upstream idles meanwhile, and the kernel's end waits until the rest is
+// pushed out at less than the link's rate.  Written through, a store is acknowledged
+// from the host's side, so the waves are paced by the link and need no tuning for it
+// (from 64 KiB in flight on every shape moves 57.1 GB/s out, where 112 waves of
+// non-temporal stores came to 55.8), the L2 stays the other kernels', and an HBM-bound
+// reader beside a swap-out keeps 6.8 instead of 6.5 TB/s.  Kernel time in us, plain /
+// non-temporal / written through: out 0.5 MiB 18.7 / 18.6 / 13.6, 2 MiB 64 / 58 / 41,
+// 256 MiB 4890 / 4813 / 4700; both ways 2 MiB each 79 / 73 / 48, 256 MiB 5418 / 5341 / 5320.
+// Narrower vectors are part of a 128-byte line per access more often, and every part
+// of a line is a write of its own on the link where the L2 would have joined them: 8-byte
+// vectors are written through (`through`) where a block is one piece of the pool (tiles
+// begin on lines: 840-byte segments, 40 MiB both ways 901 -> 873 us), but not where every
+// segment begins and ends inside a line (1143 -> 1367); of 4 bytes and less (180-byte
+// segments 1187 -> 1557) none are.
+template <typename V, bool THROUGH>
+__device__ __forceinline__ void store_host(const V &v, V *dst)
+{
+    if constexpr (THROUGH && sizeof(V) == 16) {
+        __builtin_amdgcn_global_store_b128((__attribute__((address_space(1))) u32x4 *)dst, v, "");
+    } else if constexpr (THROUGH) {
+        static_assert(sizeof(V) == 8);
+        __scoped_atomic_store_n(reinterpret_cast<uint64_t *>(dst), __builtin_bit_cast(uint64_t, v), __ATOMIC_RELAXED,
+                                __MEMORY_SCOPE_SYSTEM);
+    } else {
+        __builtin_nontemporal_store(v, dst);
+    }
+}
+
+// Stores of one job.  Stores to host memory: store_host.  Into the cache, LINK: plain
+// stores.  Pack / unpack (both sides HBM): non-temporal, one 256 MiB chunk whose source
+// is in no cache with plain loads and stores 109 us, with non-temporal stores 100 us,
+// with non-temporal loads and stores 95 us (HIP events around the launch).
+template <typename V, int U, bool THROUGH, bool FULL>
+__device__ __forceinline__ void out_stores(const Job<V, U, FULL> &j, const V (&vo)[U])
+{
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+        V *dst = FULL ? j.dst_o[0] + u * kWave : j.dst_o[FULL ? 0 : u];
+        if (FULL || (uint32_t)(u * kWave) < j.n_o) store_host<V, THROUGH>(vo[u], dst);
+    }
+}
+
 template <typename V, int U, bool LINK, bool FULL>
-__device__ __forceinline__ void job_stores(const Job<V, U, FULL> &j, const V (&vi)[U], const V (&vo)[U])
+__device__ __forceinline__ void job_stores(const Job<V, U, FULL> &j, const V (&vi)[U], const V (&vo)[U], bool through)
 {
     if (j.do_out) {
-#pragma unroll
-        for (int u = 0; u < U; u++) {
-            V *dst = FULL ? j.dst_o[0] + u * kWave : j.dst_o[FULL ? 0 : u];
-            if (FULL || (uint32_t)(u * kWave) < j.n_o) __builtin_nontemporal_store(vo[u], dst);
-        }
+        if constexpr (LINK && sizeof(V) == 16) out_stores<V, U, true, FULL>(j, vo);
+        else if (LINK && sizeof(V) == 8 && through) out_stores<V, U, LINK && sizeof(V) == 8, FULL>(j, vo);
+        else out_stores<V, U, false, FULL>(j, vo);
     }
     if (j.do_in) {
 #pragma unroll
@@ -290,13 +324,13 @@ __device__ __forceinline__ uint32_t drawn(uint32_t d)
 }
 
 // Fixed share: wave w of W takes steps w, w + W, ...  HBM-bound launches, and link-bound
-// ones of at most kFixedRounds steps per wave (512 KiB per direction in the default
-// shapes): there the counter's atomics, ~14 ns each on one address, are as long as the
-// transfer and the waves have no time to drift apart.  32 launches of 512 KiB, us alone /
-// GB/s and a reader's TB/s beside it (7.05 alone): both ways, 112 waves that draw 688 / 44,
-// 6.53, fixed shares 689 / 59, 6.27; swap-outs by 12 waves 439 / 28, 6.79 and 405 / 38,
-// 6.43.  (A wave per step, 512 of them: 721 / 47, 3.7 and 379 / 40, 3.8.)
-constexpr uint32_t kFixedRounds = 6;
+// ones of at most kFixedRounds steps per wave (512 KiB out, 768 in, 1 MiB both ways in the
+// default shapes): there the counter's atomics, ~14 ns each on one address, are as long as
+// the transfer and the waves have no time to drift apart.  Launches of 512 KiB, 32 in a row,
+// us alone / GB/s and a reader's TB/s beside them (7.04 alone): swap-outs by 16 waves that
+// draw 413 / 26.6, 6.79, fixed shares 389 / 36.7, 6.75; 8 calls of 1 MiB both ways 256 /
+// 52.5, 6.53 and 263 / 59.4, 6.45.  (A wave per step, up to 512 of them, cost the reader half.)
+constexpr uint32_t kFixedRounds = 8;
 
 template <typename V, int U, bool LINK, bool FULL>
 __device__ __forceinline__ void run_fixed(const MoveParams &p, const int32_t *__restrict__ out_ids,
@@ -315,7 +349,7 @@ __device__ __forceinline__ void run_fixed(const MoveParams &p, const int32_t *__
         const bool more = t < n_steps;
         Job<V, U, FULL> nxt = cur;
         if (more) nxt = make_job<V, U, FULL>(p, out_ids, out_slots, in_ids, in_slots, t, lane);
-        job_stores<V, U, LINK, FULL>(cur, vi, vo);
+        job_stores<V, U, LINK, FULL>(cur, vi, vo, !p.plane_major);
         if (!more) break;
         cur = nxt;
     }
@@ -367,7 +401,7 @@ __device__ __forceinline__ void run_drawn(const MoveParams &p, const int32_t *__
         const bool more = tn < n_steps;
         Job<V, U, FULL> nxt = cur;
         if (more) nxt = make_job<V, U, FULL>(p, out_ids, out_slots, in_ids, in_slots, tn, lane);
-        job_stores<V, U, LINK, FULL>(cur, vi, vo);
+        job_stores<V, U, LINK, FULL>(cur, vi, vo, !p.plane_major);
         if (!more) break;
         cur = nxt;
         t = tn;

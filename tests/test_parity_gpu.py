@@ -659,3 +659,26 @@ def test_rest_of_an_out_heavy_rotation_moves_its_own_blocks(layers, n_out, n_in,
     case.rotate(rot.inverse())
     case.check()
     case.close()
+
+
+@pytest.mark.parametrize("host_layout", LAYOUTS)
+@pytest.mark.parametrize("dim,tokens", [(128, 16), (65, 8), (60, 7), (20, 5), (18, 5), (9, 5)])
+def test_stores_into_the_pool_at_every_vector_width(dim, tokens, host_layout):
+    """Segments of 4096 and 1040 (16-byte vectors), 840 and 200 (8), 180 (4) and 90 bytes
+    (2): what reaches the pool, written through or not, is every byte of the named slots
+    and no other, just below and just above the eight steps per wave up to which waves
+    take fixed shares, and over bytes that an earlier call left there."""
+    sh = W.KVShape(6, 1, dim, tokens, n_hbm_blocks=1, n_host_slots=1)
+    block = 12 * 2 * dim * tokens
+    counts = sorted({max(1, kib * 1024 // block) for kib in (30, 480, 530, 1050, 1130)})
+    n = counts[-1]
+    sh = W.KVShape(6, 1, dim, tokens, n_hbm_blocks=2 * n + 7, n_host_slots=2 * n + 5)
+    rot = W.simple_rotation(sh, n, n, seed=dim)
+    case, _ = make_case(sh, host_layout, B.KV_PATH_AUTO, rot=rot)
+    for k in counts:
+        part = W.Rotation(rot.out_ids[:k], rot.out_slots[:k], rot.in_ids[:k], rot.in_slots[:k])
+        case.rotate(part)
+        case.swap_out(rot.in_ids[:k], rot.out_slots[:k][::-1].copy())
+        case.rotate(part.inverse())
+        case.check()
+    case.close()
