@@ -253,6 +253,7 @@ MoveParams base_params(const kv_engine *e)
     p.plane0 = 0;
     p.n_planes = e->n_planes;
     p.vec_per_seg = (uint32_t)(e->seg / (uint64_t)e->vec);
+    p.through = e->vec == 8 && (e->cfg.host_layout == KV_HOST_BLOCK_FIRST || e->seg >= 512) ? 1u : 0u;
     return p;
 }
 
@@ -265,14 +266,31 @@ uint64_t group_vecs(uint64_t vec_per_seg, uint32_t planes, bool plane_major, boo
     return whole || plane_major || entry >= 0x7FFFFFFFull ? vec_per_seg : entry;
 }
 
-// Cuts the planes [plane0, plane0 + n_planes) of every entry into tiles of `u` vectors per lane.
-void cut_tiles(MoveParams &p, int u)
+// Whether the pieces of the pool that a launch's groups are begin on 128-byte lines:
+// segments of a layer-first pool, `planes` planes of a block elsewhere.
+bool on_lines(const kv_engine *e, uint32_t planes)
+{
+    const uint64_t piece = e->cfg.host_layout == KV_HOST_LAYER_FIRST ? e->seg : (planes * e->seg) | e->block_bytes;
+    return (((uintptr_t)e->pool | piece) & 127u) == 0;
+}
+
+// MoveParams::line_mask for such pieces.  Vectors of 4 bytes and less are taken as they
+// lie: a line is half an access of theirs or more.
+uint32_t line_mask(int vec, bool lines)
+{
+    return lines || vec < 8 ? 0 : 128u / (uint32_t)vec - 1;
+}
+
+// Cuts the planes [plane0, plane0 + n_planes) of every entry into tiles of `u` vectors per
+// lane; lines: groups begin on 128-byte lines of the far side.
+void cut_tiles(MoveParams &p, int vec, int u, bool lines)
 {
     const bool whole = p.vec_per_seg % ((uint32_t)dkv::kWave * (uint32_t)u) == 0;
     const uint32_t tile = (uint32_t)dkv::kWave * (uint32_t)(whole ? u : std::min(u, dkv::kMaxRaggedU));
     p.group_vecs = (uint32_t)group_vecs(p.vec_per_seg, p.n_planes, p.plane_major != 0, whole);
     p.groups_per_entry = p.group_vecs == p.vec_per_seg ? p.n_planes : 1u;
-    p.by_tiles = dkv::make_div((p.group_vecs + tile - 1) / tile);
+    p.line_mask = whole ? 0 : line_mask(vec, lines);
+    p.by_tiles = dkv::make_div((p.group_vecs + p.line_mask + tile - 1) / tile);
     p.by_seg = p.groups_per_entry == 1 ? dkv::make_div(p.vec_per_seg) : dkv::Div{1, 0, 0};
     p.full_tiles = whole ? 1u : 0u;
 }
@@ -412,16 +430,21 @@ int mark_end(kv_engine *e, bool out_side, int k, hipStream_t s)
 // (a few capped waves: 12 x U 8 move what 24 x U 4 do); wg_lanes set alone keeps the number of waves.
 //
 // Segments that no tile divides are moved in tiles that span segments where the
-// pool holds a block in one piece, and keep the vectors per lane above unless
-// those would leave more than an eighth of the tiles empty; otherwise tiles end
-// with their segment.  Either way the waves are as many more as the tiles are
-// emptier, so that as many bytes are in flight.  (Segments of 1200 bytes, 701 of
-// 57600-byte blocks out and 633 in: tiles of one segment, 11 of the second one's
-// 64 lanes used, 1001 us; 846 us now.)  Vectors narrower than 16 bytes (odd
-// segments or pointers) get more of them per lane for the same reason.  All of this
+// pool holds a block in one piece; otherwise tiles end with their segment.  The vectors
+// per lane are those above unless they leave more than an eighth of the tiles empty, then
+// the most that leave the least empty (segments of 105 vectors fill one tile of 128 as they
+// fill two of 64: 40 MiB in 1343 us by 64, 841 by 128).  The waves are as many more as the
+// tiles are emptier, so that as many bytes are in flight, and 1.4 times that where an access
+// is parted into more requests than its bytes need: vectors narrower than 16 bytes, and
+// swap-ins from segments that begin inside 128-byte lines (swap-in of 40 MiB, us, without
+// and with: 840-byte segments 761 and 744, 180-byte 1374 and 998, 3360-byte 754 and 740).
+// Vectors narrower than 16 bytes (odd segments or pointers) also get more of them per lane.
+// Now and before all of this and line_mask, us for 40 MiB both ways / out / in: segments of
+// 1200 bytes 838 / 739 / 746 (856 / 756 / 744), in a layer-first pool 893 / 774 / 806 (968 /
+// 830 / 820), of 840 bytes there 916 / 759 / 841 (1150 / 870 / 1350).  All of this
 // goes by the tiles as they are cut, configured vectors or not: segments of 1000 vectors
 // with vecs_per_lane = 8 are cut by 4, and with the waves of 8 moved at 86 / 56 / 44 GB/s
-// both ways / out / in; 99 / 56 / 57 now.
+// both ways / out / in, with those of 4 at 99 / 56 / 57.
 enum LinkKind { kBoth, kInHeavy, kOutOnly, kInOnly };
 // A launch of no more than kShortKib per direction gets a wave per tile: no second round
 // trip over the link, and no more waves than the table above has.  (8 + 8 blocks of 16 KiB:
@@ -436,11 +459,12 @@ LinkShape link_shape(const kv_engine *e, LinkKind kind)
     const uint64_t vec_per_seg = e->seg / (uint64_t)e->vec;
     const bool plane_major = e->cfg.host_layout == KV_HOST_LAYER_FIRST;
     const uint32_t planes = e->cfg.chunk_layers > 0 ? std::min(2u * (uint32_t)e->cfg.chunk_layers, e->n_planes) : e->n_planes;
+    const bool lines = on_lines(e, planes);
     int u = cu ? cu : kind == kBoth ? (cw ? 1 : 2) : kind == kOutOnly && cw ? 8 : 4;
     auto whole = [&](int w) { return vec_per_seg % ((uint64_t)dkv::kWave * (uint64_t)w) == 0; };
     auto filled = [&](int w) {
         const uint64_t tile = (uint64_t)dkv::kWave * (uint64_t)w, g = group_vecs(vec_per_seg, planes, plane_major, false);
-        return (double)g / (double)((g + tile - 1) / tile * tile);
+        return (double)g / (double)((g + line_mask(e->vec, lines) + tile - 1) / tile * tile);
     };
     int limit_u = u;
     if (!cu && whole(1)) {  // whole tiles only: the segment must be a multiple of the tile
@@ -449,7 +473,10 @@ LinkShape link_shape(const kv_engine *e, LinkKind kind)
     } else if (!cu) {
         limit_u = 1;
         u = std::min(dkv::kMaxRaggedU, u * 16 / e->vec);
-        while (u > 1 && filled(u) < 0.875) u >>= 1;
+        int best = u;  // an eighth empty at most, else the fullest
+        for (int w = u / 2; w >= 1 && filled(best) < 0.875; w /= 2)
+            if (filled(w) > filled(best)) best = w;
+        u = best;
     }
     // what the waves follow: the vectors tiles are cut by (cut_tiles), in KiB per tile and
     // direction, and the share of a tile that is not padding, on average
@@ -462,7 +489,8 @@ LinkShape link_shape(const kv_engine *e, LinkKind kind)
     case kInHeavy: waves = kib >= 8 ? 20 : kib >= 4 ? 32 : kib >= 2 ? 64 : 112; break;
     default: waves = kib >= 8 ? 24 : kib >= 4 ? 38 : kib >= 2 ? 68 : 120; break;
     }
-    waves = (int)(waves * std::min(4.0, 1.0 / fill));
+    const bool parted = e->vec < 16 || (kind == kInOnly && !lines);
+    waves = (int)(waves * std::min(4.0, (parted && fill >= 0.5 ? 1.4 : 1.0) / fill));
     LinkShape s;
     s.u = u;
     s.limit_u = limit_u;
@@ -518,7 +546,7 @@ int launch_link(kv_engine *e, const LinkShape &sh, hipStream_t s, const MovePara
         MoveParams q = whole;
         q.plane0 = p0;
         q.n_planes = std::min(per_chunk, whole.n_planes - p0);
-        cut_tiles(q, sh.u);
+        cut_tiles(q, e->vec, sh.u, on_lines(e, q.n_planes) && (p0 * e->seg & 127u) == 0);
         // fits: the whole call's counts were checked
         if (!fill_dir(q, q.out.n, 0, sh.limit_u, q.out) || !fill_dir(q, q.in.n, 0, sh.limit_u, q.in)) return KV_EUNSUP;
         q.mix_q = whole.mix_q && q.out.tiles ? (((uint64_t)q.out.tiles << 32) + q.in.tiles - 1) / q.in.tiles : 0;
@@ -543,7 +571,7 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
         q.far_slot_stride_in = q.far_slot_stride_out;
         q.far_plane_stride_in = q.far_plane_stride_out;
         q.plane_major = e->cfg.host_layout == KV_HOST_LAYER_FIRST ? 1u : 0u;
-        cut_tiles(q, u);
+        cut_tiles(q, e->vec, u, on_lines(e, e->n_planes));
         return q;
     };
     // The link-bound kernels fetch ids and slots with scalar loads.  Where one list
@@ -898,7 +926,7 @@ MoveParams stage_params(const kv_engine *e, uint8_t *stage, uint32_t nb, uint32_
     p.far_out = p.far_in = stage - (uint64_t)p0 * ps;
     p.far_slot_stride_out = p.far_slot_stride_in = ss;
     p.far_plane_stride_out = p.far_plane_stride_in = ps;
-    cut_tiles(p, u);
+    cut_tiles(p, e->vec, u, true);  // staging is taken as it lies
     return p;
 }
 
@@ -1600,7 +1628,7 @@ int kv_rotate_static(const kv_config *cfg, void *hbm_cache, void *host_pool, voi
     p.far_slot_stride_in = p.far_slot_stride_out;
     p.far_plane_stride_in = p.far_plane_stride_out;
     p.plane_major = cfg->host_layout == KV_HOST_LAYER_FIRST ? 1u : 0u;
-    cut_tiles(p, sh.u);
+    cut_tiles(p, e->vec, sh.u, on_lines(e, e->n_planes));
     if (!fill_dir(p, (uint32_t)no, 0, sh.limit_u, p.out) || !fill_dir(p, (uint32_t)ni, 0, sh.limit_u, p.in))
         return KV_EUNSUP;
     if (p.out.tiles > 0 && p.in.tiles > p.out.tiles)

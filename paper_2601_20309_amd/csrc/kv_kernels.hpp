@@ -83,9 +83,17 @@ struct MoveParams {
     // are one range on the far side and planes apart in the cache.
     uint32_t group_vecs;        // vec_per_seg, or n_planes * vec_per_seg
     uint32_t groups_per_entry;  // n_planes, or 1
-    Div by_tiles;               // by tiles_per_group = ceil(group_vecs / (64 * U))
+    // Tiles begin on 128-byte lines of the far side, so that only the first and the last
+    // access of a group cover part of a line: 0 where groups begin on lines anyway, else
+    // the vectors of a line - 1; the first tile then holds as many vectors fewer as the
+    // group begins behind a line.  (Layer-first pool, 40 MiB both ways / out / in, us, taken
+    // as they lie and so: 3360-byte segments 892 / 773 / 758 and 877 / 768 / 758, 15120 bytes
+    // 885 / 766 / 736 and 860 / 759 / 736, 840 bytes 949 / 808 / 841 and 916 / 759 / 841.)
+    uint32_t line_mask;
+    Div by_tiles;               // by tiles_per_group = ceil((group_vecs + line_mask) / (64 * U))
     Div by_seg;                 // by vec_per_seg (quotient 0 where a group is one segment)
     uint32_t plane_major;       // group order: 1 = [plane][i], 0 = [i][plane]
+    uint32_t through;           // 8-byte vectors: 1 = written through to the host (store_host)
     uint32_t full_tiles;        // 1: group_vecs is a multiple of the tile and a group one segment
     uint64_t plane_skip;        // cache bytes between the end of a segment and the same block's next one
     // 0, or ceil(out.tiles * 2^32 / in.tiles) when the in list is the longer one and
@@ -134,25 +142,29 @@ struct Job {
     uint32_t n_i, n_o;  // vectors of the group from this lane's first one on (not FULL: what the stores go by)
 };
 
-// The lane's pointers into one tile; past the end of the group, to its last vector.
+// The lane's pointers into one tile; past the end of the group, to its last vector,
+// before its begin, to its first (in the same line, with the same value: these lanes
+// are not told apart).
 template <typename V, int U, bool FULL, int N>
 __device__ __forceinline__ void lane_pointers(const MoveParams &p, uint64_t hbm_off, uint8_t *far, uint32_t tin,
                                               uint32_t lane, V *(&in_cache)[N], V *(&in_far)[N], uint32_t &n)
 {
-    const uint32_t v0 = tin * (kWave * U) + lane;
-    n = p.group_vecs - v0;
+    int32_t v0 = (int32_t)(tin * (kWave * U) + lane);
+    if constexpr (!FULL) v0 -= (int32_t)((uint32_t)(reinterpret_cast<uintptr_t>(far) / sizeof(V)) & p.line_mask);
+    n = p.group_vecs - (uint32_t)v0;
 #pragma unroll
     for (int u = 0; u < N; u++) {
-        uint32_t v = v0 + u * kWave;
+        uint32_t v = (uint32_t)(v0 + u * kWave);
         uint64_t off = hbm_off;
         if constexpr (!FULL) {
+            if (u == 0) v = (uint32_t)max(v0, 0);
             v = min(v, p.group_vecs - 1u);
             off += (uint64_t)p.by_seg.quotient(v) * p.plane_skip;
         }
         in_cache[u] = reinterpret_cast<V *>(p.hbm + off) + v;
         in_far[u] = reinterpret_cast<V *>(far) + v;
     }
-    if (v0 >= p.group_vecs) n = 0u;
+    if (v0 >= (int32_t)p.group_vecs) n = 0u;
 }
 
 // Step t of a launch.  Normally step t is tile t of the out list and tile t of
@@ -250,11 +262,11 @@ __device__ __forceinline__ void job_loads(const Job<V, U, FULL> &j, V (&vi)[U], 
 // non-temporal / written through: out 0.5 MiB 18.7 / 18.6 / 13.6, 2 MiB 64 / 58 / 41,
 // 256 MiB 4890 / 4813 / 4700; both ways 2 MiB each 79 / 73 / 48, 256 MiB 5418 / 5341 / 5320.
 // Narrower vectors are part of a 128-byte line per access more often, and every part
-// of a line is a write of its own on the link where the L2 would have joined them: 8-byte
-// vectors are written through (`through`) where a block is one piece of the pool (tiles
-// begin on lines: 840-byte segments, 40 MiB both ways 901 -> 873 us), but not where every
-// segment begins and ends inside a line (1143 -> 1367); of 4 bytes and less (180-byte
-// segments 1187 -> 1557) none are.
+// of a line is a write of its own on the link where the L2 would have joined them.  8-byte
+// vectors are written through (`through`) unless segments of under 512 bytes begin and end
+// inside lines (40 MiB both ways, us, non-temporal / written through: 840-byte segments,
+// block-first pool 901 / 853, layer-first 948 / 916, 200-byte segments layer-first
+// 1240 / 1320); vectors of 4 bytes and less (180-byte segments 1187 / 1557) are not.
 template <typename V, bool THROUGH>
 __device__ __forceinline__ void store_host(const V &v, V *dst)
 {
@@ -284,7 +296,7 @@ __device__ __forceinline__ void out_stores(const Job<V, U, FULL> &j, const V (&v
 }
 
 template <typename V, int U, bool LINK, bool FULL>
-__device__ __forceinline__ void job_stores(const Job<V, U, FULL> &j, const V (&vi)[U], const V (&vo)[U], bool through)
+__device__ __forceinline__ void job_stores(const Job<V, U, FULL> &j, const V (&vi)[U], const V (&vo)[U], uint32_t through)
 {
     if (j.do_out) {
         if constexpr (LINK && sizeof(V) == 16) out_stores<V, U, true, FULL>(j, vo);
@@ -349,7 +361,7 @@ __device__ __forceinline__ void run_fixed(const MoveParams &p, const int32_t *__
         const bool more = t < n_steps;
         Job<V, U, FULL> nxt = cur;
         if (more) nxt = make_job<V, U, FULL>(p, out_ids, out_slots, in_ids, in_slots, t, lane);
-        job_stores<V, U, LINK, FULL>(cur, vi, vo, !p.plane_major);
+        job_stores<V, U, LINK, FULL>(cur, vi, vo, p.through);
         if (!more) break;
         cur = nxt;
     }
@@ -401,7 +413,7 @@ __device__ __forceinline__ void run_drawn(const MoveParams &p, const int32_t *__
         const bool more = tn < n_steps;
         Job<V, U, FULL> nxt = cur;
         if (more) nxt = make_job<V, U, FULL>(p, out_ids, out_slots, in_ids, in_slots, tn, lane);
-        job_stores<V, U, LINK, FULL>(cur, vi, vo, !p.plane_major);
+        job_stores<V, U, LINK, FULL>(cur, vi, vo, p.through);
         if (!more) break;
         cur = nxt;
         t = tn;

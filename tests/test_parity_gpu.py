@@ -682,3 +682,40 @@ def test_stores_into_the_pool_at_every_vector_width(dim, tokens, host_layout):
         case.rotate(part.inverse())
         case.check()
     case.close()
+
+
+@pytest.mark.parametrize("offset", [0, 16, 40, 112])
+@pytest.mark.parametrize("host_layout", LAYOUTS)
+def test_tiles_begin_on_lines_of_the_pool(host_layout, offset):
+    """Pools that begin inside a 128-byte line, and segments that do (16- and 8-byte
+    vectors): the first tile of a segment or block is shorter, and one vector more or
+    fewer decides whether there is another tile.  Each direction and both, one launch and
+    chunks of a layer, every byte against the oracle, and the bytes around the pool."""
+    rng = np.random.default_rng(offset)
+    for seg in (16, 904, 1008, 1024, 1040, 1936, 2032, 2064, 840, 504, 3984):
+        sh = W.KVShape(3, 1, seg // 2, 1, n_hbm_blocks=41, n_host_slots=37)
+        rot = W.simple_rotation(sh, 17, 15, seed=seg)
+        for chunk_layers in (0, 1):
+            cfg = B.make_config(sh, host_layout, B.KV_PATH_AUTO, chunk_layers)
+            cache = rng.integers(0, 256, B.kv_cache_bytes(cfg), dtype=np.uint8)
+            n = B.kv_pool_bytes(cfg)
+            pinned = torch.empty(n + 512, dtype=torch.uint8, pin_memory=True)
+            around = pinned.numpy()
+            assert around.ctypes.data % 128 == 0
+            around[:] = rng.integers(0, 256, n + 512, dtype=np.uint8)
+            want_cache, want = cache.copy(), around.copy()
+            pool = want[128 + offset:128 + offset + n]
+            dev = torch.from_numpy(cache).cuda()
+            torch.cuda.synchronize()
+            eng = B.Engine(cfg, dev.data_ptr(), pinned.data_ptr() + 128 + offset)
+            osh = O.shape_of(sh, host_layout, 0)
+            assert eng.kv_rotate(rot.out_ids, rot.out_slots, rot.in_ids, rot.in_slots) == 0
+            assert O.rotate(osh, want_cache, pool, rot.out_ids, rot.out_slots, rot.in_ids, rot.in_slots) == 0
+            assert eng.kv_wait() == 0
+            assert eng.kv_swap_out(rot.in_ids, rot.in_slots) == 0 and eng.kv_wait() == 0
+            assert O.swap_out(osh, want_cache, pool, rot.in_ids, rot.in_slots) == 0
+            assert eng.kv_swap_in(rot.out_slots[::-1].copy(), rot.out_ids) == 0 and eng.kv_wait() == 0
+            assert O.swap_in(osh, want_cache, pool, rot.out_slots[::-1].copy(), rot.out_ids) == 0
+            assert np.array_equal(dev.cpu().numpy(), want_cache), (seg, chunk_layers)
+            assert np.array_equal(around, want), (seg, chunk_layers)
+            eng.kv_destroy()
