@@ -97,7 +97,8 @@ typedef struct {
 typedef struct {
     uint64_t bytes_out;    /* bytes moved HBM -> host since the previous kv_wait */
     uint64_t bytes_in;     /* bytes moved host -> HBM since the previous kv_wait */
-    double ms_out;         /* device time of the out work, first start to last end (HIP events on its stream) */
+    double ms_out;         /* device time of the out work, first start to last end (the device's clock, left by the kernels themselves;
+                              HIP events where copies are enqueued, or on the caller's streams) */
     double ms_in;          /* same for the in work */
     double ms_e2e;         /* host wall time, entry of the first transfer call to return of kv_wait */
     int32_t path_used;     /* KV_PATH_* of the last call */

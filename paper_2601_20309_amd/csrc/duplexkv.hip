@@ -349,6 +349,8 @@ void open_batch(kv_engine *e)
     if (!e->batch_open) {
         e->batch_open = true;
         e->b_o0 = e->b_o1 = e->b_i0 = e->b_i1 = nullptr;
+        e->begun[0] = e->begun[1] = -1;
+        e->stamp_waves[0] = e->stamp_waves[1] = e->stamp_waves[2] = 0;
         e->t0 = now_ms();
         e->acc = kv_stats{};
     }
@@ -366,6 +368,29 @@ int mark_start(kv_engine *e, bool out_side, hipStream_t s)
         e->b_i0 = e->ev_i0;
     }
     return KV_OK;
+}
+
+// Has launches `p` of a call leave their times: the first that carries a direction in this
+// batch its begin (launch_link passes that to its first launch only), all of them their ends.
+// Ends of the batch before may lie beside them: the clock only goes up, so the latest counts.
+void stamp_launch(kv_engine *e, bool out, bool in, MoveParams &p)
+{
+    if (!e->own_streams) return;
+    const int at = out && e->begun[0] < 0 ? 0 : in && e->begun[1] < 0 ? 1 : -1;
+    if (at >= 0) p.begin = e->stamps + at;
+    if (out && e->begun[0] < 0) e->begun[0] = at;
+    if (in && e->begun[1] < 0) e->begun[1] = at;
+    p.end = e->stamps + 2 + (out && in ? 2 : in ? 1 : 0) * (size_t)dkv::kStamps;
+}
+
+// The batch's time for a direction, first begin to last end (0: nothing was carried).
+double stamped_ms(const kv_engine *e, int side)
+{
+    unsigned long long last = 0;
+    for (int kind : {side, 2})
+        for (uint32_t w = 0; w < e->stamp_waves[kind]; w++) last = std::max(last, e->stamps[2 + kind * (size_t)dkv::kStamps + w]);
+    const unsigned long long first = e->begun[side] < 0 ? last : e->stamps[e->begun[side]];
+    return last > first ? (double)(last - first) * e->stamp_ms : 0.0;
 }
 
 // Last work of a direction in this call: releases descriptor set k and is the
@@ -528,6 +553,15 @@ void launch_stage(int vec, hipStream_t s, const dkv::StageParams &p, const int32
 }
 
 // ---- FUSED / ZEROCOPY -----------------------------------------------------
+// The ends that a launch (as launch_move launches it) leaves are looked at in kv_wait.
+void note_ends(kv_engine *e, const LinkShape &sh, const MoveParams &p)
+{
+    if (!p.end) return;
+    uint32_t steps;
+    uint32_t &n = e->stamp_waves[(size_t)(p.end - (e->stamps + 2)) / dkv::kStamps];
+    n = std::max(n, std::min(dkv::kStamps, grid_of(sh, p, steps) * ((uint32_t)sh.lanes / dkv::kWave)));
+}
+
 // One link-bound launch, or, with cfg.chunk_layers set, one launch per chunk of
 // that many layers, lowest layers first, each followed by an event in `ev`, so
 // that whoever consumes the blocks (the model's layer l, a writer of the pool)
@@ -550,8 +584,11 @@ int launch_link(kv_engine *e, const LinkShape &sh, hipStream_t s, const MovePara
         // fits: the whole call's counts were checked
         if (!fill_dir(q, q.out.n, 0, sh.limit_u, q.out) || !fill_dir(q, q.in.n, 0, sh.limit_u, q.in)) return KV_EUNSUP;
         q.mix_q = whole.mix_q && q.out.tiles ? (((uint64_t)q.out.tiles << 32) + q.in.tiles - 1) / q.in.tiles : 0;
+        if (p0 > 0) q.begin = nullptr;
+        if (p0 + per_chunk < whole.n_planes) q.end = nullptr;  // the last one ends last
         launch_move(sh, e->vec, s, q, ids, true, ev && e->own_streams ? (*ev)[c] : nullptr);
         HIPTRY(e, hipGetLastError());
+        note_ends(e, sh, q);
         e->acc.n_launches += 1;
         if (ev && !e->own_streams) HIPTRY(e, hipEventRecord((*ev)[c], s));
     }
@@ -625,7 +662,10 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
             e->in_dirty = false;
         }
         if (upload_ids(true, true, e->s_out) != KV_OK) return KV_EHIP;
-        if (!e->b_o0 && !e->b_i0) {  // one start timestamp serves both directions
+        stamp_launch(e, true, true, p);
+        if (e->own_streams) {
+            stamp_launch(e, true, false, p_rest);  // behind it: its begin is not the first
+        } else if (!e->b_o0 && !e->b_i0) {  // one start timestamp serves both directions
             if (mark_start(e, true, e->s_out) != KV_OK) return KV_EHIP;
             e->b_i0 = e->b_o0;
         } else {
@@ -645,6 +685,7 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
             launch_move(sh_rest, e->vec, e->s_out, p_rest,
                         MoveIds{d_o + no_paired, d_o + no + no_paired, nullptr, nullptr, on_host}, true);
             HIPTRY(e, hipGetLastError());
+            note_ends(e, sh_rest, p_rest);
             e->acc.n_launches += 1;
         }
         if (mark_end(e, true, k, e->s_out) != KV_OK) return KV_EHIP;
@@ -701,14 +742,16 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
     e->layer_on_in = layered && ni > 0;
     if (no > 0) {
         if (upload_ids(true, false, e->s_out) != KV_OK) return KV_EHIP;
-        if (mark_start(e, true, e->s_out) != KV_OK) return KV_EHIP;
+        stamp_launch(e, true, false, p_out);
+        if (!e->own_streams && mark_start(e, true, e->s_out) != KV_OK) return KV_EHIP;
         if (launch_link(e, sh_out, e->s_out, p_out, ids_out, layered ? &e->layer_ev_out : nullptr) != KV_OK)
             return KV_EHIP;
         if (mark_end(e, true, k, e->s_out) != KV_OK) return KV_EHIP;
     }
     if (ni > 0) {
         if (upload_ids(false, true, e->s_in) != KV_OK) return KV_EHIP;
-        if (mark_start(e, false, e->s_in) != KV_OK) return KV_EHIP;
+        stamp_launch(e, false, true, p_in);
+        if (!e->own_streams && mark_start(e, false, e->s_in) != KV_OK) return KV_EHIP;
         if (launch_link(e, sh_in, e->s_in, p_in, ids_in, layered ? &e->layer_ev_in : nullptr) != KV_OK)
             return KV_EHIP;
         if (mark_end(e, false, k, e->s_in) != KV_OK) return KV_EHIP;
@@ -1396,13 +1439,19 @@ int kv_create(kv_engine **out, const kv_config *cfg, void *hbm_cache, void *host
     }
     // one call names at most min(blocks, slots) ids over both directions
     e->desc_cap = 2 * (size_t)std::min(cfg->n_hbm_blocks, cfg->n_host_slots) + 16;
-    if (hipHostMalloc((void **)&e->desc_host, kRing * e->desc_cap * sizeof(int32_t), hipHostMallocDefault) !=
-            hipSuccess ||
+    e->desc_cap += e->desc_cap % 2;  // the time stamps lie behind the sets
+    const size_t sets = kRing * e->desc_cap * sizeof(int32_t), stamps = (2 + 3 * (size_t)dkv::kStamps) * sizeof(unsigned long long);
+    if (hipHostMalloc((void **)&e->desc_host, sets + stamps, hipHostMallocDefault) != hipSuccess ||
         hipMalloc((void **)&e->desc_dev, kRing * e->desc_cap * sizeof(int32_t)) != hipSuccess ||
         hipMalloc((void **)&e->claim, 2 * kClaimStride * sizeof(unsigned int)) != hipSuccess) {
         (void)hipGetLastError();
         return fail(KV_ENOMEM);
     }
+    e->stamps = reinterpret_cast<unsigned long long *>(e->desc_host + kRing * e->desc_cap);
+    memset(e->stamps, 0, stamps);
+    int khz = 0;
+    if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, e->device) != hipSuccess || khz <= 0) return fail(KV_EHIP);
+    e->stamp_ms = 1.0 / khz;
     // the tile counters start at zero; every launch leaves them at zero again
     if (hipMemset(e->claim, 0, 2 * kClaimStride * sizeof(unsigned int)) != hipSuccess)
         return fail(KV_EHIP);
@@ -1480,11 +1529,15 @@ int kv_wait(kv_engine *e)
     if (e->batch_open) {
         e->acc.ms_e2e = now_ms() - e->t0;
         float ms = 0;
-        if (e->b_o0 && e->b_o1) {
+        if (e->begun[0] >= 0) {
+            e->acc.ms_out = stamped_ms(e, 0);
+        } else if (e->b_o0 && e->b_o1) {
             HIPTRY(e, hipEventElapsedTime(&ms, e->b_o0, e->b_o1));
             e->acc.ms_out = ms;
         }
-        if (e->b_i0 && e->b_i1) {
+        if (e->begun[1] >= 0) {
+            e->acc.ms_in = stamped_ms(e, 1);
+        } else if (e->b_i0 && e->b_i1) {
             HIPTRY(e, hipEventElapsedTime(&ms, e->b_i0, e->b_i1));
             e->acc.ms_in = ms;
         }

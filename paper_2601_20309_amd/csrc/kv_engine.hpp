@@ -114,6 +114,13 @@ struct kv_engine {
     hipEvent_t ev_o0 = nullptr, ev_o1 = nullptr, ev_i0 = nullptr, ev_i1 = nullptr;
     hipEvent_t ev_join = nullptr, ev_join_in = nullptr;  // stream_out waits for stream_in / the reverse
     hipEvent_t b_o0 = nullptr, b_o1 = nullptr, b_i0 = nullptr, b_i1 = nullptr;  // this batch's first start / last end
+    // The kernel paths on the engine's own streams: times left by the launches themselves
+    // (pinned host memory, MoveParams::begin and end), [0..1] begin of the batch's out and in
+    // work, then kStamps ends of launches that carry only out, only in, and both.
+    unsigned long long *stamps = nullptr;
+    double stamp_ms = 0;                // milliseconds per tick
+    int begun[2] = {-1, -1};            // where this batch's out / in work left its begin, -1: not yet
+    uint32_t stamp_waves[3] = {};       // ends to look at, per kind of launch; 0: no such launch in this batch
     bool batch_open = false;
     bool out_pending = false, in_pending = false;  // work enqueued since the last kv_wait
     bool in_dirty = false;                         // stream_in holds work stream_out has not joined

@@ -36,6 +36,7 @@ constexpr int kThreads = 256;      // lanes per workgroup of the HBM-bound launc
 // Vectors per lane where a tile may span segments: every vector has pointers of its
 // own there, and with eight they would not fit the registers of a 1024-lane workgroup.
 constexpr int kMaxRaggedU = 4;
+constexpr uint32_t kStamps = 512;  // at least the waves of every launch shape that the engine picks
 constexpr int kMaxThreads = 1024;  // workgroups only pack waves; any multiple of 64 up to this
 
 // Division by a number that is the same for a whole launch, x < 2^31: a multiply
@@ -103,6 +104,9 @@ struct MoveParams {
     // next unclaimed tile, [1] the waves that are done
     unsigned int *claim;
     unsigned int *clear;  // nullptr, or a pair that a later launch draws from: put to zero
+    // Pinned host memory, or nullptr: where the launch leaves the device's clock as it begins,
+    // and each wave w, in end[w % kStamps], when its last store has arrived.
+    unsigned long long *begin, *end;
     DirDesc out, in;
 };
 
@@ -425,6 +429,14 @@ __device__ __forceinline__ void run_drawn(const MoveParams &p, const int32_t *__
     }
 }
 
+// The device's clock, to host memory.  Time stamps that a launch leaves by itself cost it
+// nothing before it begins; an event recorded ahead of it is a packet of its own, 2 us
+// that the launch waits for.
+__device__ __forceinline__ void stamp(unsigned long long *to)
+{
+    __scoped_atomic_store_n(to, (unsigned long long)wall_clock64(), __ATOMIC_RELAXED, __MEMORY_SCOPE_SYSTEM);
+}
+
 // V: vector moved per lane (16 bytes when the segment allows it).
 // U: vectors per lane per tile; a tile is 64 * U consecutive vectors of a group
 //    (MoveParams), so every wave access touches 64 * sizeof(V) contiguous bytes on
@@ -455,6 +467,7 @@ __device__ __forceinline__ void move(const MoveParams &p, const int32_t *__restr
     const uint32_t wave = blockIdx.x * waves_per_wg + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const uint32_t n_waves = gridDim.x * waves_per_wg;
     if (LINK && p.clear && blockIdx.x == 0 && threadIdx.x < 2) p.clear[threadIdx.x] = 0u;
+    if (LINK && p.begin && blockIdx.x == 0 && threadIdx.x == 0) stamp(p.begin);
     const uint32_t n_steps = p.mix_q ? p.in.tiles : (p.out.tiles > p.in.tiles ? p.out.tiles : p.in.tiles);
     constexpr int UR = U < kMaxRaggedU ? U : kMaxRaggedU;  // what cut_tiles() cut by when tiles are not whole
     if (!LINK || n_steps <= (uint64_t)kFixedRounds * n_waves) {
@@ -462,12 +475,15 @@ __device__ __forceinline__ void move(const MoveParams &p, const int32_t *__restr
             run_fixed<V, U, LINK, true>(p, out_ids, out_slots, in_ids, in_slots, n_steps, wave, n_waves, lane);
         else
             run_fixed<V, UR, LINK, false>(p, out_ids, out_slots, in_ids, in_slots, n_steps, wave, n_waves, lane);
-        return;
-    }
-    if (p.full_tiles)
+    } else if (p.full_tiles) {
         run_drawn<V, U, LINK, true>(p, out_ids, out_slots, in_ids, in_slots, n_steps, wave, n_waves, lane);
-    else
+    } else {
         run_drawn<V, UR, LINK, false>(p, out_ids, out_slots, in_ids, in_slots, n_steps, wave, n_waves, lane);
+    }
+    if (LINK && p.end) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (lane == 0) stamp(p.end + wave % kStamps);
+    }
 }
 
 template <typename V, int U, bool LINK>

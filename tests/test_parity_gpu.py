@@ -719,3 +719,33 @@ def test_tiles_begin_on_lines_of_the_pool(host_layout, offset):
             assert np.array_equal(dev.cpu().numpy(), want_cache), (seg, chunk_layers)
             assert np.array_equal(around, want), (seg, chunk_layers)
             eng.kv_destroy()
+
+
+@pytest.mark.parametrize("own_streams", [True, False])
+@pytest.mark.parametrize("kw", [{}, dict(chunk_layers=3), dict(max_copy_wgs=200), dict(path=B.KV_PATH_ZEROCOPY),
+                                dict(path=B.KV_PATH_ZEROCOPY, chunk_layers=1)])
+def test_times_of_a_batch(kw, own_streams):
+    """ms_out and ms_in of one to several calls before a wait: a direction that was not
+    carried took no time, one that was took no less than its bytes need at 64 GB/s (the
+    published rate of the link) and no more than the batch; times of an earlier, longer
+    batch, with more waves, are not seen again."""
+    kw = dict(kw)
+    sh = W.KVShape(16, 8, 128, 16, n_hbm_blocks=300, n_host_slots=300)        # 1 MiB blocks
+    rot = W.simple_rotation(sh, 120, 110, seed=4)
+    case, _ = make_case(sh, B.KV_HOST_BLOCK_FIRST, kw.pop("path", B.KV_PATH_AUTO), rot=rot, own_streams=own_streams, **kw)
+    e, oi, os_, ii, is_ = case.eng, rot.out_ids, rot.out_slots, rot.in_ids, rot.in_slots
+    calls = {"rotate": lambda n: e.kv_rotate(oi[:n], os_[:n], ii[:n], is_[:n]),
+             "out": lambda n: e.kv_swap_out(oi[:n], os_[:n]), "in": lambda n: e.kv_swap_in(is_[:n], ii[:n])}
+    for batch in (["rotate"], ["out"], ["in"], ["out", "in"], ["in", "rotate"], ["out", "rotate", "in"], ["rotate", "out", "out"]):
+        for n in (100, 2):
+            for c in batch:
+                assert calls[c](n) == 0
+            assert e.kv_wait() == 0
+            st = e.kv_last_stats()
+            for key, other in (("out", "in"), ("in", "out")):
+                ms, moved = st["ms_" + key], st["bytes_" + key]
+                if batch == [other]:
+                    assert ms == 0 and moved == 0, (batch, n, st)
+                else:
+                    assert moved / 64e6 <= ms <= st["ms_e2e"], (batch, n, st)
+    case.close()
