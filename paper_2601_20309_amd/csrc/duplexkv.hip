@@ -1835,19 +1835,20 @@ int kv_reader_start(kv_engine *e, const int32_t *ids, int32_t n, int32_t passes,
     // 5 per CU 6.61 / 5.11, 56.7 / 5.10;  5.5 6.83 / 5.94, 56.7 / 5.39;  6 6.91 / 6.69, 55.7 /
     // 5.64 (the rotation 100.2 GB/s for 100.8);  7 6.90 / 3.25, 53.1 / 4.79.
     const int most_wgs = 11 * (e->n_cus > 0 ? e->n_cus : 256) / 2;
-    constexpr size_t kReadCounters = (size_t)dkv::kReadGroups * dkv::kReadStride;  // words of a pass's counters
+    constexpr size_t kReadCounters = (size_t)dkv::kReadGroups * dkv::kReadStride;  // words of one set of counters
     if (!e->s_read) {
         const size_t idb = 2 * (size_t)e->cfg.n_hbm_blocks * sizeof(int32_t);
         if (hipMalloc((void **)&e->read_ids, idb) != hipSuccess ||
             hipHostMalloc((void **)&e->read_ids_host, idb, hipHostMallocDefault) != hipSuccess ||
-            hipMalloc((void **)&e->read_part, (size_t)most_wgs * sizeof(unsigned long long) +
-                                                  kReadPasses * kReadCounters * sizeof(unsigned int)) != hipSuccess ||
+            hipMalloc((void **)&e->read_part,
+                      (size_t)most_wgs * sizeof(unsigned long long) + 2 * kReadCounters * sizeof(unsigned int)) != hipSuccess ||
             hipHostMalloc((void **)&e->read_sums, (size_t)most_wgs * sizeof(unsigned long long),
                           hipHostMallocDefault) != hipSuccess) {
             (void)hipGetLastError();
             return KV_ENOMEM;
         }
         HIPTRY(e, hipStreamCreateWithFlags(&e->s_read, hipStreamNonBlocking));
+        HIPTRY(e, hipMemsetAsync(e->read_part + most_wgs, 0, 2 * kReadCounters * sizeof(unsigned int), e->s_read));
     }
     while ((int32_t)e->read_ev.size() < passes + 1) {
         hipEvent_t x;
@@ -1892,25 +1893,36 @@ int kv_reader_start(kv_engine *e, const int32_t *ids, int32_t n, int32_t passes,
     const uint32_t rounds = p.tiles / (uint32_t)wgs;
     p.fixed = rounds < 4 ? rounds + 1 : rounds / 4;
     p.steal = rounds < 64 ? 0 : 2;
-    const bool rows = p.vec_per_seg % dkv::kWave == 0, on_host = n <= (int32_t)dkv::kInlineIds;
+    const bool rows = p.vec_per_seg % dkv::kWave == 0;
     dkv::IdArgs a;
-    if (on_host) std::copy(ids, ids + n, a.v);
-    if (n > 0 && (!on_host || rounds >= 4)) {
+    const bool singly = n <= (int32_t)dkv::kInlineIds;
+    const bool pairs = !singly && n <= 2 * (int32_t)dkv::kInlineIds && e->cfg.n_hbm_blocks <= 65536;
+    if (singly) {
+        std::copy(ids, ids + n, a.v);
+    } else if (pairs) {
+        for (int32_t i = 0; i + 1 < n; i += 2) a.v[i / 2] = (int32_t)((uint32_t)ids[i] | (uint32_t)ids[i + 1] << 16);
+        if (n % 2) a.v[n / 2] = ids[n - 1];
+    } else {
         memcpy(e->read_ids_host, ids, (size_t)n * sizeof(int32_t));
         const unsigned g = std::min(64u, ((unsigned)n + dkv::kThreads - 1) / dkv::kThreads);
-        hipLaunchKernelGGL(dkv::kv_reader_begin_kernel, dim3(g), dim3(dkv::kThreads), 0, e->s_read, e->read_ids_host,
-                           e->read_ids, p.n, next, dkv::kReadGroups * (uint32_t)passes);
+        hipLaunchKernelGGL(dkv::kv_reader_ids_kernel, dim3(g), dim3(dkv::kThreads), 0, e->s_read, e->read_ids_host,
+                           e->read_ids, p.n);
         HIPTRY(e, hipGetLastError());
     }
     HIPTRY(e, hipEventRecord(e->read_ev[0], e->s_read));
     for (int32_t k = 0; k < passes; k++) {
         if (p.tiles > 0) {
             p.pass = (uint32_t)k;
-            p.next = next + (size_t)k * kReadCounters;
+            p.next = next + e->read_turn * kReadCounters;
+            p.clear = next + (1 - e->read_turn) * kReadCounters;
+            e->read_turn = 1 - e->read_turn;
             const dim3 g((unsigned)wgs), b(dkv::kThreads);
-            if (on_host)
-                launch(rows ? dkv::kv_reader_inline_kernel<true> : dkv::kv_reader_inline_kernel<false>, g, b, e->s_read,
-                       nullptr, p, a);
+            if (singly)
+                launch(rows ? dkv::kv_reader_inline_kernel<true, dkv::IdsInArgs> : dkv::kv_reader_inline_kernel<false, dkv::IdsInArgs>,
+                       g, b, e->s_read, nullptr, p, a);
+            else if (pairs)
+                launch(rows ? dkv::kv_reader_inline_kernel<true, dkv::IdPairsInArgs> : dkv::kv_reader_inline_kernel<false, dkv::IdPairsInArgs>,
+                       g, b, e->s_read, nullptr, p, a);
             else
                 launch(rows ? dkv::kv_reader_kernel<true> : dkv::kv_reader_kernel<false>, g, b, e->s_read, nullptr, p,
                        (const int32_t *)e->read_ids);

@@ -155,7 +155,8 @@ struct kv_engine {
     hipStream_t s_read = nullptr;
     int32_t *read_ids = nullptr;               // device, 2 * n_hbm_blocks ints
     int32_t *read_ids_host = nullptr;          // pinned
-    unsigned long long *read_part = nullptr;   // device: one sum per workgroup, then the tile counters
+    unsigned long long *read_part = nullptr;   // device: one sum per workgroup, then two sets of tile counters
+    size_t read_turn = 0;                      // the set that the next pass draws from
     unsigned long long *read_sums = nullptr;   // pinned: one sum per workgroup over all passes
     int read_wgs = 0;                          // workgroups of the reader under way
     std::vector<hipEvent_t> read_ev;           // passes + 1 timestamps

@@ -108,3 +108,26 @@ def test_reader_claims_every_tile_once(vecs):
         rc, got, _ = eng.kv_reader_wait()
         assert rc == 0 and got == int(block[ids[:n]].sum()) * passes % (1 << 64), (wgs, rounds, passes)
     eng.kv_destroy()
+
+
+@pytest.mark.parametrize("vecs", [64, 5])
+@pytest.mark.parametrize("blocks", [65536, 65537])
+def test_reader_lists_in_arguments(blocks, vecs):
+    """Lists at and beyond what a launch's arguments hold, two ids to a word where the
+    cache has at most 65536 blocks, with the highest ids among them, of odd and even
+    lengths; fixed shares only and claimed tiles in turn, so that each pass finds the
+    counters that another one drew from at zero."""
+    sh = W.KVShape(1, 1, 8 * vecs, 1, n_hbm_blocks=blocks, n_host_slots=4)
+    cache = torch.randint(-2**62, 2**62, (2, blocks, 2 * vecs), device="cuda")
+    block = sum((w & 0xFFFFFFFF).sum(1) + ((w >> 32) & 0xFFFFFFFF).sum(1) for w in cache).cpu().numpy()
+    torch.cuda.synchronize()
+    eng = B.Engine(B.make_config(sh), cache.data_ptr())
+    rng = np.random.default_rng(blocks)
+    for n, passes, wgs in [(1, 1, 0), (2, 2, 0), (895, 1, 0), (896, 1, 1), (897, 2, 2), (1791, 3, 1), (1792, 1, 0), (1793, 2, 1), (5000, 1, 3),
+                           (1792, 2, 1), (7, 1, 0)]:
+        ids = rng.integers(0, blocks, n).astype(np.int32)
+        ids[-1] = blocks - 1
+        assert eng.kv_reader_start(ids, passes, wgs) == 0
+        rc, got, _ = eng.kv_reader_wait()
+        assert rc == 0 and got == int(block[ids].sum()) * passes % (1 << 64), (n, passes, wgs)
+    eng.kv_destroy()
