@@ -74,24 +74,24 @@ def _load() -> C.CDLL:
             f"{LIB_PATH} is not built; run `python -m paper_2601_20309_amd.build` "
             "(there is no CPU fallback)")
     L = C.CDLL(LIB_PATH)
-    p32, pcfg = C.POINTER(C.c_int32), C.POINTER(kv_config)
+    p32, pids, pcfg = C.POINTER(C.c_int32), C.c_void_p, C.POINTER(kv_config)    # pids: what _ids() gives
     for n in ("kv_seg_bytes", "kv_block_bytes", "kv_cache_bytes", "kv_pool_bytes"):
         getattr(L, n).restype = C.c_uint64
         getattr(L, n).argtypes = [pcfg]
     L.kv_validate.restype = C.c_int
-    L.kv_validate.argtypes = [pcfg, p32, p32, C.c_int32, p32, p32, C.c_int32]
+    L.kv_validate.argtypes = [pcfg, pids, pids, C.c_int32, pids, pids, C.c_int32]
     L.kv_create.restype = C.c_int
     L.kv_create.argtypes = [C.POINTER(C.c_void_p), pcfg, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]
     L.kv_destroy.restype = C.c_int
     L.kv_destroy.argtypes = [C.c_void_p]
     L.kv_swap_out.restype = C.c_int
-    L.kv_swap_out.argtypes = [C.c_void_p, p32, p32, C.c_int32]
+    L.kv_swap_out.argtypes = [C.c_void_p, pids, pids, C.c_int32]
     L.kv_swap_in.restype = C.c_int
-    L.kv_swap_in.argtypes = [C.c_void_p, p32, p32, C.c_int32]
+    L.kv_swap_in.argtypes = [C.c_void_p, pids, pids, C.c_int32]
     L.kv_rotate.restype = C.c_int
-    L.kv_rotate.argtypes = [C.c_void_p, p32, p32, C.c_int32, p32, p32, C.c_int32]
+    L.kv_rotate.argtypes = [C.c_void_p, pids, pids, C.c_int32, pids, pids, C.c_int32]
     L.kv_rotate_static.restype = C.c_int
-    L.kv_rotate_static.argtypes = [pcfg, C.c_void_p, C.c_void_p, C.c_void_p, p32, p32, C.c_int32, p32, p32, C.c_int32]
+    L.kv_rotate_static.argtypes = [pcfg, C.c_void_p, C.c_void_p, C.c_void_p, pids, pids, C.c_int32, pids, pids, C.c_int32]
     L.kv_wait.restype = C.c_int
     L.kv_wait.argtypes = [C.c_void_p]
     L.kv_query.restype = C.c_int
@@ -107,7 +107,7 @@ def _load() -> C.CDLL:
     L.kv_probe_link.restype = C.c_int
     L.kv_probe_link.argtypes = [C.c_uint64, C.c_int32] + [C.POINTER(C.c_double)] * 4
     L.kv_reader_start.restype = C.c_int
-    L.kv_reader_start.argtypes = [C.c_void_p, p32, C.c_int32, C.c_int32, C.c_int32]
+    L.kv_reader_start.argtypes = [C.c_void_p, pids, C.c_int32, C.c_int32, C.c_int32]
     L.kv_reader_wait.restype = C.c_int
     L.kv_reader_wait.argtypes = [C.c_void_p, C.POINTER(C.c_uint64), C.POINTER(C.c_double)]
     L.kv_table_create.restype = C.c_int
@@ -119,9 +119,9 @@ def _load() -> C.CDLL:
     L.kv_table_eager.restype = C.c_int
     L.kv_table_eager.argtypes = [C.c_void_p, C.c_int32, p32]
     L.kv_table_rotate.restype = C.c_int
-    L.kv_table_rotate.argtypes = [C.c_void_p, p32, C.c_int32, p32, C.c_int32]
+    L.kv_table_rotate.argtypes = [C.c_void_p, pids, C.c_int32, pids, C.c_int32]
     L.kv_table_rotate_eager.restype = C.c_int
-    L.kv_table_rotate_eager.argtypes = [C.c_void_p, p32, C.c_int32, p32, C.c_int32, C.c_int32, p32]
+    L.kv_table_rotate_eager.argtypes = [C.c_void_p, pids, C.c_int32, pids, C.c_int32, C.c_int32, p32]
     L.kv_table_finish.restype = C.c_int
     L.kv_table_finish.argtypes = [C.c_void_p, C.c_int32]
     L.kv_table_blocks.restype = C.c_int
@@ -149,13 +149,19 @@ def make_config(shape, host_layout=KV_HOST_BLOCK_FIRST, path=KV_PATH_AUTO, chunk
                      chunk_layers, max_copy_wgs, vecs_per_lane, wg_lanes, hbm_layout, staging_bytes)
 
 
+_INT32 = np.dtype(np.int32)
+
+
 def _ids(a):
+    """An id list as (what ctypes takes for its address, its length): the bytes of a copy,
+    or None for an empty list.  (A copy of a few KiB is had in 0.3 us; an array's own
+    address, as a ctypes pointer, in 1.3, and a call has up to four lists.)"""
     if a is None:
-        return None, 0, None
-    arr = np.ascontiguousarray(a, dtype=np.int32)
-    if arr.size == 0:
-        return None, 0, arr
-    return arr.ctypes.data_as(C.POINTER(C.c_int32)), int(arr.size), arr
+        return None, 0
+    if type(a) is not np.ndarray or a.dtype is not _INT32:
+        a = np.ascontiguousarray(a, dtype=np.int32)
+    b = a.tobytes()
+    return (b, len(b) >> 2) if b else (None, 0)
 
 
 def kv_strerror(code: int) -> str:
@@ -170,8 +176,8 @@ def kv_pool_bytes(cfg): return int(lib.kv_pool_bytes(C.byref(cfg)))
 
 def kv_validate(cfg, out_block_ids, out_host_slots, in_block_ids, in_host_slots,
                 n_out: Optional[int] = None, n_in: Optional[int] = None) -> int:
-    po, no, k1 = _ids(out_block_ids); ps, no2, k2 = _ids(out_host_slots)
-    pi, ni, k3 = _ids(in_block_ids); pis, ni2, k4 = _ids(in_host_slots)
+    po, no = _ids(out_block_ids); ps, no2 = _ids(out_host_slots)
+    pi, ni = _ids(in_block_ids); pis, ni2 = _ids(in_host_slots)
     assert no == no2 and ni == ni2
     return lib.kv_validate(C.byref(cfg), po, ps, no if n_out is None else n_out,
                            pi, pis, ni if n_in is None else n_in)
@@ -179,11 +185,11 @@ def kv_validate(cfg, out_block_ids, out_host_slots, in_block_ids, in_host_slots,
 
 def kv_rotate_static(cfg, hbm_cache_ptr: int, host_pool_ptr: int, stream: int,
                      out_block_ids, out_host_slots, in_block_ids, in_host_slots) -> int:
-    po, no, k1 = _ids(out_block_ids); ps, no2, k2 = _ids(out_host_slots)
-    pi, ni, k3 = _ids(in_block_ids); pis, ni2, k4 = _ids(in_host_slots)
+    po, no = _ids(out_block_ids); ps, no2 = _ids(out_host_slots)
+    pi, ni = _ids(in_block_ids); pis, ni2 = _ids(in_host_slots)
     assert no == no2 and ni == ni2
-    return lib.kv_rotate_static(C.byref(cfg), C.c_void_p(hbm_cache_ptr or None), C.c_void_p(host_pool_ptr or None),
-                                C.c_void_p(stream or None), po, ps, no, pi, pis, ni)
+    return lib.kv_rotate_static(C.byref(cfg), hbm_cache_ptr or None, host_pool_ptr or None, stream or None, po, ps, no,
+                                pi, pis, ni)
 
 
 def kv_probe_link(nbytes: int, reps: int = 5) -> dict:
@@ -229,30 +235,31 @@ class Engine:
             raise KVError(rc, "kv_create")
 
     def kv_swap_out(self, block_ids, host_slots) -> int:
-        pi, n, k1 = _ids(block_ids); ps, n2, k2 = _ids(host_slots)
+        pi, n = _ids(block_ids); ps, n2 = _ids(host_slots)
         assert n == n2
         return lib.kv_swap_out(self._h, pi, ps, n)
 
     def kv_swap_in(self, host_slots, block_ids) -> int:
-        ps, n, k1 = _ids(host_slots); pi, n2, k2 = _ids(block_ids)
+        ps, n = _ids(host_slots); pi, n2 = _ids(block_ids)
         assert n == n2
         return lib.kv_swap_in(self._h, ps, pi, n)
 
     def kv_rotate(self, out_block_ids, out_host_slots, in_block_ids, in_host_slots) -> int:
-        po, no, k1 = _ids(out_block_ids); ps, no2, k2 = _ids(out_host_slots)
-        pi, ni, k3 = _ids(in_block_ids); pis, ni2, k4 = _ids(in_host_slots)
+        po, no = _ids(out_block_ids); ps, no2 = _ids(out_host_slots)
+        pi, ni = _ids(in_block_ids); pis, ni2 = _ids(in_host_slots)
         assert no == no2 and ni == ni2
         return lib.kv_rotate(self._h, po, ps, no, pi, pis, ni)
 
     def prepare(self, out_block_ids, out_host_slots, in_block_ids, in_host_slots):
         """Marshal one rotation's id lists once; returns a zero-argument callable
         that performs the kv_rotate call (for loops that repeat a rotation)."""
-        po, no, k1 = _ids(out_block_ids); ps, no2, k2 = _ids(out_host_slots)
-        pi, ni, k3 = _ids(in_block_ids); pis, ni2, k4 = _ids(in_host_slots)
+        lists = [np.ascontiguousarray([] if a is None else a, dtype=np.int32)
+                 for a in (out_block_ids, out_host_slots, in_block_ids, in_host_slots)]
+        (no, no2, ni, ni2), h, f = (a.size for a in lists), self._h, lib.kv_rotate
         assert no == no2 and ni == ni2
-        h, f = self._h, lib.kv_rotate
+        po, ps, pi, pis = (a.ctypes.data if a.size else None for a in lists)
 
-        def call(_keep=(k1, k2, k3, k4)):
+        def call(_keep=lists):
             return f(h, po, ps, no, pi, pis, ni)
         return call
 
@@ -289,7 +296,7 @@ class Engine:
         return {f: getattr(st, f) for f, _ in kv_stats._fields_}
 
     def kv_reader_start(self, block_ids, passes: int = 1, max_wgs: int = 0) -> int:
-        pi, n, k1 = _ids(block_ids)
+        pi, n = _ids(block_ids)
         self._reader_passes = passes
         return lib.kv_reader_start(self._h, pi, n, passes, max_wgs)
 
@@ -341,13 +348,13 @@ class Table:
         return rc, n.value
 
     def kv_table_rotate(self, preempt, resume) -> int:
-        pp, np_, k1 = _ids(preempt)
-        pr, nr, k2 = _ids(resume)
+        pp, np_ = _ids(preempt)
+        pr, nr = _ids(resume)
         return lib.kv_table_rotate(self._h, pp, np_, pr, nr)
 
     def kv_table_rotate_eager(self, preempt, resume, eager_budget: int):
-        pp, np_, k1 = _ids(preempt)
-        pr, nr, k2 = _ids(resume)
+        pp, np_ = _ids(preempt)
+        pr, nr = _ids(resume)
         n = C.c_int32(0)
         rc = lib.kv_table_rotate_eager(self._h, pp, np_, pr, nr, eager_budget, C.byref(n))
         return rc, n.value
