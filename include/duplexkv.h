@@ -289,7 +289,8 @@ int kv_reader_start(kv_engine *engine, const int32_t *block_ids, int32_t n, int3
 
 /*
  * Waits for the reader.  checksum: the sum over all passes.  ms_per_pass: NULL
- * or an array of `passes` doubles, device time of each pass (HIP events).
+ * or an array of `passes` doubles, device time of each pass (several: HIP events between
+ * them; one: the device's clock as it begins and as its last workgroup ends, 0 for an empty list).
  */
 int kv_reader_wait(kv_engine *engine, uint64_t *checksum, double *ms_per_pass);
 

@@ -157,7 +157,7 @@ struct kv_engine {
     int32_t *read_ids_host = nullptr;          // pinned
     unsigned long long *read_part = nullptr;   // device: one sum per workgroup, then two sets of tile counters
     size_t read_turn = 0;                      // the set that the next pass draws from
-    unsigned long long *read_sums = nullptr;   // pinned: one sum per workgroup over all passes
+    unsigned long long *read_sums = nullptr;   // pinned: begin of a single pass, a gap, then per workgroup its sum over all passes and its end
     int read_wgs = 0;                          // workgroups of the reader under way
     std::vector<hipEvent_t> read_ev;           // passes + 1 timestamps
     int32_t read_passes = 0;

@@ -148,6 +148,14 @@ __device__ __forceinline__ void locate(const MoveParams &p, const DirDesc &d,
     far_off = (uint64_t)slot * slot_stride + (uint64_t)pl * plane_stride;
 }
 
+// The device's clock, to host memory.  Time stamps that a launch leaves by itself cost it
+// nothing before it begins; an event recorded ahead of it is a packet of its own, 2 us
+// that the launch waits for.
+__device__ __forceinline__ void stamp(unsigned long long *to)
+{
+    __scoped_atomic_store_n(to, (unsigned long long)wall_clock64(), __ATOMIC_RELAXED, __MEMORY_SCOPE_SYSTEM);
+}
+
 // What one wave does in one step: an in tile, an out tile, or one of each.
 // The lane's pointers are worked out a step ahead, all of them: an address
 // computed where its load is issued lands in a register of the step before, and
@@ -448,14 +456,6 @@ __device__ __forceinline__ void run_drawn(const MoveParams &p, const int32_t *__
     }
 }
 
-// The device's clock, to host memory.  Time stamps that a launch leaves by itself cost it
-// nothing before it begins; an event recorded ahead of it is a packet of its own, 2 us
-// that the launch waits for.
-__device__ __forceinline__ void stamp(unsigned long long *to)
-{
-    __scoped_atomic_store_n(to, (unsigned long long)wall_clock64(), __ATOMIC_RELAXED, __MEMORY_SCOPE_SYSTEM);
-}
-
 // V: vector moved per lane (16 bytes when the segment allows it).
 // U: vectors per lane per tile; a tile is 64 * U consecutive vectors of a group
 //    (MoveParams), so every wave access touches 64 * sizeof(V) contiguous bytes on
@@ -514,6 +514,8 @@ __global__ __launch_bounds__(kMaxThreads) void kv_move_kernel(const MoveParams p
 {
     move<V, U, LINK>(p, out_ids, out_slots, in_ids, in_slots);
 }
+
+static_assert(sizeof(MoveParams) + sizeof(IdArgs) <= 4096);  // what a kernel's arguments may take
 
 // The lists, back to back, in the arguments: out ids, out slots, in ids, in slots.
 template <typename V, int U>
@@ -592,7 +594,10 @@ __global__ __launch_bounds__(kThreads) void kv_stage_kernel(const StageParams p,
 struct ReadParams {
     const uint8_t *hbm;
     unsigned long long *part;    // one sum per workgroup, in device memory, from pass to pass
-    unsigned long long *result;  // the same in pinned host memory: where the last pass leaves them
+    // Pinned host memory: where the last pass leaves them, each with the device's clock when
+    // its workgroup was done, and (nullptr: nowhere) the clock as a pass begins.
+    u32x4 *result;
+    unsigned long long *begin;
     uint64_t hbm_block_stride;
     uint64_t hbm_plane_stride;
     uint64_t n_vecs;         // n * n_planes * vec_per_seg
@@ -729,6 +734,7 @@ __device__ __forceinline__ void read_pass(const ReadParams &p, const Ids &ids)
 {
     const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1u);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    if (p.begin && blockIdx.x == 0 && tid == 0) stamp(p.begin);
     __shared__ uint32_t claimed[2];
     __shared__ unsigned long long sums[kThreads / kWave];
     // first the fixed share, a tile every gridDim.x ...
@@ -777,8 +783,9 @@ __device__ __forceinline__ void read_pass(const ReadParams &p, const Ids &ids)
     if (tid == 0) {
         for (int w = 1; w < kThreads / kWave; w++) sum += sums[w];
         if (p.pass > 0) sum += p.part[blockIdx.x];
+        const unsigned long long now = wall_clock64();
         if (p.pass + 1u < p.passes) p.part[blockIdx.x] = sum;
-        else __builtin_nontemporal_store(sum, p.result + blockIdx.x);
+        else store_host<u32x4, true>(u32x4{(uint32_t)sum, (uint32_t)(sum >> 32), (uint32_t)now, (uint32_t)(now >> 32)}, p.result + blockIdx.x);
     }
 }
 
