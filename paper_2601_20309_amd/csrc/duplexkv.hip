@@ -449,10 +449,13 @@ int mark_end(kv_engine *e, bool out_side, int k, hipStream_t s)
 // The same waves packed four or sixteen to a workgroup do no better.
 // A configured vecs_per_lane is kept (the wave count follows it; 8 are cut to
 // kMaxRaggedU for segments that 8 do not divide); max_copy_wgs
-// counts workgroups of wg_lanes lanes and set alone keeps 256-lane workgroups, with one
-// vector per lane both ways (144 and 192 waves of U 2 would be past what the link
-// drains: 100.2 GB/s and 3.9 TB/s beside the reader for 101.1 and 4.9) and eight out
-// (a few capped waves: 12 x U 8 move what 24 x U 4 do); wg_lanes set alone keeps the number of waves.
+// counts workgroups of wg_lanes lanes and set alone keeps 256-lane workgroups; the vectors
+// per lane then follow the waves, both ways so that ~128 KiB are in flight, of one-wave
+// workgroups no more than the table has, and out eight.  (GB/s alone / beside the reader: at
+// most 64 one-wave workgroups, U 1 69, U 2 101.4 / 100.7; at most 144, U 1 101.5 / 101.4 and
+// 4.9 TB/s for the reader, 68 x U 2 101.6 / 101.1 and 5.5; 28 of 256 lanes U 1 99.4 / 91.1,
+// U 2 101.0 / 99.9; 16 of 448 lanes 94.1 / 87.2 and 99.9 / 97.2.)  wg_lanes set alone keeps
+// the number of waves.
 //
 // Segments that no tile divides are moved in tiles that span segments where the
 // pool holds a block in one piece; otherwise tiles end with their segment.  The vectors
@@ -485,7 +488,9 @@ LinkShape link_shape(const kv_engine *e, LinkKind kind)
     const bool plane_major = e->cfg.host_layout == KV_HOST_LAYER_FIRST;
     const uint32_t planes = e->cfg.chunk_layers > 0 ? std::min(2u * (uint32_t)e->cfg.chunk_layers, e->n_planes) : e->n_planes;
     const bool lines = on_lines(e, planes);
-    int u = cu ? cu : kind == kBoth ? (cw ? 1 : 2) : kind == kOutOnly && cw ? 8 : 4;
+    const int64_t cap = (int64_t)cw * (cl ? cl : dkv::kThreads) / dkv::kWave;  // configured waves
+    const bool packed = cl ? cl > dkv::kWave : cw > 0;
+    int u = cu ? cu : kind == kBoth ? (packed && cap >= 128 ? 1 : cap >= 56 || !cw ? 2 : cap >= 28 ? 4 : 8) : kind == kOutOnly && cw ? 8 : 4;
     auto whole = [&](int w) { return vec_per_seg % ((uint64_t)dkv::kWave * (uint64_t)w) == 0; };
     auto filled = [&](int w) {
         const uint64_t tile = (uint64_t)dkv::kWave * (uint64_t)w, g = group_vecs(vec_per_seg, planes, plane_major, false);
@@ -520,7 +525,8 @@ LinkShape link_shape(const kv_engine *e, LinkKind kind)
     s.u = u;
     s.limit_u = limit_u;
     s.lanes = cl ? cl : (cw ? dkv::kThreads : dkv::kWave);
-    s.wgs = cw ? cw : std::max(1, waves * dkv::kWave / s.lanes);
+    s.wgs = cw && (packed || cu || kind != kBoth) ? cw : std::max(1, waves * dkv::kWave / s.lanes);
+    if (cw) s.wgs = std::min(s.wgs, cw);
     s.short_steps = cw || cl || cu ? 0 : kShortKib / std::max(1, kib);
     return s;
 }
@@ -620,7 +626,11 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
     // new entry nearly every tile; those reads would then be an eighth of the
     // link traffic (4 KiB segments, one layer: 83 instead of 93 GB/s), so the set
     // is uploaded first, ~5 us on the launch's stream.
-    const uint64_t visit_bytes = e->cfg.host_layout == KV_HOST_LAYER_FIRST ? e->seg : e->block_bytes;
+    // (Layer by layer a launch visits an entry for its layers only: 2048 blocks of 80 layers
+    // each way, a launch per layer, 128 KiB a visit, 434 ms with the ring read in place.)
+    const uint64_t visit_bytes = e->cfg.host_layout == KV_HOST_LAYER_FIRST ? e->seg
+                                 : e->cfg.chunk_layers > 0 ? std::min(e->block_bytes, 2 * (uint64_t)e->cfg.chunk_layers * e->seg)
+                                                           : e->block_bytes;
     // A call of few blocks has no such choice to make: its lists are kernel arguments.
     const bool on_host = ids_inline(e, no, ni);
     const bool upload = !on_host && visit_bytes < (256u << 10);

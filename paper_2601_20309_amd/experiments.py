@@ -702,7 +702,7 @@ def interference():
                 read_both.append(read_bytes * len(inside) / sum(inside) / 1e9)
         ms_both = statistics.median(both)
         launch = ("no kernel, block-first cache" if path == B.KV_PATH_DMA_BLOCKS else "pack / unpack kernels"
-                  if path != B.KV_PATH_FUSED else f"{wgs} x {lanes}" if wgs else "default (112 x 64)")
+                  if path != B.KV_PATH_FUSED else f"{wgs} x {lanes}" if wgs else "default (68 x 64)")
         # what the co-runner pays: the part of the rotation's duration in which it got nothing done
         rb = statistics.median(read_both)
         lost = ms_both * (1 - rb / read_alone) / (moved / 2**30)
@@ -724,7 +724,7 @@ def interference():
     assert eng.kv_reader_start(others, 6) == 0
     rc, _, pm = eng.kv_reader_wait()
     ms_pass = statistics.median(pm[1:])
-    for d, label in (("out", "swap-out (12 waves x 8 vectors)"), ("in", "swap-in (24 waves x 4 vectors)")):
+    for d, label in (("out", "swap-out (16 waves x 4 vectors)"), ("in", "swap-in (24 waves x 4 vectors)")):
         def one(i):
             a = rot if i % 2 == 0 else inv
             rc = eng.kv_swap_out(a.out_ids, a.out_slots) if d == "out" else eng.kv_swap_in(a.in_slots, a.in_ids)
