@@ -63,7 +63,7 @@ extern "C" {
 /* ---- transfer paths ---- */
 #define KV_PATH_AUTO        0  /* engine picks: FUSED for a rotation, ZEROCOPY for one direction */
 #define KV_PATH_SDMA_STAGED 1  /* pack kernel -> staging in HBM -> hipMemcpyAsync (DMA engines), and the mirror: ~10 % slower
-                                  than the kernel paths, and takes two fifths as much, per byte, from an HBM-bound kernel beside it */
+                                  than the kernel paths, and takes half as much, per byte, as a rotation there from an HBM-bound kernel beside it */
 #define KV_PATH_ZEROCOPY    2  /* one kernel per direction, each on its own stream, reading / writing host memory directly */
 #define KV_PATH_NAIVE       3  /* one hipMemcpyAsync per segment: the baseline of Section 4.3.1, for the benchmark ladder */
 #define KV_PATH_FUSED       4  /* one kernel moves both directions, interleaved per lane: 1:1, or, when the in list is the
@@ -98,7 +98,8 @@ typedef struct {
     uint64_t bytes_out;    /* bytes moved HBM -> host since the previous kv_wait */
     uint64_t bytes_in;     /* bytes moved host -> HBM since the previous kv_wait */
     double ms_out;         /* device time of the out work, first start to last end (the device's clock, left by the kernels themselves;
-                              HIP events where copies are enqueued, or on the caller's streams) */
+                              HIP events where copies are enqueued, on the caller's streams, and for segments
+                              whose vectors are too narrow to be written through) */
     double ms_in;          /* same for the in work */
     double ms_e2e;         /* host wall time, entry of the first transfer call to return of kv_wait */
     int32_t path_used;     /* KV_PATH_* of the last call */

@@ -243,6 +243,19 @@ void hbm_strides(const kv_engine *e, uint64_t &plane_stride, uint64_t &block_str
     }
 }
 
+// Whether stores to the pool are written through (see store_host).
+bool writes_through(const kv_engine *e)
+{
+    return e->vec == 16 || (e->vec == 8 && (e->cfg.host_layout == KV_HOST_BLOCK_FIRST || e->seg >= 512));
+}
+
+// Whether transfers are timed by the launches themselves.  Stores that the L2 still holds as
+// a launch's waves end are in no time that these leave: there events time the transfers.
+bool stamps_times(const kv_engine *e)
+{
+    return e->own_streams && writes_through(e);
+}
+
 // Fills the fields common to every launch.
 MoveParams base_params(const kv_engine *e)
 {
@@ -253,7 +266,7 @@ MoveParams base_params(const kv_engine *e)
     p.plane0 = 0;
     p.n_planes = e->n_planes;
     p.vec_per_seg = (uint32_t)(e->seg / (uint64_t)e->vec);
-    p.through = e->vec == 8 && (e->cfg.host_layout == KV_HOST_BLOCK_FIRST || e->seg >= 512) ? 1u : 0u;
+    p.through = writes_through(e) ? 1u : 0u;
     return p;
 }
 
@@ -375,7 +388,7 @@ int mark_start(kv_engine *e, bool out_side, hipStream_t s)
 // Ends of the batch before may lie beside them: the clock only goes up, so the latest counts.
 void stamp_launch(kv_engine *e, bool out, bool in, MoveParams &p)
 {
-    if (!e->own_streams) return;
+    if (!stamps_times(e)) return;
     const int at = out && e->begun[0] < 0 ? 0 : in && e->begun[1] < 0 ? 1 : -1;
     if (at >= 0) p.begin = e->stamps + at;
     if (out && e->begun[0] < 0) e->begun[0] = at;
@@ -673,7 +686,7 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
         }
         if (upload_ids(true, true, e->s_out) != KV_OK) return KV_EHIP;
         stamp_launch(e, true, true, p);
-        if (e->own_streams) {
+        if (stamps_times(e)) {
             stamp_launch(e, true, false, p_rest);  // behind it: its begin is not the first
         } else if (!e->b_o0 && !e->b_i0) {  // one start timestamp serves both directions
             if (mark_start(e, true, e->s_out) != KV_OK) return KV_EHIP;
@@ -753,7 +766,7 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
     if (no > 0) {
         if (upload_ids(true, false, e->s_out) != KV_OK) return KV_EHIP;
         stamp_launch(e, true, false, p_out);
-        if (!e->own_streams && mark_start(e, true, e->s_out) != KV_OK) return KV_EHIP;
+        if (!stamps_times(e) && mark_start(e, true, e->s_out) != KV_OK) return KV_EHIP;
         if (launch_link(e, sh_out, e->s_out, p_out, ids_out, layered ? &e->layer_ev_out : nullptr) != KV_OK)
             return KV_EHIP;
         if (mark_end(e, true, k, e->s_out) != KV_OK) return KV_EHIP;
@@ -761,7 +774,7 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
     if (ni > 0) {
         if (upload_ids(false, true, e->s_in) != KV_OK) return KV_EHIP;
         stamp_launch(e, false, true, p_in);
-        if (!e->own_streams && mark_start(e, false, e->s_in) != KV_OK) return KV_EHIP;
+        if (!stamps_times(e) && mark_start(e, false, e->s_in) != KV_OK) return KV_EHIP;
         if (launch_link(e, sh_in, e->s_in, p_in, ids_in, layered ? &e->layer_ev_in : nullptr) != KV_OK)
             return KV_EHIP;
         if (mark_end(e, false, k, e->s_in) != KV_OK) return KV_EHIP;

@@ -180,22 +180,26 @@ template <typename V, int U, bool FULL, int N>
 __device__ __forceinline__ void lane_pointers(const MoveParams &p, uint64_t hbm_off, uint8_t *far, uint32_t tin,
                                               uint32_t lane, V *(&in_cache)[N], V *(&in_far)[N], uint32_t &n)
 {
-    int32_t v0 = (int32_t)(tin * (kWave * U) + lane);
-    if constexpr (!FULL) v0 -= (int32_t)((uint32_t)(reinterpret_cast<uintptr_t>(far) / sizeof(V)) & p.line_mask);
-    n = p.group_vecs - (uint32_t)v0;
+    uint32_t v0 = tin * (kWave * U) + lane;
+    bool before = false;
+    if constexpr (!FULL) {
+        const uint32_t begin = (uint32_t)(reinterpret_cast<uintptr_t>(far) / sizeof(V)) & p.line_mask;
+        before = v0 < begin;
+        v0 -= begin;
+    }
+    n = p.group_vecs - v0;
 #pragma unroll
     for (int u = 0; u < N; u++) {
-        uint32_t v = (uint32_t)(v0 + u * kWave);
+        uint32_t v = v0 + u * kWave;
         uint64_t off = hbm_off;
         if constexpr (!FULL) {
-            if (u == 0) v = (uint32_t)max(v0, 0);
-            v = min(v, p.group_vecs - 1u);
+            v = min(u == 0 && before ? 0u : v, p.group_vecs - 1u);
             off += (uint64_t)p.by_seg.quotient(v) * p.plane_skip;
         }
         in_cache[u] = reinterpret_cast<V *>(p.hbm + off) + v;
         in_far[u] = reinterpret_cast<V *>(far) + v;
     }
-    if (v0 >= (int32_t)p.group_vecs) n = 0u;
+    if (!before && v0 >= p.group_vecs) n = 0u;
 }
 
 // Step t of a launch.  Normally step t is tile t of the out list and tile t of

@@ -749,3 +749,51 @@ def test_times_of_a_batch(kw, own_streams):
                 else:
                     assert moved / 64e6 <= ms <= st["ms_e2e"], (batch, n, st)
     case.close()
+
+
+@pytest.mark.parametrize("wgs,lanes", [(3, 64), (30, 64), (60, 64), (200, 64), (6, 256), (20, 256), (3, 448), (40, 256)])
+def test_configured_waves_with_vectors_of_the_engines_choice(wgs, lanes):
+    """max_copy_wgs without vecs_per_lane: few to many waves, one to a workgroup and
+    packed, at each of which the vectors per lane differ; both ways, in-heavy and one
+    way, whole tiles and ragged ones, every byte against the oracle."""
+    for vecs in (512, 75):
+        sh = W.KVShape(3, 1, 8 * vecs, 1, n_hbm_blocks=150, n_host_slots=140)
+        for n_out, n_in in ((60, 55), (9, 70), (64, 0), (0, 64)):
+            rot = W.simple_rotation(sh, n_out, n_in, seed=wgs + n_out)
+            case, _ = make_case(sh, B.KV_HOST_BLOCK_FIRST, B.KV_PATH_AUTO, rot=rot, max_copy_wgs=wgs, wg_lanes=lanes)
+            case.rotate(rot)
+            case.check()
+            case.close()
+
+
+@pytest.mark.parametrize("path", [B.KV_PATH_AUTO, B.KV_PATH_ZEROCOPY])
+def test_long_lists_layer_by_layer(path):
+    """Lists too long for a launch's arguments, blocks large and a launch's share of one
+    small: the lists are uploaded once and every launch reads them."""
+    sh = W.KVShape(4, 8, 128, 16, n_hbm_blocks=520, n_host_slots=500)            # 256 KiB blocks, 64 KiB a layer
+    rot = W.simple_rotation(sh, 240, 230, seed=8)
+    case, _ = make_case(sh, B.KV_HOST_BLOCK_FIRST, path, rot=rot, chunk_layers=1)
+    case.rotate(rot)
+    case.check()
+    case.rotate(rot.inverse())
+    case.check()
+    case.close()
+
+
+@pytest.mark.parametrize("host_layout", LAYOUTS)
+@pytest.mark.parametrize("dim", [128, 20, 18, 9])
+def test_times_include_the_last_bytes_stored(dim, host_layout):
+    """2 MiB out in segments of 16-, 8-, 4- and 2-byte vectors: no time is shorter than
+    the link's published rate allows, also where stores wait in a cache when the waves end."""
+    sh = W.KVShape(12, 1, dim, 5, n_hbm_blocks=1, n_host_slots=1)
+    n = (2 << 20) // (2 * 12 * 10 * dim)
+    sh = W.KVShape(12, 1, dim, 5, n_hbm_blocks=2 * n + 4, n_host_slots=2 * n + 4)
+    rot = W.simple_rotation(sh, n, n, seed=dim)
+    case, _ = make_case(sh, host_layout, B.KV_PATH_AUTO, rot=rot)
+    for call in (lambda: case.eng.kv_swap_out(rot.out_ids, rot.out_slots),
+                 lambda: case.eng.kv_rotate(rot.out_ids, rot.out_slots, rot.in_ids, rot.in_slots)):
+        for _ in range(3):
+            assert call() == 0 and case.eng.kv_wait() == 0
+            st = case.eng.kv_last_stats()
+            assert st["bytes_out"] / 64e6 <= st["ms_out"] <= st["ms_e2e"], st
+    case.close()
