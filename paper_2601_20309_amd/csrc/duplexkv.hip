@@ -363,7 +363,7 @@ void open_batch(kv_engine *e)
         e->batch_open = true;
         e->b_o0 = e->b_o1 = e->b_i0 = e->b_i1 = nullptr;
         e->begun[0] = e->begun[1] = -1;
-        e->stamp_waves[0] = e->stamp_waves[1] = e->stamp_waves[2] = 0;
+        std::fill_n(e->stamp_waves, 5, 0u);
         e->t0 = now_ms();
         e->acc = kv_stats{};
     }
@@ -383,26 +383,34 @@ int mark_start(kv_engine *e, bool out_side, hipStream_t s)
     return KV_OK;
 }
 
-// Has launches `p` of a call leave their times: the first that carries a direction in this
-// batch its begin (launch_link passes that to its first launch only), all of them their ends.
-// Ends of the batch before may lie beside them: the clock only goes up, so the latest counts.
-void stamp_launch(kv_engine *e, bool out, bool in, MoveParams &p)
+// Has a launch leave its times, beside those of later ones where it is the first that carries
+// a direction in this batch.
+void stamp_launch(kv_engine *e, bool out, bool in, bool drain, const LinkShape &sh, MoveParams &p)
 {
-    if (!stamps_times(e)) return;
-    const int at = out && e->begun[0] < 0 ? 0 : in && e->begun[1] < 0 ? 1 : -1;
-    if (at >= 0) p.begin = e->stamps + at;
+    const int at = out && e->begun[0] < 0 ? 0 : in && e->begun[1] < 0 ? 1 : out && in ? 4 : in ? 3 : 2;
     if (out && e->begun[0] < 0) e->begun[0] = at;
     if (in && e->begun[1] < 0) e->begun[1] = at;
-    p.end = e->stamps + 2 + (out && in ? 2 : in ? 1 : 0) * (size_t)dkv::kStamps;
+    p.stamps = reinterpret_cast<dkv::u64x2 *>(e->stamps + at * (size_t)dkv::kStamps);
+    p.drain = drain ? 1u : 0u;
+    uint32_t steps;
+    const uint32_t waves = grid_of(sh, p, steps) * ((uint32_t)sh.lanes / dkv::kWave);
+    e->stamp_waves[at] = std::max(e->stamp_waves[at], std::min(dkv::kStamps, waves));
+    e->stamp_sides[at] = (out ? 1u : 0u) | (in ? 2u : 0u);
 }
 
-// The batch's time for a direction, first begin to last end (0: nothing was carried).
+// The batch's time for a direction, first begin to last end (0: nothing was carried).  Ends
+// of the batch before may lie beside its own: the clock only goes up, so the latest counts.
 double stamped_ms(const kv_engine *e, int side)
 {
-    unsigned long long last = 0;
-    for (int kind : {side, 2})
-        for (uint32_t w = 0; w < e->stamp_waves[kind]; w++) last = std::max(last, e->stamps[2 + kind * (size_t)dkv::kStamps + w]);
-    const unsigned long long first = e->begun[side] < 0 ? last : e->stamps[e->begun[side]];
+    unsigned long long first = ~0ull, last = 0;
+    for (int array = 0; array < 5; array++) {
+        if (!(e->stamp_sides[array] >> side & 1u)) continue;
+        for (uint32_t w = 0; w < e->stamp_waves[array]; w++) {
+            const unsigned long long *t = e->stamps[array * (size_t)dkv::kStamps + w];
+            if (array == e->begun[side]) first = std::min(first, t[0]);
+            last = std::max(last, t[1]);
+        }
+    }
     return last > first ? (double)(last - first) * e->stamp_ms : 0.0;
 }
 
@@ -572,15 +580,6 @@ void launch_stage(int vec, hipStream_t s, const dkv::StageParams &p, const int32
 }
 
 // ---- FUSED / ZEROCOPY -----------------------------------------------------
-// The ends that a launch (as launch_move launches it) leaves are looked at in kv_wait.
-void note_ends(kv_engine *e, const LinkShape &sh, const MoveParams &p)
-{
-    if (!p.end) return;
-    uint32_t steps;
-    uint32_t &n = e->stamp_waves[(size_t)(p.end - (e->stamps + 2)) / dkv::kStamps];
-    n = std::max(n, std::min(dkv::kStamps, grid_of(sh, p, steps) * ((uint32_t)sh.lanes / dkv::kWave)));
-}
-
 // One link-bound launch, or, with cfg.chunk_layers set, one launch per chunk of
 // that many layers, lowest layers first, each followed by an event in `ev`, so
 // that whoever consumes the blocks (the model's layer l, a writer of the pool)
@@ -603,11 +602,11 @@ int launch_link(kv_engine *e, const LinkShape &sh, hipStream_t s, const MovePara
         // fits: the whole call's counts were checked
         if (!fill_dir(q, q.out.n, 0, sh.limit_u, q.out) || !fill_dir(q, q.in.n, 0, sh.limit_u, q.in)) return KV_EUNSUP;
         q.mix_q = whole.mix_q && q.out.tiles ? (((uint64_t)q.out.tiles << 32) + q.in.tiles - 1) / q.in.tiles : 0;
-        if (p0 > 0) q.begin = nullptr;
-        if (p0 + per_chunk < whole.n_planes) q.end = nullptr;  // the last one ends last
+        // of several launches the first begins first and the last ends last
+        const bool last = p0 + per_chunk >= whole.n_planes;
+        if (stamps_times(e) && (p0 == 0 || last)) stamp_launch(e, q.out.n > 0, q.in.n > 0, last, sh, q);
         launch_move(sh, e->vec, s, q, ids, true, ev && e->own_streams ? (*ev)[c] : nullptr);
         HIPTRY(e, hipGetLastError());
-        note_ends(e, sh, q);
         e->acc.n_launches += 1;
         if (ev && !e->own_streams) HIPTRY(e, hipEventRecord((*ev)[c], s));
     }
@@ -685,9 +684,8 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
             e->in_dirty = false;
         }
         if (upload_ids(true, true, e->s_out) != KV_OK) return KV_EHIP;
-        stamp_launch(e, true, true, p);
         if (stamps_times(e)) {
-            stamp_launch(e, true, false, p_rest);  // behind it: its begin is not the first
+            // launch_link's launches leave their times
         } else if (!e->b_o0 && !e->b_i0) {  // one start timestamp serves both directions
             if (mark_start(e, true, e->s_out) != KV_OK) return KV_EHIP;
             e->b_i0 = e->b_o0;
@@ -705,10 +703,10 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
         e->layer_on_out = layered;
         e->layer_on_in = false;
         if (n_rest > 0) {
+            if (stamps_times(e)) stamp_launch(e, true, false, true, sh_rest, p_rest);
             launch_move(sh_rest, e->vec, e->s_out, p_rest,
                         MoveIds{d_o + no_paired, d_o + no + no_paired, nullptr, nullptr, on_host}, true);
             HIPTRY(e, hipGetLastError());
-            note_ends(e, sh_rest, p_rest);
             e->acc.n_launches += 1;
         }
         if (mark_end(e, true, k, e->s_out) != KV_OK) return KV_EHIP;
@@ -765,7 +763,6 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
     e->layer_on_in = layered && ni > 0;
     if (no > 0) {
         if (upload_ids(true, false, e->s_out) != KV_OK) return KV_EHIP;
-        stamp_launch(e, true, false, p_out);
         if (!stamps_times(e) && mark_start(e, true, e->s_out) != KV_OK) return KV_EHIP;
         if (launch_link(e, sh_out, e->s_out, p_out, ids_out, layered ? &e->layer_ev_out : nullptr) != KV_OK)
             return KV_EHIP;
@@ -773,7 +770,6 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
     }
     if (ni > 0) {
         if (upload_ids(false, true, e->s_in) != KV_OK) return KV_EHIP;
-        stamp_launch(e, false, true, p_in);
         if (!stamps_times(e) && mark_start(e, false, e->s_in) != KV_OK) return KV_EHIP;
         if (launch_link(e, sh_in, e->s_in, p_in, ids_in, layered ? &e->layer_ev_in : nullptr) != KV_OK)
             return KV_EHIP;
@@ -1462,15 +1458,15 @@ int kv_create(kv_engine **out, const kv_config *cfg, void *hbm_cache, void *host
     }
     // one call names at most min(blocks, slots) ids over both directions
     e->desc_cap = 2 * (size_t)std::min(cfg->n_hbm_blocks, cfg->n_host_slots) + 16;
-    e->desc_cap += e->desc_cap % 2;  // the time stamps lie behind the sets
-    const size_t sets = kRing * e->desc_cap * sizeof(int32_t), stamps = (2 + 3 * (size_t)dkv::kStamps) * sizeof(unsigned long long);
+    static_assert(kRing * sizeof(int32_t) % sizeof(*e->stamps) == 0);  // the time stamps lie behind the sets
+    const size_t sets = kRing * e->desc_cap * sizeof(int32_t), stamps = 5 * (size_t)dkv::kStamps * sizeof(*e->stamps);
     if (hipHostMalloc((void **)&e->desc_host, sets + stamps, hipHostMallocDefault) != hipSuccess ||
         hipMalloc((void **)&e->desc_dev, kRing * e->desc_cap * sizeof(int32_t)) != hipSuccess ||
         hipMalloc((void **)&e->claim, 2 * kClaimStride * sizeof(unsigned int)) != hipSuccess) {
         (void)hipGetLastError();
         return fail(KV_ENOMEM);
     }
-    e->stamps = reinterpret_cast<unsigned long long *>(e->desc_host + kRing * e->desc_cap);
+    e->stamps = reinterpret_cast<unsigned long long(*)[2]>(e->desc_host + kRing * e->desc_cap);
     memset(e->stamps, 0, stamps);
     int khz = 0;
     if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, e->device) != hipSuccess || khz <= 0) return fail(KV_EHIP);
@@ -1865,7 +1861,7 @@ int kv_reader_start(kv_engine *e, const int32_t *ids, int32_t n, int32_t passes,
             hipHostMalloc((void **)&e->read_ids_host, idb, hipHostMallocDefault) != hipSuccess ||
             hipMalloc((void **)&e->read_part,
                       (size_t)most_wgs * sizeof(unsigned long long) + 2 * kReadCounters * sizeof(unsigned int)) != hipSuccess ||
-            hipHostMalloc((void **)&e->read_sums, (1 + (size_t)most_wgs) * 2 * sizeof(unsigned long long),
+            hipHostMalloc((void **)&e->read_sums, (2 * (size_t)most_wgs + dkv::kReadBegins) * sizeof(unsigned long long),
                           hipHostMallocDefault) != hipSuccess) {
             (void)hipGetLastError();
             return KV_ENOMEM;
@@ -1885,7 +1881,7 @@ int kv_reader_start(kv_engine *e, const int32_t *ids, int32_t n, int32_t passes,
     dkv::ReadParams p{};
     p.hbm = e->hbm;
     p.part = e->read_part;
-    p.result = reinterpret_cast<dkv::u32x4 *>(e->read_sums + 2);
+    p.result = reinterpret_cast<dkv::u64x2 *>(e->read_sums);
     p.passes = (uint32_t)passes;
     hbm_strides(e, p.hbm_plane_stride, p.hbm_block_stride);
     p.n = (uint32_t)n;
@@ -1937,7 +1933,7 @@ int kv_reader_start(kv_engine *e, const int32_t *ids, int32_t n, int32_t passes,
         HIPTRY(e, hipGetLastError());
     }
     if (events) HIPTRY(e, hipEventRecord(e->read_ev[0], e->s_read));
-    else p.begin = e->read_sums;
+    else p.begin = e->read_sums + 2 * (size_t)wgs;
     for (int32_t k = 0; k < passes; k++) {
         if (p.tiles > 0) {
             p.pass = (uint32_t)k;
@@ -1969,14 +1965,15 @@ int kv_reader_wait(kv_engine *e, uint64_t *checksum, double *ms_per_pass)
     if (e->sticky != KV_OK) return e->sticky;
     if (e->read_passes == 0) return KV_EINVAL;
     HIPTRY(e, hipStreamSynchronize(e->s_read));
-    uint64_t sum = 0, end = 0;
+    uint64_t sum = 0, begin = ~0ull, end = 0;
     for (int w = 0; w < e->read_wgs; w++) {
-        sum += e->read_sums[2 + 2 * w];
-        end = std::max<uint64_t>(end, e->read_sums[3 + 2 * w]);
+        sum += e->read_sums[2 * w];
+        end = std::max<uint64_t>(end, e->read_sums[2 * w + 1]);
+        if (e->read_passes == 1 && w < (int)dkv::kReadBegins) begin = std::min<uint64_t>(begin, e->read_sums[2 * e->read_wgs + w]);
     }
     *checksum = sum;
     if (ms_per_pass && e->read_passes == 1) {
-        ms_per_pass[0] = e->read_wgs ? (double)(end - e->read_sums[0]) * e->stamp_ms : 0.0;
+        ms_per_pass[0] = e->read_wgs ? (double)(end - begin) * e->stamp_ms : 0.0;
     } else if (ms_per_pass) {
         for (int32_t k = 0; k < e->read_passes; k++) {
             float ms = 0;

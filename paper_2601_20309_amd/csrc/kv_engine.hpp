@@ -115,12 +115,14 @@ struct kv_engine {
     hipEvent_t ev_join = nullptr, ev_join_in = nullptr;  // stream_out waits for stream_in / the reverse
     hipEvent_t b_o0 = nullptr, b_o1 = nullptr, b_i0 = nullptr, b_i1 = nullptr;  // this batch's first start / last end
     // The kernel paths on the engine's own streams: times left by the launches themselves
-    // (pinned host memory, MoveParams::begin and end), [0..1] begin of the batch's out and in
-    // work, then kStamps ends of launches that carry only out, only in, and both.
-    unsigned long long *stamps = nullptr;
+    // (pinned host memory, MoveParams::stamps): five arrays of kStamps, for a batch's first
+    // launch that carries out work, its first that carries in work (which may be the same
+    // one), and later ones that carry only out, only in, and both.
+    unsigned long long (*stamps)[2] = nullptr;
     double stamp_ms = 0;                // milliseconds per tick
-    int begun[2] = {-1, -1};            // where this batch's out / in work left its begin, -1: not yet
-    uint32_t stamp_waves[3] = {};       // ends to look at, per kind of launch; 0: no such launch in this batch
+    int begun[2] = {-1, -1};            // the array of the launch that began this batch's out / in work, -1: not yet
+    uint32_t stamp_waves[5] = {};       // stamps to look at in each array; 0: none in this batch
+    uint32_t stamp_sides[5] = {};       // what those launches carry: 1 out work, 2 in work
     bool batch_open = false;
     bool out_pending = false, in_pending = false;  // work enqueued since the last kv_wait
     bool in_dirty = false;                         // stream_in holds work stream_out has not joined
@@ -157,7 +159,7 @@ struct kv_engine {
     int32_t *read_ids_host = nullptr;          // pinned
     unsigned long long *read_part = nullptr;   // device: one sum per workgroup, then two sets of tile counters
     size_t read_turn = 0;                      // the set that the next pass draws from
-    unsigned long long *read_sums = nullptr;   // pinned: begin of a single pass, a gap, then per workgroup its sum over all passes and its end
+    unsigned long long *read_sums = nullptr;   // pinned: per workgroup its sum over all passes and its end, then the begins
     int read_wgs = 0;                          // workgroups of the reader under way
     std::vector<hipEvent_t> read_ev;           // passes + 1 timestamps
     int32_t read_passes = 0;

@@ -20,6 +20,7 @@ namespace dkv {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
 
 // Id lists of a call that names few blocks, handed over as a kernel argument: the
 // runtime keeps arguments where the device reads them like its own memory.  From
@@ -55,7 +56,10 @@ constexpr int kThreads = 256;      // lanes per workgroup of the HBM-bound launc
 // Vectors per lane where a tile may span segments: every vector has pointers of its
 // own there, and with eight they would not fit the registers of a 1024-lane workgroup.
 constexpr int kMaxRaggedU = 4;
-constexpr uint32_t kStamps = 512;  // at least the waves of every launch shape that the engine picks
+// Places for the time stamps of a launch, one per wave: at least as many as any launch shape
+// that the engine picks has waves.  (Of more, w and w + kStamps share one; the wave that
+// ends later stores later.)
+constexpr uint32_t kStamps = 512;
 constexpr int kMaxThreads = 1024;  // workgroups only pack waves; any multiple of 64 up to this
 
 // Division by a number that is the same for a whole launch, x < 2^31: a multiply
@@ -123,9 +127,12 @@ struct MoveParams {
     // next unclaimed tile, [1] the waves that are done
     unsigned int *claim;
     unsigned int *clear;  // nullptr, or a pair that a later launch draws from: put to zero
-    // Pinned host memory, or nullptr: where the launch leaves the device's clock as it begins,
-    // and each wave w, in end[w % kStamps], when its last store has arrived.
-    unsigned long long *begin, *end;
+    // Pinned host memory, or nullptr: where each wave w leaves the device's clock, in
+    // stamps[w % kStamps], as it was when the wave began, and when it ended, with `drain` when
+    // its last store has arrived.  The launch begins with its first wave, whichever that is:
+    // beside a launch on another stream, wave 0 was up to 19 us later.
+    u64x2 *stamps;
+    uint32_t drain;
     DirDesc out, in;
 };
 
@@ -146,14 +153,6 @@ __device__ __forceinline__ void locate(const MoveParams &p, const DirDesc &d,
     const uint32_t slot = d.iota ? i : (uint32_t)slots[i];
     hbm_off = (uint64_t)pl * p.hbm_plane_stride + (uint64_t)id * p.hbm_block_stride;
     far_off = (uint64_t)slot * slot_stride + (uint64_t)pl * plane_stride;
-}
-
-// The device's clock, to host memory.  Time stamps that a launch leaves by itself cost it
-// nothing before it begins; an event recorded ahead of it is a packet of its own, 2 us
-// that the launch waits for.
-__device__ __forceinline__ void stamp(unsigned long long *to)
-{
-    __scoped_atomic_store_n(to, (unsigned long long)wall_clock64(), __ATOMIC_RELAXED, __MEMORY_SCOPE_SYSTEM);
 }
 
 // What one wave does in one step: an in tile, an out tile, or one of each.
@@ -486,11 +485,11 @@ __device__ __forceinline__ void move(const MoveParams &p, const int32_t *__restr
                                      const int32_t *__restrict__ out_slots, const int32_t *__restrict__ in_ids,
                                      const int32_t *__restrict__ in_slots)
 {
+    const unsigned long long began = LINK ? wall_clock64() : 0;  // stored at the end: here the loads would wait for it
     const uint32_t lane = threadIdx.x & (kWave - 1u), waves_per_wg = blockDim.x / kWave;
     const uint32_t wave = blockIdx.x * waves_per_wg + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const uint32_t n_waves = gridDim.x * waves_per_wg;
     if (LINK && p.clear && blockIdx.x == 0 && threadIdx.x < 2) p.clear[threadIdx.x] = 0u;
-    if (LINK && p.begin && blockIdx.x == 0 && threadIdx.x == 0) stamp(p.begin);
     const uint32_t n_steps = p.mix_q ? p.in.tiles : (p.out.tiles > p.in.tiles ? p.out.tiles : p.in.tiles);
     constexpr int UR = U < kMaxRaggedU ? U : kMaxRaggedU;  // what cut_tiles() cut by when tiles are not whole
     if (!LINK || n_steps <= (uint64_t)kFixedRounds * n_waves) {
@@ -503,9 +502,12 @@ __device__ __forceinline__ void move(const MoveParams &p, const int32_t *__restr
     } else {
         run_drawn<V, UR, LINK, false>(p, out_ids, out_slots, in_ids, in_slots, n_steps, wave, n_waves, lane);
     }
-    if (LINK && p.end) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        if (lane == 0) stamp(p.end + wave % kStamps);
+    // Time stamps that a launch leaves by itself cost it nothing before it begins; an event
+    // recorded ahead of it is a packet of its own, 2 us that the launch waits for.
+    if (LINK && p.stamps) {
+        if (p.drain) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        const unsigned long long now = wall_clock64();
+        if (lane == 0) store_host<u32x4, true>(__builtin_bit_cast(u32x4, u64x2{began, now}), reinterpret_cast<u32x4 *>(p.stamps + wave % kStamps));
     }
 }
 
@@ -599,8 +601,8 @@ struct ReadParams {
     const uint8_t *hbm;
     unsigned long long *part;    // one sum per workgroup, in device memory, from pass to pass
     // Pinned host memory: where the last pass leaves them, each with the device's clock when
-    // its workgroup was done, and (nullptr: nowhere) the clock as a pass begins.
-    u32x4 *result;
+    // its workgroup was done, and (nullptr: nowhere) when each of the first kReadBegins began.
+    u64x2 *result;
     unsigned long long *begin;
     uint64_t hbm_block_stride;
     uint64_t hbm_plane_stride;
@@ -622,6 +624,7 @@ constexpr int kReadU = 8;      // rows per wave and tile
 constexpr int kReadDepth = 1;  // rows in flight per wave
 constexpr uint32_t kReadRows = (uint32_t)kReadU * (kThreads / kWave);  // rows per tile
 constexpr uint32_t kReadVecs = kReadRows * kWave;                      // vectors per tile
+constexpr uint32_t kReadBegins = 64;  // workgroups that leave when they began: the first eight on each XCD
 // Counters, and the workgroups that share one: one of every 64 that follow one another,
 // each time one place further, so that a group lies on all XCDs and all over each, and
 // a copy beside the pass slows every group alike.  37.5 GiB alone / beside a swap-out and
@@ -736,9 +739,9 @@ __device__ __forceinline__ unsigned long long read_tile(const ReadParams &p, con
 template <bool ROWS, typename Ids>
 __device__ __forceinline__ void read_pass(const ReadParams &p, const Ids &ids)
 {
+    const unsigned long long began = wall_clock64();
     const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1u);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-    if (p.begin && blockIdx.x == 0 && tid == 0) stamp(p.begin);
     __shared__ uint32_t claimed[2];
     __shared__ unsigned long long sums[kThreads / kWave];
     // first the fixed share, a tile every gridDim.x ...
@@ -788,8 +791,9 @@ __device__ __forceinline__ void read_pass(const ReadParams &p, const Ids &ids)
         for (int w = 1; w < kThreads / kWave; w++) sum += sums[w];
         if (p.pass > 0) sum += p.part[blockIdx.x];
         const unsigned long long now = wall_clock64();
+        if (p.begin && blockIdx.x < kReadBegins) __builtin_nontemporal_store(began, p.begin + blockIdx.x);
         if (p.pass + 1u < p.passes) p.part[blockIdx.x] = sum;
-        else store_host<u32x4, true>(u32x4{(uint32_t)sum, (uint32_t)(sum >> 32), (uint32_t)now, (uint32_t)(now >> 32)}, p.result + blockIdx.x);
+        else store_host<u32x4, true>(__builtin_bit_cast(u32x4, u64x2{sum, now}), reinterpret_cast<u32x4 *>(p.result + blockIdx.x));
     }
 }
 

@@ -803,3 +803,18 @@ def test_times_include_the_last_bytes_stored(dim, host_layout):
             took.append(st["ms_out"])
         assert np.median(took) >= st["bytes_out"] / 64e6, took      # the middle one: events of the runtime are off now and then
     case.close()
+
+
+def test_times_begin_with_the_first_wave():
+    """2 MiB each way by two launches at once, many times: a launch's time begins with the
+    first of its waves, which is not always wave 0, so that no time is shorter than the
+    link's published rate allows."""
+    sh = W.KVShape(16, 8, 128, 16, n_hbm_blocks=8, n_host_slots=8)             # 1 MiB blocks
+    rot = W.simple_rotation(sh, 2, 2, seed=1)
+    case, _ = make_case(sh, B.KV_HOST_BLOCK_FIRST, B.KV_PATH_ZEROCOPY, rot=rot)
+    for _ in range(400):
+        assert case.eng.kv_rotate(rot.out_ids, rot.out_slots, rot.in_ids, rot.in_slots) == 0
+        assert case.eng.kv_wait() == 0
+        st = case.eng.kv_last_stats()
+        assert min(st["ms_out"], st["ms_in"]) >= st["bytes_out"] / 64e6 and max(st["ms_out"], st["ms_in"]) <= st["ms_e2e"], st
+    case.close()
