@@ -249,11 +249,21 @@ bool writes_through(const kv_engine *e)
     return e->vec == 16 || (e->vec == 8 && (e->cfg.host_layout == KV_HOST_BLOCK_FIRST || e->seg >= 512));
 }
 
-// Whether transfers are timed by the launches themselves.  Stores that the L2 still holds as
-// a launch's waves end are in no time that these leave: there events time the transfers.
+bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &c) == hipSuccess) return c != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
+// Whether a call's launches are to leave their times.  Events are for what they cannot tell:
+// stores that the L2 still holds as a launch's waves end, and launches that are recorded
+// into a graph.  (On the caller's streams, too, events are no better: beside work on the
+// other one, 2 MiB in took 21 us by them, which no link does.)
 bool stamps_times(const kv_engine *e)
 {
-    return e->own_streams && writes_through(e);
+    return writes_through(e) && (e->own_streams || !(capturing(e->s_out) || capturing(e->s_in)));
 }
 
 // Fills the fields common to every launch.
@@ -604,7 +614,7 @@ int launch_link(kv_engine *e, const LinkShape &sh, hipStream_t s, const MovePara
         q.mix_q = whole.mix_q && q.out.tiles ? (((uint64_t)q.out.tiles << 32) + q.in.tiles - 1) / q.in.tiles : 0;
         // of several launches the first begins first and the last ends last
         const bool last = p0 + per_chunk >= whole.n_planes;
-        if (stamps_times(e) && (p0 == 0 || last)) stamp_launch(e, q.out.n > 0, q.in.n > 0, last, sh, q);
+        if (e->stamping && (p0 == 0 || last)) stamp_launch(e, q.out.n > 0, q.in.n > 0, last, sh, q);
         launch_move(sh, e->vec, s, q, ids, true, ev && e->own_streams ? (*ev)[c] : nullptr);
         HIPTRY(e, hipGetLastError());
         e->acc.n_launches += 1;
@@ -616,6 +626,7 @@ int launch_link(kv_engine *e, const LinkShape &sh, hipStream_t s, const MovePara
 int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
 {
     int32_t *dh = e->desc_host + (size_t)k * e->desc_cap;
+    e->stamping = stamps_times(e);
     const bool fused = path == KV_PATH_FUSED && no > 0 && ni > 0;
     auto params = [&](int u, unsigned int *claim) {
         MoveParams q = base_params(e);
@@ -684,7 +695,7 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
             e->in_dirty = false;
         }
         if (upload_ids(true, true, e->s_out) != KV_OK) return KV_EHIP;
-        if (stamps_times(e)) {
+        if (e->stamping) {
             // launch_link's launches leave their times
         } else if (!e->b_o0 && !e->b_i0) {  // one start timestamp serves both directions
             if (mark_start(e, true, e->s_out) != KV_OK) return KV_EHIP;
@@ -703,7 +714,7 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
         e->layer_on_out = layered;
         e->layer_on_in = false;
         if (n_rest > 0) {
-            if (stamps_times(e)) stamp_launch(e, true, false, true, sh_rest, p_rest);
+            if (e->stamping) stamp_launch(e, true, false, true, sh_rest, p_rest);
             launch_move(sh_rest, e->vec, e->s_out, p_rest,
                         MoveIds{d_o + no_paired, d_o + no + no_paired, nullptr, nullptr, on_host}, true);
             HIPTRY(e, hipGetLastError());
@@ -763,14 +774,14 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
     e->layer_on_in = layered && ni > 0;
     if (no > 0) {
         if (upload_ids(true, false, e->s_out) != KV_OK) return KV_EHIP;
-        if (!stamps_times(e) && mark_start(e, true, e->s_out) != KV_OK) return KV_EHIP;
+        if (!e->stamping && mark_start(e, true, e->s_out) != KV_OK) return KV_EHIP;
         if (launch_link(e, sh_out, e->s_out, p_out, ids_out, layered ? &e->layer_ev_out : nullptr) != KV_OK)
             return KV_EHIP;
         if (mark_end(e, true, k, e->s_out) != KV_OK) return KV_EHIP;
     }
     if (ni > 0) {
         if (upload_ids(false, true, e->s_in) != KV_OK) return KV_EHIP;
-        if (!stamps_times(e) && mark_start(e, false, e->s_in) != KV_OK) return KV_EHIP;
+        if (!e->stamping && mark_start(e, false, e->s_in) != KV_OK) return KV_EHIP;
         if (launch_link(e, sh_in, e->s_in, p_in, ids_in, layered ? &e->layer_ev_in : nullptr) != KV_OK)
             return KV_EHIP;
         if (mark_end(e, false, k, e->s_in) != KV_OK) return KV_EHIP;
@@ -1717,9 +1728,7 @@ int kv_rotate_static(const kv_config *cfg, void *hbm_cache, void *host_pool, voi
     // with the launch that puts them into the array, 28.6 without; 4 + 3 of 2 MiB: 203.6 and 199.6.)
     if (ids_inline(e, no, ni)) {
         if (draws(sh, p)) {
-            hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-            if (hipStreamIsCapturing(s, &capture) != hipSuccess) (void)hipGetLastError();
-            if (capture != hipStreamCaptureStatusNone) {
+            if (capturing(s)) {
                 hipLaunchKernelGGL(kv_ids_kernel, dim3(1), dim3(256), 0, s, chunk, ids, 0u, p.claim);
                 HIPTRY((kv_engine *)nullptr, hipGetLastError());
             } else {

@@ -114,12 +114,13 @@ struct kv_engine {
     hipEvent_t ev_o0 = nullptr, ev_o1 = nullptr, ev_i0 = nullptr, ev_i1 = nullptr;
     hipEvent_t ev_join = nullptr, ev_join_in = nullptr;  // stream_out waits for stream_in / the reverse
     hipEvent_t b_o0 = nullptr, b_o1 = nullptr, b_i0 = nullptr, b_i1 = nullptr;  // this batch's first start / last end
-    // The kernel paths on the engine's own streams: times left by the launches themselves
+    // The kernel paths: times left by the launches themselves
     // (pinned host memory, MoveParams::stamps): five arrays of kStamps, for a batch's first
     // launch that carries out work, its first that carries in work (which may be the same
     // one), and later ones that carry only out, only in, and both.
     unsigned long long (*stamps)[2] = nullptr;
     double stamp_ms = 0;                // milliseconds per tick
+    bool stamping = false;              // this call's launches leave their times, else events do
     int begun[2] = {-1, -1};            // the array of the launch that began this batch's out / in work, -1: not yet
     uint32_t stamp_waves[5] = {};       // stamps to look at in each array; 0: none in this batch
     uint32_t stamp_sides[5] = {};       // what those launches carry: 1 out work, 2 in work
