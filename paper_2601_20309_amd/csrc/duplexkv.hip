@@ -305,10 +305,17 @@ uint32_t line_mask(int vec, bool lines)
 }
 
 // Cuts the planes [plane0, plane0 + n_planes) of every entry into tiles of `u` vectors per
-// lane; lines: groups begin on 128-byte lines of the far side.
-void cut_tiles(MoveParams &p, int vec, int u, bool lines)
+// lane; lines: groups begin on 128-byte lines of the far side; out: the launch writes there.
+// Segments that are whole tiles but begin inside lines are then cut like others: taken as
+// they lie, every access would begin and end in a part of a line, and each part, written
+// through, is a write of its own on the link.  (Pool 16 bytes behind a line, us for 64 MiB
+// both ways / out, with whole tiles and so: segments of 32 KiB in a block-first pool 1667 /
+// 1216 and 1340 / 1190, in a layer-first one of 8 KiB 1651 / 1223 and 1358 / 1194, of 2 KiB
+// 1933 / 1223 and 1423 / 1212, of 1 KiB 1506 / 1234 and 1509 / 1234.  Non-temporal, taken as
+// they lie: 1430 / 1241, 1431 / 1239, 1454 / 1265, 1540 / 1292.)
+void cut_tiles(MoveParams &p, int vec, int u, bool lines, bool out)
 {
-    const bool whole = p.vec_per_seg % ((uint32_t)dkv::kWave * (uint32_t)u) == 0;
+    const bool whole = p.vec_per_seg % ((uint32_t)dkv::kWave * (uint32_t)u) == 0 && !(out && line_mask(vec, lines));
     const uint32_t tile = (uint32_t)dkv::kWave * (uint32_t)(whole ? u : std::min(u, dkv::kMaxRaggedU));
     p.group_vecs = (uint32_t)group_vecs(p.vec_per_seg, p.n_planes, p.plane_major != 0, whole);
     p.groups_per_entry = p.group_vecs == p.vec_per_seg ? p.n_planes : 1u;
@@ -488,7 +495,7 @@ int mark_end(kv_engine *e, bool out_side, int k, hipStream_t s)
 // U 2 101.0 / 99.9; 16 of 448 lanes 94.1 / 87.2 and 99.9 / 97.2.)  wg_lanes set alone keeps
 // the number of waves.
 //
-// Segments that no tile divides are moved in tiles that span segments where the
+// Segments that no tile divides, or that begin inside lines, are moved in tiles that span segments where the
 // pool holds a block in one piece; otherwise tiles end with their segment.  The vectors
 // per lane are those above unless they leave more than an eighth of the tiles empty, then
 // the most that leave the least empty (segments of 105 vectors fill one tile of 128 as they
@@ -522,17 +529,21 @@ LinkShape link_shape(const kv_engine *e, LinkKind kind)
     const int64_t cap = (int64_t)cw * (cl ? cl : dkv::kThreads) / dkv::kWave;  // configured waves
     const bool packed = cl ? cl > dkv::kWave : cw > 0;
     int u = cu ? cu : kind == kBoth ? (packed && cap >= 128 ? 1 : cap >= 56 || !cw ? 2 : cap >= 28 ? 4 : 8) : kind == kOutOnly && cw ? 8 : 4;
-    auto whole = [&](int w) { return vec_per_seg % ((uint64_t)dkv::kWave * (uint64_t)w) == 0; };
+    auto divides = [&](int w) { return vec_per_seg % ((uint64_t)dkv::kWave * (uint64_t)w) == 0; };
+    const bool inside = kind != kInOnly && line_mask(e->vec, lines);  // begin inside lines: see cut_tiles()
+    auto whole = [&](int w) { return divides(w) && !inside; };
     auto filled = [&](int w) {
         const uint64_t tile = (uint64_t)dkv::kWave * (uint64_t)w, g = group_vecs(vec_per_seg, planes, plane_major, false);
         return (double)g / (double)((g + line_mask(e->vec, lines) + tile - 1) / tile * tile);
     };
     int limit_u = u;
+    if (!cu) {
+        limit_u = divides(1) ? u : 1;
+        while (!divides(limit_u) && limit_u > 1) limit_u >>= 1;
+    }
     if (!cu && whole(1)) {  // whole tiles only: the segment must be a multiple of the tile
-        while (!whole(u)) u >>= 1;
-        limit_u = u;
+        u = limit_u;
     } else if (!cu) {
-        limit_u = 1;
         u = std::min(dkv::kMaxRaggedU, u * 16 / e->vec);
         int best = u;  // an eighth empty at most, else the fullest
         for (int w = u / 2; w >= 1 && filled(best) < 0.875; w /= 2)
@@ -608,7 +619,7 @@ int launch_link(kv_engine *e, const LinkShape &sh, hipStream_t s, const MovePara
         MoveParams q = whole;
         q.plane0 = p0;
         q.n_planes = std::min(per_chunk, whole.n_planes - p0);
-        cut_tiles(q, e->vec, sh.u, on_lines(e, q.n_planes) && (p0 * e->seg & 127u) == 0);
+        cut_tiles(q, e->vec, sh.u, on_lines(e, q.n_planes) && (p0 * e->seg & 127u) == 0, whole.out.n > 0);
         // fits: the whole call's counts were checked
         if (!fill_dir(q, q.out.n, 0, sh.limit_u, q.out) || !fill_dir(q, q.in.n, 0, sh.limit_u, q.in)) return KV_EUNSUP;
         q.mix_q = whole.mix_q && q.out.tiles ? (((uint64_t)q.out.tiles << 32) + q.in.tiles - 1) / q.in.tiles : 0;
@@ -628,7 +639,7 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
     int32_t *dh = e->desc_host + (size_t)k * e->desc_cap;
     e->stamping = stamps_times(e);
     const bool fused = path == KV_PATH_FUSED && no > 0 && ni > 0;
-    auto params = [&](int u, unsigned int *claim) {
+    auto params = [&](int u, unsigned int *claim, bool out) {
         MoveParams q = base_params(e);
         q.claim = claim;
         q.far_out = e->pool;
@@ -637,7 +648,7 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
         q.far_slot_stride_in = q.far_slot_stride_out;
         q.far_plane_stride_in = q.far_plane_stride_out;
         q.plane_major = e->cfg.host_layout == KV_HOST_LAYER_FIRST ? 1u : 0u;
-        cut_tiles(q, e->vec, u, on_lines(e, e->n_planes));
+        cut_tiles(q, e->vec, u, on_lines(e, e->n_planes), out);
         return q;
     };
     // The link-bound kernels fetch ids and slots with scalar loads.  Where one list
@@ -681,7 +692,7 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
             !layered && no > ni && (uint64_t)(no - ni) * e->block_bytes >= kSplitBytes ? no - ni : 0;
         const int32_t no_paired = no - n_rest;
         const LinkShape sh_rest = link_shape(e, kOutOnly);
-        MoveParams p = params(sh.u, e->claim), p_rest = params(sh_rest.u, e->claim);
+        MoveParams p = params(sh.u, e->claim, true), p_rest = params(sh_rest.u, e->claim, true);
         p_rest.in = none;
         if (!fill_dir(p, (uint32_t)no_paired, 0, sh.limit_u, p.out) || !fill_dir(p, (uint32_t)ni, 0, sh.limit_u, p.in) ||
             !fill_dir(p_rest, (uint32_t)n_rest, 0, sh_rest.limit_u, p_rest.out))
@@ -744,7 +755,7 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
     }
     const MoveIds ids_out{d_o, d_o + no, nullptr, nullptr, on_host}, ids_in{nullptr, nullptr, d_i, d_i + ni, on_host};
     // launches on stream_out draw from the first pair of counters, those on stream_in from the second
-    MoveParams p_out = params(sh_out.u, e->claim), p_in = params(sh_in.u, e->claim + kClaimStride);
+    MoveParams p_out = params(sh_out.u, e->claim, true), p_in = params(sh_in.u, e->claim + kClaimStride, false);
     p_out.in = p_in.out = none;
     if (!fill_dir(p_out, (uint32_t)no, 0, sh_out.limit_u, p_out.out) ||
         !fill_dir(p_in, (uint32_t)ni, 0, sh_in.limit_u, p_in.in))
@@ -999,7 +1010,7 @@ MoveParams stage_params(const kv_engine *e, uint8_t *stage, uint32_t nb, uint32_
     p.far_out = p.far_in = stage - (uint64_t)p0 * ps;
     p.far_slot_stride_out = p.far_slot_stride_in = ss;
     p.far_plane_stride_out = p.far_plane_stride_in = ps;
-    cut_tiles(p, e->vec, u, true);  // staging is taken as it lies
+    cut_tiles(p, e->vec, u, true, true);  // staging is taken as it lies
     return p;
 }
 
@@ -1711,7 +1722,7 @@ int kv_rotate_static(const kv_config *cfg, void *hbm_cache, void *host_pool, voi
     p.far_slot_stride_in = p.far_slot_stride_out;
     p.far_plane_stride_in = p.far_plane_stride_out;
     p.plane_major = cfg->host_layout == KV_HOST_LAYER_FIRST ? 1u : 0u;
-    cut_tiles(p, e->vec, sh.u, on_lines(e, e->n_planes));
+    cut_tiles(p, e->vec, sh.u, on_lines(e, e->n_planes), no > 0);
     if (!fill_dir(p, (uint32_t)no, 0, sh.limit_u, p.out) || !fill_dir(p, (uint32_t)ni, 0, sh.limit_u, p.in))
         return KV_EUNSUP;
     if (p.out.tiles > 0 && p.in.tiles > p.out.tiles)

@@ -118,7 +118,7 @@ struct MoveParams {
     Div by_seg;                 // by vec_per_seg (quotient 0 where a group is one segment)
     uint32_t plane_major;       // group order: 1 = [plane][i], 0 = [i][plane]
     uint32_t through;           // 8-byte vectors: 1 = written through to the host (store_host)
-    uint32_t full_tiles;        // 1: group_vecs is a multiple of the tile and a group one segment
+    uint32_t full_tiles;        // 1: a group is one segment, taken in whole tiles
     uint64_t plane_skip;        // cache bytes between the end of a segment and the same block's next one
     // 0, or ceil(out.tiles * 2^32 / in.tiles) when the in list is the longer one and
     // the out tiles are to be spread evenly over it (see make_job)

@@ -817,3 +817,60 @@ def test_times_begin_with_the_first_wave(own_streams):
         st = case.eng.kv_last_stats()
         assert min(st["ms_out"], st["ms_in"]) >= st["bytes_out"] / 64e6 and max(st["ms_out"], st["ms_in"]) <= st["ms_e2e"], st
     case.close()
+
+
+def _offset_pool(sh, host_layout, offset, seed):
+    """(engine, cache on the GPU, pool and 128 bytes on either side, the pool's begin in it)"""
+    cfg = B.make_config(sh, host_layout)
+    n = B.kv_pool_bytes(cfg)
+    pinned = torch.empty(n + 512, dtype=torch.uint8, pin_memory=True)
+    assert pinned.data_ptr() % 128 == 0
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    cache = torch.randint(0, 256, (B.kv_cache_bytes(cfg),), dtype=torch.uint8, device="cuda", generator=g)
+    pinned.copy_(torch.randint(0, 256, (n + 512,), dtype=torch.uint8, device="cuda", generator=g))
+    torch.cuda.synchronize()
+    return B.Engine(cfg, cache.data_ptr(), pinned.data_ptr() + 128 + offset), cache, pinned.numpy(), 128 + offset
+
+
+@pytest.mark.parametrize("offset", [8, 16, 64])
+@pytest.mark.parametrize("host_layout", LAYOUTS)
+def test_whole_tiles_in_a_pool_that_begins_inside_a_line(host_layout, offset):
+    """Segments of whole tiles (16- and 8-byte vectors) in such a pool, from a call of a few
+    steps to one whose waves draw them: every byte of cache and pool against the oracle, and
+    the bytes around the pool."""
+    for seg, counts in ((1024, (1, 40, 500)), (2048, (3, 300)), (3072, (170,)), (8192, (2, 61)), (32768, (1, 17))):
+        n = counts[-1]
+        sh = W.KVShape(4, 1, seg // 2, 1, n_hbm_blocks=2 * n + 3, n_host_slots=2 * n + 2)
+        eng, dev, around, at = _offset_pool(sh, host_layout, offset, seg)
+        osh, want_cache, want = O.shape_of(sh, host_layout, 0), dev.cpu().numpy(), around.copy()
+        pool = want[at:at + B.kv_pool_bytes(eng.cfg)]
+        rot = W.simple_rotation(sh, n, n, seed=seg)
+        for k in counts:
+            oi, os_, ii, is_ = rot.out_ids[:k], rot.out_slots[:k], rot.in_ids[:k], rot.in_slots[:k]
+            assert eng.kv_rotate(oi, os_, ii, is_) == 0 and eng.kv_wait() == 0
+            assert O.rotate(osh, want_cache, pool, oi, os_, ii, is_) == 0
+            assert eng.kv_swap_out(ii, os_) == 0 and eng.kv_wait() == 0
+            assert O.swap_out(osh, want_cache, pool, ii, os_) == 0
+            assert eng.kv_swap_in(is_[::-1].copy(), oi) == 0 and eng.kv_wait() == 0
+            assert O.swap_in(osh, want_cache, pool, is_[::-1].copy(), oi) == 0
+            assert np.array_equal(dev.cpu().numpy(), want_cache), (seg, k)
+            assert np.array_equal(around, want), (seg, k)
+        eng.kv_destroy()
+
+
+@pytest.mark.parametrize("host_layout,seg", [(B.KV_HOST_BLOCK_FIRST, 32768), (B.KV_HOST_LAYER_FIRST, 8192)])
+def test_a_pool_that_begins_inside_a_line_costs_little(host_layout, seg):
+    """64 MiB each way into a pool 16 bytes behind a line take no more than 1.1 times what
+    they take into one on a line, in turn (1.24 times where accesses end in parts of lines)."""
+    n = (64 << 20) // (64 * seg)
+    sh = W.KVShape(32, 1, seg // 2, 1, n_hbm_blocks=2 * n + 2, n_host_slots=2 * n + 2)
+    rot = W.simple_rotation(sh, n, n, seed=3)
+    cases = [_offset_pool(sh, host_layout, offset, 1) for offset in (0, 16)]
+    took = [[], []]
+    for _ in range(9):
+        for k, (eng, *_) in enumerate(cases):
+            assert eng.kv_rotate(rot.out_ids, rot.out_slots, rot.in_ids, rot.in_slots) == 0 and eng.kv_wait() == 0
+            took[k].append(eng.kv_last_stats()["ms_out"])
+    assert np.median(took[1]) < 1.1 * np.median(took[0]), took
+    for eng, *_ in cases:
+        eng.kv_destroy()
