@@ -85,7 +85,9 @@ typedef struct {
     int32_t path;          /* KV_PATH_* */
     int32_t chunk_layers;  /* layers per chunk: DMA-staged path, 0 = engine picks; kernel paths, 0 = one launch, c > 0 =
                               c layers per launch with a completion mark each (kv_stream_wait_layer) */
-    int32_t max_copy_wgs;  /* workgroups (of wg_lanes lanes; of 256 if wg_lanes is 0) a copy kernel may occupy; 0 = engine picks */
+    int32_t max_copy_wgs;  /* workgroups (of wg_lanes lanes; of 256 if wg_lanes is 0) a copy kernel may occupy; 0 = engine picks.
+                              What limits a copy's rate, and what it takes from a kernel beside it, is the bytes its waves keep
+                              in flight: with vecs_per_lane at 0 a rotation's then have one vector per lane each */
     int32_t vecs_per_lane; /* 16-byte vectors each lane keeps in flight per direction in the link kernels: 0 = engine picks, else 1, 2, 4 or 8
                               (8 is taken as 4, with the more waves, where the segment is not a multiple of 64 * 8 vectors) */
     int32_t wg_lanes;      /* lanes per workgroup of the link kernels (workgroups only pack waves; a wave is the unit of work):

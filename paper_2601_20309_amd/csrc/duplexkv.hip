@@ -151,8 +151,9 @@ struct MoveIds {
 
 // A launch's shape: workgroups, lanes per workgroup, vectors per lane per tile;
 // short_steps: with no more steps than this, a wave per step; limit_u: the
-// vectors per lane by which dir_tiles() counts.
-struct LinkShape { int wgs, lanes, u, short_steps, limit_u; };
+// vectors per lane by which dir_tiles() counts; through: it has waves enough to write
+// through to the pool.
+struct LinkShape { int wgs, lanes, u, short_steps, limit_u; bool through; };
 
 template <typename... P, typename... A>
 void launch(void (*kernel)(P...), dim3 g, dim3 b, hipStream_t s, hipEvent_t stop, const A &...args)
@@ -257,16 +258,19 @@ bool capturing(hipStream_t s)
     return true;
 }
 
-// Whether a call's launches are to leave their times.  Events are for what they cannot tell:
-// stores that the L2 still holds as a launch's waves end, and launches that are recorded
-// into a graph.  (On the caller's streams, too, events are no better: beside work on the
-// other one, 2 MiB in took 21 us by them, which no link does.)
-bool stamps_times(const kv_engine *e)
+// Decides whether the launches of this call leave their times.  Events are for what they
+// cannot tell: stores that the L2 still holds as a launch's waves end, and launches that are
+// recorded into a graph.  (On the caller's streams, too, events are no better: beside work on
+// the other one, 2 MiB in took 21 us by them, which no link does.)  Returns whether stores
+// that can be written through have to be: where calls before it in the batch left their times.
+bool decide_stamps(kv_engine *e)
 {
-    return writes_through(e) && (e->own_streams || !(capturing(e->s_out) || capturing(e->s_in)));
+    if (e->batch_stamps < 0) e->batch_stamps = writes_through(e) && e->shapes_through ? 1 : 0;
+    e->stamping = e->batch_stamps && (e->own_streams || !(capturing(e->s_out) || capturing(e->s_in)));
+    return e->batch_stamps != 0;
 }
 
-// Fills the fields common to every launch.
+// Fills the fields common to every launch (`through` is left at 0).
 MoveParams base_params(const kv_engine *e)
 {
     MoveParams p{};
@@ -276,7 +280,6 @@ MoveParams base_params(const kv_engine *e)
     p.plane0 = 0;
     p.n_planes = e->n_planes;
     p.vec_per_seg = (uint32_t)(e->seg / (uint64_t)e->vec);
-    p.through = writes_through(e) ? 1u : 0u;
     return p;
 }
 
@@ -379,7 +382,7 @@ void open_batch(kv_engine *e)
     if (!e->batch_open) {
         e->batch_open = true;
         e->b_o0 = e->b_o1 = e->b_i0 = e->b_i1 = nullptr;
-        e->begun[0] = e->begun[1] = -1;
+        e->begun[0] = e->begun[1] = e->batch_stamps = -1;
         std::fill_n(e->stamp_waves, 5, 0u);
         e->t0 = now_ms();
         e->acc = kv_stats{};
@@ -487,13 +490,27 @@ int mark_end(kv_engine *e, bool out_side, int k, hipStream_t s)
 // The same waves packed four or sixteen to a workgroup do no better.
 // A configured vecs_per_lane is kept (the wave count follows it; 8 are cut to
 // kMaxRaggedU for segments that 8 do not divide); max_copy_wgs
-// counts workgroups of wg_lanes lanes and set alone keeps 256-lane workgroups; the vectors
-// per lane then follow the waves, both ways so that ~128 KiB are in flight, of one-wave
-// workgroups no more than the table has, and out eight.  (GB/s alone / beside the reader: at
-// most 64 one-wave workgroups, U 1 69, U 2 101.4 / 100.7; at most 144, U 1 101.5 / 101.4 and
-// 4.9 TB/s for the reader, 68 x U 2 101.6 / 101.1 and 5.5; 28 of 256 lanes U 1 99.4 / 91.1,
-// U 2 101.0 / 99.9; 16 of 448 lanes 94.1 / 87.2 and 99.9 / 97.2.)  wg_lanes set alone keeps
-// the number of waves.
+// counts workgroups of wg_lanes lanes and set alone keeps 256-lane workgroups; wg_lanes set
+// alone keeps the number of waves.  max_copy_wgs limits what a copy takes from a kernel
+// beside it, so a rotation's waves then have one vector per lane each, unless vecs_per_lane
+// says otherwise: fewer waves are fewer bytes in flight.  (At most 24 / 48 / 64 / 96 one-wave
+// workgroups: 34 / 67 / 86 / 100 GB/s alone, 26 / 50 / 64 / 90 beside the reader, which keeps
+// 6.6 / 6.2 / 6.05 / 5.7 of 7.0 TB/s; with vectors enough for 128 KiB in flight it kept 5.5
+// beside any of them.)  From kFewWaves one-wave workgroups on the default's waves take no
+// more than those would (at most 144: 101.5 / 100.7 GB/s and 5.46 TB/s by 68 x U 2, 101.1 /
+// 101.0 and 4.87 by 144 x U 1).  A swap-out has eight vectors per lane then.  Workgroups of
+// several waves share the ports of a CU, and do best with one vector per lane (alone, 14 x
+// 512 lanes 97 GB/s by U 1, 83 by U 2; 7 x 1024 lanes 77 and 50).
+//
+// A wave that writes through waits for the host's acknowledgement, so a shape that has
+// fewer bytes in flight than fill the link moves less that way, and its stores stay
+// non-temporal (`through`; GB/s alone, reader beside in TB/s, non-temporal and written
+// through): out 8 x U 8 56.9 (6.80) and 52.8 (6.82), 12 x U 8 56.7 (6.34) and 57.0 (6.71), 16 x
+// U 2 57.0 and 54.0, 64 x U 1 56.5 (5.56) and 57.0 (6.45), two workgroups of 14 waves 56.7
+// and 50.9; both ways 96 x U 1 100.4 and 98.6, 112 x U 1 100.9 and 100.8, 48 x U 2 99.7 and
+// 96.3, 64 x U 2 101.0 and 101.2, 32 x U 4 100.3 and 99.7, 40 x U 4 99.9 and 101.3, 20 x 256
+// lanes 86.1 and 78.5, 36 x 256 lanes 101.1 and 101.3; in-heavy 24 x U 4 83.2 and 81.6, 32 x
+// U 4 86.1 and 86.2.
 //
 // Segments that no tile divides, or that begin inside lines, are moved in tiles that span segments where the
 // pool holds a block in one piece; otherwise tiles end with their segment.  The vectors
@@ -518,6 +535,7 @@ enum LinkKind { kBoth, kInHeavy, kOutOnly, kInOnly };
 // 20.8.  16 + 16 blocks: 128 waves 30.6, the table's 68 28.0.  With a wave per tile up to
 // 512 KiB the reader beside lost 10-14 ms per GiB moved instead of 2-4.)
 constexpr int kShortKib = 128;
+constexpr int kFewWaves = 112;
 
 LinkShape link_shape(const kv_engine *e, LinkKind kind)
 {
@@ -528,7 +546,8 @@ LinkShape link_shape(const kv_engine *e, LinkKind kind)
     const bool lines = on_lines(e, planes);
     const int64_t cap = (int64_t)cw * (cl ? cl : dkv::kThreads) / dkv::kWave;  // configured waves
     const bool packed = cl ? cl > dkv::kWave : cw > 0;
-    int u = cu ? cu : kind == kBoth ? (packed && cap >= 128 ? 1 : cap >= 56 || !cw ? 2 : cap >= 28 ? 4 : 8) : kind == kOutOnly && cw ? 8 : 4;
+    const bool few = kind == kBoth && !cu && (packed || (cw && cap < kFewWaves));
+    int u = cu ? cu : kind == kBoth ? (few ? 1 : 2) : kind == kOutOnly && (cw || cl > 512) ? 8 : 4;
     auto divides = [&](int w) { return vec_per_seg % ((uint64_t)dkv::kWave * (uint64_t)w) == 0; };
     const bool inside = kind != kInOnly && line_mask(e->vec, lines);  // begin inside lines: see cut_tiles()
     auto whole = [&](int w) { return divides(w) && !inside; };
@@ -567,9 +586,15 @@ LinkShape link_shape(const kv_engine *e, LinkKind kind)
     s.u = u;
     s.limit_u = limit_u;
     s.lanes = cl ? cl : (cw ? dkv::kThreads : dkv::kWave);
-    s.wgs = cw && (packed || cu || kind != kBoth) ? cw : std::max(1, waves * dkv::kWave / s.lanes);
+    s.wgs = cw && (few || cu || kind != kBoth) ? cw : std::max(1, waves * dkv::kWave / s.lanes);
     if (cw) s.wgs = std::min(s.wgs, cw);
     s.short_steps = cw || cl || cu ? 0 : kShortKib / std::max(1, kib);
+    const int all = s.wgs * s.lanes / dkv::kWave, flight = all * std::max(1, kib);
+    s.through = true;
+    if (!cw && !cl && !cu) return s;
+    if (kind == kOutOnly) s.through = flight >= 64 && all >= 12 && s.wgs >= 4;
+    if (kind == kInHeavy) s.through = flight >= 112 && s.wgs >= 4;
+    if (kind == kBoth) s.through = flight >= (packed || kib >= 4 ? 144 : 120);
     return s;
 }
 
@@ -637,10 +662,11 @@ int launch_link(kv_engine *e, const LinkShape &sh, hipStream_t s, const MovePara
 int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
 {
     int32_t *dh = e->desc_host + (size_t)k * e->desc_cap;
-    e->stamping = stamps_times(e);
+    const bool wait_out = decide_stamps(e);
     const bool fused = path == KV_PATH_FUSED && no > 0 && ni > 0;
-    auto params = [&](int u, unsigned int *claim, bool out) {
+    auto params = [&](const LinkShape &sh, unsigned int *claim, bool out) {
         MoveParams q = base_params(e);
+        q.through = out && writes_through(e) && (wait_out || sh.through) ? 1u : 0u;
         q.claim = claim;
         q.far_out = e->pool;
         q.far_in = e->pool;
@@ -648,7 +674,7 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
         q.far_slot_stride_in = q.far_slot_stride_out;
         q.far_plane_stride_in = q.far_plane_stride_out;
         q.plane_major = e->cfg.host_layout == KV_HOST_LAYER_FIRST ? 1u : 0u;
-        cut_tiles(q, e->vec, u, on_lines(e, e->n_planes), out);
+        cut_tiles(q, e->vec, sh.u, on_lines(e, e->n_planes), out);
         return q;
     };
     // The link-bound kernels fetch ids and slots with scalar loads.  Where one list
@@ -692,7 +718,7 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
             !layered && no > ni && (uint64_t)(no - ni) * e->block_bytes >= kSplitBytes ? no - ni : 0;
         const int32_t no_paired = no - n_rest;
         const LinkShape sh_rest = link_shape(e, kOutOnly);
-        MoveParams p = params(sh.u, e->claim, true), p_rest = params(sh_rest.u, e->claim, true);
+        MoveParams p = params(sh, e->claim, true), p_rest = params(sh_rest, e->claim, true);
         p_rest.in = none;
         if (!fill_dir(p, (uint32_t)no_paired, 0, sh.limit_u, p.out) || !fill_dir(p, (uint32_t)ni, 0, sh.limit_u, p.in) ||
             !fill_dir(p_rest, (uint32_t)n_rest, 0, sh_rest.limit_u, p_rest.out))
@@ -755,7 +781,7 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
     }
     const MoveIds ids_out{d_o, d_o + no, nullptr, nullptr, on_host}, ids_in{nullptr, nullptr, d_i, d_i + ni, on_host};
     // launches on stream_out draw from the first pair of counters, those on stream_in from the second
-    MoveParams p_out = params(sh_out.u, e->claim, true), p_in = params(sh_in.u, e->claim + kClaimStride, false);
+    MoveParams p_out = params(sh_out, e->claim, true), p_in = params(sh_in, e->claim + kClaimStride, false);
     p_out.in = p_in.out = none;
     if (!fill_dir(p_out, (uint32_t)no, 0, sh_out.limit_u, p_out.out) ||
         !fill_dir(p_in, (uint32_t)ni, 0, sh_in.limit_u, p_in.in))
@@ -1048,7 +1074,7 @@ int run_staged(kv_engine *e, int k, const int32_t *oi, const int32_t *os, int32_
     int32_t *d_out = dd, *d_in = dd + 2 * (size_t)no;
     constexpr int U = 4;                         // capped launches: persistent waves, 4 KiB tiles
     const int cap_wgs = e->cfg.max_copy_wgs;     // 0: one wave per 1 KiB tile, kv_stage_kernel
-    const LinkShape capped{cap_wgs, dkv::kThreads, U, 0, U};
+    const LinkShape capped{cap_wgs, dkv::kThreads, U, 0, U, false};
     ChunkPlan po{}, pi{};
     if (no > 0) {
         int rc = plan_chunks(e, (uint32_t)no, po);
@@ -1468,6 +1494,7 @@ int kv_create(kv_engine **out, const kv_config *cfg, void *hbm_cache, void *host
         e->own_pool = true;
     }
     e->vec = pick_vec(e);
+    e->shapes_through = link_shape(e, kBoth).through && link_shape(e, kInHeavy).through && link_shape(e, kOutOnly).through;
 
     if (stream_out) {
         e->s_out = (hipStream_t)stream_out;
@@ -1717,6 +1744,7 @@ int kv_rotate_static(const kv_config *cfg, void *hbm_cache, void *host_pool, voi
     const LinkKind kind = no == 0 ? kInOnly : ni == 0 ? kOutOnly : ni >= 2 * (int64_t)no ? kInHeavy : kBoth;
     const LinkShape sh = link_shape(e, kind);
     MoveParams p = base_params(e);
+    p.through = writes_through(e) && sh.through ? 1u : 0u;
     p.far_out = p.far_in = e->pool;
     pool_strides(e, p.far_slot_stride_out, p.far_plane_stride_out);
     p.far_slot_stride_in = p.far_slot_stride_out;

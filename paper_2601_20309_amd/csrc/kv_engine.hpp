@@ -121,6 +121,8 @@ struct kv_engine {
     unsigned long long (*stamps)[2] = nullptr;
     double stamp_ms = 0;                // milliseconds per tick
     bool stamping = false;              // this call's launches leave their times, else events do
+    int batch_stamps = -1;              // whether this batch's calls do (-1: not decided yet): one clock for all of them
+    bool shapes_through = false;        // every launch shape of this engine writes through to the pool
     int begun[2] = {-1, -1};            // the array of the launch that began this batch's out / in work, -1: not yet
     uint32_t stamp_waves[5] = {};       // stamps to look at in each array; 0: none in this batch
     uint32_t stamp_sides[5] = {};       // what those launches carry: 1 out work, 2 in work

@@ -117,7 +117,7 @@ struct MoveParams {
     Div by_tiles;               // by tiles_per_group = ceil((group_vecs + line_mask) / (64 * U))
     Div by_seg;                 // by vec_per_seg (quotient 0 where a group is one segment)
     uint32_t plane_major;       // group order: 1 = [plane][i], 0 = [i][plane]
-    uint32_t through;           // 8-byte vectors: 1 = written through to the host (store_host)
+    uint32_t through;           // vectors of 8 bytes and more: 1 = written through to the host (store_host)
     uint32_t full_tiles;        // 1: a group is one segment, taken in whole tiles
     uint64_t plane_skip;        // cache bytes between the end of a segment and the same block's next one
     // 0, or ceil(out.tiles * 2^32 / in.tiles) when the in list is the longer one and
@@ -333,8 +333,8 @@ template <typename V, int U, bool LINK, bool FULL>
 __device__ __forceinline__ void job_stores(const Job<V, U, FULL> &j, const V (&vi)[U], const V (&vo)[U], uint32_t through)
 {
     if (j.do_out) {
-        if constexpr (LINK && sizeof(V) == 16) out_stores<V, U, true, FULL>(j, vo);
-        else if (LINK && sizeof(V) == 8 && through) out_stores<V, U, LINK && sizeof(V) == 8, FULL>(j, vo);
+        constexpr bool can = LINK && sizeof(V) >= 8;
+        if (can && through) out_stores<V, U, can, FULL>(j, vo);
         else out_stores<V, U, false, FULL>(j, vo);
     }
     if (j.do_in) {

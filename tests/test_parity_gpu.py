@@ -874,3 +874,33 @@ def test_a_pool_that_begins_inside_a_line_costs_little(host_layout, seg):
     assert np.median(took[1]) < 1.1 * np.median(took[0]), took
     for eng, *_ in cases:
         eng.kv_destroy()
+
+
+def test_configured_waves_keep_their_rates():
+    """What a configured launch shape moves, against the default's rate in turn.  A cap on the
+    workgroups is a cap on the rate (24 one-wave workgroups a third; the engine does not make
+    up for it with more vectors per lane), and few waves lose nothing by their stores'
+    acknowledgements: 64 x 1 vector 0.85 (0.71 written through), 4 waves out 0.75 (0.51), and
+    wg_lanes = 1024 alone 0.76 (0.50 with two vectors per lane)."""
+    sh = W.KVShape(16, 8, 128, 16, n_hbm_blocks=260, n_host_slots=260)         # 1 MiB blocks
+    rot = W.simple_rotation(sh, 128, 128, seed=9)
+    cases = [("rotate", {}, 0, 0), ("rotate", dict(max_copy_wgs=24, wg_lanes=64), 0, 0.45),
+             ("rotate", dict(max_copy_wgs=64, wg_lanes=64, vecs_per_lane=1), 0.78, 0.92),
+             ("rotate", dict(wg_lanes=1024), 0.63, 1), ("out", {}, 0, 0), ("out", dict(max_copy_wgs=4, wg_lanes=64), 0.65, 0.9)]
+    engines, took = [], [[] for _ in cases]
+    for kind, kw, *_ in cases:
+        engines.append(make_case(sh, B.KV_HOST_BLOCK_FIRST, B.KV_PATH_AUTO, rot=rot, **kw)[0])
+    for _ in range(7):
+        for k, (kind, *_) in enumerate(cases):
+            e = engines[k].eng
+            rc = e.kv_rotate(rot.out_ids, rot.out_slots, rot.in_ids, rot.in_slots) if kind == "rotate" else \
+                e.kv_swap_out(rot.out_ids, rot.out_slots)
+            assert rc == 0 and e.kv_wait() == 0
+            took[k].append(e.kv_last_stats()["ms_e2e"])
+    ms = [np.median(t) for t in took]
+    for k, (kind, kw, least, most) in enumerate(cases):
+        if kw:
+            rate = ms[0 if kind == "rotate" else 4] / ms[k]
+            assert least <= rate <= most, (kw, rate, ms)
+    for c in engines:
+        c.close()
