@@ -244,10 +244,19 @@ void hbm_strides(const kv_engine *e, uint64_t &plane_stride, uint64_t &block_str
     }
 }
 
-// Whether stores to the pool are written through (see store_host).
-bool writes_through(const kv_engine *e)
+// Whether stores to the pool can be written through (see store_host).
+bool writes_through(const kv_engine *e) { return e->vec >= 8; }
+
+// What a launch moves to or from the pool at one place of it.
+uint64_t piece_bytes(const kv_engine *e)
 {
-    return e->vec == 16 || (e->vec == 8 && (e->cfg.host_layout == KV_HOST_BLOCK_FIRST || e->seg >= 512));
+    if (e->cfg.host_layout == KV_HOST_LAYER_FIRST) return e->seg;
+    return e->cfg.chunk_layers > 0 ? std::min(e->block_bytes, 2 * (uint64_t)e->cfg.chunk_layers * e->seg) : e->block_bytes;
+}
+
+bool leaves_to_l2(const kv_engine *e, const int32_t *out_slots, int32_t no, int32_t ni)
+{
+    return dkv::leaves_to_l2(e->vec, piece_bytes(e), e->cfg.host_layout == KV_HOST_LAYER_FIRST, e->block_bytes, out_slots, no, ni);
 }
 
 bool capturing(hipStream_t s)
@@ -261,11 +270,12 @@ bool capturing(hipStream_t s)
 // Decides whether the launches of this call leave their times.  Events are for what they
 // cannot tell: stores that the L2 still holds as a launch's waves end, and launches that are
 // recorded into a graph.  (On the caller's streams, too, events are no better: beside work on
-// the other one, 2 MiB in took 21 us by them, which no link does.)  Returns whether stores
-// that can be written through have to be: where calls before it in the batch left their times.
-bool decide_stamps(kv_engine *e)
+// the other one, 2 MiB in took 21 us by them, which no link does.)  held: the call had better
+// leave its stores to the L2.  Returns whether they have to be written through nevertheless:
+// where calls before it in the batch left their times.
+bool decide_stamps(kv_engine *e, bool held)
 {
-    if (e->batch_stamps < 0) e->batch_stamps = writes_through(e) && e->shapes_through ? 1 : 0;
+    if (e->batch_stamps < 0) e->batch_stamps = writes_through(e) && e->shapes_through && !held ? 1 : 0;
     e->stamping = e->batch_stamps && (e->own_streams || !(capturing(e->s_out) || capturing(e->s_in)));
     return e->batch_stamps != 0;
 }
@@ -662,11 +672,11 @@ int launch_link(kv_engine *e, const LinkShape &sh, hipStream_t s, const MovePara
 int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
 {
     int32_t *dh = e->desc_host + (size_t)k * e->desc_cap;
-    const bool wait_out = decide_stamps(e);
+    const bool held = leaves_to_l2(e, dh + no, no, ni), timed = decide_stamps(e, held);
     const bool fused = path == KV_PATH_FUSED && no > 0 && ni > 0;
-    auto params = [&](const LinkShape &sh, unsigned int *claim, bool out) {
+    auto params = [&](const LinkShape &sh, unsigned int *claim, bool out, bool hold) {
         MoveParams q = base_params(e);
-        q.through = out && writes_through(e) && (wait_out || sh.through) ? 1u : 0u;
+        q.through = out && writes_through(e) && (timed || (sh.through && !hold)) ? 1u : 0u;
         q.claim = claim;
         q.far_out = e->pool;
         q.far_in = e->pool;
@@ -688,12 +698,9 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
     // is uploaded first, ~5 us on the launch's stream.
     // (Layer by layer a launch visits an entry for its layers only: 2048 blocks of 80 layers
     // each way, a launch per layer, 128 KiB a visit, 434 ms with the ring read in place.)
-    const uint64_t visit_bytes = e->cfg.host_layout == KV_HOST_LAYER_FIRST ? e->seg
-                                 : e->cfg.chunk_layers > 0 ? std::min(e->block_bytes, 2 * (uint64_t)e->cfg.chunk_layers * e->seg)
-                                                           : e->block_bytes;
     // A call of few blocks has no such choice to make: its lists are kernel arguments.
     const bool on_host = ids_inline(e, no, ni);
-    const bool upload = !on_host && visit_bytes < (256u << 10);
+    const bool upload = !on_host && piece_bytes(e) < (256u << 10);
     int32_t *dd = upload ? e->desc_dev + (size_t)k * e->desc_cap : dh;
     int32_t *d_o = dd, *d_i = dd + 2 * (size_t)no;  // each: [ids | slots]
     auto upload_ids = [&](bool out_part, bool in_part, hipStream_t s) -> int {
@@ -718,7 +725,7 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
             !layered && no > ni && (uint64_t)(no - ni) * e->block_bytes >= kSplitBytes ? no - ni : 0;
         const int32_t no_paired = no - n_rest;
         const LinkShape sh_rest = link_shape(e, kOutOnly);
-        MoveParams p = params(sh, e->claim, true), p_rest = params(sh_rest, e->claim, true);
+        MoveParams p = params(sh, e->claim, true, held), p_rest = params(sh_rest, e->claim, true, false);
         p_rest.in = none;
         if (!fill_dir(p, (uint32_t)no_paired, 0, sh.limit_u, p.out) || !fill_dir(p, (uint32_t)ni, 0, sh.limit_u, p.in) ||
             !fill_dir(p_rest, (uint32_t)n_rest, 0, sh_rest.limit_u, p_rest.out))
@@ -781,7 +788,7 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
     }
     const MoveIds ids_out{d_o, d_o + no, nullptr, nullptr, on_host}, ids_in{nullptr, nullptr, d_i, d_i + ni, on_host};
     // launches on stream_out draw from the first pair of counters, those on stream_in from the second
-    MoveParams p_out = params(sh_out, e->claim, true), p_in = params(sh_in, e->claim + kClaimStride, false);
+    MoveParams p_out = params(sh_out, e->claim, true, held), p_in = params(sh_in, e->claim + kClaimStride, false, false);
     p_out.in = p_in.out = none;
     if (!fill_dir(p_out, (uint32_t)no, 0, sh_out.limit_u, p_out.out) ||
         !fill_dir(p_in, (uint32_t)ni, 0, sh_in.limit_u, p_in.in))
@@ -1744,7 +1751,7 @@ int kv_rotate_static(const kv_config *cfg, void *hbm_cache, void *host_pool, voi
     const LinkKind kind = no == 0 ? kInOnly : ni == 0 ? kOutOnly : ni >= 2 * (int64_t)no ? kInHeavy : kBoth;
     const LinkShape sh = link_shape(e, kind);
     MoveParams p = base_params(e);
-    p.through = writes_through(e) && sh.through ? 1u : 0u;
+    p.through = writes_through(e) && sh.through && !leaves_to_l2(e, os, no, ni) ? 1u : 0u;
     p.far_out = p.far_in = e->pool;
     pool_strides(e, p.far_slot_stride_out, p.far_plane_stride_out);
     p.far_slot_stride_in = p.far_slot_stride_out;

@@ -69,6 +69,35 @@ constexpr int kReadPasses = 256;  // most passes of one kv_reader_start
 // stream run one after the other), each pair in a 256-byte stretch of its own.
 constexpr int kClaimStride = 64;
 
+// Whether a call's stores to the pool are left to the L2 (non-temporal), which joins what
+// several accesses store into one line, although the launch could write them through:
+// rotations of much in pieces (what is contiguous in the pool, bytes) of a line and less, or
+// in the segments of a layer-first pool below 1 KiB whose slots do not follow one another (of
+// 8-byte vectors below 512 bytes, in any slots).  Written through, each part of a line is a
+// write of its own on the link, and there it takes room from the reads of the other
+// direction.  A call of less than 8 MiB gains more by not waiting for the L2 at its end, and
+// one that moves much more one way than the other has room on the link.
+//   us, non-temporal / written through, in runs of consecutive slots after the comma:
+//   layer-first, 24 MiB each way: 64-byte segments 1509 / 1680, 1289 / 1378; 128 812 / 893,
+//   771 / 850; 208 887 / 917, 778 / 692; 400 763 / 803, 657 / 610; 640 617 / 643, 576 / 566;
+//   8-byte vectors: 200 1022 / 1069, 801 / 821; 520 716 / 770
+//   16 MiB: 520 464 / 495, 442 / 405; 1040 411 / 413, 397 / 376; 1280 370 / 362; 2048 367 / 358
+//   2 MiB: 80 173 / 162; 128 135 / 109; 208 124 / 103; 640 91 / 66; 200 122 / 102
+//   24 out with 12 in: 64 1375 / 1458; 128 748 / 773; 208 744 / 744; 520 616 / 603
+//   6 out with 24 in: 128 757 / 750.  24 out alone: 128 651 / 631; 208 579 / 548; 200 603 / 554
+//   block-first, 16 MiB each way: blocks of 128 bytes 1366 / 1439, of 160 1203 / 1196
+inline bool leaves_to_l2(int vec, uint64_t piece, bool layer_first, uint64_t block_bytes, const int32_t *out_slots,
+                         int64_t n_out, int64_t n_in)
+{
+    const bool line = piece <= 128;
+    if ((line ? 8 : 2) * n_in <= n_out || 2 * n_out < n_in || (uint64_t)n_out * block_bytes < (8ull << 20)) return false;
+    if (line || piece >= 1024 || !layer_first) return line;
+    if (vec < 16 && piece < 512) return true;
+    int64_t next = 0;
+    for (int64_t i = 1; i < n_out; i++) next += out_slots[i] == out_slots[i - 1] + 1;
+    return 2 * next < n_out;
+}
+
 inline bool list_bad(const int32_t *p, int32_t n) { return n < 0 || (n > 0 && !p); }
 
 }  // namespace dkv

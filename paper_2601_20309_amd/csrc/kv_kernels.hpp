@@ -295,12 +295,11 @@ __device__ __forceinline__ void job_loads(const Job<V, U, FULL> &j, V (&vi)[U], 
 // reader beside a swap-out keeps 6.8 instead of 6.5 TB/s.  Kernel time in us, plain /
 // non-temporal / written through: out 0.5 MiB 18.7 / 18.6 / 13.6, 2 MiB 64 / 58 / 41,
 // 256 MiB 4890 / 4813 / 4700; both ways 2 MiB each 79 / 73 / 48, 256 MiB 5418 / 5341 / 5320.
-// Narrower vectors are part of a 128-byte line per access more often, and every part
-// of a line is a write of its own on the link where the L2 would have joined them.  8-byte
-// vectors are written through (`through`) unless segments of under 512 bytes begin and end
-// inside lines (40 MiB both ways, us, non-temporal / written through: 840-byte segments,
-// block-first pool 901 / 853, layer-first 948 / 916, 200-byte segments layer-first
-// 1240 / 1320); vectors of 4 bytes and less (180-byte segments 1187 / 1557) are not.
+// So do 8-byte vectors (40 MiB both ways, us, non-temporal / written through: 840-byte segments
+// in a block-first pool 901 / 853).  Every part of a line is a write of its own on the link,
+// though, where the L2 would have joined them: vectors of 4 bytes and less (180-byte segments
+// 1187 / 1557) are never written through, and wider ones not in the calls that
+// leaves_to_l2() names.
 template <typename V, bool THROUGH>
 __device__ __forceinline__ void store_host(const V &v, V *dst)
 {

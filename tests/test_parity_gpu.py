@@ -904,3 +904,58 @@ def test_configured_waves_keep_their_rates():
             assert least <= rate <= most, (kw, rate, ms)
     for c in engines:
         c.close()
+
+
+@pytest.mark.parametrize("host_layout,seg,runs", [(B.KV_HOST_LAYER_FIRST, 64, False), (B.KV_HOST_LAYER_FIRST, 128, True),
+                                                  (B.KV_HOST_LAYER_FIRST, 200, False), (B.KV_HOST_LAYER_FIRST, 640, False),
+                                                  (B.KV_HOST_LAYER_FIRST, 640, True), (B.KV_HOST_BLOCK_FIRST, 64, False)])
+def test_rotations_of_much_in_small_pieces(host_layout, seg, runs):
+    """9 MiB each way in pieces of half a line to five of them, scattered or not, whose stores
+    are left to the L2 or written through: alone, and behind a call of the same batch that
+    left its times; every byte against NumPy's indexing (the oracle compares lists pairwise,
+    which takes minutes for lists as long as these), and no time shorter than the link allows."""
+    layers = 4 if host_layout == B.KV_HOST_LAYER_FIRST else 1
+    n = (9 << 20) // (2 * layers * seg)
+    sh = W.KVShape(layers, 1, seg // 2, 1, n_hbm_blocks=2 * n + 6, n_host_slots=2 * n + 6)
+    rot = W.simple_rotation(sh, n + 1, n, seed=seg, contiguous_slots=runs)
+    case, _ = make_case(sh, host_layout, B.KV_PATH_AUTO, rot=rot)
+    cache, pool = case.ref_cache.reshape(2 * layers, -1, seg // 2), case.ref_pool    # [plane, block or slot, element]
+    pool = pool.reshape(2 * layers, -1, seg // 2) if host_layout == B.KV_HOST_LAYER_FIRST else \
+        pool.reshape(-1, 2 * layers, seg // 2).transpose(1, 0, 2)
+
+    def rotate(r):
+        assert case.eng.kv_rotate(r.out_ids, r.out_slots, r.in_ids, r.in_slots) == 0
+        out, into = cache[:, r.out_ids].copy(), pool[:, r.in_slots].copy()
+        pool[:, r.out_slots], cache[:, r.in_ids] = out, into
+
+    first = W.Rotation(rot.out_ids[1:], rot.out_slots[1:], rot.in_ids, rot.in_slots)
+    rotate(first)
+    case.check()
+    st = case.eng.kv_last_stats()
+    assert min(st["ms_out"], st["ms_in"]) >= st["bytes_out"] / 64e6, st
+    assert case.eng.kv_swap_out(rot.out_ids[:1], rot.out_slots[:1]) == 0
+    pool[:, rot.out_slots[0]] = cache[:, rot.out_ids[0]]
+    rotate(first.inverse())
+    case.check()
+    st = case.eng.kv_last_stats()
+    assert st["bytes_out"] > st["bytes_in"] and min(st["ms_out"], st["ms_in"]) >= st["bytes_in"] / 64e6, st
+    case.close()
+
+
+def test_small_pieces_are_joined_before_they_leave():
+    """24 MiB each way in 64-byte segments of a layer-first pool: a call whose stores are left
+    to the L2 takes less than 0.96 of one whose stores are written through, which the second
+    call of a batch is when the first has left its times (0.90)."""
+    sh = W.KVShape(8, 1, 32, 1, n_hbm_blocks=50000, n_host_slots=50000)
+    rot = W.simple_rotation(sh, 24577, 24576, seed=2)
+    oi, os_, ii, is_ = rot.out_ids[1:], rot.out_slots[1:], rot.in_ids, rot.in_slots
+    case, _ = make_case(sh, B.KV_HOST_LAYER_FIRST, B.KV_PATH_AUTO, rot=rot)
+    held, through = [], []
+    for _ in range(9):
+        assert case.eng.kv_rotate(oi, os_, ii, is_) == 0 and case.eng.kv_wait() == 0
+        held.append(case.eng.kv_last_stats()["ms_e2e"])
+        assert case.eng.kv_swap_out(rot.out_ids[:1], rot.out_slots[:1]) == 0
+        assert case.eng.kv_rotate(oi, os_, ii, is_) == 0 and case.eng.kv_wait() == 0
+        through.append(case.eng.kv_last_stats()["ms_e2e"])
+    assert np.median(held) < 0.96 * np.median(through), (held, through)
+    case.close()
