@@ -661,8 +661,14 @@ def test_rest_of_an_out_heavy_rotation_moves_its_own_blocks(layers, n_out, n_in,
     case.close()
 
 
+# What launches of the default shapes move, KiB per direction, with eight steps per wave, up to
+# which waves take fixed shares: rotations and swap-outs in a block-first pool, then layer-first.
+EIGHT_STEPS = {(128, 16): ((1088, 512), (1088, 512)), (65, 8): ((960, 510), (1081, 569)), (60, 7): ((1512, 803), (1339, 715)),
+               (20, 5): ((671, 356), (480, 255)), (18, 5): ((336, 178), (335, 179)), (9, 5): ((168, 89), (167, 89))}
+
+
 @pytest.mark.parametrize("host_layout", LAYOUTS)
-@pytest.mark.parametrize("dim,tokens", [(128, 16), (65, 8), (60, 7), (20, 5), (18, 5), (9, 5)])
+@pytest.mark.parametrize("dim,tokens", list(EIGHT_STEPS))
 def test_stores_into_the_pool_at_every_vector_width(dim, tokens, host_layout):
     """Segments of 4096 and 1040 (16-byte vectors), 840 and 200 (8), 180 (4) and 90 bytes
     (2): what reaches the pool, written through or not, is every byte of the named slots
@@ -670,7 +676,8 @@ def test_stores_into_the_pool_at_every_vector_width(dim, tokens, host_layout):
     take fixed shares, and over bytes that an earlier call left there."""
     sh = W.KVShape(6, 1, dim, tokens, n_hbm_blocks=1, n_host_slots=1)
     block = 12 * 2 * dim * tokens
-    counts = sorted({max(1, kib * 1024 // block) for kib in (30, 480, 530, 1050, 1130)})
+    limits = EIGHT_STEPS[dim, tokens][0 if host_layout == B.KV_HOST_BLOCK_FIRST else 1]
+    counts = sorted({max(1, int(kib * 1024 / block)) for kib in (30, *(x * y for x in limits for y in (0.93, 1.07)))})
     n = counts[-1]
     sh = W.KVShape(6, 1, dim, tokens, n_hbm_blocks=2 * n + 7, n_host_slots=2 * n + 5)
     rot = W.simple_rotation(sh, n, n, seed=dim)
