@@ -274,6 +274,8 @@ def main():
             "frac_of_measured_memcpy_peak": round((bytes_out + bytes_in) / (kern_ms * 1e6) /
                                                   (link["d2h"] + link["h2d"]), 4),
             "kernel_ms": round(kern_ms, 4),
+            # what the kernels leave is 3 us less than events around them: no dispatch, no write-back
+            "kernel_ms_clock": "device clock, first wave to last store" if path_name in ("fused", "zerocopy") else "HIP events",
             "traffic": traffic, "profile": traffic_src,
             # per launch: the move kernel reads and writes both directions' bytes once; a pack or
             # unpack launch reads and writes one direction's

@@ -540,7 +540,9 @@ int mark_end(kv_engine *e, bool out_side, int k, hipStream_t s)
 // both ways / out / in, with those of 4 at 99 / 56 / 57.
 enum LinkKind { kBoth, kInHeavy, kOutOnly, kInOnly };
 // A launch of no more than kShortKib per direction gets a wave per tile: no second round
-// trip over the link, and no more waves than the table above has.  (8 + 8 blocks of 16 KiB:
+// trip over the link.  (One-way launches in 4 KiB tiles then have up to 32 waves where the
+// table above has 16 and 24, those in 1 KiB tiles up to 128 where it has 64 to 120, for the
+// 15 to 20 us that they take.)  (8 + 8 blocks of 16 KiB:
 // 64 waves x U 2 24.8 us, 40 waves 25.1, 16 waves 28.1; 8 blocks in: 32 x U 4 20.3, 24 x U 4
 // 20.8.  16 + 16 blocks: 128 waves 30.6, the table's 68 28.0.  With a wave per tile up to
 // 512 KiB the reader beside lost 10-14 ms per GiB moved instead of 2-4.)
@@ -1905,9 +1907,9 @@ int kv_reader_start(kv_engine *e, const int32_t *ids, int32_t n, int32_t passes,
     if (e->seg % 16 != 0 || ((uintptr_t)e->hbm & 15u) != 0) return KV_EUNSUP;
     // Workgroups: 5.5 per CU.  With one row in flight per wave (kReadDepth) that is 5.6 MiB
     // in flight, enough for the HBM rate alone, and the most that a copy beside it bears
-    // without loss (8 GiB passes, TB/s alone / beside a swap-out, and its GB/s / a rotation):
-    // 5 per CU 6.61 / 5.11, 56.7 / 5.10;  5.5 6.83 / 5.94, 56.7 / 5.39;  6 6.91 / 6.69, 55.7 /
-    // 5.64 (the rotation 100.2 GB/s for 100.8);  7 6.90 / 3.25, 53.1 / 4.79.
+    // without loss (8 GiB passes, TB/s alone / beside a swap-out, and its GB/s / beside a
+    // rotation, and its GB/s): 5 per CU 6.77 / 6.55, 56.9 / 5.19, 101.0;  5.5 7.00 / 6.74, 56.8 /
+    // 5.48, 101.0;  6 7.09 / 5.62, 55.4 / 4.50, 98.5;  7 6.41 / 5.77, 55.5 / 4.66, 98.5.
     const int most_wgs = 11 * (e->n_cus > 0 ? e->n_cus : 256) / 2;
     constexpr size_t kReadCounters = (size_t)dkv::kReadGroups * dkv::kReadStride;  // words of one set of counters
     if (!e->s_read) {
@@ -1958,16 +1960,16 @@ int kv_reader_start(kv_engine *e, const int32_t *ids, int32_t n, int32_t passes,
     // workgroup takes its fixed share, no counter.  Longer ones: a quarter in fixed shares,
     // the rest claimed from the workgroup's group, and in passes of 64 rounds and more,
     // which a last look at other groups' counters does not lengthen, from two groups behind it.
-    // TB/s alone / beside a swap-out / a swap-in / rotations of 112 and of 192 copy waves:
-    //   37.5 GiB from no other group 7.02 / 6.26 / 5.36 / 5.42, 3.33, from two 7.04 / 6.45 / 5.41 / 5.49, 3.73
-    //    8   GiB                     6.81 / 6.05 / 5.27 / 5.33, 3.06           6.81 / 5.94 / 5.33 / 5.38, 3.62
-    //    2   GiB                     6.47 / 5.66 / 5.18 / 5.11, 2.97           6.46 / 4.88 / 5.20 / 5.12, 3.18
-    //    256 MiB                     5.35 / 3.73 / 4.14 / 3.86, 1.59           5.24 / 2.69 / 3.95 / 3.60, 1.44
-    // (from four and sixteen beside a swap-out: 8 GiB 5.89 and 5.60, 2 GiB 4.89 and 3.94).  An
-    // eighth or a sixteenth in fixed shares changes nothing beyond 2 %; with half or all
-    // fixed, workgroups that a copy slows set the pace (all: 2.9 beside a swap-out of 4 GiB);
-    // under four rounds that is over before it matters: 64 and 128 MiB 37 and 43 us beside a
-    // swap-out, 17 and 27 alone.
+    // TB/s alone / beside a swap-out / a swap-in / the default rotation, one by 192 waves:
+    //   37.5 GiB from no other group 7.04 / 6.80 / 5.34 / 5.47, 4.94, from two 7.04 / 6.82 / 5.38 / 5.52, 4.94
+    //    8   GiB                     7.02 / 6.74 / 5.38 / 5.38, 4.92           7.01 / 6.75 / 5.41 / 5.48, 4.91
+    //    2   GiB                     6.70 / 6.46 / 5.48 / 5.53, 4.46           6.68 / 6.44 / 5.51 / 5.66, 4.43
+    //    256 MiB                     5.43 / 4.99 / 4.23 / 4.19, 3.37           5.39 / 4.80 / 4.08 / 3.98, 2.83
+    // Beside swap-outs that slowed it more (their stores went through the L2), an eighth or a
+    // sixteenth in fixed shares changed nothing beyond 2 %; with half or all fixed,
+    // workgroups that a copy slows set the pace (all: 2.9 TB/s beside a swap-out of 4 GiB).
+    // Under four rounds that is over before it matters: 64 and 128 MiB take 18 and 27 us alone,
+    // 24 and 34 beside a swap-out, 31 and 45 beside a rotation.
     const uint32_t rounds = p.tiles / (uint32_t)wgs;
     p.fixed = rounds < 4 ? rounds + 1 : rounds / 4;
     p.steal = rounds < 64 ? 0 : 2;

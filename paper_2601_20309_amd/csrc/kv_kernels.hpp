@@ -582,14 +582,14 @@ __global__ __launch_bounds__(kThreads) void kv_stage_kernel(const StageParams p,
 // cut into tiles of kReadRows rows of 64 vectors (32 KiB, 8 KiB per wave), so a
 // tile is full whatever the segment size.  (Tiles that ended with their segment
 // read 1500 blocks of 64 x 4 KiB in 243 us, 1/8 of each tile used; the pass alone takes
-// 65 us = 6.0 TB/s now, a call with its launches and its wait 86.)
+// 63 us = 6.2 TB/s now, a call with its launch and its wait 79.)
 //
 // A wave has kReadDepth rows in flight.  One is right: 22 waves per CU with a row
 // each are 5.6 MiB over the chip, which is the HBM rate times its latency.  More
 // only queue in front of HBM, and a copy over the link that runs beside the
-// reader stands in the same queues: 37.5 GiB in rows of 1, 2, 8 in flight, TB/s
-// alone 7.02, 7.07, 6.98, and GB/s of a rotation beside them 100.8, 94.2, 87.9,
-// of a swap-out 56.9, 51.5, 48.1.
+// reader stands in the same queues: 37.5 GiB with 1, 2, 8 rows in flight, TB/s
+// alone 7.05, 7.09, 6.99, and GB/s of a rotation beside them 101.1, 89.0, 54.3,
+// of a swap-out 56.5, 40.9, 24.0.
 //
 // No two workgroups meet on an address while they read.  An atomic on one address
 // is served every ~14 ns: one counter for the tiles limits claims to 2.3 TB/s per
@@ -626,8 +626,8 @@ constexpr uint32_t kReadVecs = kReadRows * kWave;                      // vector
 constexpr uint32_t kReadBegins = 64;  // workgroups that leave when they began: the first eight on each XCD
 // Counters, and the workgroups that share one: one of every 64 that follow one another,
 // each time one place further, so that a group lies on all XCDs and all over each, and
-// a copy beside the pass slows every group alike.  37.5 GiB alone / beside a swap-out and
-// 2 GiB beside it, TB/s: so placed 7.02 / 6.39, 5.88; groups of 22 that follow one another,
+// a copy beside the pass slows every group alike.  37.5 GiB alone / beside a swap-out (whose
+// stores went through the L2) and 2 GiB beside it, TB/s: so placed 7.02 / 6.39, 5.88; groups of 22 that follow one another,
 // that is on the same three CUs of every XCD, 6.73 / 6.10, 3.55; every 64th workgroup,
 // all of a group on one XCD, 6.92 / 5.94, 2.11.  Fewer groups meet more often on their
 // counter: 16 read 6.78 alone, 8 6.51.
@@ -636,8 +636,8 @@ constexpr uint32_t kReadStride = 32;  // 32-bit words from one counter to the ne
 // A claim is 4 tiles, 2 and at last 1: as long as the group has kReadMargin times as
 // many left for each of its workgroups.  A workgroup on a CU with a copy's waves reads
 // several times slower than the others and holds two claims, the one it reads and the
-// one behind it: they must not outlast the pass.  (8 GiB, TB/s alone / beside a swap-out /
-// a rotation: claims of 1 6.61 / 5.80 / 5.37, of 4 6.81 / 5.94 / 5.38, of 8 6.81 / 5.96 / 5.39;
+// one behind it: they must not outlast the pass.  (8 GiB, TB/s alone / beside a swap-out, as
+// above, / a rotation: claims of 1 6.61 / 5.80 / 5.37, of 4 6.81 / 5.94 / 5.38, of 8 6.81 / 5.96 / 5.39;
 // claims of 16 with a margin of 2 came to 4.25 beside a swap-out.)
 constexpr uint32_t kReadMargin = 16;
 
@@ -807,6 +807,8 @@ __global__ __launch_bounds__(kThreads) void kv_reader_inline_kernel(const ReadPa
 {
     read_pass<ROWS>(p, Ids{a});
 }
+
+static_assert(sizeof(ReadParams) + sizeof(IdArgs) <= 4096);
 
 // Before the passes of a list that arguments do not hold: from pinned host memory to the
 // device.  (A list of 1500 blocks of 64 x 4 KiB was read in 85 us with it, and is in 81
