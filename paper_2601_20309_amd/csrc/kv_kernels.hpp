@@ -623,7 +623,7 @@ constexpr int kReadU = 8;      // rows per wave and tile
 constexpr int kReadDepth = 1;  // rows in flight per wave
 constexpr uint32_t kReadRows = (uint32_t)kReadU * (kThreads / kWave);  // rows per tile
 constexpr uint32_t kReadVecs = kReadRows * kWave;                      // vectors per tile
-constexpr uint32_t kReadBegins = 64;  // workgroups that leave when they began: the first eight on each XCD
+constexpr uint32_t kReadBegins = 8;  // workgroups that leave when they began: the first on each XCD
 // Counters, and the workgroups that share one: one of every 64 that follow one another,
 // each time one place further, so that a group lies on all XCDs and all over each, and
 // a copy beside the pass slows every group alike.  37.5 GiB alone / beside a swap-out (whose
@@ -738,8 +738,9 @@ __device__ __forceinline__ unsigned long long read_tile(const ReadParams &p, con
 template <bool ROWS, typename Ids>
 __device__ __forceinline__ void read_pass(const ReadParams &p, const Ids &ids)
 {
-    const unsigned long long began = wall_clock64();
     const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1u);
+    if (p.begin && blockIdx.x < kReadBegins && tid == 0)
+        __scoped_atomic_store_n(p.begin + blockIdx.x, (unsigned long long)wall_clock64(), __ATOMIC_RELAXED, __MEMORY_SCOPE_SYSTEM);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     __shared__ uint32_t claimed[2];
     __shared__ unsigned long long sums[kThreads / kWave];
@@ -790,7 +791,6 @@ __device__ __forceinline__ void read_pass(const ReadParams &p, const Ids &ids)
         for (int w = 1; w < kThreads / kWave; w++) sum += sums[w];
         if (p.pass > 0) sum += p.part[blockIdx.x];
         const unsigned long long now = wall_clock64();
-        if (p.begin && blockIdx.x < kReadBegins) __builtin_nontemporal_store(began, p.begin + blockIdx.x);
         if (p.pass + 1u < p.passes) p.part[blockIdx.x] = sum;
         else store_host<u32x4, true>(__builtin_bit_cast(u32x4, u64x2{sum, now}), reinterpret_cast<u32x4 *>(p.result + blockIdx.x));
     }

@@ -652,19 +652,18 @@ def interference():
     print("| rotation path | copy WGs x lanes | rotation alone GB/s (out+in) | rotation beside reader GB/s | "
           "reader alone TB/s | reader beside rotation TB/s | reader time lost, ms per GiB moved |")
     print("|---|---|---|---|---|---|---|")
-    for path, wgs, lanes, contiguous in [(B.KV_PATH_FUSED, 0, 0, False), (B.KV_PATH_FUSED, 128, 64, False),
-                                         (B.KV_PATH_FUSED, 96, 64, False), (B.KV_PATH_FUSED, 80, 64, False),
-                                         (B.KV_PATH_FUSED, 64, 64, False), (B.KV_PATH_FUSED, 48, 64, False),
-                                         (B.KV_PATH_FUSED, 32, 64, False), (B.KV_PATH_FUSED, 17, 256, False),
-                                         (B.KV_PATH_FUSED, 5, 896, False),
-                                         (B.KV_PATH_SDMA_STAGED, 0, 0, True), (B.KV_PATH_DMA_BLOCKS, 0, 0, False)]:
+    # max_copy_wgs, wg_lanes, vecs_per_lane (0: the engine picks, under a cap one vector)
+    shapes = [(0, 0, 0), (144, 64, 0), (96, 64, 0), (64, 64, 0), (32, 64, 0), (28, 256, 0), (16, 448, 0), (8, 896, 0),
+              (128, 64, 2), (96, 64, 2), (64, 64, 2), (48, 64, 2)]
+    for path, (wgs, lanes, vecs), contiguous in [(B.KV_PATH_FUSED, s, False) for s in shapes] + \
+            [(B.KV_PATH_SDMA_STAGED, (0, 0, 0), True), (B.KV_PATH_DMA_BLOCKS, (0, 0, 0), False)]:
         rot = W.config_rotation(name, contiguous_slots=contiguous)
         named = np.zeros(shape.n_hbm_blocks, bool)
         named[rot.out_ids] = True; named[rot.in_ids] = True
         others = np.flatnonzero(~named)[:19200].astype(np.int32)
         # one DMA copy per block needs whole blocks to be contiguous: the block-first cache
         hbm_layout = B.KV_HBM_BLOCK_FIRST if path == B.KV_PATH_DMA_BLOCKS else B.KV_HBM_LAYER_FIRST
-        eng = B.Engine(B.make_config(shape, path=path, max_copy_wgs=wgs, wg_lanes=lanes, vecs_per_lane=2 if wgs else 0,
+        eng = B.Engine(B.make_config(shape, path=path, max_copy_wgs=wgs, wg_lanes=lanes, vecs_per_lane=vecs,
                                      hbm_layout=hbm_layout), cache.data_ptr())
         blk = B.kv_block_bytes(eng.cfg)
         calls = _rot_calls(eng, rot)
@@ -702,7 +701,8 @@ def interference():
                 read_both.append(read_bytes * len(inside) / sum(inside) / 1e9)
         ms_both = statistics.median(both)
         launch = ("no kernel, block-first cache" if path == B.KV_PATH_DMA_BLOCKS else "pack / unpack kernels"
-                  if path != B.KV_PATH_FUSED else f"{wgs} x {lanes}, 2 vectors" if wgs else "default (68 x 64, 2 vectors)")
+                  if path != B.KV_PATH_FUSED else f"{wgs} x {lanes}" + (f", {vecs} vectors" if vecs else "") if wgs
+                  else "default (68 x 64, 2 vectors)")
         # what the co-runner pays: the part of the rotation's duration in which it got nothing done
         rb = statistics.median(read_both)
         lost = ms_both * (1 - rb / read_alone) / (moved / 2**30)
