@@ -105,8 +105,9 @@ typedef struct {
     double ms_out;         /* device time of the out work, first start to last end: by the device's clock, which the kernels themselves
                               leave, from the first wave of the first launch to the last wave's last store (without the dispatch of
                               launches and the write-back of caches that ends them, 3 us); by HIP events where copies are enqueued,
-                              under stream capture, and where stores to the pool are not written through (vectors too narrow
-                              for that).  Beside work on the other stream events can be off by 20 us */
+                              under stream capture, and where stores to the pool are not written through (vectors of 4 bytes and
+                              less, rotations of much in small pieces, shapes configured to have little in flight).  Beside
+                              work on the other stream events can be off by 20 us */
     double ms_in;          /* same for the in work */
     double ms_e2e;         /* host wall time, entry of the first transfer call to return of kv_wait */
     int32_t path_used;     /* KV_PATH_* of the last call */

@@ -522,9 +522,9 @@ int mark_end(kv_engine *e, bool out_side, int k, hipStream_t s)
 // lanes 86.1 and 78.5, 36 x 256 lanes 101.1 and 101.3; in-heavy 24 x U 4 83.2 and 81.6, 32 x
 // U 4 86.1 and 86.2.
 //
-// Segments that no tile divides, or that begin inside lines, are moved in tiles that span segments where the
-// pool holds a block in one piece; otherwise tiles end with their segment.  The vectors
-// per lane are those above unless they leave more than an eighth of the tiles empty, then
+// Segments that no tile divides, or that begin inside lines, are moved in tiles that span
+// segments where the pool holds a block in one piece; otherwise tiles end with their
+// segment.  The vectors per lane are those above unless they leave more than an eighth of the tiles empty, then
 // the most that leave the least empty (segments of 105 vectors fill one tile of 128 as they
 // fill two of 64: 40 MiB in 1343 us by 64, 841 by 128).  The waves are as many more as the
 // tiles are emptier, so that as many bytes are in flight, and 1.4 times that where an access
@@ -601,7 +601,7 @@ LinkShape link_shape(const kv_engine *e, LinkKind kind)
     s.wgs = cw && (few || cu || kind != kBoth) ? cw : std::max(1, waves * dkv::kWave / s.lanes);
     if (cw) s.wgs = std::min(s.wgs, cw);
     s.short_steps = cw || cl || cu ? 0 : kShortKib / std::max(1, kib);
-    const int all = s.wgs * s.lanes / dkv::kWave, flight = all * std::max(1, kib);
+    const int64_t all = (int64_t)s.wgs * s.lanes / dkv::kWave, flight = all * std::max(1, kib);
     s.through = true;
     if (!cw && !cl && !cu) return s;
     if (kind == kOutOnly) s.through = flight >= 64 && all >= 12 && s.wgs >= 4;

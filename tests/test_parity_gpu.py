@@ -966,3 +966,16 @@ def test_small_pieces_are_joined_before_they_leave():
         through.append(case.eng.kv_last_stats()["ms_e2e"])
     assert np.median(held) < 0.96 * np.median(through), (held, through)
     case.close()
+
+
+@pytest.mark.parametrize("lanes", [0, 64, 1024])
+def test_a_cap_beyond_every_launch(lanes):
+    """The largest max_copy_wgs there is: as many workgroups as a call has work for, and
+    times left by the launches, as without a cap."""
+    case, rot = make_case("tiny", B.KV_HOST_BLOCK_FIRST, B.KV_PATH_AUTO, max_copy_wgs=2**31 - 1, wg_lanes=lanes)
+    for r in (rot, rot.inverse()):
+        case.rotate(r)
+        case.check()
+        st = case.eng.kv_last_stats()
+        assert 0 < st["ms_out"] == st["ms_in"] < st["ms_e2e"], st
+    case.close()
