@@ -25,6 +25,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "kv_engine.hpp"
@@ -1949,12 +1950,22 @@ int kv_reader_start(kv_engine *e, const int32_t *ids, int32_t n, int32_t passes,
     if (!dir_tiles(p.n, e->n_planes, (p.vec_per_seg + dkv::kReadVecs - 1) / dkv::kReadVecs, by_segment))
         return KV_EUNSUP;
     p.n_vecs = (uint64_t)p.n * e->n_planes * p.vec_per_seg;
-    p.tiles = (uint32_t)((p.n_vecs + dkv::kReadVecs - 1) / dkv::kReadVecs);
+    int wgs = most_wgs;
+    if (max_wgs > 0) wgs = std::min(wgs, (int)max_wgs);
+    constexpr uint32_t waves_per_wg = dkv::kThreads / dkv::kWave;
+    const uint64_t n_rows = (p.n_vecs + dkv::kWave - 1) / dkv::kWave;
+    const uint64_t each = (n_rows + (uint64_t)wgs * waves_per_wg - 1) / ((uint64_t)wgs * waves_per_wg);  // rows of a wave
+    const bool is_short = each <= dkv::kReadShortRows;
+    p.rows = (uint32_t)dkv::kReadU;
+    if (is_short) {
+        const uint32_t rounds = std::max(1u, ((uint32_t)each + dkv::kReadU - 1) / dkv::kReadU);
+        p.rows = std::max(1u, ((uint32_t)each + rounds - 1) / rounds);
+        p.rows += p.rows % dkv::kReadShortDepth;
+    }
+    p.tiles = (uint32_t)((n_rows + p.rows * waves_per_wg - 1) / (p.rows * waves_per_wg));
     // a rounded-up reciprocal is exact while index * divisor stays below 2^64 (and 2^64 / 1 has no room)
     if (p.vec_per_seg > 1 && p.n_vecs <= ~0ull / p.vec_per_seg) p.seg_magic = ~0ull / p.vec_per_seg + 1;
     unsigned int *const next = reinterpret_cast<unsigned int *>(e->read_part + most_wgs);
-    int wgs = most_wgs;
-    if (max_wgs > 0) wgs = std::min(wgs, (int)max_wgs);
     wgs = (int)std::min<uint32_t>((uint32_t)wgs, std::max<uint32_t>(p.tiles, 1u));
     // Who reads which tile.  Short passes (under four rounds of the grid, 176 MiB): every
     // workgroup takes its fixed share, no counter.  Longer ones: a quarter in fixed shares,
@@ -1968,8 +1979,8 @@ int kv_reader_start(kv_engine *e, const int32_t *ids, int32_t n, int32_t passes,
     // Beside swap-outs that slowed it more (their stores went through the L2), an eighth or a
     // sixteenth in fixed shares changed nothing beyond 2 %; with half or all fixed,
     // workgroups that a copy slows set the pace (all: 2.9 TB/s beside a swap-out of 4 GiB).
-    // Under four rounds that is over before it matters: 64 and 128 MiB take 18 and 27 us alone,
-    // 24 and 34 beside a swap-out, 31 and 45 beside a rotation.
+    // Under four rounds that is over before it matters: 90 and 160 MiB take 23 and 33 us alone,
+    // 30 and 41 beside a swap-out, 42 and 59 beside a rotation.
     const uint32_t rounds = p.tiles / (uint32_t)wgs;
     p.fixed = rounds < 4 ? rounds + 1 : rounds / 4;
     p.steal = rounds < 64 ? 0 : 2;
@@ -1998,15 +2009,18 @@ int kv_reader_start(kv_engine *e, const int32_t *ids, int32_t n, int32_t passes,
             p.clear = next + (1 - e->read_turn) * kReadCounters;
             e->read_turn = 1 - e->read_turn;
             const dim3 g((unsigned)wgs), b(dkv::kThreads);
-            if (singly)
-                launch(rows ? dkv::kv_reader_inline_kernel<true, dkv::IdsInArgs> : dkv::kv_reader_inline_kernel<false, dkv::IdsInArgs>,
-                       g, b, e->s_read, nullptr, p, a);
-            else if (pairs)
-                launch(rows ? dkv::kv_reader_inline_kernel<true, dkv::IdPairsInArgs> : dkv::kv_reader_inline_kernel<false, dkv::IdPairsInArgs>,
-                       g, b, e->s_read, nullptr, p, a);
-            else
-                launch(rows ? dkv::kv_reader_kernel<true> : dkv::kv_reader_kernel<false>, g, b, e->s_read, nullptr, p,
-                       (const int32_t *)e->read_ids);
+            auto go = [&](auto has_rows, auto is_short_pass) {
+                constexpr bool R = decltype(has_rows)::value, S = decltype(is_short_pass)::value;
+                if (singly) launch(dkv::kv_reader_inline_kernel<R, S, dkv::IdsInArgs>, g, b, e->s_read, nullptr, p, a);
+                else if (pairs) launch(dkv::kv_reader_inline_kernel<R, S, dkv::IdPairsInArgs>, g, b, e->s_read, nullptr, p, a);
+                else launch(dkv::kv_reader_kernel<R, S>, g, b, e->s_read, nullptr, p, (const int32_t *)e->read_ids);
+            };
+            const std::true_type yes;
+            const std::false_type no;
+            if (rows && is_short) go(yes, yes);
+            else if (rows) go(yes, no);
+            else if (is_short) go(no, yes);
+            else go(no, no);
             HIPTRY(e, hipGetLastError());
         }
         if (events) HIPTRY(e, hipEventRecord(e->read_ev[(size_t)k + 1], e->s_read));

@@ -595,6 +595,16 @@ __global__ __launch_bounds__(kThreads) void kv_stage_kernel(const StageParams p,
 // alone 7.05, 7.09, 6.99, and GB/s of a rotation beside them 101.1, 89.0, 54.3,
 // of a swap-out 56.5, 40.9, 24.0.
 //
+// Short passes (up to kReadShortRows rows for each wave of the whole grid, 66 MiB) are latency and
+// nothing else: tiles of eight rows left most of the grid idle (2 MiB: 64 workgroups, eight
+// latencies one behind the other) or half of it in the second of two rounds.  Their tiles are
+// as many rows as give every wave as much, and two rows are in flight.  us alone / beside a
+// swap-out / a rotation, and its GB/s, one pass behind the other, before and now:
+//    2 MiB  9.7 / 14.4 / 22.1, 85.3 and 6.9 / 10.6 / 15.0, 77.0     48 MiB 16.7 / 23.5 / 33.8, 90.5 and 14.0 / 17.9 / 24.3, 86.3
+//   28 MiB 12.8 / 18.1 / 25.8, 87.5 and 11.5 / 15.5 / 20.9, 84.3    64 MiB 18.5 / 25.1 / 36.4, 91.3 and 17.5 / 20.7 / 26.9, 86.4
+// (what the copy loses goes by the number of launches beside it, each of which ends with the
+// caches written back).  From 80 MiB on a pass alone gains nothing by it.
+//
 // No two workgroups meet on an address while they read.  An atomic on one address
 // is served every ~14 ns: one counter for the tiles limits claims to 2.3 TB/s per
 // 32 KiB, and one sum for all waves (5632 atomics) ended every pass with ~80 us
@@ -614,6 +624,7 @@ struct ReadParams {
     uint32_t n;              // blocks
     uint32_t vec_per_seg;    // seg_bytes / 16
     uint32_t tiles;
+    uint32_t rows;           // rows per wave and tile, at most kReadU; a short pass's are even
     uint32_t fixed;          // tiles each workgroup takes without asking (see kv_reader_kernel)
     uint32_t pass, passes;   // pass 0: part[] holds nothing yet
     uint32_t steal;          // groups besides its own that a workgroup takes tiles from
@@ -625,6 +636,8 @@ struct ReadParams {
 
 constexpr int kReadU = 8;      // rows per wave and tile
 constexpr int kReadDepth = 1;  // rows in flight per wave
+constexpr int kReadShortDepth = 2;  // the same in a short pass
+constexpr uint32_t kReadShortRows = 12;
 constexpr uint32_t kReadRows = (uint32_t)kReadU * (kThreads / kWave);  // rows per tile
 constexpr uint32_t kReadVecs = kReadRows * kWave;                      // vectors per tile
 constexpr uint32_t kReadBegins = 8;  // workgroups that leave when they began: the first on each XCD
@@ -662,22 +675,23 @@ struct SmallDiv {
     }
 };
 
-// One wave's share of tile t: kReadU rows.  ROWS: segments are whole rows, so a
+// One wave's share of tile t: kReadU rows (SHORT: p.rows).  ROWS: segments are whole rows, so a
 // row has one block id, fetched with a scalar load.  Otherwise rows straddle
 // segments and every lane finds its own block and fetches its id itself.  All
 // ids are fetched before the first row is.  Past the end of the sequence a row
 // (or a lane) repeats the last one that exists, so that no load is conditional,
 // and is left out of the sum.  The loads are non-temporal (nothing is read
 // twice): worth 16 % on the block-first cache, whose segments lie a whole block apart.
-template <bool ROWS, typename Ids>
+template <bool ROWS, bool SHORT, typename Ids>
 __device__ __forceinline__ unsigned long long read_tile(const ReadParams &p, const Ids &ids, uint32_t t, uint32_t wave,
                                                         uint32_t lane)
 {
-    const uint32_t row0 = t * kReadRows + wave * (uint32_t)kReadU;
+    const uint32_t rows = SHORT ? p.rows : (uint32_t)kReadU;
+    const uint32_t row0 = (t * (uint32_t)(kThreads / kWave) + wave) * rows;
     const uint64_t g0 = (uint64_t)row0 * kWave;
     if (g0 >= p.n_vecs) return 0;
     // vectors from this wave's first to the end, as far as they matter here
-    const uint32_t left = (uint32_t)min(p.n_vecs - g0, (uint64_t)(kReadU * kWave));
+    const uint32_t left = (uint32_t)min(p.n_vecs - g0, (uint64_t)(rows * kWave));
     const u32x4 *src[kReadU];
     if constexpr (ROWS) {
         const uint32_t rps = p.vec_per_seg / kWave, n_rows = left / kWave;
@@ -687,6 +701,7 @@ __device__ __forceinline__ unsigned long long read_tile(const ReadParams &p, con
         uint32_t word[kReadU], entry[kReadU], plane[kReadU], at[kReadU];
 #pragma unroll
         for (uint32_t u = 0; u < (uint32_t)kReadU; u++) {
+            if (SHORT && u >= rows) break;
             word[u] = ids.word(i);
             entry[u] = i;
             plane[u] = pl;
@@ -701,9 +716,11 @@ __device__ __forceinline__ unsigned long long read_tile(const ReadParams &p, con
             pl += next_plane;
         }
 #pragma unroll
-        for (int u = 0; u < kReadU; u++)
+        for (uint32_t u = 0; u < (uint32_t)kReadU; u++) {
+            if (SHORT && u >= rows) break;
             src[u] = reinterpret_cast<const u32x4 *>(p.hbm + (uint64_t)plane[u] * p.hbm_plane_stride +
                                                      (uint64_t)ids.id(word[u], entry[u]) * p.hbm_block_stride) + at[u] * kWave + lane;
+        }
     } else {
         const uint32_t segidx = (uint32_t)(p.seg_magic ? __umul64hi(g0, p.seg_magic) : g0 / p.vec_per_seg);
         const uint32_t off0 = (uint32_t)(g0 - (uint64_t)segidx * p.vec_per_seg);
@@ -712,7 +729,8 @@ __device__ __forceinline__ unsigned long long read_tile(const ReadParams &p, con
         const uint32_t last = left - 1u;
         uint32_t word[kReadU], entry[kReadU], plane[kReadU], at[kReadU];
 #pragma unroll
-        for (int u = 0; u < kReadU; u++) {
+        for (uint32_t u = 0; u < (uint32_t)kReadU; u++) {
+            if (SHORT && u >= rows) break;
             const uint32_t x = off0 + min(u * kWave + lane, last), s = by_seg.quotient(x);
             const uint32_t y = i0 + s, w = by_list.quotient(y);
             entry[u] = y - w * p.n;
@@ -721,18 +739,22 @@ __device__ __forceinline__ unsigned long long read_tile(const ReadParams &p, con
             at[u] = x - s * p.vec_per_seg;
         }
 #pragma unroll
-        for (int u = 0; u < kReadU; u++)
+        for (uint32_t u = 0; u < (uint32_t)kReadU; u++) {
+            if (SHORT && u >= rows) break;
             src[u] = reinterpret_cast<const u32x4 *>(p.hbm + (uint64_t)plane[u] * p.hbm_plane_stride +
                                                      (uint64_t)ids.id(word[u], entry[u]) * p.hbm_block_stride) + at[u];
+        }
     }
+    constexpr int DEPTH = SHORT ? kReadShortDepth : kReadDepth;
     unsigned long long sum = 0;
 #pragma unroll
-    for (int u0 = 0; u0 < kReadU; u0 += kReadDepth) {
-        u32x4 v[kReadDepth];
+    for (uint32_t u0 = 0; u0 < (uint32_t)kReadU; u0 += DEPTH) {
+        if (SHORT && u0 >= rows) break;
+        u32x4 v[DEPTH];
 #pragma unroll
-        for (int k = 0; k < kReadDepth; k++) v[k] = __builtin_nontemporal_load(src[u0 + k]);
+        for (int k = 0; k < DEPTH; k++) v[k] = __builtin_nontemporal_load(src[u0 + k]);
 #pragma unroll
-        for (int k = 0; k < kReadDepth; k++) {
+        for (int k = 0; k < DEPTH; k++) {
             const unsigned long long s = (unsigned long long)v[k].x + v[k].y + (unsigned long long)v[k].z + v[k].w;
             sum += (u0 + k) * kWave + lane < left ? s : 0ull;
         }
@@ -741,7 +763,7 @@ __device__ __forceinline__ unsigned long long read_tile(const ReadParams &p, con
     return sum;
 }
 
-template <bool ROWS, typename Ids>
+template <bool ROWS, bool SHORT, typename Ids>
 __device__ __forceinline__ void read_pass(const ReadParams &p, const Ids &ids)
 {
     const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1u);
@@ -768,7 +790,7 @@ __device__ __forceinline__ void read_pass(const ReadParams &p, const Ids &ids)
     unsigned long long sum = 0;
     uint32_t t = blockIdx.x, end = n_fixed, step = gridDim.x;
     for (uint32_t turn = 0;; turn ^= 1u) {
-        for (; t < end; t += step) sum += read_tile<ROWS>(p, ids, t, wave, lane);
+        for (; t < end; t += step) sum += read_tile<ROWS, SHORT>(p, ids, t, wave, lane);
         if (!shared) break;
         if (tid == 0) claimed[turn] = pending;
         __syncthreads();  // one per claim: the two slots alternate
@@ -802,16 +824,16 @@ __device__ __forceinline__ void read_pass(const ReadParams &p, const Ids &ids)
     }
 }
 
-template <bool ROWS>
+template <bool ROWS, bool SHORT>
 __global__ __launch_bounds__(kThreads) void kv_reader_kernel(const ReadParams p, const int32_t *__restrict__ ids)
 {
-    read_pass<ROWS>(p, IdsInMemory{ids});
+    read_pass<ROWS, SHORT>(p, IdsInMemory{ids});
 }
 
-template <bool ROWS, typename Ids>
+template <bool ROWS, bool SHORT, typename Ids>
 __global__ __launch_bounds__(kThreads) void kv_reader_inline_kernel(const ReadParams p, const IdArgs a)
 {
-    read_pass<ROWS>(p, Ids{a});
+    read_pass<ROWS, SHORT>(p, Ids{a});
 }
 
 static_assert(sizeof(ReadParams) + sizeof(IdArgs) <= 4096);
