@@ -303,37 +303,47 @@ uint64_t group_vecs(uint64_t vec_per_seg, uint32_t planes, bool plane_major, boo
     return whole || plane_major || entry >= 0x7FFFFFFFull ? vec_per_seg : entry;
 }
 
-// Whether the pieces of the pool that a launch's groups are begin on 128-byte lines:
-// segments of a layer-first pool, `planes` planes of a block elsewhere.
-bool on_lines(const kv_engine *e, uint32_t planes)
+// What every piece of the pool that a launch's groups are begins on a multiple of, at most
+// kStretch: segments of a layer-first pool, `planes` planes of a block elsewhere.
+uint32_t piece_align(const kv_engine *e, uint32_t planes)
 {
     const uint64_t piece = e->cfg.host_layout == KV_HOST_LAYER_FIRST ? e->seg : (planes * e->seg) | e->block_bytes;
-    return (((uintptr_t)e->pool | piece) & 127u) == 0;
+    const uint64_t a = (uintptr_t)e->pool | piece | dkv::kStretch;
+    return (uint32_t)(a & (0 - a));
 }
 
-// MoveParams::line_mask for such pieces.  Vectors of 4 bytes and less are taken as they
-// lie: a line is half an access of theirs or more.
-uint32_t line_mask(int vec, bool lines)
+// Whether tiles are moved to begin where a write on the link does (MoveParams::line_mask).
+// Vectors of 4 bytes and less are taken as they lie: a line is half an access of theirs or more.
+bool inside_lines(int vec, uint32_t align) { return vec >= 8 && align < dkv::kStretch; }
+
+// MoveParams::line_mask for groups of that many vectors in tiles of `tile`.  For vectors of 8 bytes,
+// of which a stretch is half an access, lines of 128 bytes do where whole stretches would take
+// one more tile.  (840-byte segments in a layer-first pool, 2 MiB / 20 MiB out, in, both ways, us:
+// by lines 41, 44, 51 / 392, 420, 469, by stretches 44, 50, 56 / 392, 426, 469; 360 bytes, 20 MiB
+// both ways 532 and 554.  16-byte vectors gain nevertheless: 896 bytes, 24 MiB out 464 and 449.)
+uint32_t line_mask(int vec, uint32_t align, uint64_t group, uint32_t tile)
 {
-    return lines || vec < 8 ? 0 : 128u / (uint32_t)vec - 1;
+    if (!inside_lines(vec, align)) return 0;
+    auto mask = [&](uint32_t bytes) { return align >= bytes ? 0u : bytes / (uint32_t)vec - 1u; };
+    auto tiles = [&](uint32_t m) { return (group + m + tile - 1) / tile; };
+    const uint32_t stretch = mask(dkv::kStretch), line = mask(128);
+    return vec == 8 && tiles(stretch) > tiles(line) ? line : stretch;
 }
 
 // Cuts the planes [plane0, plane0 + n_planes) of every entry into tiles of `u` vectors per
-// lane; lines: groups begin on 128-byte lines of the far side; out: the launch writes there.
-// Segments that are whole tiles but begin inside lines are then cut like others: taken as
-// they lie, every access would begin and end in a part of a line, and each part, written
-// through, is a write of its own on the link.  (Pool 16 bytes behind a line, us for 64 MiB
-// both ways / out, with whole tiles and so: segments of 32 KiB in a block-first pool 1667 /
-// 1216 and 1340 / 1190, in a layer-first one of 8 KiB 1651 / 1223 and 1358 / 1194, of 2 KiB
-// 1933 / 1223 and 1423 / 1212, of 1 KiB 1506 / 1234 and 1509 / 1234.  Non-temporal, taken as
-// they lie: 1430 / 1241, 1431 / 1239, 1454 / 1265, 1540 / 1292.)
-void cut_tiles(MoveParams &p, int vec, int u, bool lines, bool out)
+// lane; align: what groups begin on multiples of on the far side; out: the launch writes there.
+// Segments that are whole tiles but begin inside stretches are then cut like others: taken as
+// they lie, every access would begin and end in a part of one, and each part, written
+// through, is a write of its own on the link.  (24 MiB both ways / out, us, taken as they lie and so:
+// segments of 4 KiB and of 32 KiB in a pool 128 bytes behind a stretch 535 / 473 and 501 / 443; pool 16
+// bytes behind a line, 64 MiB, 32 KiB segments 1667 / 1216 and 1340 / 1190, by lines.)
+void cut_tiles(MoveParams &p, int vec, int u, uint32_t align, bool out)
 {
-    const bool whole = p.vec_per_seg % ((uint32_t)dkv::kWave * (uint32_t)u) == 0 && !(out && line_mask(vec, lines));
+    const bool whole = p.vec_per_seg % ((uint32_t)dkv::kWave * (uint32_t)u) == 0 && !(out && inside_lines(vec, align));
     const uint32_t tile = (uint32_t)dkv::kWave * (uint32_t)(whole ? u : std::min(u, dkv::kMaxRaggedU));
     p.group_vecs = (uint32_t)group_vecs(p.vec_per_seg, p.n_planes, p.plane_major != 0, whole);
     p.groups_per_entry = p.group_vecs == p.vec_per_seg ? p.n_planes : 1u;
-    p.line_mask = whole ? 0 : line_mask(vec, lines);
+    p.line_mask = whole ? 0 : line_mask(vec, align, p.group_vecs, tile);
     p.by_tiles = dkv::make_div((p.group_vecs + p.line_mask + tile - 1) / tile);
     p.by_seg = p.groups_per_entry == 1 ? dkv::make_div(p.vec_per_seg) : dkv::Div{1, 0, 0};
     p.full_tiles = whole ? 1u : 0u;
@@ -530,12 +540,13 @@ int mark_end(kv_engine *e, bool out_side, int k, hipStream_t s)
 // fill two of 64: 40 MiB in 1343 us by 64, 841 by 128).  The waves are as many more as the
 // tiles are emptier, so that as many bytes are in flight, and 1.4 times that where an access
 // is parted into more requests than its bytes need: vectors narrower than 16 bytes, and
-// swap-ins from segments that begin inside 128-byte lines (swap-in of 40 MiB, us, without
-// and with: 840-byte segments 761 and 744, 180-byte 1374 and 998, 3360-byte 754 and 740).
+// swap-ins from segments that are no whole tiles or begin inside stretches of 256 bytes (swap-in of
+// 40 MiB, us, without and with: 840-byte segments 761 and 744, 180-byte 1374 and 998, 3360-byte 754
+// and 740, of 1200 bytes in blocks of 57600 751 and 742).
 // Vectors narrower than 16 bytes (odd segments or pointers) also get more of them per lane.
 // Now and before all of this and line_mask, us for 40 MiB both ways / out / in: segments of
-// 1200 bytes 838 / 739 / 746 (856 / 756 / 744), in a layer-first pool 893 / 774 / 806 (968 /
-// 830 / 820), of 840 bytes there 916 / 759 / 841 (1150 / 870 / 1350).  All of this
+// 1200 bytes 835 / 736 / 731 (856 / 756 / 744), in a layer-first pool 876 / 749 / 802 (968 /
+// 830 / 820), of 840 bytes there 945 / 756 / 838 (1150 / 870 / 1350).  All of this
 // goes by the tiles as they are cut, configured vectors or not: segments of 1000 vectors
 // with vecs_per_lane = 8 are cut by 4, and with the waves of 8 moved at 86 / 56 / 44 GB/s
 // both ways / out / in, with those of 4 at 99 / 56 / 57.
@@ -556,17 +567,17 @@ LinkShape link_shape(const kv_engine *e, LinkKind kind)
     const uint64_t vec_per_seg = e->seg / (uint64_t)e->vec;
     const bool plane_major = e->cfg.host_layout == KV_HOST_LAYER_FIRST;
     const uint32_t planes = e->cfg.chunk_layers > 0 ? std::min(2u * (uint32_t)e->cfg.chunk_layers, e->n_planes) : e->n_planes;
-    const bool lines = on_lines(e, planes);
+    const uint32_t align = piece_align(e, planes);
     const int64_t cap = (int64_t)cw * (cl ? cl : dkv::kThreads) / dkv::kWave;  // configured waves
     const bool packed = cl ? cl > dkv::kWave : cw > 0;
     const bool few = kind == kBoth && !cu && (packed || (cw && cap < kFewWaves));
     int u = cu ? cu : kind == kBoth ? (few ? 1 : 2) : kind == kOutOnly && (cw || cl > 512) ? 8 : 4;
     auto divides = [&](int w) { return vec_per_seg % ((uint64_t)dkv::kWave * (uint64_t)w) == 0; };
-    const bool inside = kind != kInOnly && line_mask(e->vec, lines);  // begin inside lines: see cut_tiles()
+    const bool inside = kind != kInOnly && inside_lines(e->vec, align);  // see cut_tiles()
     auto whole = [&](int w) { return divides(w) && !inside; };
     auto filled = [&](int w) {
         const uint64_t tile = (uint64_t)dkv::kWave * (uint64_t)w, g = group_vecs(vec_per_seg, planes, plane_major, false);
-        return (double)g / (double)((g + line_mask(e->vec, lines) + tile - 1) / tile * tile);
+        return (double)g / (double)((g + line_mask(e->vec, align, g, (uint32_t)tile) + tile - 1) / tile * tile);
     };
     int limit_u = u;
     if (!cu) {
@@ -593,7 +604,7 @@ LinkShape link_shape(const kv_engine *e, LinkKind kind)
     case kInHeavy: waves = kib >= 8 ? 20 : kib >= 4 ? 32 : kib >= 2 ? 64 : 112; break;
     default: waves = kib >= 8 ? 24 : kib >= 4 ? 38 : kib >= 2 ? 68 : 120; break;
     }
-    const bool parted = e->vec < 16 || (kind == kInOnly && !lines);
+    const bool parted = e->vec < 16 || (kind == kInOnly && (align < dkv::kStretch || !whole(u)));
     waves = (int)(waves * std::min(4.0, (parted && fill >= 0.5 ? 1.4 : 1.0) / fill));
     LinkShape s;
     s.u = u;
@@ -657,7 +668,8 @@ int launch_link(kv_engine *e, const LinkShape &sh, hipStream_t s, const MovePara
         MoveParams q = whole;
         q.plane0 = p0;
         q.n_planes = std::min(per_chunk, whole.n_planes - p0);
-        cut_tiles(q, e->vec, sh.u, on_lines(e, q.n_planes) && (p0 * e->seg & 127u) == 0, whole.out.n > 0);
+        const uint64_t begins = p0 * e->seg | piece_align(e, q.n_planes);
+        cut_tiles(q, e->vec, sh.u, (uint32_t)(begins & (0 - begins)), whole.out.n > 0);
         // fits: the whole call's counts were checked
         if (!fill_dir(q, q.out.n, 0, sh.limit_u, q.out) || !fill_dir(q, q.in.n, 0, sh.limit_u, q.in)) return KV_EUNSUP;
         q.mix_q = whole.mix_q && q.out.tiles ? (((uint64_t)q.out.tiles << 32) + q.in.tiles - 1) / q.in.tiles : 0;
@@ -687,7 +699,7 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
         q.far_slot_stride_in = q.far_slot_stride_out;
         q.far_plane_stride_in = q.far_plane_stride_out;
         q.plane_major = e->cfg.host_layout == KV_HOST_LAYER_FIRST ? 1u : 0u;
-        cut_tiles(q, e->vec, sh.u, on_lines(e, e->n_planes), out);
+        cut_tiles(q, e->vec, sh.u, piece_align(e, e->n_planes), out);
         return q;
     };
     // The link-bound kernels fetch ids and slots with scalar loads.  Where one list
@@ -1046,7 +1058,7 @@ MoveParams stage_params(const kv_engine *e, uint8_t *stage, uint32_t nb, uint32_
     p.far_out = p.far_in = stage - (uint64_t)p0 * ps;
     p.far_slot_stride_out = p.far_slot_stride_in = ss;
     p.far_plane_stride_out = p.far_plane_stride_in = ps;
-    cut_tiles(p, e->vec, u, true, true);  // staging is taken as it lies
+    cut_tiles(p, e->vec, u, dkv::kStretch, true);  // staging is taken as it lies
     return p;
 }
 
@@ -1760,7 +1772,7 @@ int kv_rotate_static(const kv_config *cfg, void *hbm_cache, void *host_pool, voi
     p.far_slot_stride_in = p.far_slot_stride_out;
     p.far_plane_stride_in = p.far_plane_stride_out;
     p.plane_major = cfg->host_layout == KV_HOST_LAYER_FIRST ? 1u : 0u;
-    cut_tiles(p, e->vec, sh.u, on_lines(e, e->n_planes), no > 0);
+    cut_tiles(p, e->vec, sh.u, piece_align(e, e->n_planes), no > 0);
     if (!fill_dir(p, (uint32_t)no, 0, sh.limit_u, p.out) || !fill_dir(p, (uint32_t)ni, 0, sh.limit_u, p.in))
         return KV_EUNSUP;
     if (p.out.tiles > 0 && p.in.tiles > p.out.tiles)

@@ -60,6 +60,7 @@ constexpr int kThreads = 256;      // lanes per workgroup of the HBM-bound launc
 // Vectors per lane where a tile may span segments: every vector has pointers of its
 // own there, and with eight they would not fit the registers of a 1024-lane workgroup.
 constexpr int kMaxRaggedU = 4;
+constexpr uint32_t kStretch = 256;  // bytes of the far side that tiles begin on a multiple of (MoveParams::line_mask)
 // Places for the time stamps of a launch, one per wave: at least as many as any launch shape
 // that the engine picks has waves.  (Of more, w and w + kStamps share one; the wave that
 // ends later stores later.)
@@ -111,12 +112,15 @@ struct MoveParams {
     // are one range on the far side and planes apart in the cache.
     uint32_t group_vecs;        // vec_per_seg, or n_planes * vec_per_seg
     uint32_t groups_per_entry;  // n_planes, or 1
-    // Tiles begin on 128-byte lines of the far side, so that only the first and the last
-    // access of a group cover part of a line: 0 where groups begin on lines anyway, else
-    // the vectors of a line - 1; the first tile then holds as many vectors fewer as the
-    // group begins behind a line.  (Layer-first pool, 40 MiB both ways / out / in, us, taken
-    // as they lie and so: 3360-byte segments 892 / 773 / 758 and 877 / 768 / 758, 15120 bytes
-    // 885 / 766 / 736 and 860 / 759 / 736, 840 bytes 949 / 808 / 841 and 916 / 759 / 841.)
+    // Tiles begin on stretches of kStretch bytes of the far side, so that only the first and the
+    // last access of a group cover part of one: 0 where groups begin on stretches anyway, else
+    // the vectors of a stretch - 1; the first tile then holds as many vectors fewer as the
+    // group begins behind one.  A write on the link carries up to 256 bytes, none across a multiple of 256: an
+    // access of 1 KiB that begins on an odd line is five of them instead of four.  (Layer-first
+    // pool, 24 MiB both ways / out / in, us, tiles on 128-byte lines and on stretches: 2400-byte segments
+    // 533 / 464 / 461 and 513 / 447 / 458, 2688 bytes 523 / 460 / 446 and 503 / 442 / 439, 1600 bytes 526 / 462 /
+    // 459 and 515 / 448 / 459; blocks of 28800 bytes, block-first, 521 / 458 / 450 and 505 / 443 / 440.  Taken as
+    // they lie, 3360-byte segments, 40 MiB, lost another 15 / 5 / 0.)
     uint32_t line_mask;
     Div by_tiles;               // by tiles_per_group = ceil((group_vecs + line_mask) / (64 * U))
     Div by_seg;                 // by vec_per_seg (quotient 0 where a group is one segment)
@@ -177,8 +181,7 @@ struct Job {
 };
 
 // The lane's pointers into one tile; past the end of the group, to its last vector,
-// before its begin, to its first (in the same line, with the same value: these lanes
-// are not told apart).
+// before its begin, to its first (with the same value: these lanes are not told apart).
 template <typename V, int U, bool FULL, int N>
 __device__ __forceinline__ void lane_pointers(const MoveParams &p, uint64_t hbm_off, uint8_t *far, uint32_t tin,
                                               uint32_t lane, V *(&in_cache)[N], V *(&in_far)[N], uint32_t &n)

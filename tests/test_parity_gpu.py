@@ -728,6 +728,43 @@ def test_tiles_begin_on_lines_of_the_pool(host_layout, offset):
             eng.kv_destroy()
 
 
+@pytest.mark.parametrize("offset", [0, 128, 144, 248])
+@pytest.mark.parametrize("host_layout", LAYOUTS)
+def test_tiles_begin_on_stretches_of_the_pool(host_layout, offset):
+    """Segments, blocks and pools that begin on an odd line or inside one of the 256-byte
+    stretches that tiles begin on: segments that a stretch's worth of vectors more or fewer
+    cuts into another tile (16-byte vectors, and 8-byte ones, which then keep to lines),
+    and whole tiles.  Each direction and both, one launch and chunks of a layer, every byte
+    of the cache and the pool, and the bytes around the pool."""
+    rng = np.random.default_rng(offset)
+    for seg in (128, 384, 784, 800, 896, 1024, 1152, 1808, 1824, 2688, 3968, 4096, 264, 520, 776, 840, 1800):
+        sh = W.KVShape(3, 1, seg // 2, 1, n_hbm_blocks=41, n_host_slots=37)
+        rot = W.simple_rotation(sh, 15, 17, seed=seg)
+        for chunk_layers in (0, 1):
+            cfg = B.make_config(sh, host_layout, B.KV_PATH_AUTO, chunk_layers)
+            cache = rng.integers(0, 256, B.kv_cache_bytes(cfg), dtype=np.uint8)
+            n = B.kv_pool_bytes(cfg)
+            pinned = torch.empty(n + 768, dtype=torch.uint8, pin_memory=True)
+            around = pinned.numpy()
+            assert around.ctypes.data % 256 == 0
+            around[:] = rng.integers(0, 256, n + 768, dtype=np.uint8)
+            want_cache, want = cache.copy(), around.copy()
+            pool = want[256 + offset:256 + offset + n]
+            dev = torch.from_numpy(cache).cuda()
+            torch.cuda.synchronize()
+            eng = B.Engine(cfg, dev.data_ptr(), pinned.data_ptr() + 256 + offset)
+            osh = O.shape_of(sh, host_layout, 0)
+            assert eng.kv_rotate(rot.out_ids, rot.out_slots, rot.in_ids, rot.in_slots) == 0 and eng.kv_wait() == 0
+            assert O.rotate(osh, want_cache, pool, rot.out_ids, rot.out_slots, rot.in_ids, rot.in_slots) == 0
+            assert eng.kv_swap_out(rot.in_ids, rot.in_slots) == 0 and eng.kv_wait() == 0
+            assert O.swap_out(osh, want_cache, pool, rot.in_ids, rot.in_slots) == 0
+            assert eng.kv_swap_in(rot.out_slots[::-1].copy(), rot.out_ids) == 0 and eng.kv_wait() == 0
+            assert O.swap_in(osh, want_cache, pool, rot.out_slots[::-1].copy(), rot.out_ids) == 0
+            assert np.array_equal(dev.cpu().numpy(), want_cache), (seg, chunk_layers)
+            assert np.array_equal(around, want), (seg, chunk_layers)
+            eng.kv_destroy()
+
+
 @pytest.mark.parametrize("own_streams", [True, False])
 @pytest.mark.parametrize("kw", [{}, dict(chunk_layers=3), dict(max_copy_wgs=200), dict(path=B.KV_PATH_ZEROCOPY),
                                 dict(path=B.KV_PATH_ZEROCOPY, chunk_layers=1)])
