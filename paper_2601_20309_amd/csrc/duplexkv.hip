@@ -632,13 +632,18 @@ LinkShape link_shape(const kv_engine *e, LinkKind kind)
 // shape has a kernel of its own (kv_stage_kernel).  A configured max_copy_wgs (a
 // copy that has to stay small beside other kernels) keeps that many persistent
 // workgroups of the move kernel with 4 KiB tiles.
+// ids: of the chunk's blocks, on the device, or (on_host) few enough to be kernel arguments.
 template <bool UNPACK>
-void launch_stage(int vec, hipStream_t s, const dkv::StageParams &p, const int32_t *ids)
+void launch_stage(int vec, hipStream_t s, const dkv::StageParams &p, const int32_t *ids, bool on_host)
 {
     // four waves to a workgroup for the gather, one for the scatter (see kv_stage_kernel)
     const uint32_t waves_per_wg = UNPACK ? 1u : dkv::kThreads / dkv::kWave;
     dim3 g((p.tiles + waves_per_wg - 1) / waves_per_wg), b(waves_per_wg * dkv::kWave);
-#define DKV_STAGE(V) hipLaunchKernelGGL((dkv::kv_stage_kernel<V, UNPACK>), g, b, 0, s, p, ids)
+    dkv::IdArgs a;
+    if (on_host) std::copy(ids, ids + p.n, a.v);
+#define DKV_STAGE(V)                                                                               \
+    if (on_host) hipLaunchKernelGGL((dkv::kv_stage_inline_kernel<V, UNPACK>), g, b, 0, s, p, a);   \
+    else hipLaunchKernelGGL((dkv::kv_stage_kernel<V, UNPACK>), g, b, 0, s, p, ids)
     switch (vec) {
     case 16: DKV_STAGE(dkv::u32x4); break;
     case 8: DKV_STAGE(dkv::u32x2); break;
@@ -1119,12 +1124,18 @@ int run_staged(kv_engine *e, int k, const int32_t *oi, const int32_t *os, int32_
             (ni > 0 && !dir_tiles(pi.blocks_per_chunk, pi.planes_per_chunk, tiles_per_seg, unused)))
             return KV_EUNSUP;
     }
+    // A chunk of few blocks gets their ids as kernel arguments: a copy ahead of the chunks costs each
+    // direction a launch, and the first DMA copy of a swap-in, which needs no ids, a wait for it.
+    // (us a call with the copies and without: 2 + 1 blocks of 34 KiB 47.9 and 43.1, 2 + 3 of 128 KiB 62.4 and
+    // 55.8, 1 + 1 of 4 MiB 130 and 125, of 5 MiB in 160 planes 149 and 144; 120 + 96 of 2 MiB 5861 and 5865.)
+    const bool args_out = cap_wgs == 0 && po.blocks_per_chunk <= dkv::kInlineIds;
+    const bool args_in = cap_wgs == 0 && pi.blocks_per_chunk <= dkv::kInlineIds;
     if (no > 0) {
-        HIPTRY(e, hipMemcpyAsync(d_out, h_out, 2 * (size_t)no * sizeof(int32_t), hipMemcpyHostToDevice, e->s_out));
+        if (!args_out) HIPTRY(e, hipMemcpyAsync(d_out, h_out, 2 * (size_t)no * sizeof(int32_t), hipMemcpyHostToDevice, e->s_out));
         if (mark_start(e, true, e->s_out) != KV_OK) return KV_EHIP;
     }
     if (ni > 0) {
-        HIPTRY(e, hipMemcpyAsync(d_in, h_in, 2 * (size_t)ni * sizeof(int32_t), hipMemcpyHostToDevice, e->s_in));
+        if (!args_in) HIPTRY(e, hipMemcpyAsync(d_in, h_in, 2 * (size_t)ni * sizeof(int32_t), hipMemcpyHostToDevice, e->s_in));
         if (mark_start(e, false, e->s_in) != KV_OK) return KV_EHIP;
     }
     // Chunks of the two directions are enqueued alternately so both streams fill
@@ -1156,7 +1167,7 @@ int run_staged(kv_engine *e, int k, const int32_t *oi, const int32_t *os, int32_
             } else {
                 dkv::StageParams q;
                 if (!stage_kernel_params(e, e->stage_out, j1 - co.j0, co.p0, p1 - co.p0, q)) return KV_EUNSUP;
-                launch_stage<false>(e->vec, e->s_out, q, d_out + co.j0);
+                launch_stage<false>(e->vec, e->s_out, q, (args_out ? h_out : d_out) + co.j0, args_out);
             }
             HIPTRY(e, hipGetLastError());
             if (chunk_copies(e, true, e->stage_out, h_out + no, co.j0, j1, co.p0, p1, e->s_out, n_ops) != KV_OK)
@@ -1180,7 +1191,7 @@ int run_staged(kv_engine *e, int k, const int32_t *oi, const int32_t *os, int32_
             } else {
                 dkv::StageParams q;
                 if (!stage_kernel_params(e, e->stage_in, j1 - ci.j0, ci.p0, p1 - ci.p0, q)) return KV_EUNSUP;
-                launch_stage<true>(e->vec, e->s_in, q, d_in + ci.j0);
+                launch_stage<true>(e->vec, e->s_in, q, (args_in ? h_in : d_in) + ci.j0, args_in);
             }
             HIPTRY(e, hipGetLastError());
             if (layered) HIPTRY(e, hipEventRecord(e->layer_ev_in[ci.p0 / pi.planes_per_chunk], e->s_in));

@@ -558,7 +558,7 @@ struct StageParams {
 };
 
 template <typename V, bool UNPACK>
-__global__ __launch_bounds__(kThreads) void kv_stage_kernel(const StageParams p, const int32_t *__restrict__ ids)
+__device__ __forceinline__ void stage(const StageParams &p, const int32_t *__restrict__ ids)
 {
     const uint32_t lane = threadIdx.x & (kWave - 1u);
     const uint32_t t = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
@@ -579,6 +579,20 @@ __global__ __launch_bounds__(kThreads) void kv_stage_kernel(const StageParams p,
     V *in_stage = reinterpret_cast<V *>(p.stage + (uint64_t)i * p.slot_stride + (uint64_t)pl * p.plane_stride) + v;
     if constexpr (UNPACK) __builtin_nontemporal_store(__builtin_nontemporal_load(in_stage), in_cache);
     else __builtin_nontemporal_store(__builtin_nontemporal_load(in_cache), in_stage);
+}
+
+template <typename V, bool UNPACK>
+__global__ __launch_bounds__(kThreads) void kv_stage_kernel(const StageParams p, const int32_t *__restrict__ ids)
+{
+    stage<V, UNPACK>(p, ids);
+}
+
+static_assert(sizeof(StageParams) + sizeof(IdArgs) <= 4096);
+
+template <typename V, bool UNPACK>
+__global__ __launch_bounds__(kThreads) void kv_stage_inline_kernel(const StageParams p, const IdArgs a)
+{
+    stage<V, UNPACK>(p, a.v);
 }
 
 // Synthetic decode reader: streams every segment of the named blocks, plane by

@@ -574,6 +574,26 @@ def test_staged_rows_are_joined_where_that_pays(host_layout, layers, heads, chun
     case.close()
 
 
+@pytest.mark.parametrize("host_layout", LAYOUTS)
+@pytest.mark.parametrize("seg", [64, 72, 36, 6])
+def test_staged_chunks_at_what_arguments_hold(host_layout, seg):
+    """The DMA-staged path with chunks of 895, 896 and 897 blocks, whose ids are kernel
+    arguments up to 896 of them, as the whole list and as one of several chunks, the two
+    directions on different sides of that limit; vectors of 16, 8, 4 and 2 bytes."""
+    sh = W.KVShape(2, 1, seg // 2, 1, n_hbm_blocks=2800, n_host_slots=2800)
+    rot = W.simple_rotation(sh, 1300, 1300, seed=seg, contiguous_slots=True)
+    for per_chunk, no, ni in [(0, 895, 897), (0, 897, 896), (896, 1300, 897), (897, 1300, 896)]:
+        # a chunk's part of a block is 4 segments in a block-first pool, at least 2 in a layer-first one
+        staging = -(-per_chunk * (4 if host_layout == B.KV_HOST_BLOCK_FIRST else 2) * seg // 256) * 256
+        part = W.Rotation(rot.out_ids[:no], rot.out_slots[:no], rot.in_ids[:ni], rot.in_slots[:ni])
+        case, _ = make_case(sh, host_layout, B.KV_PATH_SDMA_STAGED, rot=part, staging_bytes=staging)
+        case.rotate(part)
+        case.check()
+        case.rotate(part.inverse())
+        case.check()
+        case.close()
+
+
 def test_staged_rows_far_apart():
     """Joined rows of a layer-first pool of real size, 128 MiB between the planes of a slot:
     the named slots and blocks exchange their bytes, every other byte of the pool stays."""
