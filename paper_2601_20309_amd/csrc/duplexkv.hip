@@ -707,20 +707,17 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
         cut_tiles(q, e->vec, sh.u, piece_align(e, e->n_planes), out);
         return q;
     };
-    // The link-bound kernels fetch ids and slots with scalar loads.  Where one list
-    // entry stands for many tiles (a whole block in block-first pool order) they
-    // read the pinned ring in place: a few thousand 64-byte reads over a link that
-    // moves gigabytes, no upload, nothing between the call and the launch.  Where
-    // an entry stands for little (small segments, few layers, or plane-major
-    // order, in which every segment is its own visit) every workgroup fetches a
-    // new entry nearly every tile; those reads would then be an eighth of the
-    // link traffic (4 KiB segments, one layer: 83 instead of 93 GB/s), so the set
-    // is uploaded first, ~5 us on the launch's stream.
-    // (Layer by layer a launch visits an entry for its layers only: 2048 blocks of 80 layers
-    // each way, a launch per layer, 128 KiB a visit, 434 ms with the ring read in place.)
-    // A call of few blocks has no such choice to make: its lists are kernel arguments.
+    // The link-bound kernels fetch ids and slots with scalar loads, for every tile anew.  A call of
+    // few blocks has its lists in the launches' arguments; other lists are uploaded first, ~5 us
+    // on the launch's stream: read in place from the pinned ring, over the link, they cost a rotation
+    // more, by what an entry stands for (us for 460 + 460 blocks in a block-first pool, in place and uploaded:
+    // 28800 bytes a block 288 and 256, 128 KiB 665 and 631, 256 KiB 2460 and 2400, 512 KiB 4813 and 4771, 2 MiB
+    // 19010 and 18998; swap-ins half of that, swap-outs a tenth; layer by layer a launch visits
+    // an entry for its layers only).  Only where the vectors are too narrow for arguments and a call of few
+    // blocks moves much at each place the ring is read in place.
     const bool on_host = ids_inline(e, no, ni);
-    const bool upload = !on_host && piece_bytes(e) < (256u << 10);
+    const bool few = 2 * ((int64_t)no + ni) <= (int64_t)dkv::kInlineIds && piece_bytes(e) >= (256u << 10);
+    const bool upload = !on_host && !few;
     int32_t *dd = upload ? e->desc_dev + (size_t)k * e->desc_cap : dh;
     int32_t *d_o = dd, *d_i = dd + 2 * (size_t)no;  // each: [ids | slots]
     auto upload_ids = [&](bool out_part, bool in_part, hipStream_t s) -> int {

@@ -625,6 +625,23 @@ def test_staged_rows_far_apart():
     eng.kv_destroy()
 
 
+@pytest.mark.parametrize("dim,total", [(4100, 448), (4100, 449), (4096, 449)])
+def test_lists_of_large_blocks(dim, total):
+    """Blocks of just over 256 KiB in segments of 8-byte vectors, whose lists never are
+    arguments: the pinned ring read in place up to 448 blocks, the uploaded copy beyond; and of
+    256 KiB in 16-byte vectors, uploaded.  Both directions and each, every byte."""
+    sh = W.KVShape(16, 1, dim, 1, n_hbm_blocks=total + 9, n_host_slots=total + 5)
+    rot = W.simple_rotation(sh, total // 2, total - total // 2, seed=total)
+    case, _ = make_case(sh, B.KV_HOST_BLOCK_FIRST, B.KV_PATH_AUTO, rot=rot)
+    case.rotate(rot)
+    case.check()
+    case.swap_out(np.concatenate([rot.out_ids, rot.in_ids]), np.concatenate([rot.in_slots, rot.out_slots])[:total])
+    case.check()
+    case.swap_in(np.concatenate([rot.out_slots, rot.in_slots])[::-1].copy(), np.concatenate([rot.in_ids, rot.out_ids])[:total])
+    case.check()
+    case.close()
+
+
 @pytest.mark.parametrize("host_layout", LAYOUTS)
 @pytest.mark.parametrize("vecs,planes", [(64, 4), (75, 4), (520, 2)])
 @pytest.mark.parametrize("total", [447, 448, 449, 1300])
