@@ -77,22 +77,26 @@ using dkv::list_bad;
 
 bool out_of_range(const int32_t *p, int32_t n, int32_t lim)
 {
-    for (int32_t i = 0; i < n; i++)
-        if (p[i] < 0 || p[i] >= lim) return true;
-    return false;
+    uint32_t bad = 0;  // no early end: several ids to an instruction
+    for (int32_t i = 0; i < n; i++) bad |= (uint32_t)p[i] >= (uint32_t)lim ? 1u : 0u;
+    return bad != 0;
 }
 
-// Marks `p` with `bit`; reports a repeat inside this list and a hit on the other list.
+// Marks `p` with `bit`; reports a repeat inside this list and a hit on the other list.  (A mark of
+// this epoch is at least its first one, and no mark is of a later epoch.)
 void mark_list(std::vector<uint32_t> &m, uint32_t epoch, const int32_t *p, int32_t n, uint32_t bit,
                bool &dup, bool &overlap)
 {
+    const uint32_t first = epoch << 2;
+    uint32_t *const marks = m.data();
+    uint32_t hits = 0;
     for (int32_t i = 0; i < n; i++) {
-        uint32_t &w = m[(size_t)p[i]];
-        uint32_t bits = (w >> 2) == epoch ? (w & 3u) : 0u;
-        if (bits & bit) dup = true;
-        if (bits & ~bit) overlap = true;
-        w = (epoch << 2) | bits | bit;
+        uint32_t &w = marks[(size_t)p[i]];
+        hits |= w >= first ? w : 0u;
+        w = std::max(w, first) | bit;
     }
+    dup = dup || (hits & bit) != 0;
+    overlap = overlap || (hits & ~bit & 3u) != 0;
 }
 
 int admit(const kv_config *c, Marks &mk, const int32_t *oi, const int32_t *os, int32_t no,

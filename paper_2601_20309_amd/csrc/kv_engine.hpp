@@ -35,14 +35,17 @@ struct Marks {
 struct Hazards {
     std::vector<uint32_t> blk_read, blk_written, slot_read, slot_written;  // by stream_out / stream_in work
     uint32_t epoch = 1;
+    bool any = false;  // something was stamped since the last join
     void reset(size_t nb, size_t ns)
     {
+        any = false;
         blk_read.assign(nb, 0); blk_written.assign(nb, 0);
         slot_read.assign(ns, 0); slot_written.assign(ns, 0);
         epoch = 1;
     }
     void join()
     {
+        any = false;
         if (++epoch == 0xFFFFFFFFu) reset(blk_read.size(), slot_read.size());
     }
     // out part: reads blocks, writes slots, on stream_out; in part: reads slots,
@@ -50,6 +53,7 @@ struct Hazards {
     bool races(const int32_t *oi, const int32_t *os, int32_t no, const int32_t *ii, const int32_t *is,
                int32_t ni) const
     {
+        if (!any) return false;
         for (int32_t k = 0; k < no; k++)
             if (blk_written[(size_t)oi[k]] == epoch || slot_read[(size_t)os[k]] == epoch) return true;
         for (int32_t k = 0; k < ni; k++)
@@ -58,6 +62,7 @@ struct Hazards {
     }
     void stamp(const int32_t *oi, const int32_t *os, int32_t no, const int32_t *ii, const int32_t *is, int32_t ni)
     {
+        any = true;
         for (int32_t k = 0; k < no; k++) { blk_read[(size_t)oi[k]] = epoch; slot_written[(size_t)os[k]] = epoch; }
         for (int32_t k = 0; k < ni; k++) { blk_written[(size_t)ii[k]] = epoch; slot_read[(size_t)is[k]] = epoch; }
     }
