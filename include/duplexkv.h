@@ -92,7 +92,7 @@ typedef struct {
                               (8 is taken as 4, with the more waves, where the segment is not a multiple of 64 * 8 vectors) */
     int32_t wg_lanes;      /* lanes per workgroup of the link kernels (workgroups only pack waves; a wave is the unit of work):
                               0 = engine picks, else a multiple of 64 up to 1024.  With max_copy_wgs also 0: one-wave workgroups, 16 to 68 of
-                              them by the kind of call for segments of whole tiles; several times more (up to 480) where segments are short,
+                              them by the kind of call for segments of whole tiles; several times more (up to 504) where segments are short,
                               odd or of narrow vectors, so that their tiles are partly empty, up to 128 in calls of less than 128 KiB, and
                               288 in each of the two kernels of KV_PATH_ZEROCOPY */
     int32_t hbm_layout;    /* KV_HBM_* */

@@ -547,7 +547,10 @@ int mark_end(kv_engine *e, bool out_side, int k, hipStream_t s)
 // swap-ins from segments that are no whole tiles or begin inside stretches of 256 bytes (swap-in of
 // 40 MiB, us, without and with: 840-byte segments 761 and 744, 180-byte 1374 and 998, 3360-byte 754
 // and 740, of 1200 bytes in blocks of 57600 751 and 742).
-// Vectors narrower than 16 bytes (odd segments or pointers) also get more of them per lane.
+// Vectors narrower than 16 bytes (odd segments or pointers) also get more of them per lane, and where
+// 8-byte ones have one a lane nevertheless, what moves in gets 1.5 times the waves (24 MiB both ways / in, us,
+// without and with: 200-byte segments 572 / 579 and 508 / 445, layer-first 1192-byte ones 567 / 572 and 532 /
+// 489; one direction out is the same, and both ways in tiles not half full, 200 bytes layer-first, lose: 751, 795).
 // Now and before all of this and line_mask, us for 40 MiB both ways / out / in: segments of
 // 1200 bytes 835 / 736 / 731 (856 / 756 / 744), in a layer-first pool 876 / 749 / 802 (968 /
 // 830 / 820), of 840 bytes there 945 / 756 / 838 (1150 / 870 / 1350).  All of this
@@ -610,6 +613,8 @@ LinkShape link_shape(const kv_engine *e, LinkKind kind)
     }
     const bool parted = e->vec < 16 || (kind == kInOnly && (align < dkv::kStretch || !whole(u)));
     waves = (int)(waves * std::min(4.0, (parted && fill >= 0.5 ? 1.4 : 1.0) / fill));
+    // tiles of 512 bytes: what comes in is half of what the table counts on
+    if (e->vec == 8 && cut == 1 && (kind == kInOnly || (kind != kOutOnly && fill >= 0.5))) waves += waves / 2;
     LinkShape s;
     s.u = u;
     s.limit_u = limit_u;
