@@ -94,7 +94,7 @@ typedef struct {
                               0 = engine picks, else a multiple of 64 up to 1024.  With max_copy_wgs also 0: one-wave workgroups, 16 to 68 of
                               them by the kind of call for segments of whole tiles; several times more (up to 504) where segments are short,
                               odd or of narrow vectors, so that their tiles are partly empty, up to 128 in calls of less than 128 KiB, and
-                              288 in each of the two kernels of KV_PATH_ZEROCOPY */
+                              up to 288 in each of the two kernels of KV_PATH_ZEROCOPY */
     int32_t hbm_layout;    /* KV_HBM_* */
     uint64_t staging_bytes;/* SDMA_STAGED: bytes of HBM staging per direction = largest chunk; 0 = engine picks (256 MiB) */
 } kv_config;

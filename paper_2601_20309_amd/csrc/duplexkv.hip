@@ -804,12 +804,22 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
     // they only reach the rate of the fused launch if each has at least one
     // workgroup per CU (measured, one-wave workgroups per kernel, U = 1, 512 + 512
     // MiB: 64 -> 68.9, 112 -> 84.9, 160 -> 92.2, 192 -> 95.1, 256 -> 101.1, 288 -> 101.1
-    // GB/s; U = 2: 96 -> 91.3; U = 4: 48 -> 89.2).
+    // GB/s; U = 2: 96 -> 91.3; U = 4: 48 -> 89.2).  With at least twice as much coming in as going out
+    // the larger share of fewer, wider waves does better: it leaves the reads their rate (out + in MiB, us with
+    // 288 x U 1 each and with 96 + 144 x U 2: 32 + 64 1262 and 1189, 16 + 64 1226 and 1189, 4 + 8 182
+    // and 171).  A launch of less than kPairBytes is over before the rate counts: it has the shape
+    // of one direction (8 + 8 blocks of 16 KiB 23.0 and 20.8, 30 + 30 31.3 and 29.3; 2 + 2 MiB 64.7 and 66.8).
     LinkShape sh_out = link_shape(e, kOutOnly), sh_in = link_shape(e, kInOnly);
-    if (no > 0 && ni > 0 && !e->cfg.max_copy_wgs && !e->cfg.wg_lanes && !e->cfg.vecs_per_lane) {
-        sh_out.wgs = sh_in.wgs = 9 * (e->n_cus > 0 ? e->n_cus : 256) / 8;
+    constexpr uint64_t kPairBytes = 1ull << 20;
+    const uint64_t planes = e->cfg.chunk_layers > 0 ? std::min(2u * (uint32_t)e->cfg.chunk_layers, e->n_planes) : e->n_planes;
+    const bool pair = (uint64_t)std::max(no, ni) * planes * e->seg >= kPairBytes;
+    if (no > 0 && ni > 0 && pair && !e->cfg.max_copy_wgs && !e->cfg.wg_lanes && !e->cfg.vecs_per_lane) {
+        const int cus = e->n_cus > 0 ? e->n_cus : 256;
+        const bool in_heavy = ni >= 2 * (int64_t)no && e->seg % (2 * dkv::kWave * (uint64_t)e->vec) == 0;
+        sh_out.wgs = in_heavy ? 3 * cus / 8 : 9 * cus / 8;
+        sh_in.wgs = in_heavy ? 9 * cus / 16 : 9 * cus / 8;
         sh_out.lanes = sh_in.lanes = dkv::kWave;
-        sh_out.u = sh_in.u = sh_out.limit_u = sh_in.limit_u = 1;
+        sh_out.u = sh_in.u = sh_out.limit_u = sh_in.limit_u = in_heavy ? 2 : 1;
         sh_out.short_steps = sh_in.short_steps = 0;
     }
     const MoveIds ids_out{d_o, d_o + no, nullptr, nullptr, on_host}, ids_in{nullptr, nullptr, d_i, d_i + ni, on_host};

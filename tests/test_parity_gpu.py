@@ -625,6 +625,25 @@ def test_staged_rows_far_apart():
     eng.kv_destroy()
 
 
+@pytest.mark.parametrize("chunk_layers", [0, 2])
+@pytest.mark.parametrize("dim", [1024, 600, 100])
+def test_two_kernels_at_the_edges_of_their_shapes(dim, chunk_layers):
+    """Both directions by a kernel each, where their launch shapes change: launches of just
+    under and of 1 MiB, and just under and twice as much coming in as going out, in
+    segments of whole tiles of two vectors a lane and in others."""
+    layers = 4
+    sh = W.KVShape(layers, 1, dim, 1, n_hbm_blocks=2400, n_host_slots=2400)
+    n = -(-(1 << 20) // (2 * (chunk_layers or layers) * 2 * dim))             # blocks that make a launch of 1 MiB
+    rot = W.simple_rotation(sh, min(n, 1100), min(n + 1, 1200), seed=dim)
+    case, _ = make_case(sh, B.KV_HOST_BLOCK_FIRST, B.KV_PATH_ZEROCOPY, rot=rot, chunk_layers=chunk_layers)
+    for no, ni in [(n - 1, n - 1), (n, n - 1), (n // 2, n), (n // 2 + 1, n), (n // 2 - 3, n - 1), (1, n + 1)]:
+        no, ni = min(no, 1100), min(ni, 1200)
+        part = W.Rotation(rot.out_ids[:no], rot.out_slots[:no], rot.in_ids[:ni], rot.in_slots[:ni])
+        case.rotate(part)
+        case.check()
+    case.close()
+
+
 @pytest.mark.parametrize("dim,total", [(4100, 448), (4100, 449), (4096, 449)])
 def test_lists_of_large_blocks(dim, total):
     """Blocks of just over 256 KiB in segments of 8-byte vectors, whose lists never are
