@@ -157,8 +157,8 @@ struct MoveIds {
 // A launch's shape: workgroups, lanes per workgroup, vectors per lane per tile;
 // short_steps: with no more steps than this, a wave per step; limit_u: the
 // vectors per lane by which dir_tiles() counts; through: it has waves enough to write
-// through to the pool.
-struct LinkShape { int wgs, lanes, u, short_steps, limit_u; bool through; };
+// through to the pool; even: see grid_of().
+struct LinkShape { int wgs, lanes, u, short_steps, limit_u; bool through, even; };
 
 template <typename... P, typename... A>
 void launch(void (*kernel)(P...), dim3 g, dim3 b, hipStream_t s, hipEvent_t stop, const A &...args)
@@ -168,12 +168,26 @@ void launch(void (*kernel)(P...), dim3 g, dim3 b, hipStream_t s, hipEvent_t stop
 }
 
 // Workgroups of a launch.  Its waves are the workers, and no more of them are launched
-// than it has steps.
+// than it has steps.  Where they take fixed shares (run_fixed) that come to several rounds,
+// no more than fill the last round as well as the others (even): the launch lasts as many round
+// trips over the link as it has rounds, and a round with fewer bytes in it is a shorter one.  Rounds of what
+// comes in, that is: where the out list is the longer one, the in list's are not to become more (138 KiB
+// out with 83 in, 70 steps, 42 with an in tile: by 69 waves 18.4 us, by 35 19.9).  us a call, before
+// and so: both ways 144 KiB 21.8 and 20.2, 224 22.8 and 21.4, 288 24.7 and 22.7, 560 30.9 and 28.9, 1 MiB 39.6
+// and 38.7, 1.5 MiB in four chunks 67.0 and 65.0; in, 150 KiB 19.3 and 18.2, 300 21.7 and 20.8; out, 300 KiB
+// 20.7 and 20.1.  Not where most comes in and the out tiles ride along, nor for two launches at once: with
+// a fifth of the waves gone these fill the link no more (400 KiB in with 133 out 24.6 and 25.5, 800 KiB
+// each way by two kernels 41.0 and 41.9).
 uint32_t grid_of(const LinkShape &sh, const MoveParams &p, uint32_t &steps)
 {
     steps = p.mix_q ? p.in.tiles : std::max(p.out.tiles, p.in.tiles);
     const uint32_t waves_per_wg = (uint32_t)sh.lanes / dkv::kWave, most = (steps + waves_per_wg - 1) / waves_per_wg;
-    return std::max(1u, steps <= (uint32_t)sh.short_steps ? most : std::min<uint32_t>((uint32_t)sh.wgs, most));
+    if (most == 0 || steps <= (uint32_t)sh.short_steps || most <= (uint32_t)sh.wgs) return std::max(1u, most);
+    auto rounds = [&](uint32_t tiles, uint32_t wgs) { return ((tiles + waves_per_wg - 1) / waves_per_wg + wgs - 1) / wgs; };
+    const uint32_t all = rounds(steps, (uint32_t)sh.wgs);
+    if (!sh.even || all > dkv::kFixedRounds) return (uint32_t)sh.wgs;
+    const uint32_t fewer = (most + all - 1) / all;
+    return rounds(p.in.tiles, fewer) > rounds(p.in.tiles, (uint32_t)sh.wgs) ? (uint32_t)sh.wgs : fewer;
 }
 
 // Whether the waves of a link-bound launch draw steps from its counters.
@@ -624,6 +638,7 @@ LinkShape link_shape(const kv_engine *e, LinkKind kind)
     s.short_steps = cw || cl || cu ? 0 : kShortKib / std::max(1, kib);
     const int64_t all = (int64_t)s.wgs * s.lanes / dkv::kWave, flight = all * std::max(1, kib);
     s.through = true;
+    s.even = kind != kInHeavy;
     if (!cw && !cl && !cu) return s;
     if (kind == kOutOnly) s.through = flight >= 64 && all >= 12 && s.wgs >= 4;
     if (kind == kInHeavy) s.through = flight >= 112 && s.wgs >= 4;
@@ -813,6 +828,7 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
     constexpr uint64_t kPairBytes = 1ull << 20;
     const uint64_t planes = e->cfg.chunk_layers > 0 ? std::min(2u * (uint32_t)e->cfg.chunk_layers, e->n_planes) : e->n_planes;
     const bool pair = (uint64_t)std::max(no, ni) * planes * e->seg >= kPairBytes;
+    if (no > 0 && ni > 0) sh_out.even = sh_in.even = false;
     if (no > 0 && ni > 0 && pair && !e->cfg.max_copy_wgs && !e->cfg.wg_lanes && !e->cfg.vecs_per_lane) {
         const int cus = e->n_cus > 0 ? e->n_cus : 256;
         const bool in_heavy = ni >= 2 * (int64_t)no && e->seg % (2 * dkv::kWave * (uint64_t)e->vec) == 0;
@@ -1117,7 +1133,7 @@ int run_staged(kv_engine *e, int k, const int32_t *oi, const int32_t *os, int32_
     int32_t *d_out = dd, *d_in = dd + 2 * (size_t)no;
     constexpr int U = 4;                         // capped launches: persistent waves, 4 KiB tiles
     const int cap_wgs = e->cfg.max_copy_wgs;     // 0: one wave per 1 KiB tile, kv_stage_kernel
-    const LinkShape capped{cap_wgs, dkv::kThreads, U, 0, U, false};
+    const LinkShape capped{cap_wgs, dkv::kThreads, U, 0, U, false, false};
     ChunkPlan po{}, pi{};
     if (no > 0) {
         int rc = plan_chunks(e, (uint32_t)no, po);

@@ -625,6 +625,29 @@ def test_staged_rows_far_apart():
     eng.kv_destroy()
 
 
+@pytest.mark.parametrize("vecs", [128, 80])
+def test_rounds_of_the_default_launches(vecs):
+    """Launches of the default shapes that end just before, at and just behind a full round of
+    their waves, from one round to nine, where steps are drawn: each direction, both, with a
+    shorter list beside (in or out); every byte against the oracle."""
+    per_block = 2 * vecs * 16 // 2048 or 1                                     # steps of 2 KiB of a block
+    blocks = sorted({max(1, (r * waves + d) // per_block) for waves, per in ((68, 1), (24, 2), (16, 2)) for r in (1, 2, 3, 8, 9)
+                     for d in (-per, 0, per) if r * waves * per < 640})
+    n = blocks[-1] + 1
+    sh = W.KVShape(1, 1, 8 * vecs, 1, n_hbm_blocks=2 * n + 3, n_host_slots=2 * n + 1)
+    rot = W.simple_rotation(sh, n, n, seed=vecs)
+    case, _ = make_case(sh, B.KV_HOST_BLOCK_FIRST, B.KV_PATH_AUTO, rot=rot)
+    for k in blocks:
+        for no, ni in ((k, k), (k, max(1, 2 * k // 3)), (max(1, 2 * k // 3), k)):
+            case.rotate(W.Rotation(rot.out_ids[:no], rot.out_slots[:no], rot.in_ids[:ni], rot.in_slots[:ni]))
+        case.wait()
+        case.swap_out(rot.in_ids[:k], rot.out_slots[:k])
+        case.wait()
+        case.swap_in(rot.in_slots[:k], rot.out_ids[:k])
+        case.check()
+    case.close()
+
+
 @pytest.mark.parametrize("chunk_layers", [0, 2])
 @pytest.mark.parametrize("dim", [1024, 600, 100])
 def test_two_kernels_at_the_edges_of_their_shapes(dim, chunk_layers):
