@@ -185,7 +185,7 @@ uint32_t grid_of(const LinkShape &sh, const MoveParams &p, uint32_t &steps)
     if (most == 0 || steps <= (uint32_t)sh.short_steps || most <= (uint32_t)sh.wgs) return std::max(1u, most);
     auto rounds = [&](uint32_t tiles, uint32_t wgs) { return ((tiles + waves_per_wg - 1) / waves_per_wg + wgs - 1) / wgs; };
     const uint32_t all = rounds(steps, (uint32_t)sh.wgs);
-    if (!sh.even || all > dkv::kFixedRounds) return (uint32_t)sh.wgs;
+    if (!sh.even || all > dkv::fixed_rounds(p)) return (uint32_t)sh.wgs;
     const uint32_t fewer = (most + all - 1) / all;
     return rounds(p.in.tiles, fewer) > rounds(p.in.tiles, (uint32_t)sh.wgs) ? (uint32_t)sh.wgs : fewer;
 }
@@ -195,7 +195,7 @@ bool draws(const LinkShape &sh, const MoveParams &p)
 {
     uint32_t steps;
     const uint64_t waves = (uint64_t)grid_of(sh, p, steps) * ((uint32_t)sh.lanes / dkv::kWave);
-    return steps > dkv::kFixedRounds * waves;
+    return steps > dkv::fixed_rounds(p) * waves;
 }
 
 // `stop` (may be nullptr) is recorded by the launch itself.

@@ -376,13 +376,22 @@ __device__ __forceinline__ uint32_t drawn(uint32_t d)
 }
 
 // Fixed share: wave w of W takes steps w, w + W, ...  HBM-bound launches, and link-bound
-// ones of at most kFixedRounds steps per wave (512 KiB out, 768 in, 1 MiB both ways in the
-// default shapes): there the counter's atomics, ~14 ns each on one address, are as long as
-// the transfer and the waves have no time to drift apart.  Launches of 512 KiB, 32 in a row,
-// us alone / GB/s and a reader's TB/s beside them (7.04 alone): swap-outs by 16 waves that
-// draw 413 / 26.6, 6.79, fixed shares 389 / 36.7, 6.75; 8 calls of 1 MiB both ways 256 /
-// 52.5, 6.53 and 263 / 59.4, 6.45.  (A wave per step, up to 512 of them, cost the reader half.)
-constexpr uint32_t kFixedRounds = 8;
+// ones of at most fixed_rounds() steps per wave (1.5 MiB out, 2.25 in, 2.1 both ways in the
+// default shapes): there the waves have no time to drift apart, and the counter's atomics, ~14 ns
+// each on one address and slower beside a kernel that fills the memory's queues, are no small part of
+// the launch.  With shares to 8, 16 and 24 rounds, us a call alone, and beside a reader over 8 GiB with the ms
+// that it loses per GiB moved: 1.1 MiB both ways 40.8, 41.8, - and 49.4 (1.34), 44.3 (1.48), -; 1.5 MiB out
+// 43.0, 42.3, 41.7 and 49.2 (1.06), 49.1 (1.05), 45.7 (0.76); 1.4 MiB in 42.3, 41.6, - and 50.6 (2.17), 45.6
+// (2.20), -; 2 MiB in 53.2, 52.6, 53.1 and 62.3 (1.88), 62.0 (1.85), 57.2 (1.99).  Eight launches of 2.5 MiB both
+// ways 480, 480, 486, of 2.25 MiB in 386, 386, 383, of 1.5 MiB out 268, 268, 264: both ways, where a
+// step is two tiles and the lists differ, the waves drift further apart.  (A wave per step,
+// up to 512 of them, cost the reader half.)
+constexpr uint32_t kFixedRounds = 24, kFixedRoundsBoth = 16;
+
+__host__ __device__ inline uint32_t fixed_rounds(const MoveParams &p)
+{
+    return p.out.tiles && p.in.tiles ? kFixedRoundsBoth : kFixedRounds;
+}
 
 template <typename V, int U, bool LINK, bool FULL>
 __device__ __forceinline__ void run_fixed(const MoveParams &p, const int32_t *__restrict__ out_ids,
@@ -498,7 +507,7 @@ __device__ __forceinline__ void move(const MoveParams &p, const int32_t *__restr
     if (LINK && p.clear && blockIdx.x == 0 && threadIdx.x < 2) p.clear[threadIdx.x] = 0u;
     const uint32_t n_steps = p.mix_q ? p.in.tiles : (p.out.tiles > p.in.tiles ? p.out.tiles : p.in.tiles);
     constexpr int UR = U < kMaxRaggedU ? U : kMaxRaggedU;  // what cut_tiles() cut by when tiles are not whole
-    if (!LINK || n_steps <= (uint64_t)kFixedRounds * n_waves) {
+    if (!LINK || n_steps <= (uint64_t)fixed_rounds(p) * n_waves) {
         if (p.full_tiles)
             run_fixed<V, U, LINK, true>(p, out_ids, out_slots, in_ids, in_slots, n_steps, wave, n_waves, lane);
         else

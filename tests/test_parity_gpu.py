@@ -628,11 +628,11 @@ def test_staged_rows_far_apart():
 @pytest.mark.parametrize("vecs", [128, 80])
 def test_rounds_of_the_default_launches(vecs):
     """Launches of the default shapes that end just before, at and just behind a full round of
-    their waves, from one round to nine, where steps are drawn: each direction, both, with a
+    their waves, from one round to 25, where steps are drawn: each direction, both, with a
     shorter list beside (in or out); every byte against the oracle."""
     per_block = 2 * vecs * 16 // 2048 or 1                                     # steps of 2 KiB of a block
-    blocks = sorted({max(1, (r * waves + d) // per_block) for waves, per in ((68, 1), (24, 2), (16, 2)) for r in (1, 2, 3, 8, 9)
-                     for d in (-per, 0, per) if r * waves * per < 640})
+    blocks = sorted({max(1, (r * waves + d) // per_block) for waves, per in ((68, 1), (24, 2), (16, 2)) for r in (1, 2, 3, 16, 17, 24, 25)
+                     for d in (-per, 0, per)})
     n = blocks[-1] + 1
     sh = W.KVShape(1, 1, 8 * vecs, 1, n_hbm_blocks=2 * n + 3, n_host_slots=2 * n + 1)
     rot = W.simple_rotation(sh, n, n, seed=vecs)
