@@ -376,17 +376,17 @@ __device__ __forceinline__ uint32_t drawn(uint32_t d)
 }
 
 // Fixed share: wave w of W takes steps w, w + W, ...  HBM-bound launches, and link-bound
-// ones of at most fixed_rounds() steps per wave (1.5 MiB out, 2.25 in, 2.1 both ways in the
+// ones of at most fixed_rounds() steps per wave (1.5 MiB out, 2.25 in, 1.1 both ways in the
 // default shapes): there the waves have no time to drift apart, and the counter's atomics, ~14 ns
 // each on one address and slower beside a kernel that fills the memory's queues, are no small part of
-// the launch.  With shares to 8, 16 and 24 rounds, us a call alone, and beside a reader over 8 GiB with the ms
-// that it loses per GiB moved: 1.1 MiB both ways 40.8, 41.8, - and 49.4 (1.34), 44.3 (1.48), -; 1.5 MiB out
-// 43.0, 42.3, 41.7 and 49.2 (1.06), 49.1 (1.05), 45.7 (0.76); 1.4 MiB in 42.3, 41.6, - and 50.6 (2.17), 45.6
-// (2.20), -; 2 MiB in 53.2, 52.6, 53.1 and 62.3 (1.88), 62.0 (1.85), 57.2 (1.99).  Eight launches of 2.5 MiB both
-// ways 480, 480, 486, of 2.25 MiB in 386, 386, 383, of 1.5 MiB out 268, 268, 264: both ways, where a
-// step is two tiles and the lists differ, the waves drift further apart.  (A wave per step,
-// up to 512 of them, cost the reader half.)
-constexpr uint32_t kFixedRounds = 24, kFixedRoundsBoth = 16;
+// the launch.  With shares to 8, 16 and 24 rounds one way, us a call alone, and beside a reader over 8 GiB with
+// the ms that it loses per GiB moved: 1.5 MiB out 43.0, 42.3, 41.7 and 49.2 (1.06), 49.1 (1.05), 45.7 (0.76);
+// 1.4 MiB in 42.3, 41.6, - and 50.6 (2.17), 45.6 (2.20), -; 2 MiB in 53.2, 52.6, 53.1 and 62.3 (1.88), 62.0
+// (1.85), 57.2 (1.99).  Eight launches of 1.5 MiB out 268, 268, 264.  Both ways, where a step is two
+// tiles, the waves drift further apart: with shares to 8, 12 and 16 rounds calls of one block of 1.3 MiB 44.6, 44.9,
+// 45.3, of five of 270 KiB 45.2, 46.0, 45.4, of one of 2 MiB 59.1, 59.1, 59.4 (beside the reader, though,
+// 1.1 MiB 49.4 (1.34), - and 44.3 (1.48)).  (A wave per step, up to 512 of them, cost the reader half.)
+constexpr uint32_t kFixedRounds = 24, kFixedRoundsBoth = 8;
 
 __host__ __device__ inline uint32_t fixed_rounds(const MoveParams &p)
 {
