@@ -241,9 +241,11 @@ def main():
 
     path_name = B.PATH_NAMES[st["path_used"]]
     # the kernel of the step: the move kernel (up to 448 blocks the one whose lists are arguments), or, on
-    # the DMA-staged path, the pack / unpack kernel (its bench-traffic line is per launch of that kernel, one chunk)
+    # the DMA-staged path, the pack / unpack kernel (its bench-traffic line is per launch of that kernel, one
+    # chunk; up to 896 blocks the one whose ids are arguments)
     inline_ids = len(rot.out_ids) + len(rot.in_ids) <= 448
-    kernel_name = "kv_stage_kernel" if path_name == "sdma_staged" else \
+    inline_chunk = min(max(len(rot.out_ids), len(rot.in_ids)), ((args.staging_mib or 256) << 20) // blk) <= 896
+    kernel_name = ("kv_stage_inline_kernel" if inline_chunk else "kv_stage_kernel") if path_name == "sdma_staged" else \
         "kv_move_inline_kernel" if inline_ids else "kv_move_kernel"
     traffic, traffic_src = measured_traffic(args.workload, path_name, kernel_name)
     res = {
