@@ -157,8 +157,8 @@ struct MoveIds {
 // A launch's shape: workgroups, lanes per workgroup, vectors per lane per tile;
 // short_steps: with no more steps than this, a wave per step; limit_u: the
 // vectors per lane by which dir_tiles() counts; through: it has waves enough to write
-// through to the pool; even: see grid_of().
-struct LinkShape { int wgs, lanes, u, short_steps, limit_u; bool through, even; };
+// through to the pool; even: see grid_of(); fixed_rounds: see run_fixed().
+struct LinkShape { int wgs, lanes, u, short_steps, limit_u; bool through, even; uint32_t fixed_rounds; };
 
 template <typename... P, typename... A>
 void launch(void (*kernel)(P...), dim3 g, dim3 b, hipStream_t s, hipEvent_t stop, const A &...args)
@@ -185,7 +185,7 @@ uint32_t grid_of(const LinkShape &sh, const MoveParams &p, uint32_t &steps)
     if (most == 0 || steps <= (uint32_t)sh.short_steps || most <= (uint32_t)sh.wgs) return std::max(1u, most);
     auto rounds = [&](uint32_t tiles, uint32_t wgs) { return ((tiles + waves_per_wg - 1) / waves_per_wg + wgs - 1) / wgs; };
     const uint32_t all = rounds(steps, (uint32_t)sh.wgs);
-    if (!sh.even || all > dkv::fixed_rounds(p)) return (uint32_t)sh.wgs;
+    if (!sh.even || all > p.fixed_rounds) return (uint32_t)sh.wgs;
     const uint32_t fewer = (most + all - 1) / all;
     return rounds(p.in.tiles, fewer) > rounds(p.in.tiles, (uint32_t)sh.wgs) ? (uint32_t)sh.wgs : fewer;
 }
@@ -195,7 +195,7 @@ bool draws(const LinkShape &sh, const MoveParams &p)
 {
     uint32_t steps;
     const uint64_t waves = (uint64_t)grid_of(sh, p, steps) * ((uint32_t)sh.lanes / dkv::kWave);
-    return steps > dkv::fixed_rounds(p) * waves;
+    return steps > p.fixed_rounds * waves;
 }
 
 // `stop` (may be nullptr) is recorded by the launch itself.
@@ -639,6 +639,7 @@ LinkShape link_shape(const kv_engine *e, LinkKind kind)
     const int64_t all = (int64_t)s.wgs * s.lanes / dkv::kWave, flight = all * std::max(1, kib);
     s.through = true;
     s.even = kind != kInHeavy;
+    s.fixed_rounds = kind == kOutOnly || kind == kInOnly ? dkv::kFixedRounds : dkv::kFixedRoundsBoth;
     if (!cw && !cl && !cu) return s;
     if (kind == kOutOnly) s.through = flight >= 64 && all >= 12 && s.wgs >= 4;
     if (kind == kInHeavy) s.through = flight >= 112 && s.wgs >= 4;
@@ -720,6 +721,7 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
     const bool fused = path == KV_PATH_FUSED && no > 0 && ni > 0;
     auto params = [&](const LinkShape &sh, unsigned int *claim, bool out, bool hold) {
         MoveParams q = base_params(e);
+        q.fixed_rounds = sh.fixed_rounds;
         q.through = out && writes_through(e) && (timed || (sh.through && !hold)) ? 1u : 0u;
         q.claim = claim;
         q.far_out = e->pool;
@@ -845,6 +847,24 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
     if (!fill_dir(p_out, (uint32_t)no, 0, sh_out.limit_u, p_out.out) ||
         !fill_dir(p_in, (uint32_t)ni, 0, sh_in.limit_u, p_in.in))
         return KV_EUNSUP;  // before anything is enqueued
+    // Fixed shares beside one another: both launches' waves take them, up to as many rounds as where a
+    // launch has the link to itself, or neither's do beyond the rounds of a launch that carries both
+    // directions.  Where one side has its shares and the other draws, the one that draws falls behind.  (us, out + in MiB,
+    // limits of 8 and 24 for each side by itself: 2.5 + 2.5 77.6 and 75.3, 3 + 3 89.9 and 86.3, 6 + 6 151.5 and
+    // 148.6, beside a reader 83.6 and 80.0, 94.9 and 91.2, 156.0 and 152.9; but 4 + 8, out 21 rounds and in 28, 171.8 and 175.7, in
+    // segments of 1200 bytes 184 and 192, 7 + 5 165 and 171, 6 + 7 168 and 183.)  Vectors of 8 bytes gain
+    // nothing (840-byte segments, 2.3 + 2.3 89 and 94, 2.8 + 1.9 88 and 91), and layer by layer, where a launch of one
+    // side meets several of the other, they lose (8 chunks of 3 + 3 MiB 670 and 754, 10 of 3 + 3 in 1680-byte segments
+    // 850 and 1110, 4 of 3.5 + 4.5 440 and 558; short chunks in the shapes of one direction gain: 16 of
+    // 0.8 + 0.8 458 and 432).  Configured launches keep to the fewer.
+    if (no > 0 && ni > 0) {
+        auto shares = [&](const LinkShape &sh, const MoveParams &p, uint32_t tiles) {
+            return (uint64_t)tiles * planes <= (uint64_t)dkv::kFixedRounds * (uint64_t)sh.wgs * (uint64_t)(sh.lanes / dkv::kWave) * p.n_planes;
+        };
+        const bool both = e->vec == 16 && !(pair && e->cfg.chunk_layers) && !e->cfg.max_copy_wgs && !e->cfg.wg_lanes && !e->cfg.vecs_per_lane &&
+                          shares(sh_out, p_out, p_out.out.tiles) && shares(sh_in, p_in, p_in.in.tiles);
+        p_out.fixed_rounds = p_in.fixed_rounds = both ? dkv::kFixedRounds : dkv::kFixedRoundsBoth;
+    }
     // The block table promises that no block or slot is overwritten while an
     // earlier transfer still reads it, and none read while an earlier one still
     // writes it.  Its lists are conflict-free within a call but reuse, across
@@ -1133,7 +1153,7 @@ int run_staged(kv_engine *e, int k, const int32_t *oi, const int32_t *os, int32_
     int32_t *d_out = dd, *d_in = dd + 2 * (size_t)no;
     constexpr int U = 4;                         // capped launches: persistent waves, 4 KiB tiles
     const int cap_wgs = e->cfg.max_copy_wgs;     // 0: one wave per 1 KiB tile, kv_stage_kernel
-    const LinkShape capped{cap_wgs, dkv::kThreads, U, 0, U, false, false};
+    const LinkShape capped{cap_wgs, dkv::kThreads, U, 0, U, false, false, 0};
     ChunkPlan po{}, pi{};
     if (no > 0) {
         int rc = plan_chunks(e, (uint32_t)no, po);
@@ -1809,6 +1829,7 @@ int kv_rotate_static(const kv_config *cfg, void *hbm_cache, void *host_pool, voi
     const LinkKind kind = no == 0 ? kInOnly : ni == 0 ? kOutOnly : ni >= 2 * (int64_t)no ? kInHeavy : kBoth;
     const LinkShape sh = link_shape(e, kind);
     MoveParams p = base_params(e);
+    p.fixed_rounds = sh.fixed_rounds;
     p.through = writes_through(e) && sh.through && !leaves_to_l2(e, os, no, ni) ? 1u : 0u;
     p.far_out = p.far_in = e->pool;
     pool_strides(e, p.far_slot_stride_out, p.far_plane_stride_out);

@@ -141,6 +141,7 @@ struct MoveParams {
     // beside a launch on another stream, wave 0 was up to 19 us later.
     u64x2 *stamps;
     uint32_t drain;
+    uint32_t fixed_rounds;  // link-bound launches of at most this many steps per wave take fixed shares
     DirDesc out, in;
 };
 
@@ -376,8 +377,10 @@ __device__ __forceinline__ uint32_t drawn(uint32_t d)
 }
 
 // Fixed share: wave w of W takes steps w, w + W, ...  HBM-bound launches, and link-bound
-// ones of at most fixed_rounds() steps per wave (1.5 MiB out, 2.25 in, 1.1 both ways in the
-// default shapes): there the waves have no time to drift apart, and the counter's atomics, ~14 ns
+// ones of at most MoveParams::fixed_rounds steps per wave, which the host sets: kFixedRounds where a
+// launch carries one direction (1.5 MiB out, 2.25 in, by the default shapes of whole tiles),
+// kFixedRoundsBoth where it carries two (1.1 MiB); two launches beside one another: see run_zero_copy().
+// In those the waves have no time to drift apart, and the counter's atomics, ~14 ns
 // each on one address and slower beside a kernel that fills the memory's queues, are no small part of
 // the launch.  With shares to 8, 16 and 24 rounds one way, us a call alone, and beside a reader over 8 GiB with
 // the ms that it loses per GiB moved: 1.5 MiB out 43.0, 42.3, 41.7 and 49.2 (1.06), 49.1 (1.05), 45.7 (0.76);
@@ -387,11 +390,6 @@ __device__ __forceinline__ uint32_t drawn(uint32_t d)
 // 45.3, of five of 270 KiB 45.2, 46.0, 45.4, of one of 2 MiB 59.1, 59.1, 59.4 (beside the reader, though,
 // 1.1 MiB 49.4 (1.34), - and 44.3 (1.48)).  (A wave per step, up to 512 of them, cost the reader half.)
 constexpr uint32_t kFixedRounds = 24, kFixedRoundsBoth = 8;
-
-__host__ __device__ inline uint32_t fixed_rounds(const MoveParams &p)
-{
-    return p.out.tiles && p.in.tiles ? kFixedRoundsBoth : kFixedRounds;
-}
 
 template <typename V, int U, bool LINK, bool FULL>
 __device__ __forceinline__ void run_fixed(const MoveParams &p, const int32_t *__restrict__ out_ids,
@@ -507,7 +505,7 @@ __device__ __forceinline__ void move(const MoveParams &p, const int32_t *__restr
     if (LINK && p.clear && blockIdx.x == 0 && threadIdx.x < 2) p.clear[threadIdx.x] = 0u;
     const uint32_t n_steps = p.mix_q ? p.in.tiles : (p.out.tiles > p.in.tiles ? p.out.tiles : p.in.tiles);
     constexpr int UR = U < kMaxRaggedU ? U : kMaxRaggedU;  // what cut_tiles() cut by when tiles are not whole
-    if (!LINK || n_steps <= (uint64_t)fixed_rounds(p) * n_waves) {
+    if (!LINK || n_steps <= (uint64_t)p.fixed_rounds * n_waves) {
         if (p.full_tiles)
             run_fixed<V, U, LINK, true>(p, out_ids, out_slots, in_ids, in_slots, n_steps, wave, n_waves, lane);
         else

@@ -1,0 +1,46 @@
+"""The launches that calls become, on the CPU: the engine's host code against a stand-in for the
+HIP runtime that notes every launch."""
+import os
+
+import pytest
+
+from paper_2601_20309_amd import binding as B
+from tests import launches as L
+
+pytestmark = pytest.mark.skipif(not os.path.exists(L.HIPCC), reason="needs hipcc")
+
+
+@pytest.fixture(scope="module")
+def exe(tmp_path_factory):
+    return L.build(str(tmp_path_factory.mktemp("launches")))
+
+
+def test_two_launches_at_once_both_take_shares_or_neither(exe):
+    """Both directions by a kernel each: fixed shares on both sides up to 24 rounds of each
+    side's waves, else drawn steps beyond 8 rounds; vectors of 8 bytes, configured launches and chunks
+    of layers of 1 MiB and more always by 8; a launch that has the link to itself by 24, one that carries both ways by 8."""
+    zero = B.KV_PATH_ZEROCOPY
+
+    def drawn(out_kib, in_kib, dim, **kw):
+        block = 4 * dim * kw.get("layers", 1)
+        kw = {"path": zero, **kw}
+        got = L.launches(exe, [L.move(out_kib * 1024 // block, in_kib * 1024 // block, dim, **kw)])[0]
+        return [x["drawn"] for x in got]
+
+    whole = 2048                                                               # segments of 4 KiB: rounds of 288 KiB each way
+    assert drawn(3000, 3000, whole) == [0, 0]
+    assert drawn(24 * 288, 24 * 288, whole) == [0, 0]
+    assert drawn(24 * 288, 24 * 288 + 8, whole) == [1, 1]
+    assert drawn(24 * 288 + 8, 24 * 288, whole) == [1, 1]
+    assert drawn(7000, 5000, whole) == [1, 1]
+    assert drawn(7000, 2304, whole) == [1, 0]                                  # 8 rounds in: over before it matters
+    assert drawn(7000, 2312, whole) == [1, 1]
+    assert drawn(24 * 192, 2 * 24 * 192, whole) == [1, 1]                      # in-heavy: rounds of 192 KiB out and of 288 in
+    assert drawn(16 * 192, 24 * 288, whole) == [0, 0]
+    assert drawn(6000, 6000, whole, layers=8, chunk_layers=4) == [1] * 4       # 3000 KiB a launch, layer by layer
+    assert drawn(1800, 1800, whole, layers=8, chunk_layers=4) == [0] * 4       # under 1 MiB: rounds of 64 and 96 KiB
+    assert drawn(2000, 2000, 420, host_layout=1) == [1, 1]                     # 840-byte segments: 8-byte vectors
+    assert drawn(3000, 3000, whole, vecs_per_lane=2, wg_lanes=64) == [1, 1]
+    assert drawn(1500, 0, whole) == [0] and drawn(0, 2200, whole) == [0]
+    assert drawn(1700, 0, whole) == [1] and drawn(0, 2400, whole) == [1]
+    assert drawn(1000, 1000, whole, path=B.KV_PATH_AUTO) == [0] and drawn(1200, 1200, whole, path=B.KV_PATH_AUTO) == [1]
