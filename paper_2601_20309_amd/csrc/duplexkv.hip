@@ -562,9 +562,15 @@ int mark_end(kv_engine *e, bool out_side, int k, hipStream_t s)
 // 40 MiB, us, without and with: 840-byte segments 761 and 744, 180-byte 1374 and 998, 3360-byte 754
 // and 740, of 1200 bytes in blocks of 57600 751 and 742).
 // Vectors narrower than 16 bytes (odd segments or pointers) also get more of them per lane, and where
-// 8-byte ones have one a lane nevertheless, what moves in gets 1.5 times the waves (24 MiB both ways / in, us,
-// without and with: 200-byte segments 572 / 579 and 508 / 445, layer-first 1192-byte ones 567 / 572 and 532 /
-// 489; one direction out is the same, and both ways in tiles not half full, 200 bytes layer-first, lose: 751, 795).
+// 8-byte ones have one a lane nevertheless, what moves in gets 1.5 times the waves: alone always, both ways
+// where groups are several tiles of which no more than a third is empty.  (us without and with, layer-first; beside a
+// reader over 8 GiB, and the ms that it loses per GiB moved, behind the semicolon.  24 MiB both ways: segments of 1048
+// bytes 596 and 564, 1160 591 and 558; 563 (2.5) and 469 (3.5) for 20 MiB, 1400 599 and 571, 200 bytes in blocks of 3200 619
+// and 556; 604 (2.9) and 467 (3.1) for 20 MiB.  But a third empty and more, 1000 bytes 588 and 591, 2 MiB 70.5 and 72.6,
+// and single tiles, 360 bytes 665 and 692, 2 MiB 75.6 and 78.1, 392 bytes 653 and 677.  1 MiB out with 2.4 in:
+// 1048 bytes 75.6 and 76.6, 1400 bytes 71.8 and 70.4; 10 with 24, 1048 bytes 524 and 515, 1160 516 and 505.  24 MiB in: 392 bytes 619 and 600; 588 (5.1) and
+// 512 (8.2) for 20 MiB, 1160 579 and 501; 572 (4.6) and 437 (5.3), 200 in blocks 596 and 467; 586 (5.3) and 423 (4.8).
+// One direction out is the same.)
 // Now and before all of this and line_mask, us for 40 MiB both ways / out / in: segments of
 // 1200 bytes 835 / 736 / 731 (856 / 756 / 744), in a layer-first pool 876 / 749 / 802 (968 /
 // 830 / 820), of 840 bytes there 945 / 756 / 838 (1150 / 870 / 1350).  All of this
@@ -628,7 +634,8 @@ LinkShape link_shape(const kv_engine *e, LinkKind kind)
     const bool parted = e->vec < 16 || (kind == kInOnly && (align < dkv::kStretch || !whole(u)));
     waves = (int)(waves * std::min(4.0, (parted && fill >= 0.5 ? 1.4 : 1.0) / fill));
     // tiles of 512 bytes: what comes in is half of what the table counts on
-    if (e->vec == 8 && cut == 1 && (kind == kInOnly || (kind != kOutOnly && fill >= 0.5))) waves += waves / 2;
+    const bool several = group_vecs(vec_per_seg, planes, plane_major, whole(u)) > (uint64_t)dkv::kWave * (uint64_t)cut;
+    if (e->vec == 8 && cut == 1 && (kind == kInOnly || (kind != kOutOnly && several && fill >= 2.0 / 3))) waves += waves / 2;
     LinkShape s;
     s.u = u;
     s.limit_u = limit_u;

@@ -44,3 +44,24 @@ def test_two_launches_at_once_both_take_shares_or_neither(exe):
     assert drawn(1500, 0, whole) == [0] and drawn(0, 2200, whole) == [0]
     assert drawn(1700, 0, whole) == [1] and drawn(0, 2400, whole) == [1]
     assert drawn(1000, 1000, whole, path=B.KV_PATH_AUTO) == [0] and drawn(1200, 1200, whole, path=B.KV_PATH_AUTO) == [1]
+
+
+def test_more_waves_for_tiles_of_512_bytes(exe):
+    """8-byte vectors in tiles of 64: what comes in alone gets 1.5 times the waves, both ways only
+    where groups are several tiles no more than a third empty (segments of a layer-first pool; blocks of a block-first one)."""
+    def waves(seg, out_mib, in_mib, **kw):
+        kw = {"host_layout": 1, "layers": 4, **kw}
+        block = 2 * kw["layers"] * seg
+        return L.launches(exe, [L.move((out_mib << 20) // block, (in_mib << 20) // block, seg // 2, **kw)])[0][0]["waves"]
+
+    def base(table, vecs, tiles):
+        return int(table * 1.4 / (vecs / (64 * tiles)))
+
+    for seg, vecs, tiles, more in [(328, 41, 1, False), (360, 45, 1, False), (392, 49, 1, False), (1000, 125, 3, False),
+                                   (1016, 127, 3, False), (1048, 131, 3, True), (1160, 145, 3, True), (1400, 175, 3, True)]:
+        both, heavy, alone = base(120, vecs, tiles), base(112, vecs, tiles), base(80, vecs, tiles)
+        assert waves(seg, 24, 24) == both + both // 2 * more, seg
+        assert waves(seg, 12, 30) == heavy + heavy // 2 * more, seg
+        assert waves(seg, 0, 30) == alone + alone // 2, seg
+        assert waves(seg, 30, 0) == base(64, vecs, tiles), seg
+    assert waves(200, 24, 24, host_layout=0, layers=8) == base(120, 400, 7) * 3 // 2
