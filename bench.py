@@ -47,6 +47,27 @@ def measured_traffic(workload, path, kernel):
     return None, None
 
 
+def step_kernels(path, shape, layout, n_out, n_in, chunk_layers=0, max_copy_wgs=0, staging_bytes=0):
+    """Names of the kernels that a step launches, each once: the move kernel (up to 448 blocks of
+    16-byte vectors the one whose lists are arguments), or, on the DMA-staged path, the pack / unpack kernel of
+    each direction's chunks (up to 896 blocks the one whose ids are arguments; the move kernel under a
+    workgroup cap)."""
+    seg = shape.block_size * shape.n_kv_heads * shape.head_dim * shape.elem_bytes
+    if path != "sdma_staged":
+        return ["kv_move_inline_kernel" if n_out + n_in <= 448 and seg % 16 == 0 else "kv_move_kernel"]
+    if max_copy_wgs:
+        return ["kv_move_kernel"]
+    cap, names = staging_bytes or 256 << 20, []
+    for n in (n_out, n_in):
+        if layout == 0:                             # block-first: whole blocks, or their planes of a chunk of layers
+            planes = min(2 * (chunk_layers or shape.n_layers), 2 * shape.n_layers, max(2, cap // seg // 2 * 2))
+            blocks = min(n, cap // (planes * seg))
+        else:                                       # layer-first: the whole list, layer by layer
+            blocks = min(n, cap // (2 * seg))
+        names.append("kv_stage_inline_kernel" if blocks <= 896 else "kv_stage_kernel")
+    return sorted(set(names))
+
+
 def host_topology():
     """NUMA nodes with their CPU lists, and the CPUs this process may run on."""
     nodes = {}
@@ -240,13 +261,9 @@ def main():
         log("whole cache verified after the timed loop")
 
     path_name = B.PATH_NAMES[st["path_used"]]
-    # the kernel of the step: the move kernel (up to 448 blocks the one whose lists are arguments), or, on
-    # the DMA-staged path, the pack / unpack kernel (its bench-traffic line is per launch of that kernel, one
-    # chunk; up to 896 blocks the one whose ids are arguments)
-    inline_ids = len(rot.out_ids) + len(rot.in_ids) <= 448
-    inline_chunk = min(max(len(rot.out_ids), len(rot.in_ids)), ((args.staging_mib or 256) << 20) // blk) <= 896
-    kernel_name = ("kv_stage_inline_kernel" if inline_chunk else "kv_stage_kernel") if path_name == "sdma_staged" else \
-        "kv_move_inline_kernel" if inline_ids else "kv_move_kernel"
+    kernels = step_kernels(path_name, shape, layout, len(rot.out_ids), len(rot.in_ids), args.chunk_layers, args.max_copy_wgs,
+                           args.staging_mib << 20)
+    kernel_name = " and ".join(kernels)             # no profile covers a step of two kernels
     traffic, traffic_src = measured_traffic(args.workload, path_name, kernel_name)
     res = {
         "metric": "duplex KV rotation GB/s (out+in) and % of measured host-link peak",

@@ -65,3 +65,22 @@ def test_more_waves_for_tiles_of_512_bytes(exe):
         assert waves(seg, 0, 30) == alone + alone // 2, seg
         assert waves(seg, 30, 0) == base(64, vecs, tiles), seg
     assert waves(200, 24, 24, host_layout=0, layers=8) == base(120, 400, 7) * 3 // 2
+
+
+@pytest.mark.parametrize("layout", [B.KV_HOST_BLOCK_FIRST, B.KV_HOST_LAYER_FIRST])
+def test_bench_names_the_kernels_that_run(exe, layout):
+    """bench.py names the kernel of its step from the call's sizes: the engine launches that one,
+    in either pool layout, with chunks of layers, under a workgroup cap, and with lists of different lengths."""
+    import bench
+    from paper_2601_20309_amd import workloads as W
+    sh = W.KVShape(32, 8, 128, 16, n_hbm_blocks=9, n_host_slots=9)            # blocks of 2 MiB
+    small = W.KVShape(2, 1, 128, 16, n_hbm_blocks=9, n_host_slots=9)          # of 16 KiB
+    plans = [(s, path, n_out, n_in, kw) for s in (sh, small) for path in ("sdma_staged", "fused", "zerocopy")
+             for n_out, n_in in ((128, 128), (224, 224), (224, 225), (900, 2000), (2000, 700), (896, 897))
+             for kw in ({}, {"chunk_layers": 1}, {"max_copy_wgs": 8})]
+    code = {name: n for n, name in B.PATH_NAMES.items()}
+    got = L.launches(exe, [L.move(no, ni, s.head_dim, layers=s.n_layers, heads=s.n_kv_heads, tokens=s.block_size, path=code[path],
+                                  host_layout=layout, **kw) for s, path, no, ni, kw in plans])
+    for (s, path, no, ni, kw), launches in zip(plans, got):
+        named = bench.step_kernels(path, s, layout, no, ni, **kw)
+        assert set(named) == {x["kernel"] for x in launches}, (s.n_layers, path, no, ni, kw)
