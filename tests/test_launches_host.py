@@ -84,3 +84,59 @@ def test_bench_names_the_kernels_that_run(exe, layout):
     for (s, path, no, ni, kw), launches in zip(plans, got):
         named = bench.step_kernels(path, s, layout, no, ni, **kw)
         assert set(named) == {x["kernel"] for x in launches}, (s.n_layers, path, no, ni, kw)
+
+
+def kinds(n, dim, **kw):
+    return [L.move(n, n, dim, **kw), L.move(n, 0, dim, **kw), L.move(0, n, dim, **kw)]
+
+
+@pytest.mark.parametrize("layout", [B.KV_HOST_BLOCK_FIRST, B.KV_HOST_LAYER_FIRST])
+@pytest.mark.parametrize("dim,tokens", list(L.SHARES))
+def test_lengths_that_end_the_fixed_share(exe, dim, tokens, layout):
+    """L.SHARES: by a block more the waves draw, both ways, out and in, at every vector width."""
+    for kind, n in enumerate(L.SHARES[dim, tokens][layout]):
+        kw = dict(dim=dim, tokens=tokens, layers=6, host_layout=layout)
+        below, above = L.launches(exe, [kinds(n, **kw)[kind], kinds(n + 1, **kw)[kind]])
+        assert [below[0]["drawn"], above[0]["drawn"]] == [0, 1], kind
+
+
+@pytest.mark.parametrize("vecs", list(L.ROUNDS))
+def test_rounds_of_the_default_shapes(exe, vecs):
+    """L.ROUNDS: the waves and steps that the engine launches, full rounds and the end of the fixed share between two of the lengths."""
+    lengths = L.round_lengths(vecs)
+    for kind, (waves, steps) in enumerate(L.ROUNDS[vecs]):
+        got = {n: L.launches(exe, [kinds(n, 8 * vecs)[kind]])[0][0] for n in lengths}
+        assert got[max(lengths)]["waves"] == waves and all(x["steps"] == n * steps for n, x in got.items())
+        limit = L.BOTH_WAYS if kind == 0 else L.ONE_WAY
+        for r in (1, 2, 3, limit):
+            n = r * waves // steps
+            assert n in got and n + 1 in got and n * steps <= r * waves < (n + 1) * steps
+        assert [got[n]["drawn"] for n in (limit * waves // steps, limit * waves // steps + 1)] == [0, 1]
+
+
+@pytest.mark.parametrize("vecs", [64, 75])
+@pytest.mark.parametrize("wgs,lanes", [(1, 64), (3, 64), (1, 256), (2, 320)])
+def test_lengths_around_the_limits_of_configured_shapes(exe, wgs, lanes, vecs):
+    """L.configured_lengths: of each kind some take fixed shares and some draw, the nearest two a block apart, and some draw four steps at a time."""
+    lengths = L.configured_lengths(wgs, lanes, vecs)
+    for kind in range(3):
+        got = [L.launches(exe, [kinds(n, 8 * vecs, layers=2, max_copy_wgs=wgs, wg_lanes=lanes, vecs_per_lane=1)[kind]])[0][0] for n in lengths]
+        drawn = [x["drawn"] for x in got]
+        first = drawn.index(1)
+        assert drawn == sorted(drawn) and first > 0 and lengths[first] == lengths[first - 1] + 1
+        assert got[-1]["waves"] == wgs * lanes // 64 and got[-1]["steps"] > 9 * got[-1]["waves"]
+
+
+def test_tiles_of_short_reader_passes(exe):
+    """Rows of a tile: even and at most eight, with no more rows than a wave's share makes them in as
+    many rounds; tiles cover the list; from 13 rows a wave on tiles of eight."""
+    for wgs in (0, 1, 3, 300):
+        waves = 4 * (wgs or 1408)
+        ns = sorted({max(1, rows * waves // 2 + d) for rows in range(1, 14) for d in (-1, 0, 1)})  # blocks of two rows
+        for n, got in zip(ns, L.launches(exe, [L.read(n, 512, max_wgs=wgs) for n in ns])):
+            x = got[-1]
+            each = -(-2 * n // waves)
+            rounds = -(-each // 8)
+            want = -(-each // rounds)
+            assert x["rows"] == (want + want % 2 if each <= 12 else 8), (wgs, n)
+            assert x["tiles"] * 4 * x["rows"] >= 2 * n > (x["tiles"] - 1) * 4 * x["rows"]

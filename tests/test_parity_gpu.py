@@ -10,6 +10,7 @@ from paper_2601_20309_amd import binding as B
 from paper_2601_20309_amd import workloads as W
 from tests.gpu_harness import GpuCase, make_case
 from tests import kvviews as V
+from tests import launches as L
 
 pytestmark = pytest.mark.gpu
 
@@ -496,17 +497,15 @@ def test_staged_copies_of_several_rows(host_layout, tokens, heads, chunk_layers,
 @pytest.mark.parametrize("vecs", [64, 75])
 @pytest.mark.parametrize("wgs,lanes", [(1, 64), (3, 64), (1, 256), (2, 320)])
 def test_launches_at_the_edge_of_the_fixed_share(wgs, lanes, vecs):
-    """Launches of up to six steps per wave take fixed shares, longer ones draw from the
-    counter, which the next call finds at zero: one to a few steps around one, six and
-    fourteen rounds of the launch's waves (where all draws are single, and where the
-    first are of four), each direction and both, whole tiles and partly empty ones,
-    every byte against the oracle."""
-    waves = wgs * lanes // 64
-    per_block = 4 * vecs // 64 if vecs % 64 == 0 else -(-4 * vecs // 64)          # steps of a block, tiles of 64 vectors
-    lengths = sorted({max(1, (r * waves + d) // per_block) for r in (1, 6, 14) for d in (-1, 0, per_block, 3 * per_block)})
+    """Launches of up to 24 steps per wave one way and eight both ways take fixed shares, longer
+    ones draw from the counter, which the next call finds at zero: around one round of the
+    launch's waves, both limits, fourteen and 33 rounds (draws of four steps as well as
+    single ones), each direction and both, whole tiles and partly empty ones, every byte
+    against the oracle."""
+    lengths = L.configured_lengths(wgs, lanes, vecs)
     n = 2 * max(lengths) + 2
     sh = W.KVShape(2, 1, 8 * vecs, 1, n_hbm_blocks=n + 5, n_host_slots=n + 3)
-    rot = W.simple_rotation(sh, max(lengths), max(lengths), seed=vecs + waves)
+    rot = W.simple_rotation(sh, max(lengths), max(lengths), seed=vecs + wgs * lanes // 64)
     case, _ = make_case(sh, B.KV_HOST_BLOCK_FIRST, B.KV_PATH_AUTO, rot=rot, max_copy_wgs=wgs, wg_lanes=lanes, vecs_per_lane=1)
     for k in lengths:
         part = W.Rotation(rot.out_ids[:k], rot.out_slots[:k], rot.in_ids[:k], rot.in_slots[:k])
@@ -628,11 +627,9 @@ def test_staged_rows_far_apart():
 @pytest.mark.parametrize("vecs", [128, 80])
 def test_rounds_of_the_default_launches(vecs):
     """Launches of the default shapes that end just before, at and just behind a full round of
-    their waves, from one round to 25, where steps are drawn: each direction, both, with a
+    their waves, from one round to the first launch that draws its steps: each direction, both, with a
     shorter list beside (in or out); every byte against the oracle."""
-    per_block = 2 * vecs * 16 // 2048 or 1                                     # steps of 2 KiB of a block
-    blocks = sorted({max(1, (r * waves + d) // per_block) for waves, per in ((68, 1), (24, 2), (16, 2)) for r in (1, 2, 3, 8, 9, 24, 25)
-                     for d in (-per, 0, per)})
+    blocks = L.round_lengths(vecs)
     n = blocks[-1] + 1
     sh = W.KVShape(1, 1, 8 * vecs, 1, n_hbm_blocks=2 * n + 3, n_host_slots=2 * n + 1)
     rot = W.simple_rotation(sh, n, n, seed=vecs)
@@ -740,23 +737,16 @@ def test_rest_of_an_out_heavy_rotation_moves_its_own_blocks(layers, n_out, n_in,
     case.close()
 
 
-# What launches of the default shapes move, KiB per direction, with eight steps per wave, up to
-# which waves take fixed shares: rotations and swap-outs in a block-first pool, then layer-first.
-EIGHT_STEPS = {(128, 16): ((1088, 512), (1088, 512)), (65, 8): ((960, 510), (1081, 569)), (60, 7): ((1512, 803), (1339, 715)),
-               (20, 5): ((671, 356), (480, 255)), (18, 5): ((336, 178), (335, 179)), (9, 5): ((168, 89), (167, 89))}
-
-
 @pytest.mark.parametrize("host_layout", LAYOUTS)
-@pytest.mark.parametrize("dim,tokens", list(EIGHT_STEPS))
+@pytest.mark.parametrize("dim,tokens", list(L.SHARES))
 def test_stores_into_the_pool_at_every_vector_width(dim, tokens, host_layout):
     """Segments of 4096 and 1040 (16-byte vectors), 840 and 200 (8), 180 (4) and 90 bytes
     (2): what reaches the pool, written through or not, is every byte of the named slots
-    and no other, just below and just above the eight steps per wave up to which waves
-    take fixed shares, and over bytes that an earlier call left there."""
-    sh = W.KVShape(6, 1, dim, tokens, n_hbm_blocks=1, n_host_slots=1)
+    and no other, and what leaves it is, in calls of 30 KiB and of the most blocks that waves
+    move by fixed shares and one more, both ways and each, and over bytes that an earlier call left there."""
     block = 12 * 2 * dim * tokens
-    limits = EIGHT_STEPS[dim, tokens][0 if host_layout == B.KV_HOST_BLOCK_FIRST else 1]
-    counts = sorted({max(1, int(kib * 1024 / block)) for kib in (30, *(x * y for x in limits for y in (0.93, 1.07)))})
+    both, out, into = L.SHARES[dim, tokens][0 if host_layout == B.KV_HOST_BLOCK_FIRST else 1]
+    counts = sorted({max(1, 30 * 1024 // block), both, both + 1, 2 * both, out, out + 1, into, into + 1})
     n = counts[-1]
     sh = W.KVShape(6, 1, dim, tokens, n_hbm_blocks=2 * n + 7, n_host_slots=2 * n + 5)
     rot = W.simple_rotation(sh, n, n, seed=dim)
@@ -766,6 +756,8 @@ def test_stores_into_the_pool_at_every_vector_width(dim, tokens, host_layout):
         case.rotate(part)
         case.swap_out(rot.in_ids[:k], rot.out_slots[:k][::-1].copy())
         case.rotate(part.inverse())
+        case.check()
+        case.swap_in(rot.out_slots[:k], rot.in_ids[:k][::-1].copy())
         case.check()
     case.close()
 

@@ -133,23 +133,23 @@ def test_reader_lists_in_arguments(blocks, vecs):
     eng.kv_destroy()
 
 
-@pytest.mark.parametrize("vecs", [64, 192, 105])
+@pytest.mark.parametrize("vecs", [64, 192, 105, 2048])
 def test_reader_short_passes(vecs):
     """Passes of every number of rows per wave up to the most that counts as short and one
     more, where tiles go back to eight rows: the last workgroup's tile full, of one row and
     of one vector, lists in the arguments, there in pairs and in memory, whole rows to a
-    segment and rows that straddle them, a whole grid and a few workgroups."""
-    nb = 2100
+    segment and rows that straddle them, the whole grid (there up to 75 MiB) and a few workgroups."""
+    nb = 2100 if vecs == 2048 else 20000
     sh = W.KVShape(1, 1, 8 * vecs, 1, n_hbm_blocks=nb, n_host_slots=4)
     cache = torch.randint(-2**62, 2**62, (2, nb, 2 * vecs), device="cuda")
     block = sum((w & 0xFFFFFFFF).sum(1) + ((w >> 32) & 0xFFFFFFFF).sum(1) for w in cache).cpu().numpy()
     torch.cuda.synchronize()
     eng = B.Engine(B.make_config(sh), cache.data_ptr())
     rng = np.random.default_rng(vecs)
-    for wgs in (1, 3, 40, 150, 300):
+    for wgs in (1, 3, 40, 150, 300, 0):
         for rows in range(1, 14):
-            most = rows * 4 * wgs * 64 // (2 * vecs)                     # blocks that this many rows a wave hold
-            for n in {most - 1, most, most + 1, most - 2 * wgs} & set(range(1, 2 * nb + 1)):
+            most = rows * 4 * (wgs or 1408) * 64 // (2 * vecs)           # blocks that this many rows a wave hold
+            for n in {most - 1, most, most + 1, most - 2 * (wgs or 1408)} & set(range(1, 2 * nb + 1)):
                 ids = rng.integers(0, nb, n).astype(np.int32)
                 passes = 1 + n % 2
                 assert eng.kv_reader_start(ids, passes, wgs) == 0
