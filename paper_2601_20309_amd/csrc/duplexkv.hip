@@ -352,9 +352,11 @@ uint32_t line_mask(int vec, uint32_t align, uint64_t group, uint32_t tile)
 // lane; align: what groups begin on multiples of on the far side; out: the launch writes there.
 // Segments that are whole tiles but begin inside stretches are then cut like others: taken as
 // they lie, every access would begin and end in a part of one, and each part, written
-// through, is a write of its own on the link.  (24 MiB both ways / out, us, taken as they lie and so:
-// segments of 4 KiB and of 32 KiB in a pool 128 bytes behind a stretch 535 / 473 and 501 / 443; pool 16
-// bytes behind a line, 64 MiB, 32 KiB segments 1667 / 1216 and 1340 / 1190, by lines.)
+// through, is a write of its own on the link.  (24 MiB both ways / out, us, taken as they lie and so, in a pool 128
+// bytes behind a stretch: layer-first segments of 1 KiB 575 / 498 and 555 / 471, 2 KiB 555 / 493 and 535 / 465, 4 KiB 553 /
+// 487 and 528 / 459; 8-byte vectors, whose tiles then have no lines to begin on but may be wider ones, 512 bytes 605 / 476
+// and 605 / 476, 2 KiB 540 / 455 and 532 / 455.  16 bytes behind a line: 1 KiB 574 / 472 and 574 / 472, 2 KiB 621 / 470
+// and 546 / 466; 64 MiB, 32 KiB segments 1667 / 1216 and 1340 / 1190, by lines.)
 void cut_tiles(MoveParams &p, int vec, int u, uint32_t align, bool out)
 {
     const bool whole = p.vec_per_seg % ((uint32_t)dkv::kWave * (uint32_t)u) == 0 && !(out && inside_lines(vec, align));
@@ -571,9 +573,10 @@ int mark_end(kv_engine *e, bool out_side, int k, hipStream_t s)
 // 1048 bytes 75.6 and 76.6, 1400 bytes 71.8 and 70.4; 10 with 24, 1048 bytes 524 and 515, 1160 516 and 505.  24 MiB in: 392 bytes 619 and 600; 588 (5.1) and
 // 512 (8.2) for 20 MiB, 1160 579 and 501; 572 (4.6) and 437 (5.3), 200 in blocks 596 and 467; 586 (5.3) and 423 (4.8).
 // One direction out is the same.)
-// Now and before all of this and line_mask, us for 40 MiB both ways / out / in: segments of
-// 1200 bytes 835 / 736 / 731 (856 / 756 / 744), in a layer-first pool 876 / 749 / 802 (968 /
-// 830 / 820), of 840 bytes there 945 / 756 / 838 (1150 / 870 / 1350).  All of this
+// Now, with tiles on lines instead of stretches and before all of this and line_mask (on another card), us for 40 MiB
+// both ways / out / in: segments of 1200 bytes 854 / 753 / 750 (855 / 754 / 762; 856 / 756 / 744), in a
+// layer-first pool 903 / 773 / 825 (921 / 796 / 828; 968 / 830 / 820), of 840 bytes there 974 / 781 / 862 (979 / 783 /
+// 866; 1150 / 870 / 1350).  All of this
 // goes by the tiles as they are cut, configured vectors or not: segments of 1000 vectors
 // with vecs_per_lane = 8 are cut by 4, and with the waves of 8 moved at 86 / 56 / 44 GB/s
 // both ways / out / in, with those of 4 at 99 / 56 / 57.
@@ -832,7 +835,10 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
     // the larger share of fewer, wider waves does better: it leaves the reads their rate (out + in MiB, us with
     // 288 x U 1 each and with 96 + 144 x U 2: 32 + 64 1262 and 1189, 16 + 64 1226 and 1189, 4 + 8 182
     // and 171).  A launch of less than kPairBytes is over before the rate counts: it has the shape
-    // of one direction (8 + 8 blocks of 16 KiB 23.0 and 20.8, 30 + 30 31.3 and 29.3; 2 + 2 MiB 64.7 and 66.8).
+    // of one direction (8 + 8 blocks of 16 KiB 23.0 and 20.8, 30 + 30 31.3 and 29.3; 2 + 2 MiB 64.7 and 66.8), also
+    // layer by layer, where many follow one another: in chunks of 800 + 800 KiB 16 in 464 and 424, of 937 + 937 80 in 2514
+    // and 2256, of 256 + 256 80 in 1179 and 1044, of 64 + 64 80 in 700 and 702.  (Beside a reader 485 and 458, 2514 and 2418,
+    // 1190 and 1222, 859 and 861; it loses 10.5 and 2.0, 9.6 and 1.7, 9.1 and 3.5, 8.9 and 8.6 ms per GiB moved.)
     LinkShape sh_out = link_shape(e, kOutOnly), sh_in = link_shape(e, kInOnly);
     constexpr uint64_t kPairBytes = 1ull << 20;
     const uint64_t planes = e->cfg.chunk_layers > 0 ? std::min(2u * (uint32_t)e->cfg.chunk_layers, e->n_planes) : e->n_planes;
@@ -1186,7 +1192,10 @@ int run_staged(kv_engine *e, int k, const int32_t *oi, const int32_t *os, int32_
     // A chunk of few blocks gets their ids as kernel arguments: a copy ahead of the chunks costs each
     // direction a launch, and the first DMA copy of a swap-in, which needs no ids, a wait for it.
     // (us a call with the copies and without: 2 + 1 blocks of 34 KiB 47.9 and 43.1, 2 + 3 of 128 KiB 62.4 and
-    // 55.8, 1 + 1 of 4 MiB 130 and 125, of 5 MiB in 160 planes 149 and 144; 120 + 96 of 2 MiB 5861 and 5865.)
+    // 55.8, 1 + 1 of 4 MiB 130 and 125, of 5 MiB in 160 planes 149 and 144; 120 + 96 of 2 MiB 5861 and 5865.
+    // The arguments of its one-wave workgroups make an unpack kernel 0.5 us longer where a chunk is 256 MiB, 93.1 and 92.5
+    // in one run, 0.1 at 64 MiB; the copy costs the call more there, too: blocks of 2 MiB in, 16 629.0 and 625.3, 64
+    // 2419.6 and 2416.0, 128 4813.9 and 4808.8, 512 19237 and 19234.)
     const bool args_out = cap_wgs == 0 && po.blocks_per_chunk <= dkv::kInlineIds;
     const bool args_in = cap_wgs == 0 && pi.blocks_per_chunk <= dkv::kInlineIds;
     if (no > 0) {

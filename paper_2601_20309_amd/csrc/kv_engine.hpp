@@ -91,6 +91,10 @@ constexpr int kClaimStride = 64;
 //   24 out with 12 in: 64 1375 / 1458; 128 748 / 773; 208 744 / 744; 520 616 / 603
 //   6 out with 24 in: 128 757 / 750.  24 out alone: 128 651 / 631; 208 579 / 548; 200 603 / 554
 //   block-first, 16 MiB each way: blocks of 128 bytes 1366 / 1439, of 160 1203 / 1196
+// These are of tiles on 128-byte lines.  With tiles on stretches (MoveParams::line_mask) a layer-first pool's
+// segments of more than a line are slower this way in scattered slots, too, 8-byte ones from 264 bytes on in any: 24 MiB
+// each way 208 817 / 793, 400 670 / 631, 640 575 / 554, 1008 585 / 559, 264 761 / 736, 504 641 / 599, but 200 803 / 846,
+// 128 779 / 858.
 inline bool leaves_to_l2(int vec, uint64_t piece, bool layer_first, uint64_t block_bytes, const int32_t *out_slots,
                          int64_t n_out, int64_t n_in)
 {

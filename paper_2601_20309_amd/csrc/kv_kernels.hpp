@@ -383,12 +383,12 @@ __device__ __forceinline__ uint32_t drawn(uint32_t d)
 // In those the waves have no time to drift apart, and the counter's atomics, ~14 ns
 // each on one address and slower beside a kernel that fills the memory's queues, are no small part of
 // the launch.  With shares to 8, 16 and 24 rounds one way, us a call alone, and beside a reader over 8 GiB with
-// the ms that it loses per GiB moved: 1.5 MiB out 43.0, 42.3, 41.7 and 49.2 (1.06), 49.1 (1.05), 45.7 (0.76);
-// 1.4 MiB in 42.3, 41.6, - and 50.6 (2.17), 45.6 (2.20), -; 2 MiB in 53.2, 52.6, 53.1 and 62.3 (1.88), 62.0
-// (1.85), 57.2 (1.99).  Eight launches of 1.5 MiB out 268, 268, 264.  Both ways, where a step is two
-// tiles, the waves drift further apart: with shares to 8, 12 and 16 rounds calls of one block of 1.3 MiB 44.6, 44.9,
-// 45.3, of five of 270 KiB 45.2, 46.0, 45.4, of one of 2 MiB 59.1, 59.1, 59.4 (beside the reader, though,
-// 1.1 MiB 49.4 (1.34), - and 44.3 (1.48)).  (A wave per step, up to 512 of them, cost the reader half.)
+// the ms that it loses per GiB moved: 1.5 MiB out 42.9, 42.6, 42.3 and 48.4 (1.34), 48.2 (1.32), 45.0 (1.10);
+// 1.4 MiB in 42.2, 41.6, 41.6 and 49.2 (2.28), 44.4 (2.31), 44.4; 2 MiB in 53.1, 53.0, 53.2 and 60.6 (2.10), 60.5
+// (2.08), 56.0 (2.13).  Both ways, where a step is two tiles, the waves drift further apart, and what more shares
+// are worth alone goes by the call: with shares to 8, 12 and 16 rounds one block of 1.3 MiB 44.7, 45.1, 45.0, 80 of
+// 16 KiB 44.7, 44.5, 44.3, one of 2 MiB 59.2, 59.2, 59.6.  (Beside the reader they would be 5 to 8 % faster, the one
+// block 50.8 (1.40), 47.3 (1.52), 47.3 (1.54).  A wave per step, up to 512 of them, cost the reader half.)
 constexpr uint32_t kFixedRounds = 24, kFixedRoundsBoth = 8;
 
 template <typename V, int U, bool LINK, bool FULL>
@@ -622,12 +622,17 @@ __global__ __launch_bounds__(kThreads) void kv_stage_inline_kernel(const StagePa
 // Short passes (up to kReadShortRows rows for each wave of the whole grid, 66 MiB) are latency and
 // nothing else: tiles of eight rows left most of the grid idle (2 MiB: 64 workgroups, eight
 // latencies one behind the other) or half of it in the second of two rounds.  Their tiles are
-// as many rows as give every wave as much, and two rows are in flight.  us alone / beside a
-// swap-out / a rotation, and its GB/s, one pass behind the other, before and now:
-//    2 MiB  9.7 / 14.4 / 22.1, 85.3 and 6.9 / 10.6 / 15.0, 77.0     48 MiB 16.7 / 23.5 / 33.8, 90.5 and 14.0 / 17.9 / 24.3, 86.3
-//   28 MiB 12.8 / 18.1 / 25.8, 87.5 and 11.5 / 15.5 / 20.9, 84.3    64 MiB 18.5 / 25.1 / 36.4, 91.3 and 17.5 / 20.7 / 26.9, 86.4
-// (what the copy loses goes by the number of launches beside it, each of which ends with the
-// caches written back).  From 80 MiB on a pass alone gains nothing by it.
+// as many rows as give every wave about as much, and two rows are in flight.  (As much where a
+// wave has 2, 4, 6, 8 or 12 rows: others are rounded up to pairs, so that with one row a wave half of the
+// grid has none, and of nine to eleven the second round of six is not full.)  us alone / beside a
+// swap-out / a rotation, each with its GB/s, one pass behind the other, before and now:
+//    2 MiB  6.8 / 14.9, 57.1 / 22.0, 98.4 and  6.0 /  9.6, 57.1 / 13.9, 95.9
+//   28 MiB 11.5 / 17.2, 57.1 / 24.4, 98.2 and 10.5 / 14.5, 57.0 / 19.7, 97.4
+//   46 MiB 14.7 / 22.2, 57.0 / 32.6, 99.2 and 13.1 / 16.7, 56.9 / 23.3, 98.1
+//   64 MiB 16.6 / 24.0, 57.0 / 34.8, 99.2 and 16.0 / 19.6, 55.4 / 25.4, 97.9
+// What the copy loses goes by the number of launches beside it, each of which ends with the caches
+// written back, and from 28 MiB on by the second row, too: with one, 64 MiB took 17.7 / 23.5, 57.0 / 31.6, 99.0.
+// From 80 MiB on a pass alone gains nothing by it.
 //
 // No two workgroups meet on an address while they read.  An atomic on one address
 // is served every ~14 ns: one counter for the tiles limits claims to 2.3 TB/s per
