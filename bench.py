@@ -264,7 +264,9 @@ def main():
     kernels = step_kernels(path_name, shape, layout, len(rot.out_ids), len(rot.in_ids), args.chunk_layers, args.max_copy_wgs,
                            args.staging_mib << 20)
     kernel_name = " and ".join(kernels)             # no profile covers a step of two kernels
-    traffic, traffic_src = measured_traffic(args.workload, path_name, kernel_name)
+    # the profiles are of one launch for the whole list (a chunk that holds it, on the DMA-staged path)
+    whole = not args.chunk_layers and not args.staging_mib
+    traffic, traffic_src = measured_traffic(args.workload, path_name, kernel_name) if whole else (None, None)
     res = {
         "metric": "duplex KV rotation GB/s (out+in) and % of measured host-link peak",
         "value": round(gbps_out + gbps_in, 2), "unit": "GB/s", "n_gpus": 1, "steps": steps,
