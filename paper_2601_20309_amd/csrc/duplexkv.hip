@@ -565,19 +565,19 @@ int mark_end(kv_engine *e, bool out_side, int k, hipStream_t s)
 // and 740, of 1200 bytes in blocks of 57600 751 and 742).
 // Vectors narrower than 16 bytes (odd segments or pointers) also get more of them per lane, and where
 // 8-byte ones have one a lane nevertheless, what moves in gets 1.5 times the waves: alone always, both ways
-// where groups are several tiles of which no more than a third is empty.  (us without and with, layer-first; beside a
-// reader over 8 GiB, and the ms that it loses per GiB moved, behind the semicolon.  24 MiB both ways: segments of 1048
-// bytes 596 and 564, 1160 591 and 558; 563 (2.5) and 469 (3.5) for 20 MiB, 1400 599 and 571, 200 bytes in blocks of 3200 619
-// and 556; 604 (2.9) and 467 (3.1) for 20 MiB.  But a third empty and more, 1000 bytes 588 and 591, 2 MiB 70.5 and 72.6,
-// and single tiles, 360 bytes 665 and 692, 2 MiB 75.6 and 78.1, 392 bytes 653 and 677.  1 MiB out with 2.4 in:
-// 1048 bytes 75.6 and 76.6, 1400 bytes 71.8 and 70.4; 10 with 24, 1048 bytes 524 and 515, 1160 516 and 505.  24 MiB in: 392 bytes 619 and 600; 588 (5.1) and
-// 512 (8.2) for 20 MiB, 1160 579 and 501; 572 (4.6) and 437 (5.3), 200 in blocks 596 and 467; 586 (5.3) and 423 (4.8).
-// One direction out is the same.)
+// where groups are several tiles of which no more than a third is empty.  us without and with; in brackets for 20 MiB
+// beside a reader over 8 GiB, and the ms that it loses per GiB moved:
+//   24 MiB both ways, layer-first segments of 1048 bytes 596 and 564, 1400 599 and 571, 1160 591 and 558 (563, 2.5 and
+//     469, 3.5), of 200 bytes in blocks of 3200 619 and 556 (604, 2.9 and 467, 3.1)
+//   a third empty and more: 1000 bytes 588 and 591, 2 MiB 70.5 and 72.6; single tiles: 360 bytes 665 and 692, 2 MiB 75.6
+//     and 78.1, 392 bytes 653 and 677
+//   1 MiB out with 2.4 in: 1048 bytes 75.6 and 76.6, 1400 71.8 and 70.4; 10 with 24: 1048 bytes 524 and 515, 1160 516 and 505
+//   24 MiB in: 392 bytes 619 and 600 (588, 5.1 and 512, 8.2), 1160 579 and 501 (572, 4.6 and 437, 5.3), 200 in blocks
+//     596 and 467 (586, 5.3 and 423, 4.8); out is the same either way
 // Now, with tiles on lines instead of stretches and before all of this and line_mask (on another card), us for 40 MiB
 // both ways / out / in: segments of 1200 bytes 854 / 753 / 750 (855 / 754 / 762; 856 / 756 / 744), in a
 // layer-first pool 903 / 773 / 825 (921 / 796 / 828; 968 / 830 / 820), of 840 bytes there 974 / 781 / 862 (979 / 783 /
-// 866; 1150 / 870 / 1350).  All of this
-// goes by the tiles as they are cut, configured vectors or not: segments of 1000 vectors
+// 866; 1150 / 870 / 1350).  All of this goes by the tiles as they are cut, configured vectors or not: segments of 1000 vectors
 // with vecs_per_lane = 8 are cut by 4, and with the waves of 8 moved at 86 / 56 / 44 GB/s
 // both ways / out / in, with those of 4 at 99 / 56 / 57.
 enum LinkKind { kBoth, kInHeavy, kOutOnly, kInOnly };
@@ -872,9 +872,11 @@ int run_zero_copy(kv_engine *e, int path, int k, int32_t no, int32_t ni)
     // 0.8 + 0.8 458 and 432).  Configured launches keep to the fewer.
     if (no > 0 && ni > 0) {
         auto shares = [&](const LinkShape &sh, const MoveParams &p, uint32_t tiles) {
-            return (uint64_t)tiles * planes <= (uint64_t)dkv::kFixedRounds * (uint64_t)sh.wgs * (uint64_t)(sh.lanes / dkv::kWave) * p.n_planes;
+            const uint64_t waves = (uint64_t)sh.wgs * (uint64_t)(sh.lanes / dkv::kWave);
+            return (uint64_t)tiles * planes <= dkv::kFixedRounds * waves * p.n_planes;
         };
-        const bool both = e->vec == 16 && !(pair && e->cfg.chunk_layers) && !e->cfg.max_copy_wgs && !e->cfg.wg_lanes && !e->cfg.vecs_per_lane &&
+        const bool configured = e->cfg.max_copy_wgs || e->cfg.wg_lanes || e->cfg.vecs_per_lane;
+        const bool both = e->vec == 16 && !(pair && e->cfg.chunk_layers) && !configured &&
                           shares(sh_out, p_out, p_out.out.tiles) && shares(sh_in, p_in, p_in.in.tiles);
         p_out.fixed_rounds = p_in.fixed_rounds = both ? dkv::kFixedRounds : dkv::kFixedRoundsBoth;
     }

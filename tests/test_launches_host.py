@@ -102,7 +102,8 @@ def test_lengths_that_end_the_fixed_share(exe, dim, tokens, layout):
 
 @pytest.mark.parametrize("vecs", list(L.ROUNDS))
 def test_rounds_of_the_default_shapes(exe, vecs):
-    """L.ROUNDS: the waves and steps that the engine launches, full rounds and the end of the fixed share between two of the lengths."""
+    """L.ROUNDS: the waves and steps that the engine launches; full rounds and the end of the fixed share lie between two of
+    the lengths."""
     lengths = L.round_lengths(vecs)
     for kind, (waves, steps) in enumerate(L.ROUNDS[vecs]):
         got = {n: L.launches(exe, [kinds(n, 8 * vecs)[kind]])[0][0] for n in lengths}
@@ -117,10 +118,12 @@ def test_rounds_of_the_default_shapes(exe, vecs):
 @pytest.mark.parametrize("vecs", [64, 75])
 @pytest.mark.parametrize("wgs,lanes", [(1, 64), (3, 64), (1, 256), (2, 320)])
 def test_lengths_around_the_limits_of_configured_shapes(exe, wgs, lanes, vecs):
-    """L.configured_lengths: of each kind some take fixed shares and some draw, the nearest two a block apart, and some draw four steps at a time."""
+    """L.configured_lengths: of each kind some take fixed shares and some draw, the nearest two a block apart, and some
+    draw four steps at a time."""
     lengths = L.configured_lengths(wgs, lanes, vecs)
     for kind in range(3):
-        got = [L.launches(exe, [kinds(n, 8 * vecs, layers=2, max_copy_wgs=wgs, wg_lanes=lanes, vecs_per_lane=1)[kind]])[0][0] for n in lengths]
+        calls = [kinds(n, 8 * vecs, layers=2, max_copy_wgs=wgs, wg_lanes=lanes, vecs_per_lane=1)[kind] for n in lengths]
+        got = [x[0] for x in L.launches(exe, calls)]
         drawn = [x["drawn"] for x in got]
         first = drawn.index(1)
         assert drawn == sorted(drawn) and first > 0 and lengths[first] == lengths[first - 1] + 1
